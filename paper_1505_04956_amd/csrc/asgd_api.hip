@@ -47,7 +47,9 @@ struct asgd_ctx {
     // Error flag of the kernels (an expired bounded wait), in pinned host memory that the device writes directly: the
     // host clears and reads it around a run without a memset or a copy on the stream (each is a separate operation
     // of several microseconds, which counts when a run is one launch of less than a millisecond).
-    int *flag_host = nullptr;
+    int *flag_host = nullptr;      // [0] error flag, [1] set while loading if a sample is not finite
+    void *split_scratch = nullptr; // matrix-core form of the shape-agnostic kernel, allocated on first use
+    size_t split_bytes = 0;
     long long *ncum = nullptr, *counters = nullptr;
     double *qpart = nullptr, *qout = nullptr;
     int32_t *dump = nullptr;
@@ -85,7 +87,7 @@ size_t kd_of(const asgd_ctx *c) { return (size_t)c->k * c->d; }
 void free_all(asgd_ctx *c)
 {
     void *ptrs[] = {c->w, c->slot, c->acc, c->xabsmax, c->mean, c->stamp, c->consumed, c->cnt, c->assign_tmp,
-                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab};
+                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (c->flag_host) (void)hipHostFree(c->flag_host);
@@ -322,7 +324,7 @@ int asgd_create(asgd_ctx **out, int k, int d, int W, int b, float lr)
         e = hipMalloc(a.p, a.bytes);
         if (e != hipSuccess) { fail(e); break; }
     }
-    if (rc == ASGD_OK && (e = hipHostMalloc((void **)&c->flag_host, sizeof(int), hipHostMallocDefault)) != hipSuccess) fail(e);
+    if (rc == ASGD_OK && (e = hipHostMalloc((void **)&c->flag_host, 2 * sizeof(int), hipHostMallocDefault)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev0)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev1)) != hipSuccess) fail(e);
     if (rc != ASGD_OK) {
@@ -453,7 +455,8 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     HIP_TRY(ctx, hipMemsetAsync(ctx->counters, 0, (size_t)ctx->W * CNT_STRIDE * sizeof(long long), ctx->stream));
     // per-dimension max |x| over the rows the workers own: input of the rounding-error bound
     // that decides when an assignment is recomputed exactly
-    HIP_TRY(ctx, launch_absmax(x_dev, H * ctx->W, ctx->d, ctx->xabsmax, ctx->stream));
+    ctx->flag_host[1] = 0;
+    HIP_TRY(ctx, launch_absmax(x_dev, H * ctx->W, ctx->d, ctx->xabsmax, ctx->flag_host + 1, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     ctx->loaded = true;
     return ASGD_OK;
@@ -630,6 +633,25 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         p.shift_tab = ctx->shift_tab;
         p.shift_r0 = ctx->tab_r0;
     }
+    // The shape-agnostic kernel has a matrix-core form, launched step by step over all workers (no waits inside a launch,
+    // so the modes do not matter).
+    // (ASGD_OPT_TUNE bit 0: one workgroup per worker.)
+    bool split = kernel == ASGD_KERNEL_GENERIC && !(ctx->tune & 1) && ctx->flag_host[1] == 0 &&
+                 split_kernel_supports(ctx->k, ctx->d, ctx->b) && steps > 0;
+    if (split) {
+        const size_t need = split_scratch_bytes(p);
+        if (need > ctx->split_bytes) {
+            if (ctx->split_scratch) (void)hipFree(ctx->split_scratch);
+            ctx->split_scratch = nullptr;
+            ctx->split_bytes = 0;
+            if (hipMalloc(&ctx->split_scratch, need) == hipSuccess) {
+                ctx->split_bytes = need;
+            } else {
+                (void)hipGetLastError();         // no room: the form that needs no scratch
+                split = false;
+            }
+        }
+    }
     // Deterministic mode: a worker may only read the message of round r-1 once its sender has
     // finished that round.  Either the whole run is one launch of co-resident workgroups that wait
     // for each other's stamps (small-state and matrix-core kernels, when the workers all fit the
@@ -667,6 +689,11 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
                 HIP_TRY(ctx, e);
             }
         }
+    }
+    if (split) {
+        HIP_TRY(ctx, launch_split_steps(p, ctx->t, t_end, ctx->split_scratch, ctx->stream, &launches));
+        ctx->passed_t = -1;
+        t_done = t_end;
     }
     for (long long ta = t_done; ta < t_end;) {
         long long tb = t_end;

@@ -48,8 +48,14 @@ struct StepParams {
 
 // Launchers (each returns the hipError_t of its launch).
 hipError_t launch_init_first_k(const StepParams &p, hipStream_t s);
-hipError_t launch_absmax(const float *x, long long rows, int d, float *out, hipStream_t s);
+// nonfinite: pinned host memory, set to 1 if an element is infinite or not a number
+hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, hipStream_t s);
 hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1, hipStream_t s);
+// Matrix-core form of the shape-agnostic kernel (any row length; finite samples): launches of its own per step, all on
+// `scratch` (split_scratch_bytes() of device memory, nothing in it is kept between calls).
+bool split_kernel_supports(int k, int d, int b);
+size_t split_scratch_bytes(const StepParams &p);
+hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, void *scratch, hipStream_t s, int *launches);
 bool small_kernel_supports(int k, int d, int b);
 // bytes of one exchange buffer in the small-state kernel's own message format (0: kernel not applicable)
 size_t small_kernel_message_bytes(int k, int d);

@@ -59,14 +59,14 @@ __device__ __forceinline__ double gen_wave_sum(double v)
 
 __global__ void init_first_k_kernel(StepParams p)
 {
-    // Worker i starts from the first k rows of its own shard.
+    // Worker i starts from the first k rows of its own shard; gridDim.y workgroups per worker.
     const size_t kd = (size_t)p.k * p.d;
     const int i = blockIdx.x;
-    for (size_t e = threadIdx.x; e < kd; e += blockDim.x)
+    for (size_t e = (size_t)blockIdx.y * blockDim.x + threadIdx.x; e < kd; e += (size_t)gridDim.y * blockDim.x)
         p.w[i * kd + e] = p.x[(size_t)i * p.H * p.d + e];
 }
 
-__global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, int d, float *partial)
+__global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, int d, float *partial, int *nonfinite)
 {
     // partial[block][j] = max |x[row][j]| over the elements this block visits.  The flat array
     // is walked with a stride that is a multiple of d, so a thread always sees one dimension.
@@ -79,15 +79,23 @@ __global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, 
     __syncthreads();
     if (g < stride) {
         float m = 0.0f;
+        unsigned bits = 0;            // (the maximum of two floats drops a NaN, that of their bit patterns does not)
         long long e = g;
         for (; e + 7 * stride < total; e += 8 * stride) {      // eight independent loads in flight per thread
             float v[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = x[e + q * stride];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) m = fmaxf(m, fabsf(v[q]));
+            for (int q = 0; q < 8; ++q) {
+                m = fmaxf(m, fabsf(v[q]));
+                bits = max(bits, __float_as_uint(v[q]) & 0x7fffffffu);
+            }
         }
-        for (; e < total; e += stride) m = fmaxf(m, fabsf(x[e]));
+        for (; e < total; e += stride) {
+            m = fmaxf(m, fabsf(x[e]));
+            bits = max(bits, __float_as_uint(x[e]) & 0x7fffffffu);
+        }
+        if (bits >= 0x7f800000u) __hip_atomic_store(nonfinite, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         // max is order independent; |x| >= 0, so the integer order of the bit patterns is the
         // floating-point order and an integer atomic is exact
         atomicMax((unsigned int *)&sm[g % d], __float_as_uint(m));
@@ -96,11 +104,24 @@ __global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, 
     for (int j = threadIdx.x; j < d; j += blockDim.x) partial[(size_t)blockIdx.x * d + j] = sm[j];
 }
 
-__global__ void absmax_final_kernel(const float *partial, int nblocks, int d, float *out)
+// A workgroup of 16 waves takes 64 columns, a wave every 16th block's maxima, eight of them in flight (one thread per
+// column walking all the blocks took 0.1 to 0.5 ms, 1024 dependent steps and more than once around for d > 256).
+__global__ __launch_bounds__(1024) void absmax_final_kernel(const float *partial, int nblocks, int d, float *out)
 {
-    for (int j = blockIdx.x * blockDim.x + threadIdx.x; j < d; j += gridDim.x * blockDim.x) {
-        float m = 0.0f;
-        for (int bidx = 0; bidx < nblocks; ++bidx) m = fmaxf(m, partial[(size_t)bidx * d + j]);
+    __shared__ float red[16][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
+    float m = 0.0f;
+    for (int q0 = wave; q0 < nblocks; q0 += 128) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)min(q0 + 16 * u, nblocks - 1) * d + (j < d ? j : 0)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) m = fmaxf(m, v[u]);
+    }
+    red[wave][lane] = m;
+    __syncthreads();
+    if (wave == 0 && j < d) {
+        for (int q = 0; q < 16; ++q) m = fmaxf(m, red[q][lane]);
         out[j] = m;
     }
 }
@@ -418,19 +439,22 @@ __global__ void mean_state_kernel(const float *w, int W, int kd, float *out)
 // ------------------------------------------------------------------------------------------
 hipError_t launch_init_first_k(const StepParams &p, hipStream_t s)
 {
-    hipLaunchKernelGGL(init_first_k_kernel, dim3(p.W), dim3(256), 0, s, p);
+    // four elements per thread, as long as that is at most 64 workgroups per worker (one per worker took 0.15 ms for 64
+    // states of 98304 floats and 0.22 ms for 256 of 131072)
+    const size_t per = ((size_t)p.k * p.d + 1023) / 1024;
+    hipLaunchKernelGGL(init_first_k_kernel, dim3(p.W, (unsigned)(per < 64 ? per : 64)), dim3(256), 0, s, p);
     return hipGetLastError();
 }
 
-hipError_t launch_absmax(const float *x, long long rows, int d, float *out, hipStream_t s)
+hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, hipStream_t s)
 {
     // out: d floats; uses a temporary of nblocks*d floats that is freed before returning
     const int nblocks = 1024;
     float *partial = nullptr;
     hipError_t e = hipMalloc((void **)&partial, (size_t)nblocks * d * sizeof(float));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(absmax_partial_kernel, dim3(nblocks), dim3(256), (size_t)d * sizeof(float), s, x, rows, d, partial);
-    hipLaunchKernelGGL(absmax_final_kernel, dim3(1), dim3(256), 0, s, partial, nblocks, d, out);
+    hipLaunchKernelGGL(absmax_partial_kernel, dim3(nblocks), dim3(256), (size_t)d * sizeof(float), s, x, rows, d, partial, nonfinite);
+    hipLaunchKernelGGL(absmax_final_kernel, dim3((d + 63) / 64), dim3(1024), 0, s, partial, nblocks, d, out);
     e = hipGetLastError();
     hipError_t e2 = hipStreamSynchronize(s);
     (void)hipFree(partial);

@@ -1,0 +1,84 @@
+"""The matrix-core form of the shape-agnostic kernel (fp32 operands as two fp16 parts, any row length): against the oracle
+at the edges of its tiles, and against the form with one workgroup per worker where the data are awkward."""
+import numpy as np
+import pytest
+
+from tests.test_parity_gpu import B, make_data, run_both, to_dev  # noqa: F401  (fixtures)
+
+pytestmark = pytest.mark.gpu
+
+ONE_WORKGROUP = 1      # ASGD_OPT_TUNE of the shape-agnostic kernel: one workgroup per worker
+
+
+# row lengths around the groups of 8 and chunks of 16 columns, the last one with its operands in registers (128) and the
+# long-row kernel (129 ...); centroids around the blocks of 32 rows; mini-batches around the groups of 64 samples
+@pytest.mark.parametrize("k,d,W,b,E,buffers,parts", [
+    (2, 1, 3, 1, 2, 1, 1), (3, 2, 3, 63, 2, 1, 1), (31, 7, 5, 64, 2, 1, 1), (32, 8, 4, 65, 1, 1, 1), (33, 9, 3, 130, 3, 2, 1),
+    (64, 15, 3, 300, 2, 1, 1), (65, 16, 2, 257, 1, 1, 1), (20, 17, 6, 100, 2, 1, 4), (40, 31, 3, 200, 2, 2, 3),
+    (37, 33, 4, 129, 2, 1, 1), (12, 65, 3, 500, 2, 1, 1), (70, 111, 2, 128, 1, 1, 1), (5, 127, 3, 200, 2, 1, 1),
+    (96, 128, 2, 320, 1, 1, 1), (300, 61, 2, 640, 1, 1, 1), (9, 129, 3, 96, 2, 1, 1), (97, 135, 2, 260, 1, 1, 1),
+    (34, 257, 3, 70, 2, 2, 1), (130, 40, 2, 1500, 1, 1, 1), (6, 520, 3, 64, 1, 1, 2), (700, 12, 2, 1400, 1, 1, 1),
+])
+def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
+    H = max(3 * b + 7, k)
+    X = make_data(W * H + 1, d, k, seed=100 + d)
+    g, _ = run_both(B, oracle, X, k, W, b, 0.05, E, 7, kernel=B.KERNEL_GENERIC, buffers=buffers, parts=parts)
+    assert g.stats().launches > 7                     # launches of its own for every step
+    again = B.ASGD(k, d, W, b, 0.05, E=E, kernel=B.KERNEL_GENERIC, buffers=buffers, parts=parts)
+    again.load_shards(to_dev(X))
+    again.run_steps(3)
+    again.run_steps(4)
+    assert np.array_equal(g.get_state(), again.get_state())        # bit for bit, however the run is cut
+
+
+@pytest.mark.parametrize("k,d,b", [(7, 5, 200), (40, 77, 333), (12, 140, 90)])
+def test_split_kernel_running_mean(B, oracle, k, d, b):
+    X = make_data(4 * (5 * b + 3), d, k, seed=5)
+    run_both(B, oracle, X, k, 4, b, 0.1, 0, 9, lr_mode=1, kernel=B.KERNEL_GENERIC)
+
+
+def pair(B, X, k, W, b, steps, w0=None, **kw):
+    """States of the matrix-core form and of the one-workgroup form, same run."""
+    out = []
+    for tune in (0, ONE_WORKGROUP):
+        g = B.ASGD(k, X.shape[1], W, b, 0.1, E=2, kernel=B.KERNEL_GENERIC, tune=tune, **kw)
+        g.load_shards(to_dev(X))
+        if w0 is not None:
+            g.set_state(-1, w0)
+        g.run_steps(steps)
+        out.append((g.get_state(), g.stats()))
+    return out
+
+
+@pytest.mark.parametrize("k,d", [(20, 13), (40, 150)])
+@pytest.mark.parametrize("what", ["far", "columns", "identical", "w0_far", "w0_zero"])
+def test_split_kernel_awkward_data(B, k, d, what):
+    """Both forms assign exactly, so they differ by the rounding of sums of b terms and of the update only: a few 2^-24
+    of the column's size per step."""
+    W, b, steps = 4, 150, 6
+    X = make_data(W * (3 * b + 11), d, k, seed=9, sigma=0.5)
+    w0 = None
+    if what == "far":
+        X = X + np.float32(1.0e4)
+    elif what == "columns":
+        X = X * (np.float32(10.0) ** np.linspace(-6, 6, d).astype(np.float32))
+    elif what == "identical":
+        X[:] = X[0]
+    elif what == "w0_far":
+        w0 = np.float32(3.0e5) * make_data(k, d, k, seed=3)
+    elif what == "w0_zero":
+        w0 = np.zeros((k, d), dtype=np.float32)
+    (wa, sa), (wb, sb) = pair(B, np.ascontiguousarray(X, dtype=np.float32), k, W, b, steps, w0)
+    scale = np.abs(wb).max(axis=(0, 1)) + np.float32(1e-30)
+    # (identical samples: w - c G ties in Eq. 4 and equal distances are decided the same way in both forms)
+    assert np.all(np.abs(wa - wb).max(axis=(0, 1)) <= 1e-6 * scale), what
+    assert sa.sent == sb.sent and sa.received == sb.received
+
+
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_split_kernel_leaves_non_finite_samples_to_the_other_form(B, value):
+    k, d, W, b = 20, 13, 4, 100
+    X = make_data(W * 500, d, k, seed=9)
+    X[777, 5] = value
+    (wa, sa), (wb, sb) = pair(B, X, k, W, b, 6)
+    assert np.array_equal(wa, wb, equal_nan=True) and sa.launches == sb.launches
