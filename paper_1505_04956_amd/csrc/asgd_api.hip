@@ -472,8 +472,10 @@ int asgd_set_state(asgd_ctx *ctx, int worker, const float *w_host)
     if (worker >= 0) {
         HIP_TRY(ctx, hipMemcpy(ctx->w + (size_t)worker * kd_of(ctx), w_host, kdb, hipMemcpyHostToDevice));
     } else if (worker == -1) {
-        for (int i = 0; i < ctx->W; ++i)
-            HIP_TRY(ctx, hipMemcpy(ctx->w + (size_t)i * kd_of(ctx), w_host, kdb, hipMemcpyHostToDevice));
+        // one copy over the bus, the rest on the device (a copy per worker took 9 us each)
+        HIP_TRY(ctx, hipMemcpy(ctx->mean, w_host, kdb, hipMemcpyHostToDevice));
+        HIP_TRY(ctx, launch_broadcast_state(ctx->mean, ctx->W, (int)kd_of(ctx), ctx->w, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     } else {
         HIP_TRY(ctx, hipMemcpy(ctx->w, w_host, kdb * ctx->W, hipMemcpyHostToDevice));
     }
@@ -567,14 +569,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         kernel = small_ok ? ASGD_KERNEL_SMALL : (mfma_ok ? ASGD_KERNEL_MFMA : ASGD_KERNEL_GENERIC);
     }
     if (kernel == ASGD_KERNEL_SMALL && !small_ok) return ASGD_EINVAL;
-    if (kernel == ASGD_KERNEL_MFMA) {
-        if (!mfma_ok) return ASGD_EINVAL;
-        if (!ctx->xnorm2max) HIP_TRY(ctx, hipMalloc((void **)&ctx->xnorm2max, sizeof(float)));
-        if (!ctx->xnorm2max_valid) {
-            HIP_TRY(ctx, launch_rownorm2max(ctx->x, ctx->H * ctx->W, ctx->d, ctx->xnorm2max, ctx->stream));
-            ctx->xnorm2max_valid = true;
-        }
-    }
+    if (kernel == ASGD_KERNEL_MFMA && !mfma_ok) return ASGD_EINVAL;
 
     // The kernels keep a message in flight in different formats.  Messages handed over by asgd_set_exchange(), and
     // those a run of another kernel left behind, are written into the buffers in the format of this run's kernel.
@@ -633,11 +628,19 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         p.shift_tab = ctx->shift_tab;
         p.shift_r0 = ctx->tab_r0;
     }
-    // The shape-agnostic kernel has a matrix-core form, launched step by step over all workers (no waits inside a launch,
-    // so the modes do not matter).
-    // (ASGD_OPT_TUNE bit 0: one workgroup per worker.)
-    bool split = kernel == ASGD_KERNEL_GENERIC && !(ctx->tune & 1) && ctx->flag_host[1] == 0 &&
-                 split_kernel_supports(ctx->k, ctx->d, ctx->b) && steps > 0;
+    // The step kernels with fp16-split operands: the matrix-core form of the shape-agnostic kernel, and in the default
+    // variant also what the matrix-core kernel runs (three products on the fp16 matrix instructions take a fifth of the
+    // time of the fp32 ones).  Free-running mode of the latter stays with the kernel whose workers drift freely.
+    // Shape-agnostic: ASGD_OPT_TUNE bit 0 asks for one workgroup per worker, bit 1 for the matrix-core form whatever
+    // the size.  A step of the former takes 0.15 us per sample of the mini-batch or more, one of the latter 15 us or more.
+    bool split = false;
+    if (ctx->flag_host[1] == 0 && split_kernel_supports(ctx->k, ctx->d, ctx->b) && steps > 0) {
+        if (kernel == ASGD_KERNEL_GENERIC)
+            split = (ctx->tune & 2) || (!(ctx->tune & 1) && (ctx->b >= 96 || (double)ctx->b * ctx->k * ctx->d >= 8192.0));
+        else if (kernel == ASGD_KERNEL_MFMA)
+            split = ctx->tune == 0 && !ctx->drop_unannounced && ctx->wait_polls == 0 && ctx->parts == 1 &&
+                    (ctx->mode == ASGD_MODE_DETERMINISTIC || ctx->E == 0 || ctx->W < 2);
+    }
     if (split) {
         const size_t need = split_scratch_bytes(p);
         if (need > ctx->split_bytes) {
@@ -652,6 +655,13 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             }
         }
     }
+    if (kernel == ASGD_KERNEL_MFMA && !split) {
+        if (!ctx->xnorm2max) HIP_TRY(ctx, hipMalloc((void **)&ctx->xnorm2max, sizeof(float)));
+        if (!ctx->xnorm2max_valid) {
+            HIP_TRY(ctx, launch_rownorm2max(ctx->x, ctx->H * ctx->W, ctx->d, ctx->xnorm2max, ctx->stream));
+            ctx->xnorm2max_valid = true;
+        }
+    }
     // Deterministic mode: a worker may only read the message of round r-1 once its sender has
     // finished that round.  Either the whole run is one launch of co-resident workgroups that wait
     // for each other's stamps (small-state and matrix-core kernels, when the workers all fit the
@@ -662,7 +672,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     *ctx->flag_host = 0;         // (no kernel of this context is in flight: every run ends with a wait for the stream)
     HIP_TRY(ctx, hipEventRecord(ctx->ev0, ctx->stream));
     long long t_done = ctx->t;           // steps [ctx->t, t_done) have been launched
-    const bool one_launch = (kernel == ASGD_KERNEL_SMALL && (ctx->tune & 3) != 3) || (kernel == ASGD_KERNEL_MFMA && !(ctx->tune & 4));
+    const bool split_local = split && split_local_form(p);
+    const bool one_launch = split_local || (!split && ((kernel == ASGD_KERNEL_SMALL && (ctx->tune & 3) != 3) || (kernel == ASGD_KERNEL_MFMA && !(ctx->tune & 4))));
     if (rounds && one_launch && steps > 0) {
         // every worker has passed the merge points before the first step of this run
         const long long r0 = ctx->t / ctx->E;
@@ -676,13 +687,15 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         while (t_done < t_end) {
             long long tb = (t_done / ctx->E + ONE_LAUNCH_MAX_ROUNDS) * (long long)ctx->E;
             if (tb > t_end) tb = t_end;
-            hipError_t e = (kernel == ASGD_KERNEL_SMALL) ? launch_small_steps(p, t_done, tb, ctx->stream, true)
+            int one = 0;
+            hipError_t e = split_local ? launch_split_steps(p, t_done, tb, ctx->split_scratch, ctx->stream, &one)
+                           : (kernel == ASGD_KERNEL_SMALL) ? launch_small_steps(p, t_done, tb, ctx->stream, true)
                                                          : launch_mfma_steps(p, t_done, tb, ctx->xnorm2max, ctx->stream, true);
             if (e == hipSuccess) {
                 ++launches;
                 t_done = tb;
                 ctx->passed_t = tb;
-            } else if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
+            } else if (!split_local && (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported)) {
                 (void)hipGetLastError();     // the rest (or all of it): one launch per round
                 break;
             } else {
@@ -690,8 +703,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             }
         }
     }
-    if (split) {
-        HIP_TRY(ctx, launch_split_steps(p, ctx->t, t_end, ctx->split_scratch, ctx->stream, &launches));
+    if (split && t_done < t_end) {
+        HIP_TRY(ctx, launch_split_steps(p, t_done, t_end, ctx->split_scratch, ctx->stream, &launches));
         ctx->passed_t = -1;
         t_done = t_end;
     }

@@ -51,9 +51,11 @@ hipError_t launch_init_first_k(const StepParams &p, hipStream_t s);
 // nonfinite: pinned host memory, set to 1 if an element is infinite or not a number
 hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, hipStream_t s);
 hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1, hipStream_t s);
-// Matrix-core form of the shape-agnostic kernel (any row length; finite samples): launches of its own per step, all on
-// `scratch` (split_scratch_bytes() of device memory, nothing in it is kept between calls).
+// Step kernels with fp16-split operands (any row length; finite samples), all on `scratch` (split_scratch_bytes() of device
+// memory, nothing in it is kept between calls).  Local form: one launch whose workers wait for each other's messages, as
+// with `persistent` below; else a few launches per step.
 bool split_kernel_supports(int k, int d, int b);
+bool split_local_form(const StepParams &p);
 size_t split_scratch_bytes(const StepParams &p);
 hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, void *scratch, hipStream_t s, int *launches);
 bool small_kernel_supports(int k, int d, int b);
@@ -73,6 +75,7 @@ hipError_t launch_mfma_steps(const StepParams &p, long long t0, long long t1, co
                              bool persistent);
 // shift_tab[q] = 1 + round_hash(seed, r0 + q) % (W - 1) for q in [0, n)
 hipError_t launch_schedule_table(uint64_t seed, long long r0, int n, int W, int *shift_tab, hipStream_t s);
+hipError_t launch_broadcast_state(const float *src, int W, int kd, float *w, hipStream_t s);     // the same state to all workers
 hipError_t launch_mean_state(const float *w, int W, int kd, float *out, hipStream_t s);
 // Eq. 8 over rows [0, N): partials is scratch of quant_partials_count() doubles.
 int quant_partials_count();

@@ -425,6 +425,14 @@ __global__ void quant_error_final_kernel(const double *partials, int n, double *
     }
 }
 
+__global__ void broadcast_state_kernel(const float *src, int W, int kd, float *w)
+{
+    const int e = blockIdx.x * blockDim.x + threadIdx.x;
+    if (e >= kd) return;
+    const float v = src[e];
+    for (int i = blockIdx.y; i < W; i += gridDim.y) w[(size_t)i * kd + e] = v;
+}
+
 __global__ void mean_state_kernel(const float *w, int W, int kd, float *out)
 {
     const int e = blockIdx.x * blockDim.x + threadIdx.x;
@@ -506,6 +514,12 @@ __global__ void schedule_table_kernel(uint64_t seed, long long r0, int n, int W,
 hipError_t launch_schedule_table(uint64_t seed, long long r0, int n, int W, int *shift_tab, hipStream_t s)
 {
     hipLaunchKernelGGL(schedule_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, seed, r0, n, W, shift_tab);
+    return hipGetLastError();
+}
+
+hipError_t launch_broadcast_state(const float *src, int W, int kd, float *w, hipStream_t s)
+{
+    hipLaunchKernelGGL(broadcast_state_kernel, dim3((kd + 255) / 256, W < 1024 ? W : 1024), dim3(256), 0, s, src, W, kd, w);
     return hipGetLastError();
 }
 

@@ -1,0 +1,15 @@
+// Step kernels for rows of more than 128 columns.
+#include "split_steps.h"
+
+namespace asgd {
+
+hipError_t launch_split_local_0(const SplitRun &r, int blocks, unsigned lds, hipStream_t s)
+{
+    return split_launch_local<0>(r, blocks, lds, s);
+}
+hipError_t launch_split_assign_0(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s)
+{
+    return split_launch_phase<10>(l, blocks, threads, lds, s);
+}
+
+}  // namespace asgd

@@ -1,14 +1,15 @@
-// Assignment kernel for rows of up to 48 columns.
+// Step kernels for rows of 33 to 48 columns.
 #include "split_steps.h"
 
 namespace asgd {
 
-hipError_t launch_split_assign_3(const SplitArgs &a, int blocks, int threads, unsigned lds, hipStream_t s)
+hipError_t launch_split_local_3(const SplitRun &r, int blocks, unsigned lds, hipStream_t s)
 {
-    hipError_t e = hipFuncSetAttribute((const void *)split_assign_kernel<3>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(split_assign_kernel<3>, dim3(blocks), dim3(threads), lds, s, a);
-    return hipGetLastError();
+    return split_launch_local<3>(r, blocks, lds, s);
+}
+hipError_t launch_split_assign_3(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s)
+{
+    return split_launch_phase<13>(l, blocks, threads, lds, s);
 }
 
 }  // namespace asgd

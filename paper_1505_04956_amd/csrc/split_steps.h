@@ -1,6 +1,12 @@
-// Step kernels for any row length: a step is an assignment launch over (worker, share of the mini-batch), for large
-// states a launch that forms the gradient sums, and an update launch over the workers.  Shared declarations and the
-// assignment kernels; see kernels_split.hip for the others.
+// Step kernel for any row length.  A step of a worker is an assignment of its mini-batch, for large states gradient sums in
+// a pass of their own, at merge points Eq. 4, and an update; each is written as an item of work for one workgroup, and
+// there are two forms of putting them together:
+//   - local: all the steps of a call are ONE cooperative launch, a workgroup of eight waves per compute unit does all the
+//     items of its workers, and workers wait for each other's messages only.  Chosen where the workers fill the device.
+//   - phases: every phase of a step is a launch of its own over all workers, whose items are cut further (shares of the
+//     mini-batch, columns, rows), so that a few workers fill the device too.
+// (Tried between the two: one launch with barriers over the whole grid between the phases - 10 us a barrier, mostly the
+// write-back and invalidation of the L2 by every workgroup; 35 us per step where phases take 22.)
 #pragma once
 
 #include "split_core.h"
@@ -10,6 +16,7 @@ namespace asgd {
 // Operands of a worker's state rows, as the matrix instructions want them: rows in pairs of 32-row blocks, columns in
 // chunks of 16; [row pair][chunk][block of the pair][hi, lo] pieces of 1 KB, piece = 64 lanes x 8 fp16, lane l holding row
 // l % 32, columns 8 * (l / 32) .. + 7 of the chunk.
+constexpr int SPLIT_THREADS = 512;
 constexpr int SPLIT_PIECE = 1024;                    // bytes
 constexpr int SPLIT_STAGE = 8 * 4 * SPLIT_PIECE;     // a row pair's eight chunks: what the long-row kernel stages at a time
 
@@ -19,23 +26,36 @@ struct SplitState {                // one per worker and step modulo 3
     unsigned pad[29];              // a cache line each: atomics on one line wait for each other, and that took 15 us
 };
 
+struct SplitStep {                         // what is the same for all workers in a step
+    int slot, slot_next, slot_after;       // step modulo 3
+    int merge, send, round;                // merge point, messages go out, round number
+    int read_parity, send_parity, local;
+    const SplitState *state;               // W, of this step's slot
+    int32_t *dump;                         // W x b of this step, or null
+    long long row0;                        // first row of the mini-batch in a shard
+    int shift[MAX_BUFFERS];                // deterministic schedule of the round
+};
+
+// The arguments stay in the kernel argument segment and are read again (scalar loads) by every item that needs them: kept
+// in scalar registers across the phases they were 500 spills.
+#define SPLIT_ARG const __attribute__((address_space(4)))
+
 struct SplitArgs {
     const float *x, *w;              // samples, states
     const unsigned char *frag;       // W x frag_bytes
     const float *hs;                 // W x kpad: -|v_c|^2/2 * sx * sw, SPLIT_PAD_SCORE for the padding rows
-    const SplitState *state;         // W
     const float *ms;                 // dpad: -m_j * sx, zero past d
     const float *xmeta;              // sx
     const double *colscale;          // d scales of the fixed-point sums, then d inverse scales
     int *idx;                        // W x b assignments (null: not stored)
     float *part;                     // shares x W x k x d sums of a share's samples
     int *cntpart;                    // shares x W x k samples per centroid
-    int32_t *dump;                   // W x b of this step, or null
     long long *counters;
     size_t frag_bytes;
-    long long H, row0;
+    long long H;
     int k, d, b, W, kpad, nblk, dpad;
     int shares, share_len;           // share_len: samples of a share, a multiple of 64
+    int sum_shares, sum_len, dc, ncol;       // sums in a phase of their own: shares, columns per item, groups of columns
     int resident, fused, vec4;
     unsigned off_cells, off_cnt, off_hs, off_ms, off_args;
 };
@@ -60,7 +80,7 @@ __device__ __forceinline__ float split_sum(u64 cell, int count, double inv)
 // The samples of a wave (rows 0 .. nv-1 of xg, their centroids in args) into the cells.  A lane keeps its columns (four,
 // or two where rows are not 16-byte aligned) and their scales; eight or sixteen rows in flight: the reads hit a cache, and
 // with fewer in flight this pass was a chain of their latencies (75 columns, 256 workers: half of the launch).
-__device__ inline void split_accumulate(const SplitArgs &a, const float *xg, int nv, const int *args, u64 *cells, int *cnt)
+__device__ inline void split_accumulate(SPLIT_ARG SplitArgs &a, const float *xg, int nv, const int *args, u64 *cells, int *cnt)
 {
     const int lane = threadIdx.x & 63, d = a.d;
     if (lane < nv) atomicAdd(&cnt[args[lane]], 1);
@@ -118,7 +138,7 @@ __device__ inline void split_accumulate(const SplitArgs &a, const float *xg, int
 }
 
 // Sums and counts of a workgroup's cells to the share's row of `part`.
-__device__ inline void split_flush(const SplitArgs &a, int worker, int share, const u64 *cells, const int *cnt)
+__device__ inline void split_flush(SPLIT_ARG SplitArgs &a, int worker, int share, const u64 *cells, const int *cnt)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6, d = a.d;
     float *out = a.part + ((size_t)share * a.W + worker) * a.k * d;
@@ -157,7 +177,7 @@ __device__ __forceinline__ void split_init_acc(sfloatx16 &acc, const float *hs, 
 }
 
 // What a workgroup does once a group's best scores are known, the same in both assignment kernels.
-__device__ __forceinline__ void split_finish_group(const SplitArgs &a, SplitTop (&top)[2], float (&n2)[2], int worker, int g,
+__device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const SplitStep &now, SplitTop (&top)[2], float (&n2)[2], int worker, int g,
                                                    int n_hi, const float *xb, int half, int *args, u64 *cells, int *cnt,
                                                    int &rechecks)
 {
@@ -166,7 +186,7 @@ __device__ __forceinline__ void split_finish_group(const SplitArgs &a, SplitTop 
     split_combine(top, t, half);
     swap2(n2[0], n2[1]);
     const float yn = sqrtf(n2[0] + n2[1]) * 1.0001f;
-    const SplitState st = a.state[worker];
+    const SplitState st = now.state[worker];
     const float sw = st.sw, vmax = sqrtf(__uint_as_float(st.n2)) * 1.0001f * sw, sx = a.xmeta[0];
     float thr = split_c1(a.dpad) * (yn * vmax + 0.5f * vmax * vmax * (sx / sw)) + split_c2(a.dpad) * (yn + vmax);
     // a state that is not finite, or has outgrown the scale of its fp16 operands: everything in fp64
@@ -176,7 +196,7 @@ __device__ __forceinline__ void split_finish_group(const SplitArgs &a, SplitTop 
     const int arg = split_settle(t, thr, valid, xg, a.w + (size_t)worker * a.k * a.d, a.k, a.d, rechecks);
     if (valid) {
         if (a.idx) a.idx[(size_t)worker * a.b + g + lane] = arg;
-        if (a.dump) a.dump[(size_t)worker * a.b + g + lane] = arg;
+        if (now.dump) now.dump[(size_t)worker * a.b + g + lane] = arg;
     }
     if (a.fused) {
         args[lane] = valid ? arg : 0;
@@ -188,7 +208,7 @@ __device__ __forceinline__ void split_finish_group(const SplitArgs &a, SplitTop 
     }
 }
 
-__device__ __forceinline__ void split_count_rechecks(const SplitArgs &a, int worker, int rechecks)
+__device__ __forceinline__ void split_count_rechecks(SPLIT_ARG SplitArgs &a, int worker, int rechecks)
 {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) rechecks += __shfl_xor(rechecks, off, 64);
@@ -201,10 +221,8 @@ __device__ __forceinline__ void split_count_rechecks(const SplitArgs &a, int wor
 // through two stages.  fused: the gradient sums are formed right away from a second, coalesced read of the wave's
 // samples (in a cache still), in 64-bit fixed-point cells in LDS.
 template <int NC>
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NC <= 2 ? 3 : 2, NC <= 2 ? 3 : 2))) void split_assign_kernel(SplitArgs a)
+__device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-    const int worker = blockIdx.x % a.W, share = blockIdx.x / a.W;
     const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int nw = blockDim.x >> 6, npair = (a.nblk + 1) / 2;
@@ -214,9 +232,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NC <= 2 ? 3
     float *ms = reinterpret_cast<float *>(smem + a.off_ms);
     int *args = reinterpret_cast<int *>(smem + a.off_args) + wave * 64;
     const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
-    const float *xb = a.x + ((size_t)worker * a.H + (size_t)a.row0) * a.d;
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * a.d;
     const float sx = a.xmeta[0];
 
+    __syncthreads();                            // (the item before this one is done with the LDS)
     if (a.resident) split_stage(frag, smem, npair * NC * 4);
     for (int c = tid; c < a.kpad; c += blockDim.x) hs[c] = a.hs[(size_t)worker * a.kpad + c];
     for (int j = tid; j < a.dpad; j += blockDim.x) ms[j] = a.ms[j];
@@ -298,13 +317,749 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(NC <= 2 ? 3
                 split_insert(top[1], acc[1], 2 * rp + blk, big);
             }
         }
-        if (active) split_finish_group(a, top, n2, worker, g, n_hi, xb, half, args, cells, cnt, rechecks);
+        if (active) split_finish_group(a, now, top, n2, worker, g, n_hi, xb, half, args, cells, cnt, rechecks);
     }
     split_count_rechecks(a, worker, rechecks);
     if (a.fused) {
         __syncthreads();
         split_flush(a, worker, share, cells, cnt);
     }
+}
+
+// ---- assignment for rows of more than 128 columns ----
+// The operands of the samples do not fit the registers: for every pair of row blocks the samples' columns are read
+// again (from a cache) and split again, eight chunks of 16 columns per stage of the state's operands.
+__device__ inline void split_assign_long_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
+{
+    const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int nw = blockDim.x >> 6, npair = (a.nblk + 1) / 2, ncg = a.dpad / 128, nstage = npair * ncg;
+    float *hs = reinterpret_cast<float *>(smem + a.off_hs);
+    float *ms = reinterpret_cast<float *>(smem + a.off_ms);
+    const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * a.d;
+    const float sx = a.xmeta[0];
+    __syncthreads();
+    for (int c = tid; c < a.kpad; c += blockDim.x) hs[c] = a.hs[(size_t)worker * a.kpad + c];
+    for (int j = tid; j < a.dpad; j += blockDim.x) ms[j] = a.ms[j];
+    __syncthreads();
+
+    int rechecks = 0;
+    const int span = nw * 64;
+    for (int g0 = n_lo; g0 < n_hi; g0 += span) {
+        const int g = g0 + wave * 64;
+        const bool active = g < n_hi;
+        const float *row[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int n = g + 32 * m + l32;
+            row[m] = xb + (size_t)(n < n_hi ? n : n_lo) * a.d;
+        }
+        float n2[2] = {0.0f, 0.0f};
+        SplitTop top[2];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            top[m].v1 = top[m].v2 = top[m].v3 = -INFINITY;
+            top[m].i1 = top[m].i2 = 0;
+        }
+        const float big = split_opaque_infinity();
+        __syncthreads();
+        split_stage(frag, smem, SPLIT_STAGE / SPLIT_PIECE);
+        sfloatx16 acc[2][2];                  // [block of the pair][tile of samples]
+        int rp = 0, cg = 0;
+        for (int st = 0; st < nstage; ++st) {
+            split_stage_wait();
+            if (st + 1 < nstage)
+                split_stage(frag + (size_t)(st + 1) * SPLIT_STAGE, smem + ((st + 1) & 1) * SPLIT_STAGE, SPLIT_STAGE / SPLIT_PIECE);
+            if (active) {
+                if (cg == 0) {
+                    split_init_acc(acc[0][0], hs, 2 * rp, half);
+                    acc[0][1] = acc[0][0];
+                    split_init_acc(acc[1][0], hs, 2 * rp + 1, half);
+                    acc[1][1] = acc[1][0];
+                }
+                const half8 *A = reinterpret_cast<const half8 *>(smem + (st & 1) * SPLIT_STAGE) + lane;
+                // (columns past d: the last stage is zero there; their loads are clamped)
+                const bool last = cg + 1 == ncg;
+                auto chunks = [&](auto tail) {
+                    constexpr bool TAIL = decltype(tail)::value;
+                    // four chunks' columns in flight while four are multiplied (with one, the loop was a chain of
+                    // cache latencies)
+                    constexpr int PF = 4;
+                    float v[PF][2][8];
+#pragma unroll
+                    for (int q = 0; q < PF; ++q)
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) split_load8<TAIL>(v[q][m], row[m], cg * 128 + q * 16 + 8 * half, a.d);
+#pragma unroll
+                    for (int ch = 0; ch < 8; ++ch) {
+                        const int col = cg * 128 + ch * 16 + 8 * half;
+                        half8 bh[2], bl[2];
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) {
+                            float q = 0.0f;
+                            split_convert<TAIL>(v[ch % PF][m], sx, ms, col, a.d, bh[m], bl[m], q);
+                            n2[m] += rp == 0 ? q : 0.0f;
+                        }
+                        if (ch + PF < 8) {
+#pragma unroll
+                            for (int m = 0; m < 2; ++m) split_load8<TAIL>(v[ch % PF][m], row[m], col + PF * 16, a.d);
+                        }
+#pragma unroll
+                        for (int blk = 0; blk < 2; ++blk) {
+                            const half8 ah = A[ch * 256 + blk * 128], al = A[ch * 256 + blk * 128 + 64];
+#pragma unroll
+                            for (int m = 0; m < 2; ++m) {
+                                acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[m], acc[blk][m], 0, 0, 0);
+                                acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[m], acc[blk][m], 0, 0, 0);
+                                acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[m], acc[blk][m], 0, 0, 0);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                if (last) chunks(std::true_type());
+                else chunks(std::false_type());
+                if (last) {
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        split_insert(top[m], acc[0][m], 2 * rp, big);
+                        split_insert(top[m], acc[1][m], 2 * rp + 1, big);
+                    }
+                }
+            }
+            if (++cg == ncg) { cg = 0; ++rp; }
+        }
+        if (active) split_finish_group(a, now, top, n2, worker, g, n_hi, xb, half, nullptr, nullptr, nullptr, rechecks);
+    }
+    split_count_rechecks(a, worker, rechecks);
+}
+
+// ---- gradient sums of a (worker, share, group of dc columns) where the cells of a whole state do not fit LDS ----
+// 64-bit fixed-point cells as in the fused form; a wave takes 64 / dc rows at a time.
+__device__ inline void split_sums_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, int chunk, unsigned char *smem)
+{
+    const int dc = a.dc;
+    u64 *cells = reinterpret_cast<u64 *>(smem);
+    int *cnt = reinterpret_cast<int *>(smem + (size_t)a.k * dc * sizeof(u64));
+    const int n_lo = share * a.sum_len, n_hi = min(a.b, n_lo + a.sum_len);
+    const int tid = threadIdx.x, d = a.d;
+    __syncthreads();
+    for (int e = tid; e < a.k * dc; e += blockDim.x) cells[e] = 0;
+    for (int c = tid; c < a.k; c += blockDim.x) cnt[c] = 0;
+    __syncthreads();
+    const int col = tid % dc, j = chunk * dc + col, R = blockDim.x / dc;
+    const bool ok = j < d;
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * d + (ok ? j : 0);
+    const int *idx = a.idx + (size_t)worker * a.b;
+    const double s = a.colscale[ok ? j : 0];
+    for (int n0 = n_lo + tid / dc; n0 < n_hi; n0 += 8 * R) {
+        float v[8];
+        int c[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            const int n = min(n0 + u * R, n_hi - 1);
+            c[u] = idx[n];
+            v[u] = xb[(size_t)n * d];
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (n0 + u * R < n_hi) {
+                split_add(cells + c[u] * dc + col, split_term(v[u], s));
+                if (col == 0) atomicAdd(&cnt[c[u]], 1);
+            }
+    }
+    __syncthreads();
+    float *out = a.part + ((size_t)share * a.W + worker) * a.k * d;
+    for (int e = tid; e < a.k * dc; e += blockDim.x) {
+        const int c = e / dc, jj = chunk * dc + e - c * dc;
+        if (jj < d) out[(size_t)c * d + jj] = split_sum(cells[e], cnt[c], a.colscale[d + jj]);
+    }
+    if (chunk == 0) {
+        int *oc = a.cntpart + ((size_t)share * a.W + worker) * a.k;
+        for (int c = tid; c < a.k; c += blockDim.x) oc[c] = cnt[c];
+    }
+}
+
+// ---- merge, update, send and the operands of the next assignment ----
+// A worker's rows are dealt to `blocks` workgroups.  What they need to know of the whole state goes through device
+// memory between phases: the three sums of Eq. 4 (partial sums per workgroup, added in order), the largest |v| and
+// row norm (integer maxima of bit patterns, which do not depend on the order), and the power of two the fp16 operands
+// are scaled with, which follows the state one step behind.
+struct SplitShared {                       // start of the LDS: the step, and space of the gate and update phases
+    SplitStep now;
+    double red[8];
+    int delta;
+    unsigned most[2][8];
+};
+struct SplitGate { double lhs, rhs, nrm; };
+struct SplitMail { int has, round[MAX_BUFFERS]; };     // messages of a merge point: buffers that hold one, their rounds
+
+struct SplitUpdate {
+    unsigned char *frag;
+    float *hs;
+    SplitState *state;                     // 3 x W
+    SplitGate *gate;                       // W x buffers x blocks
+    SplitMail *mail;                       // W
+    const float *m, *xmeta, *part;
+    const int *cntpart;
+    size_t frag_bytes;
+    int kpad, dpad, shares, g, blocks;     // g: lanes per row, a power of two; blocks: workgroups per worker
+};
+
+// scale that takes the largest |v| to [2^9, 2^10): 2^6 below the largest fp16 number, should the state grow
+__device__ __forceinline__ float split_state_scale(unsigned vabs)
+{
+    int q = 0;
+    const float v = __uint_as_float(vabs);
+    if (v > 0.0f && v < 3.0e38f) (void)frexpf(v, &q);
+    return ldexpf(1.0f, max(-100, min(100, 10 - q)));
+}
+
+// the columns of the slots [j0, j0 + 8) of an array row (see split_column)
+__device__ __forceinline__ void split_row8(float (&v)[8], const float *row, int j0, int d) { split_load8<true>(v, row, j0, d); }
+__device__ __forceinline__ void split_put8(float *row, const float (&v)[8], int j0, int d)
+{
+    if (j0 + 8 <= d) {
+        float4u a, b;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { a[e] = v[e]; b[e] = v[4 + e]; }
+        *reinterpret_cast<float4u *>(row + j0) = a;
+        *reinterpret_cast<float4u *>(row + j0 + 4) = b;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (split_slot_used(j0 + e, d)) row[split_column(j0 + e, d)] = v[e];
+    }
+}
+// samples of centroid c, sums of eight columns of a row over the shares of the mini-batch, four shares in flight
+__device__ __forceinline__ int split_count(SPLIT_ARG SplitUpdate &u, int W, int k, int i, int c)
+{
+    int n = 0;
+    for (int s0 = 0; s0 < u.shares; s0 += 4) {
+        int v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = u.cntpart[((size_t)min(s0 + q, u.shares - 1) * W + i) * k + c];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) n += s0 + q < u.shares ? v[q] : 0;
+    }
+    return n;
+}
+__device__ __forceinline__ void split_sums8(float (&sm)[8], SPLIT_ARG SplitUpdate &u, int W, int k, int i, int c, int j0, int d)
+{
+    split_row8(sm, u.part + ((size_t)i * k + c) * d, j0, d);
+    for (int s0 = 1; s0 < u.shares; s0 += 4) {
+        float v[4][8];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) split_row8(v[q], u.part + (((size_t)min(s0 + q, u.shares - 1) * W + i) * k + c) * d, j0, d);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) sm[e] += s0 + q < u.shares ? v[q][e] : 0.0f;
+    }
+}
+
+__device__ double split_block_sum(double v, double *red)
+{
+    v = split_wave_sum(v);
+    const int wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) red[wave] = v;
+    __syncthreads();
+    double t = 0.0;
+    for (int q = 0; q < nw; ++q) t += red[q];
+    return t;
+}
+
+// The three sums of Eq. 4 over the used slots of a group of eight columns.
+__device__ __forceinline__ void split_gate8(const float (&wv)[8], const float (&sm)[8], const float (&ev)[8], int cn, int j0,
+                                            SPLIT_ARG StepParams &p, double &lhs, double &rhs, double &nrm)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const bool used = split_slot_used(j0 + e, p.d);
+        const float gq = ((float)cn * wv[e] - sm[e]) / (float)p.b;          // descent gradient of Eq. 9, (c_k w_k - S_k) / b
+        const double we = used ? (double)ev[e] : 0.0;
+        const double q = used ? ((double)wv[e] - (double)p.eps * (double)gq) - we : 0.0, q2 = used ? (double)wv[e] - we : 0.0;
+        lhs += q * q; rhs += q2 * q2; nrm += we * we;
+    }
+}
+
+// Eq. 4 at a merge point: which buffers hold a message, and (whole states) the sums over a workgroup's rows, in fp64.
+__device__ inline void split_gate_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, const SplitStep &now, int i, int blk, double *red)
+{
+    __syncthreads();
+    const int k = p.k, d = p.d;
+    const int lane_g = threadIdx.x & (u.g - 1), ngrp = (int)blockDim.x / u.g, grp = threadIdx.x / u.g;
+    const size_t kd = (size_t)k * d;
+    const int det = p.mode == ASGD_MODE_DETERMINISTIC;
+    SplitMail mail;
+    mail.has = 0;
+    for (int n = 0; n < MAX_BUFFERS; ++n) {
+        mail.round[n] = -1;
+        if (n >= p.nb) continue;
+        const int st = __hip_atomic_load(p.stamp + exchange_buffer(now.read_parity, p.nb, n, p.W, i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (det ? (st == now.round - 1) : (st >= 0)) mail.has |= 1 << n;
+        mail.round[n] = st;
+    }
+    if (blk == 0 && threadIdx.x == 0) u.mail[i] = mail;
+    if (p.parts > 1) return;
+    const float *w = p.w + (size_t)i * kd;
+    for (int n = 0; n < p.nb; ++n) {
+        double lhs = 0.0, rhs = 0.0, nrm = 0.0;
+        if (mail.has >> n & 1) {
+            const float *ext = p.slot + exchange_buffer(now.read_parity, p.nb, n, p.W, i) * kd;
+            for (int c = blk * ngrp + grp; c < k; c += u.blocks * ngrp) {
+                const int cn = split_count(u, p.W, k, i, c);
+                for (int j0 = lane_g * 8; j0 < d; j0 += u.g * 8) {
+                    float wv[8], sm[8], ev[8];
+                    split_row8(wv, w + (size_t)c * d, j0, d);
+                    split_row8(ev, ext + (size_t)c * d, j0, d);
+                    split_sums8(sm, u, p.W, k, i, c, j0, d);
+                    split_gate8(wv, sm, ev, cn, j0, p, lhs, rhs, nrm);
+                }
+            }
+        }
+        lhs = split_block_sum(lhs, red); rhs = split_block_sum(rhs, red); nrm = split_block_sum(nrm, red);
+        if (threadIdx.x == 0) u.gate[((size_t)i * p.nb + n) * u.blocks + blk] = SplitGate{lhs, rhs, nrm};
+    }
+}
+
+// MODE 0: size of the states; 1: their operands; 2: a step; 3: a step with the 1/count step size (no exchange there);
+// 4: a step with partial messages.
+// (A template: a phase this short is mostly the fetch of its own code.)
+template <int MODE>
+__device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, const SplitStep &now, int i, int blk,
+                                         SplitShared &sh)
+{
+    constexpr bool STEP = MODE >= 2, INV_COUNT = MODE == 3, ROWWISE = MODE == 4;
+    const int tid = threadIdx.x, k = p.k, d = p.d;
+    const int lane_g = tid & (u.g - 1), ngrp = (int)blockDim.x / u.g, grp = tid / u.g;
+    const size_t kd = (size_t)k * d;
+    float *w = p.w + (size_t)i * kd;
+    unsigned char *frag = u.frag + (size_t)i * u.frag_bytes;
+    float *hs = u.hs + (size_t)i * u.kpad;
+    SplitState *st_now = u.state + (size_t)now.slot * p.W + i, *st_next = u.state + (size_t)now.slot_next * p.W + i,
+               *st_after = u.state + (size_t)now.slot_after * p.W + i;
+    const float sx = u.xmeta[0];
+    const float sw = MODE == 0 ? 1.0f : split_state_scale(st_now->vabs);
+
+    __syncthreads();                                 // (the item before this one is done with the LDS)
+    SplitMail mail;
+    mail.has = 0;
+    int delta_mask = 0;
+    if (STEP && !INV_COUNT && now.merge) {
+        // which buffers take part: Eq. 4 over the whole state, every buffer on its own (Eq. 6)
+        mail = u.mail[i];
+        if (tid == 0) {
+            int received = 0, near = 0;
+            for (int n = 0; n < p.nb && !ROWWISE; ++n) {
+                if (!(mail.has >> n & 1)) continue;
+                double lhs = 0.0, rhs = 0.0, nrm = 0.0;
+                for (int q = 0; q < u.blocks; ++q) {
+                    const SplitGate gt = u.gate[((size_t)i * p.nb + n) * u.blocks + q];
+                    lhs += gt.lhs; rhs += gt.rhs; nrm += gt.nrm;
+                }
+                if (nrm > 0.0) {                       // lambda of Eq. 3: an all-zero buffer is empty
+                    received += 1;
+                    if (p.parzen ? (lhs < rhs) : 1) delta_mask |= 1 << n;
+                    if (rhs > 0.0 && fabs(lhs - rhs) / rhs < 1e-6) near += 1;
+                }
+            }
+            sh.delta = delta_mask;
+            if (blk == 0) {
+                long long *cnp = p.counters + (size_t)i * CNT_STRIDE;
+                if (received) {
+                    cnp[CNT_RECEIVED] += received;
+                    cnp[CNT_ACCEPTED] += __builtin_popcount(delta_mask);
+                    cnp[CNT_PARZEN_NEAR] += near;
+                }
+                // (deterministic mode tests for the round and need not clear; a plain store could overtake the sender's next stamp)
+                for (int n = 0; n < p.nb && p.mode != ASGD_MODE_DETERMINISTIC; ++n)
+                    p.stamp[exchange_buffer(now.read_parity, p.nb, n, p.W, i)] = -1;
+            }
+        }
+        __syncthreads();
+        delta_mask = sh.delta;
+    }
+    if (blk == 0 && tid == 0) {
+        if (MODE != 0) st_next->sw = sw;
+        st_after->vabs = st_after->n2 = 0;               // (nobody looks at it in this launch)
+    }
+    auto peer_of = [&](int n) -> int {                   // recipient of copy n of this worker's message, -1: lost on the way
+        if (p.drop_thr && message_dropped(p.seed, now.round, i, p.drop_thr, n)) return -1;
+        if (p.mode != ASGD_MODE_DETERMINISTIC) return peer_free(p.seed, now.round, i, p.W, n);
+        const int q = i + now.shift[n];
+        return q < p.W ? q : q - p.W;
+    };
+
+    // ---- Eq. 6 (one buffer: Eq. 7), Alg. 5, update and send; operands of the new state ----
+    const int units = u.dpad / 8, nch = u.dpad / 16;
+    unsigned vabs = 0, n2max = 0;
+    const float inv_all = 1.0f / (float)(__builtin_popcount(delta_mask) + 1);
+    int nz = 0, accd = 0, near_row = 0;
+    const int rows = MODE == 1 ? u.kpad : k;             // padding rows are written once
+    for (int c = blk * ngrp + grp; c < rows; c += u.blocks * ngrp) {
+        const bool real = MODE != 1 || c < k;
+        const int cn = STEP ? split_count(u, p.W, k, i, c) : 0;
+        int rowmask = delta_mask;
+        float inv = inv_all;
+        if (ROWWISE) {
+            // partial messages: lambda, Eq. 4 and Eq. 6 row by row
+            rowmask = 0;
+            for (int n = 0; n < p.nb; ++n) {
+                if (!(mail.has >> n & 1) || !row_travels(c, mail.round[n], i, n, p.parts)) continue;
+                const float *ext = p.slot + exchange_buffer(now.read_parity, p.nb, n, p.W, i) * kd;
+                double lhs = 0.0, rhs = 0.0, nrm = 0.0;
+                for (int j0 = lane_g * 8; j0 < d; j0 += u.g * 8) {
+                    float wv[8], sm[8], ev[8];
+                    split_row8(wv, w + (size_t)c * d, j0, d);
+                    split_row8(ev, ext + (size_t)c * d, j0, d);
+                    split_sums8(sm, u, p.W, k, i, c, j0, d);
+                    split_gate8(wv, sm, ev, cn, j0, p, lhs, rhs, nrm);
+                }
+                for (int off = u.g / 2; off > 0; off >>= 1) {
+                    lhs += __shfl_xor(lhs, off, 64); rhs += __shfl_xor(rhs, off, 64); nrm += __shfl_xor(nrm, off, 64);
+                }
+                if (!(nrm > 0.0)) continue;
+                nz |= 1 << n;
+                if (rhs > 0.0 && fabs(lhs - rhs) / rhs < 1e-6) near_row = 1;
+                if (p.parzen ? (lhs < rhs) : 1) rowmask |= 1 << n;
+            }
+            accd |= rowmask;
+            inv = 1.0f / (float)(__builtin_popcount(rowmask) + 1);
+        }
+        long long seen = 0;
+        if (INV_COUNT) {
+            seen = p.ncum[(size_t)i * k + c] + cn;
+            if (lane_g == 0) p.ncum[(size_t)i * k + c] = seen;
+        }
+        float sq = 0.0f;
+        for (int un = lane_g; un < units; un += u.g) {
+            const int j0 = un * 8;
+            const int lo_e = j0 + 8 <= d ? 0 : (d >= 8 ? 8 - (d - j0) : 0), hi_e = d >= 8 || j0 + 8 <= d ? 8 : d - j0;   // slots in use
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = 0.0f;
+            if (real && j0 < d) {
+                float wn[8], mid[8];
+                split_row8(wn, w + (size_t)c * d, j0, d);
+                split_row8(mid, u.m, j0, d);
+                if (STEP) {
+                    float sm[8];
+                    split_sums8(sm, u, p.W, k, i, c, j0, d);
+                    if (INV_COUNT) {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (cn > 0) wn[e] = wn[e] + (sm[e] - (float)cn * wn[e]) / (float)seen;
+                    } else {
+                        float sum[8];
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) sum[e] = wn[e];
+                        for (int n = 0; n < p.nb; ++n)
+                            if (rowmask >> n & 1) {
+                                float ev[8];
+                                split_row8(ev, p.slot + exchange_buffer(now.read_parity, p.nb, n, p.W, i) * kd + (size_t)c * d, j0, d);
+#pragma unroll
+                                for (int e = 0; e < 8; ++e) sum[e] += ev[e];
+                            }
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) {
+                            float g = ((float)cn * wn[e] - sm[e]) / (float)p.b;
+                            if (rowmask) g += wn[e] - inv * sum[e];
+                            wn[e] = wn[e] - p.eps * g;
+                        }
+                    }
+                    split_put8(w + (size_t)c * d, wn, j0, d);
+                    if (!INV_COUNT && now.send)
+                        for (int n = 0; n < p.nb; ++n) {
+                            const int peer = peer_of(n);
+                            if (peer >= 0 && (!ROWWISE || c % p.parts == message_part(now.round, peer, n, p.parts)))
+                                split_put8(p.slot + exchange_buffer(now.send_parity, p.nb, n, p.W, peer) * kd + (size_t)c * d, wn, j0, d);
+                        }
+                }
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    v[e] = e >= lo_e && e < hi_e ? wn[e] - mid[e] : 0.0f;
+                    sq = fmaf(v[e], v[e], sq);
+                    vabs = max(vabs, __float_as_uint(v[e]) & 0x7fffffffu);
+                }
+            }
+            if (MODE != 0) {
+                half8 hi, lo;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float y = v[e] * sw;
+                    hi[e] = (_Float16)y;
+                    lo[e] = (_Float16)(y - (float)hi[e]);
+                }
+                half8 *dst = reinterpret_cast<half8 *>(frag + ((((size_t)(c >> 6) * nch + (j0 >> 4)) * 2 + ((c >> 5) & 1)) * 2) * SPLIT_PIECE) +
+                             (c & 31) + 32 * ((j0 >> 3) & 1);
+                dst[0] = hi;
+                dst[64] = lo;
+            }
+        }
+        for (int off = u.g / 2; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+        n2max = max(n2max, __float_as_uint(sq) & 0x7fffffffu);
+        if (MODE != 0 && lane_g == 0) hs[c] = real ? -0.5f * sq * sx * sw : SPLIT_PAD_SCORE;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        vabs = max(vabs, (unsigned)__shfl_xor((int)vabs, off, 64));
+        n2max = max(n2max, (unsigned)__shfl_xor((int)n2max, off, 64));
+        if (ROWWISE) { nz |= __shfl_xor(nz, off, 64); accd |= __shfl_xor(accd, off, 64); near_row |= __shfl_xor(near_row, off, 64); }
+    }
+    if ((tid & 63) == 0) {
+        sh.most[0][tid >> 6] = vabs;
+        sh.most[1][tid >> 6] = n2max;
+        if (ROWWISE && mail.has) {
+            // buffers with a non-empty row, with an accepted row, a near-tie: whoever sets a flag first counts it
+            const int flags = nz << 8 | accd << 16 | near_row << 24, fresh = flags & ~atomicOr(&u.mail[i].has, flags);
+            u64 *cnp = (u64 *)(p.counters + (size_t)i * CNT_STRIDE);
+            if (fresh >> 8 & 15) atomicAdd(cnp + CNT_RECEIVED, (u64)__builtin_popcount(fresh >> 8 & 15));
+            if (fresh >> 16 & 15) atomicAdd(cnp + CNT_ACCEPTED, (u64)__builtin_popcount(fresh >> 16 & 15));
+            if (fresh >> 24) atomicAdd(cnp + CNT_PARZEN_NEAR, (u64)1);
+        }
+    }
+    __syncthreads();
+    if (tid < 2) {
+        // mode 0 prepares the slot that mode 1 reads, mode 1 the one the first step reads
+        SplitState *dst = MODE == 0 ? st_now : st_next;
+        unsigned *at = tid == 0 ? &dst->vabs : &dst->n2;
+        unsigned v = 0;
+        for (int q = 0; q < (int)(blockDim.x >> 6); ++q) v = max(v, sh.most[tid][q]);
+        if (u.blocks == 1) *at = v;
+        else atomicMax(at, v);
+    }
+    if (STEP && !INV_COUNT && now.send) {
+        if (now.local) {                        // the message first, then its stamp (in the phases form the launch ends in between)
+            __threadfence();
+            __syncthreads();
+        }
+        if (blk != 0 || tid != 0) return;
+        for (int n = 0; n < p.nb; ++n) {
+            const int peer = peer_of(n);
+            if (peer >= 0)
+                __hip_atomic_store(p.stamp + exchange_buffer(now.send_parity, p.nb, n, p.W, peer), now.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        p.counters[(size_t)i * CNT_STRIDE + CNT_SENT] += 1;
+    }
+}
+
+
+// ---- the launches ----
+struct SplitRun {
+    StepParams p;
+    SplitArgs a;
+    SplitUpdate u;
+    long long t0, t1, round0;              // local form: steps of the launch, round of the first
+    int te0;                               // first step's place in its round
+    int sync;                              // workers wait for each other's messages (deterministic exchange)
+};
+struct SplitLaunch {                       // arguments of a phase
+    SplitRun run;
+    SplitStep now;
+};
+
+// The items are functions that are really called, each with registers of its own: inlined into one loop over the steps
+// the compiler kept the values of all phases at once, hundreds of spills.  A call passes its arguments in vector
+// registers; what is uniform is read back into scalar ones.  The LDS starts with what all phases share.
+extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
+constexpr unsigned SPLIT_LDS_SHARED = 512;
+static_assert(sizeof(SplitShared) <= SPLIT_LDS_SHARED, "room at the start of the LDS");
+typedef SPLIT_ARG SplitRun *SplitRunPtr;
+__device__ __forceinline__ int split_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+__device__ __forceinline__ SplitRunPtr split_uniform(u64 p)
+{
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)p), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(p >> 32));
+    return (SplitRunPtr)((u64)hi << 32 | lo);
+}
+__device__ __forceinline__ SplitShared &split_shared() { return *reinterpret_cast<SplitShared *>(split_lds); }
+
+template <int NC>
+__device__ __noinline__ void split_assign_call(u64 run, int worker, int share)
+{
+    SplitRunPtr r = split_uniform(run);
+    const SplitStep now = split_shared().now;
+    if constexpr (NC == 0) split_assign_long_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
+    else split_assign_item<NC>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
+}
+__device__ __noinline__ inline void split_sums_call(u64 run, int worker, int share, int chunk)
+{
+    SplitRunPtr r = split_uniform(run);
+    const SplitStep now = split_shared().now;
+    split_sums_item(r->a, now, split_uniform(worker), split_uniform(share), split_uniform(chunk), split_lds + SPLIT_LDS_SHARED);
+}
+__device__ __noinline__ inline void split_gate_call(u64 run, int worker, int blk)
+{
+    SplitRunPtr r = split_uniform(run);
+    const SplitStep now = split_shared().now;
+    split_gate_item(r->p, r->u, now, split_uniform(worker), split_uniform(blk), split_shared().red);
+}
+template <int MODE>
+__device__ __noinline__ void split_update_call(u64 run, int worker, int blk)
+{
+    SplitRunPtr r = split_uniform(run);
+    const SplitStep now = split_shared().now;
+    split_update_item<MODE>(r->p, r->u, now, split_uniform(worker), split_uniform(blk), split_shared());
+}
+
+// Phases form.  WHAT: 0..4 modes of the update, 5 Eq. 4, 6 gradient sums, 10 + NC assignment (10: long rows)
+template <int WHAT>
+__global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(WHAT >= 13 || WHAT == 10 ? 2 : 3)))
+void split_phase_kernel(SplitLaunch args)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    (void)args;
+    typedef SPLIT_ARG SplitLaunch *LaunchPtr;
+    LaunchPtr l = (LaunchPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    SplitStep now;
+    now.slot = l->now.slot; now.slot_next = l->now.slot_next; now.slot_after = l->now.slot_after;
+    now.merge = l->now.merge; now.send = l->now.send; now.round = l->now.round;
+    now.read_parity = l->now.read_parity; now.send_parity = l->now.send_parity; now.local = 0;
+    now.state = l->now.state; now.dump = l->now.dump; now.row0 = l->now.row0;
+    for (int n = 0; n < MAX_BUFFERS; ++n) now.shift[n] = l->now.shift[n];
+    const int W = l->run.p.W, worker = blockIdx.x % W, rest = blockIdx.x / W;
+    if constexpr (WHAT >= 11) {
+        split_assign_item<WHAT - 10>(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
+    } else if constexpr (WHAT == 10) {
+        split_assign_long_item(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
+    } else if constexpr (WHAT == 6) {
+        const int ncol = l->run.a.ncol;
+        split_sums_item(l->run.a, now, worker, rest / ncol, rest % ncol, lds + SPLIT_LDS_SHARED);
+    } else if constexpr (WHAT == 5) {
+        split_gate_item(l->run.p, l->run.u, now, worker, rest, reinterpret_cast<SplitShared *>(lds)->red);
+    } else {
+        split_update_item<WHAT>(l->run.p, l->run.u, now, worker, rest, *reinterpret_cast<SplitShared *>(lds));
+    }
+}
+template <int WHAT>
+hipError_t split_launch_phase(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s)
+{
+    const hipError_t e = hipFuncSetAttribute((const void *)split_phase_kernel<WHAT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(split_phase_kernel<WHAT>, dim3(blocks), dim3(threads), lds, s, l);
+    return hipGetLastError();
+}
+
+// Bounded wait for a flag another workgroup writes, by one thread.  All the waits of a workgroup draw on one budget of polls
+// (about half a microsecond each) that grows with the rounds of the launch; when it is used up it waits for nothing any
+// more, so a launch outlasts its normal duration by a fraction of a second at most.
+__device__ inline bool split_wait_flag(const int *flag, int want, bool at_least, int &budget)
+{
+    while (budget > 0) {
+        const int v = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (at_least ? v >= want : v == want) return true;
+        __builtin_amdgcn_s_sleep(8);
+        --budget;
+    }
+    return false;
+}
+
+// Local form.  NC: chunks of 16 columns of a row, 0: long rows.  Workgroup g has the workers g, g + grid, ...; every wait
+// is for an event of an earlier round, and a workgroup does a step of all its workers before the next step of any, so
+// the waits cannot form a cycle.
+template <int NC>
+__global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void split_local_kernel(SplitRun args)
+{
+    (void)args;
+    SplitRunPtr r = (SplitRunPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    const u64 run = (u64)r;
+    SplitShared &sh = split_shared();
+    SplitStep now;
+    now.merge = now.send = now.round = now.read_parity = now.send_parity = 0;
+    now.local = 1;
+    now.slot = 0; now.slot_next = 1; now.slot_after = 2;
+    now.state = nullptr; now.dump = nullptr; now.row0 = 0;
+    for (int n = 0; n < MAX_BUFFERS; ++n) now.shift[n] = 0;
+    const int W = r->p.W;
+    const bool det = r->p.mode == ASGD_MODE_DETERMINISTIC;
+    int budget = 0;
+    if (threadIdx.x == 0) {
+        const long long rounds = r->p.E > 0 ? (r->t1 - r->t0) / r->p.E + 1 : 0;
+        budget = r->p.wait_polls > 0 ? r->p.wait_polls : (1 << 18) + 4096 * (int)min(rounds, 65536LL);
+        sh.now = now;
+    }
+    auto wait = [&](const int *flag, int want, bool at_least) {            // (thread 0)
+        if (budget > 0 && !split_wait_flag(flag, want, at_least, budget))
+            __hip_atomic_store(r->p.error_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    };
+    __syncthreads();
+    for (int i = blockIdx.x; i < W; i += gridDim.x) {
+        split_update_call<0>(run, i, 0);
+        __syncthreads();
+        split_update_call<1>(run, i, 0);
+    }
+    int te = r->te0;
+    long long t = r->t0, round = r->round0, s = t % r->p.S;
+    for (; t < r->t1; ++t) {
+        const int old = now.slot;
+        now.slot = now.slot_next; now.slot_next = now.slot_after; now.slot_after = old;
+        if (r->p.E > 0) {
+            now.round = (int)round;
+            now.merge = t > 0 && te == 0;
+            now.send = W > 1 && te + 1 == r->p.E;
+            now.read_parity = det ? (int)((round - 1) & 1) : 0;
+            now.send_parity = det ? (int)(round & 1) : 0;
+            if (now.send && det)
+                for (int n = 0; n < MAX_BUFFERS; ++n)
+                    if (n < r->p.nb) now.shift[n] = shift_deterministic(r->p.seed, round, W, n);
+            if (++te == r->p.E) { te = 0; ++round; }
+        }
+        now.state = r->u.state + (size_t)now.slot * W;
+        now.row0 = s * r->p.b;
+        now.dump = r->p.dump ? r->p.dump + (size_t)(t - r->p.t_dump0) * W * r->p.b : nullptr;
+        if (++s == r->p.S) s = 0;
+        __syncthreads();
+        if (threadIdx.x == 0) sh.now = now;
+        __syncthreads();
+        for (int i = blockIdx.x; i < W; i += gridDim.x) {
+            split_assign_call<NC>(run, i, 0);
+            if (!r->a.fused)
+                for (int q = 0; q < r->a.ncol; ++q) split_sums_call(run, i, 0, q);
+            if (r->sync && now.merge) {
+                // the messages of the last round (those sent before this launch are there)
+                if (threadIdx.x == 0 && t > r->t0)
+                    for (int n = 0; n < r->p.nb; ++n) {
+                        const long long rs = now.round - 1;
+                        const int sender = (i - shift_deterministic(r->p.seed, rs, W, n) + W) % W;
+                        if (r->p.drop_unannounced || !message_dropped(r->p.seed, rs, sender, r->p.drop_thr, n))
+                            wait(r->p.stamp + exchange_buffer(now.read_parity, r->p.nb, n, W, i), (int)rs, false);
+                    }
+                __syncthreads();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            }
+            if (now.merge) split_gate_call(run, i, 0);
+            if (r->sync && now.send && now.round >= 2) {
+                // a recipient's buffer still holds the message of round - 2 until it has passed merge point round - 1
+                if (threadIdx.x == 0)
+                    for (int n = 0; n < r->p.nb; ++n) {
+                        const int q = i + now.shift[n];
+                        wait(r->p.consumed + (q < W ? q : q - W), now.round - 1, true);
+                    }
+                __syncthreads();
+            }
+            if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3>(run, i, 0);
+            else split_update_call<2>(run, i, 0);
+            if (r->sync && now.merge) {
+                __syncthreads();
+                if (threadIdx.x == 0) __hip_atomic_store(r->p.consumed + i, now.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+}
+
+template <int NC>
+hipError_t split_launch_local(const SplitRun &r, int blocks, unsigned lds, hipStream_t s)
+{
+    const void *kern = (const void *)split_local_kernel<NC>;
+    hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    SplitRun rr = r;
+    void *args[] = {&rr};
+    if (r.sync && r.p.cooperative) return hipLaunchCooperativeKernel(kern, dim3(blocks), dim3(SPLIT_THREADS), args, lds, s);
+    hipLaunchKernelGGL(split_local_kernel<NC>, dim3(blocks), dim3(SPLIT_THREADS), lds, s, rr);
+    return hipGetLastError();
 }
 
 }  // namespace asgd

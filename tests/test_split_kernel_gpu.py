@@ -7,7 +7,7 @@ from tests.test_parity_gpu import B, make_data, run_both, to_dev  # noqa: F401  
 
 pytestmark = pytest.mark.gpu
 
-ONE_WORKGROUP = 1      # ASGD_OPT_TUNE of the shape-agnostic kernel: one workgroup per worker
+ONE_WORKGROUP, SPLIT = 1, 2      # ASGD_OPT_TUNE of the shape-agnostic kernel: which form, whatever the size
 
 
 # row lengths around the groups of 8 and chunks of 16 columns, the last one with its operands in registers (128) and the
@@ -22,9 +22,9 @@ ONE_WORKGROUP = 1      # ASGD_OPT_TUNE of the shape-agnostic kernel: one workgro
 def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
     H = max(3 * b + 7, k)
     X = make_data(W * H + 1, d, k, seed=100 + d)
-    g, _ = run_both(B, oracle, X, k, W, b, 0.05, E, 7, kernel=B.KERNEL_GENERIC, buffers=buffers, parts=parts)
-    assert g.stats().launches > 7                     # launches of its own for every step
-    again = B.ASGD(k, d, W, b, 0.05, E=E, kernel=B.KERNEL_GENERIC, buffers=buffers, parts=parts)
+    g, _ = run_both(B, oracle, X, k, W, b, 0.05, E, 7, kernel=B.KERNEL_GENERIC, tune=SPLIT, buffers=buffers,
+                    parts=parts)
+    again = B.ASGD(k, d, W, b, 0.05, E=E, kernel=B.KERNEL_GENERIC, tune=SPLIT, buffers=buffers, parts=parts)
     again.load_shards(to_dev(X))
     again.run_steps(3)
     again.run_steps(4)
@@ -40,7 +40,7 @@ def test_split_kernel_running_mean(B, oracle, k, d, b):
 def pair(B, X, k, W, b, steps, w0=None, **kw):
     """States of the matrix-core form and of the one-workgroup form, same run."""
     out = []
-    for tune in (0, ONE_WORKGROUP):
+    for tune in (SPLIT, ONE_WORKGROUP):
         g = B.ASGD(k, X.shape[1], W, b, 0.1, E=2, kernel=B.KERNEL_GENERIC, tune=tune, **kw)
         g.load_shards(to_dev(X))
         if w0 is not None:
