@@ -83,6 +83,9 @@ int quant_partials_count();
 // below picks one and adds the partials in a fixed order)
 hipError_t launch_quant_error_small(const float *x, long long N, int d, int k, const float *w, double *partials, int nblocks,
                                     hipStream_t s);   // shapes of small_kernel_supports()
+bool split_quant_supports(int k, int d);
+hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, const float *w, double *partials, int nblocks,
+                                    bool nan_is_inf, hipStream_t s);
 bool mfma_quant_error_supports(int k, int d, const void *x);
 hipError_t launch_quant_error_mfma(const float *x, long long N, int d, int k, const float *w, double *partials,
                                    int nblocks, hipStream_t s);

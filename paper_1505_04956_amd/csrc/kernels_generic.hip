@@ -491,6 +491,9 @@ hipError_t launch_quant_error(const float *x, long long N, int d, int k, const f
     hipError_t e = hipSuccess;
     if (small_kernel_supports(k, d, 1)) {
         e = launch_quant_error_small(x, N, d, k, w, partials, nparts, s);           // streaming shape: HBM bound
+    } else if (split_quant_supports(k, d)) {
+        nparts = 256;                                                           // one workgroup per compute unit
+        e = launch_quant_error_split(x, N, d, k, w, partials, nparts, !mfma_quant_error_supports(k, d, x), s);
     } else if (mfma_quant_error_supports(k, d, x)) {
         nparts = 256;                                                           // one workgroup per CU
         e = launch_quant_error_mfma(x, N, d, k, w, partials, nparts, s);       // contraction shape: matrix cores

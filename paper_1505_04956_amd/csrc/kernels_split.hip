@@ -1,10 +1,20 @@
 // Step kernel for any row length, host side: preparation of a call, sizes of the work items, launch.
 #include <string.h>
 
+#include "split_quant.h"
 #include "split_steps.h"
 
 namespace asgd {
 
+hipError_t launch_split_quant_0(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_1(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_2(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_3(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_4(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_5(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_6(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_7(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_8(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_local_0(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_0(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_local_1(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
@@ -331,6 +341,37 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, v
         ++*launches;
     }
     return e;
+}
+
+// ---- Eq. 8 ----
+bool split_quant_supports(int k, int d) { return k >= 2 && k <= 8192 && d <= 8192; }
+
+hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, const float *w, double *partials, int nblocks,
+                                    bool nan_is_inf, hipStream_t s)
+{
+    SplitQuant a;
+    a.x = x; a.w = w; a.N = N; a.partials = partials; a.k = k; a.d = d;
+    a.dpad = d > 128 ? (d + 127) / 128 * 128 : (d + 15) / 16 * 16;
+    a.nblk = (k + 31) / 32;
+    const int npair = (a.nblk + 1) / 2, chunks = d > 128 ? 8 : a.dpad / 16;
+    a.kpad = npair * 64;
+    a.nan_is_inf = nan_is_inf;
+    const size_t all = (size_t)npair * chunks * 4 * SPLIT_PIECE, two = (size_t)2 * chunks * 4 * SPLIT_PIECE;
+    a.resident = d <= 128 && all + (size_t)(a.kpad + a.dpad) * 4 <= SPLIT_LDS;
+    unsigned o = (unsigned)(a.resident ? all : two);
+    a.off_hs = o; o += round16((size_t)a.kpad * 4);
+    a.off_m = o;  o += round16((size_t)a.dpad * 4);
+    switch (d > 128 ? 0 : chunks) {
+        case 0: return launch_split_quant_0(a, nblocks, o, s);
+        case 1: return launch_split_quant_1(a, nblocks, o, s);
+        case 2: return launch_split_quant_2(a, nblocks, o, s);
+        case 3: return launch_split_quant_3(a, nblocks, o, s);
+        case 4: return launch_split_quant_4(a, nblocks, o, s);
+        case 5: return launch_split_quant_5(a, nblocks, o, s);
+        case 6: return launch_split_quant_6(a, nblocks, o, s);
+        case 7: return launch_split_quant_7(a, nblocks, o, s);
+        default: return launch_split_quant_8(a, nblocks, o, s);
+    }
 }
 
 }  // namespace asgd

@@ -1,4 +1,5 @@
-// Step kernels for rows of 33 to 48 columns.
+// Step and Eq. 8 kernels for rows of 33 to 48 columns.
+#include "split_quant.h"
 #include "split_steps.h"
 
 namespace asgd {
@@ -10,6 +11,10 @@ hipError_t launch_split_local_3(const SplitRun &r, int blocks, unsigned lds, hip
 hipError_t launch_split_assign_3(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s)
 {
     return split_launch_phase<13>(l, blocks, threads, lds, s);
+}
+hipError_t launch_split_quant_3(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s)
+{
+    return split_launch_quant<3>(a, blocks, lds, s);
 }
 
 }  // namespace asgd

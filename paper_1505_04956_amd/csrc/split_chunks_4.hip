@@ -1,4 +1,5 @@
-// Step kernels for rows of 49 to 64 columns.
+// Step and Eq. 8 kernels for rows of 49 to 64 columns.
+#include "split_quant.h"
 #include "split_steps.h"
 
 namespace asgd {
@@ -10,6 +11,10 @@ hipError_t launch_split_local_4(const SplitRun &r, int blocks, unsigned lds, hip
 hipError_t launch_split_assign_4(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s)
 {
     return split_launch_phase<14>(l, blocks, threads, lds, s);
+}
+hipError_t launch_split_quant_4(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s)
+{
+    return split_launch_quant<4>(a, blocks, lds, s);
 }
 
 }  // namespace asgd

@@ -17,7 +17,6 @@ namespace asgd {
 // chunks of 16; [row pair][chunk][block of the pair][hi, lo] pieces of 1 KB, piece = 64 lanes x 8 fp16, lane l holding row
 // l % 32, columns 8 * (l / 32) .. + 7 of the chunk.
 constexpr int SPLIT_THREADS = 512;
-constexpr int SPLIT_PIECE = 1024;                    // bytes
 constexpr int SPLIT_STAGE = 8 * 4 * SPLIT_PIECE;     // a row pair's eight chunks: what the long-row kernel stages at a time
 
 struct SplitState {                // one per worker and step modulo 3

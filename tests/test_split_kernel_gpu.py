@@ -82,3 +82,39 @@ def test_split_kernel_leaves_non_finite_samples_to_the_other_form(B, value):
     X[777, 5] = value
     (wa, sa), (wb, sb) = pair(B, X, k, W, b, 6)
     assert np.array_equal(wa, wb, equal_nan=True) and sa.launches == sb.launches
+
+
+def quant_error(B, X, w):
+    import torch
+    Xd, wd = to_dev(X), to_dev(w)
+    out = torch.zeros(1, dtype=torch.float64, device=Xd.device)
+    B.asgd_quant_error_noalloc(Xd.data_ptr(), X.shape[0], w.shape[0], X.shape[1], wd.data_ptr(), out.data_ptr(),
+                               torch.cuda.current_stream().cuda_stream)
+    return float(out.cpu()[0])
+
+
+# Eq. 8 at the edges of the tiles: groups of 64 and 512 samples, blocks of 32 rows, chunks of 16 columns, state resident in
+# LDS or streamed, long rows; also far from the origin
+@pytest.mark.parametrize("k,d,N", [
+    (2, 1, 1), (3, 2, 63), (5, 7, 64), (33, 8, 65), (31, 9, 511), (64, 15, 513), (65, 17, 4096), (100, 100, 3000),
+    (37, 75, 2000), (96, 127, 700), (512, 128, 1500), (2100, 40, 900), (300, 129, 800), (70, 384, 600), (12, 520, 300),
+])
+@pytest.mark.parametrize("offset", [0.0, 1.0e4])
+def test_split_quant_error_edges(B, oracle, k, d, N, offset):
+    X = make_data(N, d, k, seed=40 + d, sigma=0.5)
+    rng = np.random.default_rng(k)
+    w = (X[rng.integers(0, N, size=k)] + rng.standard_normal((k, d)) + offset).astype(np.float32)
+    X = (X + np.float32(offset)).astype(np.float32)
+    q, o = quant_error(B, X, w), oracle.quant_error(X, w.astype(np.float64))
+    # a distance is a sum of d squares in fp32, (d + 2) 2^-24 at worst; a centroid within the rounding error of the scores
+    # (a few 2^-22 of |x - m||w - m|, here at most a few hundred times the distance) may stand in for the nearest one
+    assert abs(q - o) <= ((d + 2) * 2.0 ** -24 + 2.0 ** -15) * o
+
+
+def test_split_quant_error_of_non_finite_samples(B):
+    X = make_data(1000, 13, 20, seed=9)
+    w = make_data(20, 13, 20, seed=10)
+    for value in (np.inf, np.nan):
+        Y = X.copy()
+        Y[777, 5] = value
+        assert quant_error(B, Y, w) == np.inf
