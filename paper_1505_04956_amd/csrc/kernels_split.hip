@@ -126,7 +126,7 @@ SplitPlan make_plan(const StepParams &p, bool local)
     q.npair = (q.nblk + 1) / 2;
     q.kpad = q.npair * 64;
     q.frag_bytes = (size_t)q.npair * q.nch * 4 * SPLIT_PIECE;
-    const size_t cells = (size_t)p.k * p.d * sizeof(u64) + (size_t)p.k * sizeof(int);
+    const size_t cells = (size_t)p.k * ((p.d + 1) & ~1) * sizeof(u64) + (size_t)p.k * sizeof(int);
     const size_t fixed = (size_t)q.kpad * 4 + (size_t)q.dpad * 4 + 8 * 64 * 4 + 64;
     const size_t stage2 = q.longrow ? 2 * SPLIT_STAGE : (size_t)2 * q.nch * 4 * SPLIT_PIECE;
     if (q.longrow) {
@@ -142,7 +142,7 @@ SplitPlan make_plan(const StepParams &p, bool local)
     }
     unsigned o = round16(q.resident ? q.frag_bytes : stage2);
     q.off_cells = o;
-    if (q.fused) o += round16((size_t)p.k * p.d * sizeof(u64));
+    if (q.fused) o += round16((size_t)p.k * ((p.d + 1) & ~1) * sizeof(u64));
     q.off_cnt = o;
     if (q.fused) o += round16((size_t)p.k * sizeof(int));
     q.off_hs = o;  o += round16((size_t)q.kpad * 4);
@@ -168,12 +168,14 @@ SplitPlan make_plan(const StepParams &p, bool local)
     q.share_len = (groups + q.shares - 1) / q.shares * 64;
     q.shares = (p.b + q.share_len - 1) / q.share_len;
     if (!q.fused) {
+        auto bytes = [&](int dc) { return (size_t)p.k * ((dc + 1) * 8 + 4); };
         int dc = 64;
-        while (dc > 8 && (size_t)p.k * (dc * 8 + 4) > 72 * 1024) dc /= 2;
-        while (dc > 1 && (size_t)p.k * (dc * 8 + 4) > SPLIT_LDS) dc /= 2;
+        while (dc > 8 && bytes(dc) > 72 * 1024) dc /= 2;
+        if (dc < 16 && bytes(16) <= SPLIT_LDS) dc = 16;         // (rows in pieces of 64 bytes, even with one workgroup per compute unit)
+        while (dc > 1 && bytes(dc) > SPLIT_LDS) dc /= 2;
         q.dc = dc;
         q.ncol = (p.d + dc - 1) / dc;
-        q.lds_sums = round16((size_t)p.k * (dc * 8 + 4));
+        q.lds_sums = round16(bytes(dc));
         // (every share writes and the update reads the sums of a whole state: no more than fill the device)
         int ss = local ? 1 : 2 * SPLIT_CUS / (p.W * q.ncol);
         if (ss > groups / 8) ss = groups / 8;

@@ -44,6 +44,15 @@ __device__ __forceinline__ float split_c1(int dpad)
 }
 __device__ __forceinline__ float split_c2(int dpad) { return 2.0f * 2.98023224e-8f * 1.001f * sqrtf((float)dpad); }
 
+// The lane number as a value of its own: what is derived from it (addresses, masks) is formed where it is used instead of
+// being kept in registers across the loop over the samples - 60 of them, spilled around every group.
+__device__ __forceinline__ int split_lane()
+{
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
+    return lane;
+}
+
 struct SplitTop {
     float v1, v2, v3;      // three largest scores, the accumulator register in the low mantissa bits
     int i1, i2;            // block of 32 rows (later: row) the two largest came from
@@ -143,7 +152,7 @@ __device__ __forceinline__ double split_wave_sum(double v)
 __device__ inline int split_settle(const SplitTop &t, float thr, bool valid, const float *xg, const float *w, int k, int d,
                                    int &rechecks)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = split_lane();
     int arg = min(max(t.i1, 0), k - 1);
     const int second = min(max(t.i2, 0), k - 1);
     const bool close2 = valid && !(t.v1 - t.v2 > thr);

@@ -76,61 +76,87 @@ __device__ __forceinline__ float split_sum(u64 cell, int count, double inv)
     return (float)((double)(long long)(cell - (u64)count * bias) * inv);
 }
 
-// The samples of a wave (rows 0 .. nv-1 of xg, their centroids in args) into the cells.  A lane keeps its columns (four,
-// or two where rows are not 16-byte aligned) and their scales; eight or sixteen rows in flight: the reads hit a cache, and
-// with fewer in flight this pass was a chain of their latencies (75 columns, 256 workers: half of the launch).
+// Gradient sums of a wave's samples.  A lane keeps its columns (four, or two where rows are not 16-byte aligned) and their
+// scales; a centroid's cells lie in the order (j mod 4, j / 4), or (j mod 2, j / 2), so that neighbouring lanes add to
+// neighbouring cells (in the order of j the adds of a wave fell into a quarter, or half, of the banks).  The rows come
+// from a cache; two sets of them take turns, one in flight while the other is added (with one set the pass was a chain of
+// latencies: k = d = 100, W = 512: a quarter of the launch).
+__device__ __forceinline__ int split_cell_stride(SPLIT_ARG SplitArgs &a) { return a.vec4 ? a.d : (a.d + 1) & ~1; }
+__device__ __forceinline__ int split_cell(SPLIT_ARG SplitArgs &a, int j)
+{
+    return a.vec4 ? (j & 3) * (a.d >> 2) + (j >> 2) : (j & 1) * ((a.d + 1) >> 1) + (j >> 1);
+}
+// rows 0 .. nv-1 of xg, their centroids in args
 __device__ inline void split_accumulate(SPLIT_ARG SplitArgs &a, const float *xg, int nv, const int *args, u64 *cells, int *cnt)
 {
-    const int lane = threadIdx.x & 63, d = a.d;
+    const int lane = split_lane(), d = a.d;
     if (lane < nv) atomicAdd(&cnt[args[lane]], 1);
     if (a.vec4) {
         const int q4 = d >> 2, R = 64 / q4, r = lane / q4, c = lane - r * q4;
         if (r < R) {
-            constexpr int U = 8;
+            constexpr int U = 4;
             double s[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) s[e] = a.colscale[4 * c + e];
             const float4 *src = reinterpret_cast<const float4 *>(xg) + c;
-            for (int n0 = r; n0 < nv; n0 += U * R) {
-                float4 v[U];
+            auto fetch = [&](float4 (&v)[U], int n0) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) v[u] = src[(unsigned)(min(n0 + u * R, nv - 1) * q4)];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    if (n0 + u * R < nv) {
-                        u64 *cell = cells + args[n0 + u * R] * d + 4 * c;
-                        split_add(cell + 0, split_term(v[u].x, s[0]));
-                        split_add(cell + 1, split_term(v[u].y, s[1]));
-                        split_add(cell + 2, split_term(v[u].z, s[2]));
-                        split_add(cell + 3, split_term(v[u].w, s[3]));
-                    }
-                }
-            }
-        }
-    } else {
-        // pairs of columns; the last lane of an odd row loads the pair before the end and uses its second half
-        constexpr int U = 16;
-        const int q2 = (d + 1) >> 1, R = 64 / q2, r = lane / q2, c = 2 * (lane - r * q2);
-        if (r < R) {
-            const bool odd = c + 1 == d;                       // one column left
-            const int c0 = odd ? max(d - 2, 0) : c;
-            const double s0 = a.colscale[c], s1 = a.colscale[odd ? c : c + 1];
-            for (int n0 = r; n0 < nv; n0 += U * R) {
-                float v0[U], v1[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const unsigned o = (unsigned)(min(n0 + u * R, nv - 1) * d + c0);
-                    v0[u] = xg[o];
-                    v1[u] = xg[o + (d > 1 ? 1 : 0)];
-                }
+            };
+            auto add = [&](const float4 (&v)[U], int n0) {
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     if (n0 + u * R < nv) {
                         u64 *cell = cells + args[n0 + u * R] * d + c;
-                        split_add(cell, split_term(odd ? v1[u] : v0[u], s0));
-                        if (!odd) split_add(cell + 1, split_term(v1[u], s1));
+                        split_add(cell, split_term(v[u].x, s[0]));
+                        split_add(cell + q4, split_term(v[u].y, s[1]));
+                        split_add(cell + 2 * q4, split_term(v[u].z, s[2]));
+                        split_add(cell + 3 * q4, split_term(v[u].w, s[3]));
                     }
                 }
+            };
+            float4 va[U], vb[U];
+            fetch(va, r);
+            for (int n0 = r; n0 < nv; n0 += 2 * U * R) {
+                fetch(vb, n0 + U * R);
+                add(va, n0);
+                fetch(va, n0 + 2 * U * R);
+                add(vb, n0 + U * R);
+            }
+        }
+    } else {
+        // pairs of columns; the last lane of an odd row loads the pair before the end and uses its second half
+        constexpr int U = 8;
+        const int q2 = (d + 1) >> 1, R = 64 / q2, r = lane / q2, c = lane - r * q2;
+        if (r < R) {
+            const bool odd = 2 * c + 1 == d;                   // one column left
+            const int c0 = odd ? max(d - 2, 0) : 2 * c, c1 = c0 + (d > 1 ? 1 : 0), stride = 2 * q2;
+            const double s0 = a.colscale[2 * c], s1 = a.colscale[odd ? 2 * c : 2 * c + 1];
+            auto fetch = [&](float (&v0)[U], float (&v1)[U], int n0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const float *row = xg + (unsigned)(min(n0 + u * R, nv - 1) * d);
+                    v0[u] = row[c0];
+                    v1[u] = row[c1];
+                }
+            };
+            auto add = [&](const float (&v0)[U], const float (&v1)[U], int n0) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (n0 + u * R < nv) {
+                        u64 *cell = cells + args[n0 + u * R] * stride + c;
+                        split_add(cell, split_term(odd ? v1[u] : v0[u], s0));
+                        if (!odd) split_add(cell + q2, split_term(v1[u], s1));
+                    }
+                }
+            };
+            float xa[U], ya[U], xb[U], yb[U];
+            fetch(xa, ya, r);
+            for (int n0 = r; n0 < nv; n0 += 2 * U * R) {
+                fetch(xb, yb, n0 + U * R);
+                add(xa, ya, n0);
+                fetch(xa, ya, n0 + 2 * U * R);
+                add(xb, yb, n0 + U * R);
             }
         }
     }
@@ -145,7 +171,8 @@ __device__ inline void split_flush(SPLIT_ARG SplitArgs &a, int worker, int share
     if (r < R)
         for (int j = d < 64 ? lane - r * d : lane; j < d; j += 64) {
             const double inv = a.colscale[d + j];
-            for (int c = wave * R + r; c < a.k; c += nw * R) out[c * d + j] = split_sum(cells[c * d + j], cnt[c], inv);
+            const int at = split_cell(a, j), stride = split_cell_stride(a);
+            for (int c = wave * R + r; c < a.k; c += nw * R) out[c * d + j] = split_sum(cells[c * stride + at], cnt[c], inv);
         }
     int *oc = a.cntpart + ((size_t)share * a.W + worker) * a.k;
     for (int c = threadIdx.x; c < a.k; c += blockDim.x) oc[c] = cnt[c];
@@ -180,7 +207,7 @@ __device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const
                                                    int n_hi, const float *xb, int half, int *args, u64 *cells, int *cnt,
                                                    int &rechecks)
 {
-    const int lane = threadIdx.x & 63;
+    const int lane = split_lane();
     SplitTop t;
     split_combine(top, t, half);
     swap2(n2[0], n2[1]);
@@ -239,7 +266,7 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
     for (int c = tid; c < a.kpad; c += blockDim.x) hs[c] = a.hs[(size_t)worker * a.kpad + c];
     for (int j = tid; j < a.dpad; j += blockDim.x) ms[j] = a.ms[j];
     if (a.fused) {
-        for (int e = tid; e < a.k * a.d; e += blockDim.x) cells[e] = 0;
+        for (int e = tid; e < a.k * split_cell_stride(a); e += blockDim.x) cells[e] = 0;
         for (int c = tid; c < a.k; c += blockDim.x) cnt[c] = 0;
     }
     split_stage_wait();
@@ -252,11 +279,13 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
         if (a.resident && !active) break;
         half8 bh[2][NC], bl[2][NC];
         float n2[2] = {0.0f, 0.0f};
+        // (Fetching a group's columns while the group before it is finished changed nothing where there are registers for
+        // it, and spilled where rows are long; a wave's neighbour on the SIMD works meanwhile.)
         if (active) {
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
                 const int n = g + 32 * m + l32;
-                const float *row = xb + (size_t)(n < n_hi ? n : g) * a.d;
+                const float *row = xb + (size_t)(n < n_hi ? n : n_lo) * a.d;
                 float v[NC][8];
 #pragma unroll
                 for (int ch = 0; ch + 1 < NC; ++ch) split_load8<false>(v[ch], row, ch * 16 + 8 * half, a.d);
@@ -435,48 +464,95 @@ __device__ inline void split_assign_long_item(SPLIT_ARG SplitArgs &a, const Spli
 }
 
 // ---- gradient sums of a (worker, share, group of dc columns) where the cells of a whole state do not fit LDS ----
-// 64-bit fixed-point cells as in the fused form; a wave takes 64 / dc rows at a time.
+// 64-bit fixed-point cells as in the fused form, a centroid's row padded by one so that rows start in different banks.
+// Aligned rows: four columns per lane, four rows per lane in flight (one column per lane took 356 us for 256 workers of
+// 4096 x 128 samples and 1024 centroids, most of it issuing loads).
 __device__ inline void split_sums_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, int chunk, unsigned char *smem)
 {
-    const int dc = a.dc;
+    const int dc = a.dc, stride = dc + 1, k = a.k, d = a.d, tid = threadIdx.x;
     u64 *cells = reinterpret_cast<u64 *>(smem);
-    int *cnt = reinterpret_cast<int *>(smem + (size_t)a.k * dc * sizeof(u64));
+    int *cnt = reinterpret_cast<int *>(smem + (size_t)k * stride * sizeof(u64));
     const int n_lo = share * a.sum_len, n_hi = min(a.b, n_lo + a.sum_len);
-    const int tid = threadIdx.x, d = a.d;
     __syncthreads();
-    for (int e = tid; e < a.k * dc; e += blockDim.x) cells[e] = 0;
-    for (int c = tid; c < a.k; c += blockDim.x) cnt[c] = 0;
+    for (int e = tid; e < k * stride; e += blockDim.x) cells[e] = 0;
+    for (int c = tid; c < k; c += blockDim.x) cnt[c] = 0;
     __syncthreads();
-    const int col = tid % dc, j = chunk * dc + col, R = blockDim.x / dc;
-    const bool ok = j < d;
-    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * d + (ok ? j : 0);
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * d;
     const int *idx = a.idx + (size_t)worker * a.b;
-    const double s = a.colscale[ok ? j : 0];
-    for (int n0 = n_lo + tid / dc; n0 < n_hi; n0 += 8 * R) {
-        float v[8];
-        int c[8];
+    if (a.vec4 && dc % 4 == 0) {
+        constexpr int U = 4;
+        const int L = dc / 4, col = tid % L, j = chunk * dc + 4 * col, R = blockDim.x / L, r = tid / L;
+        const bool ok = j < d;                           // (d is a multiple of four)
+        double s[4];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int n = min(n0 + u * R, n_hi - 1);
-            c[u] = idx[n];
-            v[u] = xb[(size_t)n * d];
-        }
+        for (int e = 0; e < 4; ++e) s[e] = a.colscale[ok ? j + e : 0];
+        const float *xc = xb + (ok ? j : 0);
+        float4 va[U], vb[U];
+        int ca[U], cb[U];
+        auto fetch = [&](float4 (&v)[U], int (&c)[U], int n0) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-            if (n0 + u * R < n_hi) {
-                split_add(cells + c[u] * dc + col, split_term(v[u], s));
+            for (int u = 0; u < U; ++u) {
+                const int n = min(n0 + u * R, n_hi - 1);
+                c[u] = idx[n];
+                v[u] = *reinterpret_cast<const float4 *>(xc + (size_t)n * d);
+            }
+        };
+        auto add = [&](const float4 (&v)[U], const int (&c)[U], int n0) {
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (n0 + u * R >= n_hi) continue;
+                u64 *cell = cells + c[u] * stride + col;
+                split_add(cell, split_term(v[u].x, s[0]));
+                split_add(cell + L, split_term(v[u].y, s[1]));
+                split_add(cell + 2 * L, split_term(v[u].z, s[2]));
+                split_add(cell + 3 * L, split_term(v[u].w, s[3]));
                 if (col == 0) atomicAdd(&cnt[c[u]], 1);
             }
+        };
+        if (n_lo + r < n_hi) {
+            fetch(va, ca, n_lo + r);
+            for (int n0 = n_lo + r; n0 < n_hi; n0 += 2 * U * R) {
+                fetch(vb, cb, n0 + U * R);
+                add(va, ca, n0);
+                fetch(va, ca, n0 + 2 * U * R);
+                add(vb, cb, n0 + U * R);
+            }
+        }
+    } else {
+        const int col = tid % dc, j = chunk * dc + col, R = blockDim.x / dc;
+        const bool ok = j < d;
+        const float *xc = xb + (ok ? j : 0);
+        const double s = a.colscale[ok ? j : 0];
+        for (int n0 = n_lo + tid / dc; n0 < n_hi; n0 += 8 * R) {
+            float v[8];
+            int c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int n = min(n0 + u * R, n_hi - 1);
+                c[u] = idx[n];
+                v[u] = xc[(size_t)n * d];
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (n0 + u * R < n_hi) {
+                    split_add(cells + c[u] * stride + col, split_term(v[u], s));
+                    if (col == 0) atomicAdd(&cnt[c[u]], 1);
+                }
+        }
     }
     __syncthreads();
-    float *out = a.part + ((size_t)share * a.W + worker) * a.k * d;
-    for (int e = tid; e < a.k * dc; e += blockDim.x) {
-        const int c = e / dc, jj = chunk * dc + e - c * dc;
-        if (jj < d) out[(size_t)c * d + jj] = split_sum(cells[e], cnt[c], a.colscale[d + jj]);
+    float *out = a.part + ((size_t)share * a.W + worker) * k * d;
+    {
+        const int col = tid % dc, j = chunk * dc + col;
+        const int at = a.vec4 && dc % 4 == 0 ? (col & 3) * (dc / 4) + (col >> 2) : col;
+        if (j < d) {
+            const double inv = a.colscale[d + j];
+            for (int c = tid / dc; c < k; c += blockDim.x / dc) out[(size_t)c * d + j] = split_sum(cells[c * stride + at], cnt[c], inv);
+        }
     }
     if (chunk == 0) {
-        int *oc = a.cntpart + ((size_t)share * a.W + worker) * a.k;
-        for (int c = tid; c < a.k; c += blockDim.x) oc[c] = cnt[c];
+        int *oc = a.cntpart + ((size_t)share * a.W + worker) * k;
+        for (int c = tid; c < k; c += blockDim.x) oc[c] = cnt[c];
     }
 }
 
