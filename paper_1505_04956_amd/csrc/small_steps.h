@@ -806,7 +806,7 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
     // centroid's first, i.e. into the next centroid's cells, which is harmless: nothing is written there.
     constexpr int CE = (D + 1) % 2 ? D + 1 : D + 2;
     constexpr int RPP = RL / NPART;                 // copies one lane sums in the reduction
-    static_assert(NW == 1 || NW == 2, "one or two waves per worker");
+    static_assert(NW == 1 || NW == 2 || NW == 4, "one, two or four waves per worker");
     static_assert(RS == 1 || RS == 2, "one copy of the cells per lane, or shared copies");
     static_assert(PF >= 2, "the ring needs the previous group's buffer");
     static_assert(RL % NPART == 0 && RPP % 4 == 0, "state too large for this kernel");
@@ -1123,12 +1123,12 @@ hipError_t launch_variant(const StepParams &p, long long t0, long long t1, hipSt
 {
     if (p.nb == 1 && p.parts == 1)
         return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 1, false>, 64 * NW, p, t0, t1, s, persistent);
-    if constexpr (PF <= 4 && RS == 2) {
+    if constexpr (PF <= 4 && RS == 2 && NW <= 2) {
         if (p.nb == 1) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 1, true>, 64 * NW, p, t0, t1, s, persistent);
         if (p.nb == 2) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 2, true>, 64 * NW, p, t0, t1, s, persistent);
         if (p.nb == 3) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 3, true>, 64 * NW, p, t0, t1, s, persistent);
     }
-    if constexpr (PF == 2 && RS == 2) {
+    if constexpr (PF == 2 && RS == 2 && NW <= 2) {
         if (p.nb == 4) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 4, true>, 64 * NW, p, t0, t1, s, persistent);
     }
     return hipErrorInvalidValue;
@@ -1160,13 +1160,19 @@ hipError_t launch_shape(const StepParams &p, long long t0, long long t1, hipStre
 // one wave with private cells (ALL: built for the streaming workload's own shape only, the others take shared cells).
 // tune: bits 2-3 pick the shape, bits 0-1 limit the ring depth (1: 4, 2: 2); the value 3 in bits 0-1 is handled by
 // the caller (one launch per round).
+constexpr int SMALL_FOUR_WAVES = 256;
 template <int K, int D, bool ALL>
 hipError_t launch_small_kd(const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
 {
     int shape = (p.tune >> 2) & 3;          // 0 = by number of workers, 1 = 1 wave private cells, 2 = 1 wave shared cells, 3 = 2 waves
     if (shape == 0) shape = p.W > 1024 ? 2 : 3;
     if (!ALL && shape == 1) shape = 2;
-    const int nw = shape == 3 ? 2 : 1;
+    // Four waves per worker where every worker has a compute unit to itself (the SIMDs of two would be idle) and a
+    // mini-batch has a group of 64 samples for each of them and more: k = d = 10, W = 4, b = 500: 3.53 -> 3.08 us per
+    // step, W = 256, b = 2000: 8.80 -> 5.77; k = 16, d = 12, W = 256, b = 1000: 8.70 -> 6.22.  (Two workers per compute
+    // unit: W = 512, k = d = 10 +4 % at b = 500, -10 % at b = 1000; k = 16, d = 12 up to 50 % slower: two waves there.)
+    const bool four = (p.tune & 12) == 0 && p.nb == 1 && p.parts == 1 && p.b > 256 && p.W <= SMALL_FOUR_WAVES;
+    const int nw = four ? 4 : shape == 3 ? 2 : 1;
     const int ngw = ((p.b + 63) / 64 + nw - 1) / nw;
     // ring depth: the largest of 8, 4 that divides the number of groups per mini-batch and wave, else 2
     // (the kernel then pads the group count with masked groups)
@@ -1177,6 +1183,7 @@ hipError_t launch_small_kd(const StepParams &p, long long t0, long long t1, hipS
     if constexpr (ALL) {
         if (shape == 1) return launch_shape<K, D, 1, 1>(p, t0, t1, s, persistent, pf);
     }
+    if (four) return launch_shape<K, D, 4, 2>(p, t0, t1, s, persistent, pf);
     if (shape == 2) return launch_shape<K, D, 1, 2>(p, t0, t1, s, persistent, pf);
     return launch_shape<K, D, 2, 2>(p, t0, t1, s, persistent, pf);
 }
