@@ -128,7 +128,7 @@ SplitPlan make_plan(const StepParams &p, bool local)
     q.frag_bytes = (size_t)q.npair * q.nch * 4 * SPLIT_PIECE;
     const size_t cells = (size_t)p.k * ((p.d + 1) & ~1) * sizeof(u64) + (size_t)p.k * sizeof(int);
     const size_t fixed = (size_t)q.kpad * 4 + (size_t)q.dpad * 4 + 8 * 64 * 4 + 64;
-    const size_t stage2 = q.longrow ? 2 * SPLIT_STAGE : (size_t)2 * q.nch * 4 * SPLIT_PIECE;
+    const size_t stage2 = q.longrow ? 0 : (size_t)2 * q.nch * 4 * SPLIT_PIECE;
     if (q.longrow) {
         q.resident = q.fused = false;
     } else if (q.frag_bytes + cells + fixed <= SPLIT_LDS) {
@@ -147,7 +147,7 @@ SplitPlan make_plan(const StepParams &p, bool local)
     if (q.fused) o += round16((size_t)p.k * sizeof(int));
     q.off_hs = o;  o += round16((size_t)q.kpad * 4);
     q.off_ms = o;  o += round16((size_t)q.dpad * 4);
-    q.off_args = o; o += 8 * 64 * 4;
+    q.off_args = o; o += 8 * 64 * 4 * (q.longrow ? 5 : 1);
     q.lds = o;
     // Phases: waves of a workgroup and shares of a mini-batch - enough workgroups for the compute units first, then as many
     // waves per workgroup as share the staged operands, and as many workgroups as are resident at once (three waves per
@@ -155,7 +155,15 @@ SplitPlan make_plan(const StepParams &p, bool local)
     const int groups = (p.b + 63) / 64;
     q.waves = 8;
     q.shares = 1;
-    if (!local) {
+    if (q.longrow) {
+        // (the waves of a workgroup share the row pairs of its groups of samples, see split_assign_long_item)
+        int rsplit = 1;
+        while (2 * rsplit <= q.npair && 2 * rsplit <= 8) rsplit *= 2;
+        const int max_shares = (groups + 8 / rsplit - 1) / (8 / rsplit);
+        if (!local) q.shares = (2 * SPLIT_CUS + p.W - 1) / p.W;
+        if (q.shares > max_shares) q.shares = max_shares;
+        if (q.shares > 64) q.shares = 64;
+    } else if (!local) {
         int nw = q.lds <= 50 * 1024 ? 4 : 8;
         while (nw > 1 && (long long)p.W * ((groups + nw - 1) / nw) < SPLIT_CUS) nw /= 2;
         q.waves = nw;

@@ -17,7 +17,6 @@ namespace asgd {
 // chunks of 16; [row pair][chunk][block of the pair][hi, lo] pieces of 1 KB, piece = 64 lanes x 8 fp16, lane l holding row
 // l % 32, columns 8 * (l / 32) .. + 7 of the chunk.
 constexpr int SPLIT_THREADS = 512;
-constexpr int SPLIT_STAGE = 8 * 4 * SPLIT_PIECE;     // a row pair's eight chunks: what the long-row kernel stages at a time
 
 struct SplitState {                // one per worker and step modulo 3
     float sw;                      // scale of the operands
@@ -202,16 +201,12 @@ __device__ __forceinline__ void split_init_acc(sfloatx16 &acc, const float *hs, 
     }
 }
 
-// What a workgroup does once a group's best scores are known, the same in both assignment kernels.
-__device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const SplitStep &now, SplitTop (&top)[2], float (&n2)[2], int worker, int g,
-                                                   int n_hi, const float *xb, int half, int *args, u64 *cells, int *cnt,
-                                                   int &rechecks)
+// What a wave does once the best scores of its 64 samples are known (lane l: sample l), the same in both assignment items.
+__device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const SplitStep &now, const SplitTop &t, float n2, int worker, int g,
+                                                   int n_hi, const float *xb, int *args, u64 *cells, int *cnt, int &rechecks)
 {
     const int lane = split_lane();
-    SplitTop t;
-    split_combine(top, t, half);
-    swap2(n2[0], n2[1]);
-    const float yn = sqrtf(n2[0] + n2[1]) * 1.0001f;
+    const float yn = sqrtf(n2) * 1.0001f;
     const SplitState st = now.state[worker];
     const float sw = st.sw, vmax = sqrtf(__uint_as_float(st.n2)) * 1.0001f * sw, sx = a.xmeta[0];
     float thr = split_c1(a.dpad) * (yn * vmax + 0.5f * vmax * vmax * (sx / sw)) + split_c2(a.dpad) * (yn + vmax);
@@ -345,7 +340,12 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
                 split_insert(top[1], acc[1], 2 * rp + blk, big);
             }
         }
-        if (active) split_finish_group(a, now, top, n2, worker, g, n_hi, xb, half, args, cells, cnt, rechecks);
+        if (active) {
+            SplitTop t;
+            split_combine(top, t, half);
+            swap2(n2[0], n2[1]);
+            split_finish_group(a, now, t, n2[0] + n2[1], worker, g, n_hi, xb, args, cells, cnt, rechecks);
+        }
     }
     split_count_rechecks(a, worker, rechecks);
     if (a.fused) {
@@ -356,14 +356,25 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
 
 // ---- assignment for rows of more than 128 columns ----
 // The operands of the samples do not fit the registers: for every pair of row blocks the samples' columns are read
-// again (from a cache) and split again, eight chunks of 16 columns per stage of the state's operands.
+// again (from a cache) and split again.  The waves of a workgroup share out the row pairs of a group of 64 samples (as far
+// as there are any), so that few samples still make many waves, and read the state's operands straight from the L2 into
+// registers, two chunks ahead: no stage, no barrier inside (staged in LDS with a wave per group of samples, k = 256,
+// d = 384, 64 workers: 135 us per launch, most of it waiting at the barriers of the stage).
+__device__ __forceinline__ int split_long_rows(int npair, int waves)       // waves that share a group's row pairs
+{
+    int r = 1;
+    while (2 * r <= npair && 2 * r <= waves) r *= 2;
+    return r;
+}
 __device__ inline void split_assign_long_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
 {
     const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-    const int nw = blockDim.x >> 6, npair = (a.nblk + 1) / 2, ncg = a.dpad / 128, nstage = npair * ncg;
+    const int nw = blockDim.x >> 6, npair = (a.nblk + 1) / 2, nch = a.dpad / 16;
+    const int rsplit = split_long_rows(npair, nw), rw = wave % rsplit, gw = wave / rsplit, ng = nw / rsplit;
     float *hs = reinterpret_cast<float *>(smem + a.off_hs);
     float *ms = reinterpret_cast<float *>(smem + a.off_ms);
+    float *tops = reinterpret_cast<float *>(smem + a.off_args);          // [wave][5][64]
     const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
     const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * a.d;
     const float sx = a.xmeta[0];
@@ -373,9 +384,8 @@ __device__ inline void split_assign_long_item(SPLIT_ARG SplitArgs &a, const Spli
     __syncthreads();
 
     int rechecks = 0;
-    const int span = nw * 64;
-    for (int g0 = n_lo; g0 < n_hi; g0 += span) {
-        const int g = g0 + wave * 64;
+    for (int g0 = n_lo; g0 < n_hi; g0 += ng * 64) {
+        const int g = g0 + gw * 64;
         const bool active = g < n_hi;
         const float *row[2];
 #pragma unroll
@@ -391,74 +401,81 @@ __device__ inline void split_assign_long_item(SPLIT_ARG SplitArgs &a, const Spli
             top[m].i1 = top[m].i2 = 0;
         }
         const float big = split_opaque_infinity();
-        __syncthreads();
-        split_stage(frag, smem, SPLIT_STAGE / SPLIT_PIECE);
-        sfloatx16 acc[2][2];                  // [block of the pair][tile of samples]
-        int rp = 0, cg = 0;
-        for (int st = 0; st < nstage; ++st) {
-            split_stage_wait();
-            if (st + 1 < nstage)
-                split_stage(frag + (size_t)(st + 1) * SPLIT_STAGE, smem + ((st + 1) & 1) * SPLIT_STAGE, SPLIT_STAGE / SPLIT_PIECE);
-            if (active) {
-                if (cg == 0) {
-                    split_init_acc(acc[0][0], hs, 2 * rp, half);
-                    acc[0][1] = acc[0][0];
-                    split_init_acc(acc[1][0], hs, 2 * rp + 1, half);
-                    acc[1][1] = acc[1][0];
+        for (int rp = rw; active && rp < npair; rp += rsplit) {
+            sfloatx16 acc[2][2];                  // [block of the pair][tile of samples]
+            split_init_acc(acc[0][0], hs, 2 * rp, half);
+            acc[0][1] = acc[0][0];
+            split_init_acc(acc[1][0], hs, 2 * rp + 1, half);
+            acc[1][1] = acc[1][0];
+            const half8 *A = reinterpret_cast<const half8 *>(frag + (size_t)rp * nch * 4 * SPLIT_PIECE) + lane;
+            // two chunks per set: operands of the state, columns of the samples
+            auto fetch = [&](half8 (&av)[2][4], float (&v)[2][2][8], int ch) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int c = min(ch + u, nch - 1);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) av[u][q] = A[c * 256 + q * 64];
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) split_load8<true>(v[u][m], row[m], min(c * 16 + 8 * half, (a.d - 1) & ~7), a.d);
                 }
-                const half8 *A = reinterpret_cast<const half8 *>(smem + (st & 1) * SPLIT_STAGE) + lane;
-                // (columns past d: the last stage is zero there; their loads are clamped)
-                const bool last = cg + 1 == ncg;
-                auto chunks = [&](auto tail) {
-                    constexpr bool TAIL = decltype(tail)::value;
-                    // four chunks' columns in flight while four are multiplied (with one, the loop was a chain of
-                    // cache latencies)
-                    constexpr int PF = 4;
-                    float v[PF][2][8];
+            };
+            auto multiply = [&](const half8 (&av)[2][4], const float (&v)[2][2][8], int ch) {
 #pragma unroll
-                    for (int q = 0; q < PF; ++q)
-#pragma unroll
-                        for (int m = 0; m < 2; ++m) split_load8<TAIL>(v[q][m], row[m], cg * 128 + q * 16 + 8 * half, a.d);
-#pragma unroll
-                    for (int ch = 0; ch < 8; ++ch) {
-                        const int col = cg * 128 + ch * 16 + 8 * half;
-                        half8 bh[2], bl[2];
-#pragma unroll
-                        for (int m = 0; m < 2; ++m) {
-                            float q = 0.0f;
-                            split_convert<TAIL>(v[ch % PF][m], sx, ms, col, a.d, bh[m], bl[m], q);
-                            n2[m] += rp == 0 ? q : 0.0f;
-                        }
-                        if (ch + PF < 8) {
-#pragma unroll
-                            for (int m = 0; m < 2; ++m) split_load8<TAIL>(v[ch % PF][m], row[m], col + PF * 16, a.d);
-                        }
-#pragma unroll
-                        for (int blk = 0; blk < 2; ++blk) {
-                            const half8 ah = A[ch * 256 + blk * 128], al = A[ch * 256 + blk * 128 + 64];
-#pragma unroll
-                            for (int m = 0; m < 2; ++m) {
-                                acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bl[m], acc[blk][m], 0, 0, 0);
-                                acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(al, bh[m], acc[blk][m], 0, 0, 0);
-                                acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, bh[m], acc[blk][m], 0, 0, 0);
-                            }
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                };
-                if (last) chunks(std::true_type());
-                else chunks(std::false_type());
-                if (last) {
+                for (int u = 0; u < 2; ++u) {
+                    half8 bh[2], bl[2];
 #pragma unroll
                     for (int m = 0; m < 2; ++m) {
-                        split_insert(top[m], acc[0][m], 2 * rp, big);
-                        split_insert(top[m], acc[1][m], 2 * rp + 1, big);
+                        float q = 0.0f;
+                        split_convert<true>(v[u][m], sx, ms, (ch + u) * 16 + 8 * half, a.d, bh[m], bl[m], q);
+                        n2[m] += rp == rw ? q : 0.0f;
                     }
+#pragma unroll
+                    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+                        for (int m = 0; m < 2; ++m) {
+                            acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[u][2 * blk], bl[m], acc[blk][m], 0, 0, 0);
+                            acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[u][2 * blk + 1], bh[m], acc[blk][m], 0, 0, 0);
+                            acc[blk][m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[u][2 * blk], bh[m], acc[blk][m], 0, 0, 0);
+                        }
                 }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            half8 a0[2][4], a1[2][4];
+            float v0[2][2][8], v1[2][2][8];
+            fetch(a0, v0, 0);
+            for (int ch = 0; ch < nch; ch += 4) {          // (nch is a multiple of eight)
+                fetch(a1, v1, ch + 2);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a0, v0, ch);
+                fetch(a0, v0, ch + 4);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a1, v1, ch + 2);
             }
-            if (++cg == ncg) { cg = 0; ++rp; }
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                split_insert(top[m], acc[0][m], 2 * rp, big);
+                split_insert(top[m], acc[1][m], 2 * rp + 1, big);
+            }
         }
-        if (active) split_finish_group(a, now, top, n2, worker, g, n_hi, xb, half, nullptr, nullptr, nullptr, rechecks);
+        SplitTop t;
+        split_combine(top, t, half);
+        float *mine = tops + wave * 5 * 64 + lane;
+        if (rw != 0) {
+            mine[0] = t.v1; mine[64] = t.v2; mine[128] = t.v3;
+            mine[192] = __int_as_float(t.i1); mine[256] = __int_as_float(t.i2);
+        }
+        __syncthreads();
+        if (rw == 0 && active) {
+            for (int q = 1; q < rsplit; ++q) {
+                const float *o = mine + q * 5 * 64;
+                split_merge(t, o[0], __float_as_int(o[192]));
+                split_merge(t, o[64], __float_as_int(o[256]));
+                t.v3 = fmaxf(t.v3, o[128]);
+            }
+            swap2(n2[0], n2[1]);
+            split_finish_group(a, now, t, n2[0] + n2[1], worker, g, n_hi, xb, nullptr, nullptr, nullptr, rechecks);
+        }
+        __syncthreads();                          // (tops are written again)
     }
     split_count_rechecks(a, worker, rechecks);
 }
