@@ -63,7 +63,8 @@ enum {
                                     Default auto.  All give the same results to rounding.  The kernels keep
                                     messages in flight in different formats; when the kernel changes between
                                     two runs the library carries them over (see asgd_get_exchange). */
-    ASGD_OPT_TUNE = 8,           /* launch-shape variant of the chosen kernel (0 = default); for
+    ASGD_OPT_TUNE = 8,           /* launch-shape variant of the chosen kernel (0 = default; shape-agnostic kernel: 1 one
+                                    workgroup per worker, 2 matrix cores, whatever the size); for
                                     performance experiments: the variants compute the same thing and may
                                     differ in the rounding of their sums */
     ASGD_OPT_COOPERATIVE = 9,    /* 1 (default): a run that needs all its workgroups resident at the
@@ -197,10 +198,11 @@ int asgd_set_exchange(asgd_ctx *ctx, const float *values_host, const int32_t *ro
  * Eq. 7), update w <- w - eps * step (Alg. 5, update) and, when (t+1) mod E == 0, the
  * send of the new state to one other worker (Alg. 5, send).  Returns after the work
  * has finished on the device.  The result does not depend on how a run is cut into
- * calls (deterministic mode: bit for bit), the time does: where all workers fit the
- * device at once, a call is ONE kernel launch for every 1024 communication rounds it
- * covers, and the start and the tail of a launch are then paid once per launch, not once
- * per epoch (asgd_stats.launches).
+ * calls (deterministic mode: bit for bit), the time does: with the streaming kernel, and
+ * with the others where the workers fill the device and exchange every fourth step or less
+ * often, a call is ONE kernel launch for every 1024 communication rounds it covers, and the
+ * start and the tail of a launch are then paid once per launch, not once per epoch
+ * (asgd_stats.launches); else every phase of a step is a launch over all workers.
  */
 int asgd_run_epochs(asgd_ctx *ctx, int epochs);
 

@@ -73,6 +73,10 @@ namespace {
 // rounds one launch with in-kernel waits covers at most (a longer call becomes several such launches)
 constexpr long long ONE_LAUNCH_MAX_ROUNDS = 1024;
 
+// device memory the step kernels with fp16-split operands may take besides the context's own (a state's operands are
+// padded to 64 rows and 16 columns, which for a great many tiny states is a multiple of their size)
+constexpr size_t SPLIT_SCRATCH_MAX = (size_t)32 << 30;
+
 #define HIP_TRY(ctx, call)                              \
     do {                                                \
         hipError_t e__ = (call);                        \
@@ -643,7 +647,9 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     }
     if (split) {
         const size_t need = split_scratch_bytes(p);
-        if (need > ctx->split_bytes) {
+        if (need > SPLIT_SCRATCH_MAX) {
+            split = false;
+        } else if (need > ctx->split_bytes) {
             if (ctx->split_scratch) (void)hipFree(ctx->split_scratch);
             ctx->split_scratch = nullptr;
             ctx->split_bytes = 0;

@@ -483,6 +483,19 @@ hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1,
 
 int quant_partials_count() { return QE_BLOCKS; }
 
+// fp16-split operands or not.  A sample costs the split kernel about 50 ps whatever its size, the kernel with a thread per
+// sample 0.5 to 1 ps per k * d as long as rows are shorter than a quarter of a cache line (20e6 samples: k = 12, d = 7:
+// 1.62 and 1.47 ms; k = 20, d = 2: 1.30 and 0.44; but k = 4, d = 16: 1.02 and 2.5; k = 30, d = 9: 0.98 and 5.7).  Against the
+// fp32 matrix kernel it needs more than 128 centroids, and samples enough for the 15 us its workgroups take to split the
+// state (k = 256, d = 16, 2e6 samples: 0.17 and 0.31 ms; k = 300, d = 128, 20000: 70 and 64 us; k = 64, d = 32, 2e6: 168
+// and 115 us; k = d = 100: the same).
+static bool quant_error_split_pays(const float *x, long long N, int d, int k)
+{
+    if (!split_quant_supports(k, d)) return false;
+    if (mfma_quant_error_supports(k, d, x)) return k > 128 && N > 65536;
+    return d >= 8 || k * d > 84;
+}
+
 hipError_t launch_quant_error(const float *x, long long N, int d, int k, const float *w, double *partials, double *out,
                               hipStream_t s)
 {
@@ -491,7 +504,7 @@ hipError_t launch_quant_error(const float *x, long long N, int d, int k, const f
     hipError_t e = hipSuccess;
     if (small_kernel_supports(k, d, 1)) {
         e = launch_quant_error_small(x, N, d, k, w, partials, nparts, s);           // streaming shape: HBM bound
-    } else if (split_quant_supports(k, d)) {
+    } else if (quant_error_split_pays(x, N, d, k)) {
         nparts = 256;                                                           // one workgroup per compute unit
         e = launch_quant_error_split(x, N, d, k, w, partials, nparts, !mfma_quant_error_supports(k, d, x), s);
     } else if (mfma_quant_error_supports(k, d, x)) {

@@ -98,7 +98,8 @@ __global__ void split_scales_kernel(const float *xabsmax, float *m, int d, int d
 }  // namespace
 
 // ---- host side ----
-bool split_kernel_supports(int k, int d, int b) { return k >= 2 && k <= 8192 && d <= 8192 && b <= (1 << 20); }
+// (k: the cells of one column and the counts have to fit the LDS, 20 bytes a centroid; d: the middle of the data by slot)
+bool split_kernel_supports(int k, int d, int b) { return k >= 2 && k <= 7680 && d <= 8192 && b <= (1 << 20); }
 
 namespace {
 

@@ -1072,9 +1072,11 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
     if (lane == 0 && kp.wait_failed) __hip_atomic_store(p.error_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);   // host memory
 }
 
-// resident workgroups of a kernel on the current device (queried once per device and kernel)
-template <typename Kern>
-hipError_t resident_capacity(Kern kern, int threads, long long *out)
+// resident workgroups of a kernel on the current device (queried once per device and kernel: the kernel is a template
+// argument, all of them have the same type)
+typedef void (*SmallKernel)(StepParams, long long, long long, int);
+template <SmallKernel KERN>
+hipError_t resident_capacity(int threads, long long *out)
 {
     static long long cached_capacity[64] = {0};
     int dev = 0;
@@ -1084,7 +1086,7 @@ hipError_t resident_capacity(Kern kern, int threads, long long *out)
     if (capacity == 0) {
         int per_cu = 0, cus = 0;
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, 0);
+        if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERN, threads, 0);
         if (e != hipSuccess) return e;
         capacity = (long long)per_cu * cus;
         if (dev >= 0 && dev < 64) cached_capacity[dev] = capacity;
@@ -1093,16 +1095,16 @@ hipError_t resident_capacity(Kern kern, int threads, long long *out)
     return hipSuccess;
 }
 
-template <typename Kern>
-hipError_t launch_kernel(Kern kern, int threads, const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
+template <SmallKernel KERN>
+hipError_t launch_kernel(int threads, const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
 {
     if (!persistent) {
-        hipLaunchKernelGGL(kern, dim3(p.W), dim3(threads), 0, s, p, t0, t1, 0);
+        hipLaunchKernelGGL(KERN, dim3(p.W), dim3(threads), 0, s, p, t0, t1, 0);
         return hipGetLastError();
     }
     // one launch for the whole run: every workgroup must be resident at the same time
     long long capacity = 0;
-    hipError_t e = resident_capacity(kern, threads, &capacity);
+    hipError_t e = resident_capacity<KERN>(threads, &capacity);
     if (e != hipSuccess) return e;
     if (capacity < 1) return hipErrorCooperativeLaunchTooLarge;
     const int grid = (int)(p.W < capacity ? p.W : capacity);
@@ -1110,8 +1112,8 @@ hipError_t launch_kernel(Kern kern, int threads, const StepParams &p, long long 
     long long a0 = t0, a1 = t1;
     int sync = 1;
     void *args[] = {&pp, &a0, &a1, &sync};
-    if (p.cooperative) return hipLaunchCooperativeKernel((const void *)kern, dim3(grid), dim3(threads), args, 0, s);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, s, pp, a0, a1, sync);
+    if (p.cooperative) return hipLaunchCooperativeKernel((const void *)KERN, dim3(grid), dim3(threads), args, 0, s);
+    hipLaunchKernelGGL(KERN, dim3(grid), dim3(threads), 0, s, pp, a0, a1, sync);
     return hipGetLastError();
 }
 
@@ -1122,14 +1124,14 @@ template <int K, int D, int PF, int NW, int RS>
 hipError_t launch_variant(const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
 {
     if (p.nb == 1 && p.parts == 1)
-        return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 1, false>, 64 * NW, p, t0, t1, s, persistent);
+        return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false>>(64 * NW, p, t0, t1, s, persistent);
     if constexpr (PF <= 4 && RS == 2 && NW <= 2) {
-        if (p.nb == 1) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 1, true>, 64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 2) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 2, true>, 64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 3) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 3, true>, 64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 1) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, true>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 2) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 2, true>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 3) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 3, true>>(64 * NW, p, t0, t1, s, persistent);
     }
     if constexpr (PF == 2 && RS == 2 && NW <= 2) {
-        if (p.nb == 4) return launch_kernel(small_steps_kernel<K, D, PF, NW, RS, 4, true>, 64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 4) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 4, true>>(64 * NW, p, t0, t1, s, persistent);
     }
     return hipErrorInvalidValue;
 }

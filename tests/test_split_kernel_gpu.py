@@ -17,7 +17,7 @@ ONE_WORKGROUP, SPLIT = 1, 2      # ASGD_OPT_TUNE of the shape-agnostic kernel: w
     (64, 15, 3, 300, 2, 1, 1), (65, 16, 2, 257, 1, 1, 1), (20, 17, 6, 100, 2, 1, 4), (40, 31, 3, 200, 2, 2, 3),
     (37, 33, 4, 129, 2, 1, 1), (12, 65, 3, 500, 2, 1, 1), (70, 111, 2, 128, 1, 1, 1), (5, 127, 3, 200, 2, 1, 1),
     (96, 128, 2, 320, 1, 1, 1), (300, 61, 2, 640, 1, 1, 1), (9, 129, 3, 96, 2, 1, 1), (97, 135, 2, 260, 1, 1, 1),
-    (34, 257, 3, 70, 2, 2, 1), (130, 40, 2, 1500, 1, 1, 1), (6, 520, 3, 64, 1, 1, 2), (700, 12, 2, 1400, 1, 1, 1),
+    (34, 257, 3, 70, 2, 2, 1), (7680, 3, 2, 100, 1, 1, 1), (130, 40, 2, 1500, 1, 1, 1), (6, 520, 3, 64, 1, 1, 2), (700, 12, 2, 1400, 1, 1, 1),
 ])
 def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
     H = max(3 * b + 7, k)
@@ -96,8 +96,8 @@ def quant_error(B, X, w):
 # Eq. 8 at the edges of the tiles: groups of 64 and 512 samples, blocks of 32 rows, chunks of 16 columns, state resident in
 # LDS or streamed, long rows; also far from the origin
 @pytest.mark.parametrize("k,d,N", [
-    (2, 1, 1), (3, 2, 63), (5, 7, 64), (33, 8, 65), (31, 9, 511), (64, 15, 513), (65, 17, 4096), (100, 100, 3000),
-    (37, 75, 2000), (96, 127, 700), (512, 128, 1500), (2100, 40, 900), (300, 129, 800), (70, 384, 600), (12, 520, 300),
+    (2, 8, 1), (13, 7, 63), (11, 8, 64), (33, 8, 65), (31, 9, 511), (64, 15, 513), (65, 17, 4096), (100, 101, 3000),
+    (37, 75, 2000), (96, 127, 700), (512, 128, 66000), (2100, 41, 900), (300, 129, 800), (70, 384, 600), (12, 520, 300),
 ])
 @pytest.mark.parametrize("offset", [0.0, 1.0e4])
 def test_split_quant_error_edges(B, oracle, k, d, N, offset):
