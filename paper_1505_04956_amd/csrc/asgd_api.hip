@@ -114,6 +114,7 @@ StepParams make_params(const asgd_ctx *c)
     p.cooperative = c->cooperative;
     p.wait_polls = c->wait_polls;
     p.drop_unannounced = c->drop_unannounced;
+    p.one_launch = 0;
     return p;
 }
 
@@ -258,6 +259,23 @@ int import_exchange(asgd_ctx *c, int kernel, const float *values, const int32_t 
             HIP_TRY(c, hipMemcpy(c->stamp + buf0, stamps.data(), W * sizeof(int), hipMemcpyHostToDevice));
     }
     return ASGD_OK;
+}
+
+// Whether the fp16-split step kernels are faster than the fp32 matrix kernel (the default variant of
+// ASGD_KERNEL_MFMA).  They take 15 to 20 us per step whatever its size, the latter a step of one workgroup per worker,
+// and both sides were measured over k x d from 12 x 8 to 500 x 24 and 4 to 1000 workers (us per step, fp32 -> split):
+//   up to 256 workers: 600 samples 1.02 to 1.9 times as fast (W = 256, k = 64, d = 32: 33.1 -> 32.5; W = 4, k = d = 100:
+//     64 -> 48), 2400 samples 1.3 to 4; 150 samples 0.7 to 0.96 (W = 32, k = 64, d = 32: 14.3 -> 20.8), but k = 500 1.05
+//     to 1.2 (the fp32 kernel streams the state);
+//   exchange at every step, 100 workers and more: always (fp32 waits for messages every step: 31 -> 24, 89 -> 55);
+//   more than 256 workers where the fp32 kernel keeps two of them on a compute unit: only long steps (k = d = 100,
+//     b = 600: 121 -> 155, b = 2000: 270 -> 250); otherwise always (k = 500, d = 24: 201 -> 133).
+bool mfma_split_pays(const asgd_ctx *c)
+{
+    const bool often = c->E > 0 && c->E < 4 && c->W > 1;
+    if (c->W > 256)
+        return often || !mfma_kernel_two_per_cu(c->k, c->d, c->b) || (double)c->b * c->k * c->d >= 1.5e7;
+    return (often && c->W >= 100) || c->b >= 512 || c->k > 256;
 }
 
 }  // namespace
@@ -641,9 +659,11 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     if (ctx->flag_host[1] == 0 && split_kernel_supports(ctx->k, ctx->d, ctx->b) && steps > 0) {
         if (kernel == ASGD_KERNEL_GENERIC)
             split = (ctx->tune & 2) || (!(ctx->tune & 1) && (ctx->b >= 96 || (double)ctx->b * ctx->k * ctx->d >= 8192.0));
-        else if (kernel == ASGD_KERNEL_MFMA)
+        else if (kernel == ASGD_KERNEL_MFMA) {
             split = ctx->tune == 0 && !ctx->drop_unannounced && ctx->wait_polls == 0 && ctx->parts == 1 &&
-                    (ctx->mode == ASGD_MODE_DETERMINISTIC || ctx->E == 0 || ctx->W < 2);
+                    (ctx->mode == ASGD_MODE_DETERMINISTIC || ctx->E == 0 || ctx->W < 2) && mfma_split_pays(ctx);
+            p.one_launch = 1;
+        }
     }
     if (split) {
         const size_t need = split_scratch_bytes(p);

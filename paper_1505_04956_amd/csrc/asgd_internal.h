@@ -43,6 +43,7 @@ struct StepParams {
     int tune;              // variant selector for experiments (0 = default)
     int cooperative;       // use the cooperative launch API for single-launch runs
     int wait_polls;        // polls a workgroup may spend on all the waits of a launch (test hook; 0 = the kernel's default)
+    int one_launch;        // fp16-split step kernels: one launch per call also where phases are a little faster
     int drop_unannounced;  // test hook: the recipient does not know which messages the loss hook drops and waits for them
 };
 
@@ -68,6 +69,8 @@ void small_kernel_pack_message(int k, int d, const float *rows, const int *row_r
 hipError_t launch_small_steps(const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent);
 // Matrix-core kernel: needs d % 4 == 0, d <= 128, 16-byte aligned samples and its LDS budget.
 bool mfma_kernel_supports(int k, int d, int b, const void *x);
+// the variant with four waves and the state resident in LDS, two workers per compute unit
+bool mfma_kernel_two_per_cu(int k, int d, int b);
 hipError_t launch_rownorm2max(const float *x, long long rows, int d, float *out, hipStream_t s);   // max_n |x_n|^2
 // persistent = true: as for the small-state kernel (deterministic mode; hipErrorCooperativeLaunchTooLarge when the
 // workers do not all fit the device at once)

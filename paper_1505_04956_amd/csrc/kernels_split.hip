@@ -166,7 +166,9 @@ SplitPlan make_plan(const StepParams &p, bool local)
         if (q.shares > 64) q.shares = 64;
     } else if (!local) {
         int nw = q.lds <= 50 * 1024 ? 4 : 8;
-        while (nw > 1 && (long long)p.W * ((groups + nw - 1) / nw) < SPLIT_CUS) nw /= 2;
+        // (with one workgroup per compute unit a second round must not begin)
+        const int fill = q.lds > 78 * 1024 ? SPLIT_CUS * 3 / 8 : SPLIT_CUS;
+        while (nw > 1 && (long long)p.W * ((groups + nw - 1) / nw) < fill) nw /= 2;
         q.waves = nw;
         const int max_shares = (groups + nw - 1) / nw;
         const int want = SPLIT_CUS * (q.nch <= 2 && q.lds <= 50 * 1024 ? 12 : 8) / nw;
@@ -233,16 +235,18 @@ Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
 
 }  // namespace
 
-// Local form: the workers fill the device, one workgroup of eight waves each - at most a quarter of the compute units' time
-// is lost to a last round that is not full (fewer workers: phases, which cut their mini-batches) -, and exchange every
-// fourth step at most (every message costs its sender a write-back and its recipient an invalidation of the L2, which
-// phases get from the end of a launch: k = 64, d = 32, b = 500, E = 1: 105 us per step local, 33 us in phases).
+// Local form: the workers fill the device, one workgroup of eight waves each (three quarters of them at least: fewer are
+// better off with phases, which cut their mini-batches), and exchange every fourth step at most (every message costs its
+// sender a write-back and its recipient an invalidation of the L2, which phases get from the end of a launch: k = 64,
+// d = 32, b = 500, E = 1: 105 us per step local, 33 us in phases).  Two rounds of workers and more take as long as
+// phases or longer (512 workers, E = 8: k = 12, d = 8, b = 600: 47 us per step local, 34 in phases; k = d = 100,
+// b = 2000: 252 and 236): only where the caller wants one launch.
 bool split_local_form(const StepParams &p)
 {
     const int rounds = (p.W + SPLIT_CUS - 1) / SPLIT_CUS;
     int dev = 0, cus = 0;                  // (a partition of a device may have fewer compute units: not resident at once)
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-    return cus >= SPLIT_CUS && p.parts == 1 && 4LL * p.W >= 3LL * rounds * SPLIT_CUS && (p.E == 0 || p.W < 2 || (p.mode == ASGD_MODE_DETERMINISTIC && p.E >= 4));
+    return cus >= SPLIT_CUS && p.parts == 1 && 4LL * p.W >= 3LL * rounds * SPLIT_CUS && (rounds == 1 || p.one_launch) && (p.E == 0 || p.W < 2 || (p.mode == ASGD_MODE_DETERMINISTIC && p.E >= 4));
 }
 
 size_t split_scratch_bytes(const StepParams &p) { return scratch_layout(p, make_plan(p, split_local_form(p))).bytes; }
