@@ -31,6 +31,19 @@ def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
     assert np.array_equal(g.get_state(), again.get_state())        # bit for bit, however the run is cut
 
 
+# both sides of the rules that choose between the kernels and between the one launch and the phases: mini-batches of 512,
+# k of 256, exchange at every step from 100 workers on, workers beyond one and two per compute unit
+@pytest.mark.parametrize("kernel", ["MFMA", "GENERIC"])
+@pytest.mark.parametrize("k,d,W,b,E,buffers", [
+    (64, 32, 8, 511, 4, 1), (64, 32, 8, 512, 4, 2), (256, 16, 4, 100, 4, 1), (257, 16, 4, 100, 4, 1),
+    (12, 8, 99, 100, 1, 1), (12, 8, 100, 100, 1, 1), (32, 16, 191, 97, 4, 1), (32, 16, 192, 520, 4, 1), (40, 8, 256, 512, 4, 2),
+    (32, 16, 257, 97, 4, 1), (500, 24, 300, 64, 4, 1), (32, 16, 384, 97, 3, 1), (24, 8, 600, 100, 0, 1),
+])
+def test_split_kernel_dispatch(B, oracle, k, d, W, b, E, buffers, kernel):
+    X = make_data(W * max(2 * b + 5, k), d, k, seed=200 + W)
+    run_both(B, oracle, X, k, W, b, 0.05, E, 9, kernel=getattr(B, "KERNEL_" + kernel), buffers=buffers)
+
+
 @pytest.mark.parametrize("k,d,b", [(7, 5, 200), (40, 77, 333), (12, 140, 90)])
 def test_split_kernel_running_mean(B, oracle, k, d, b):
     X = make_data(4 * (5 * b + 3), d, k, seed=5)
