@@ -269,7 +269,9 @@ int import_exchange(asgd_ctx *c, int kernel, const float *values, const int32_t 
 //     to 1.2 (the fp32 kernel streams the state);
 //   exchange at every step, 100 workers and more: always (fp32 waits for messages every step: 31 -> 24, 89 -> 55);
 //   more than 256 workers where the fp32 kernel keeps two of them on a compute unit: only long steps (k = d = 100,
-//     b = 600: 121 -> 155, b = 2000: 270 -> 250); otherwise always (k = 500, d = 24: 201 -> 133).
+//     b = 600: 121 -> 155, b = 2000: 270 -> 250; a job of two epochs from loading to states 14.6 -> 11.2 ms; calls of ten
+//     epochs late in a run, when few samples lie between centroids and the fp32 kernel's two workers per compute unit have
+//     drifted apart: 237 -> 241); otherwise always (k = 500, d = 24: 201 -> 133).
 bool mfma_split_pays(const asgd_ctx *c)
 {
     const bool often = c->E > 0 && c->E < 4 && c->W > 1;
