@@ -483,17 +483,20 @@ hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1,
 
 int quant_partials_count() { return QE_BLOCKS; }
 
-// fp16-split operands or not.  A sample costs the split kernel about 50 ps whatever its size, the kernel with a thread per
-// sample 0.5 to 1 ps per k * d as long as rows are shorter than a quarter of a cache line (20e6 samples: k = 12, d = 7:
-// 1.62 and 1.47 ms; k = 20, d = 2: 1.30 and 0.44; but k = 4, d = 16: 1.02 and 2.5; k = 30, d = 9: 0.98 and 5.7).  Against the
-// fp32 matrix kernel it needs more than 128 centroids, and samples enough for the 15 us its workgroups take to split the
-// state (k = 256, d = 16, 2e6 samples: 0.17 and 0.31 ms; k = 300, d = 128, 20000: 70 and 64 us; k = 64, d = 32, 2e6: 168
-// and 115 us; k = d = 100: the same).
+// fp16-split operands or not; in microseconds, the split kernel and the other one:
+// Against a thread per sample: 0.5 to 0.7 ps per sample and k * d for rows shorter than a quarter of a cache line, 3 ps and
+// more for others, where the split kernel takes 50 to 58 ps per sample for up to 32 centroids and 16 columns, and 80 ps from the
+// rows of d < 8 (20e6 samples: k = 20, d = 5: 1640, 1410; k = 40, d = 3: 1620, 1270; k = 100, d = 3: 1970, 3130; k = 4, d = 9:
+// 1030, 876; k = 12, d = 9: 1100, 2350; k = 2, d = 16: 1140, 1360).  Its workgroups split the state first, 20 us with the
+// launch, which few samples of small rows do not repay (1000 samples: k = 20, d = 9: 20, 29; k = 100, d = 9: 26, 82).
+// Against the fp32 matrix kernel it needs more than 128 centroids (k = d = 100: the same; k = 64, d = 32, 2e6 samples: 168,
+// 110), and samples enough for that start (k = 256, d = 16: 7e4 samples 29, 35; 2e6 216, 315; k = 300, d = 128: 2e4 70, 65, 7e4
+// 89, 112; k = 1024, d = 128: 7e4 200, 309).
 static bool quant_error_split_pays(const float *x, long long N, int d, int k)
 {
     if (!split_quant_supports(k, d)) return false;
     if (mfma_quant_error_supports(k, d, x)) return k > 128 && N > 65536;
-    return d >= 8 || k * d > 84;
+    return (d >= 16 || k * d > (d >= 8 ? 48 : 160)) && (N > 100000 || k * d > 150);
 }
 
 hipError_t launch_quant_error(const float *x, long long N, int d, int k, const float *w, double *partials, double *out,
