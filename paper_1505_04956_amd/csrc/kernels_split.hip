@@ -56,14 +56,14 @@ __global__ __launch_bounds__(1024) void split_middle_kernel(const float *x, long
 #pragma unroll
         for (int u = 0; u < 8; ++u) v[u] = x[(size_t)(min(q0 + 16 * u, n - 1) * step) * d + (j < d ? j : 0)];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) s += q0 + 16 * u < n ? v[u] : 0.0f;
+        for (int u = 0; u < 8; ++u) s += q0 + 16 * u < n ? v[u] * (1.0f / (float)n) : 0.0f;     // (the sum could overflow)
     }
     red[wave][lane] = s;
     __syncthreads();
     if (wave == 0 && j < d) {
         s = 0.0f;
         for (int q = 0; q < 16; ++q) s += red[q][lane];
-        m[j] = s / (float)n;
+        m[j] = s;
     }
 }
 // sx: power of two with max_j (max|x_j| + |m_j|) * sx in [2^13, 2^14); ms = -m * sx; scale of column j of the sums: 2^e
@@ -73,7 +73,7 @@ __global__ void split_scales_kernel(const float *xabsmax, float *m, int d, int d
     __shared__ float red[256];
     const int tid = threadIdx.x;
     float a = 0.0f;
-    for (int j = tid; j < d; j += 256) a = fmaxf(a, xabsmax[j] + fabsf(m[j]));
+    for (int j = tid; j < d; j += 256) a = fmaxf(a, fminf(xabsmax[j] + fabsf(m[j]), 3.4e38f));
     red[tid] = a;
     __syncthreads();
     for (int off = 128; off > 0; off >>= 1) {
@@ -82,7 +82,7 @@ __global__ void split_scales_kernel(const float *xabsmax, float *m, int d, int d
     }
     int q = 0;
     if (red[0] > 0.0f) (void)frexpf(red[0], &q);
-    const float sx = ldexpf(1.0f, max(-100, min(100, 14 - q)));
+    const float sx = ldexpf(1.0f, max(-120, min(126, 14 - q)));
     if (tid == 0) xmeta[0] = sx;
     for (int j = tid; j < dpad; j += 256) ms[j] = split_slot_used(j, d) ? -m[split_column(j, d)] * sx : 0.0f;
     for (int j = tid; j < d; j += 256) {

@@ -20,7 +20,7 @@ constexpr int SPLIT_THREADS = 512;
 
 struct SplitState {                // one per worker and step modulo 3
     float sw;                      // scale of the operands
-    unsigned vabs, n2;             // bit patterns of the largest |v_cj| and |v_c|^2; above those of all numbers if not finite
+    unsigned vabs, n2;             // bit patterns of the largest |v_cj| and of the largest |sw v_c|^2; above those of all numbers if not finite
     unsigned pad[29];              // a cache line each: atomics on one line wait for each other, and that took 15 us
 };
 
@@ -41,7 +41,7 @@ struct SplitStep {                         // what is the same for all workers i
 struct SplitArgs {
     const float *x, *w;              // samples, states
     const unsigned char *frag;       // W x frag_bytes
-    const float *hs;                 // W x kpad: -|v_c|^2/2 * sx * sw, SPLIT_PAD_SCORE for the padding rows
+    const float *hs;                 // W x kpad: -|sw v_c|^2/2 * sx / sw, SPLIT_PAD_SCORE for the padding rows
     const float *ms;                 // dpad: -m_j * sx, zero past d
     const float *xmeta;              // sx
     const double *colscale;          // d scales of the fixed-point sums, then d inverse scales
@@ -208,10 +208,14 @@ __device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const
     const int lane = split_lane();
     const float yn = sqrtf(n2) * 1.0001f;
     const SplitState st = now.state[worker];
-    const float sw = st.sw, vmax = sqrtf(__uint_as_float(st.n2)) * 1.0001f * sw, sx = a.xmeta[0];
-    float thr = split_c1(a.dpad) * (yn * vmax + 0.5f * vmax * vmax * (sx / sw)) + split_c2(a.dpad) * (yn + vmax);
-    // a state that is not finite, or has outgrown the scale of its fp16 operands: everything in fp64
-    if (st.n2 >= 0x7f800000u || st.vabs >= 0x7f800000u || !(__uint_as_float(st.vabs) * sw < 32768.0f)) thr = INFINITY;
+    const float sw = st.sw, n2max = __uint_as_float(st.n2), vmax = sqrtf(n2max) * 1.0001f, ratio = a.xmeta[0] / sw;
+    const float offset = 0.5f * vmax * vmax * ratio;
+    float thr = split_c1(a.dpad) * (yn * vmax + offset) + split_c2(a.dpad) * (yn + vmax);
+    // Everything in fp64: a state that is not finite, has outgrown the scale of its fp16 operands or has shrunk so far below it
+    // that its squares lose their last places, scores that come near the offset of the padding rows.
+    if (st.n2 >= 0x7f800000u || st.vabs >= 0x7f800000u || !(__uint_as_float(st.vabs) * sw < 32768.0f) || !(n2max > 1.0e-27f) ||
+        !(yn * vmax + offset < -0.1f * SPLIT_PAD_SCORE))
+        thr = INFINITY;
     const float *xg = xb + (size_t)g * a.d;
     const bool valid = g + lane < n_hi;
     const int arg = split_settle(t, thr, valid, xg, a.w + (size_t)worker * a.k * a.d, a.k, a.d, rechecks);
@@ -604,8 +608,8 @@ __device__ __forceinline__ float split_state_scale(unsigned vabs)
 {
     int q = 0;
     const float v = __uint_as_float(vabs);
-    if (v > 0.0f && v < 3.0e38f) (void)frexpf(v, &q);
-    return ldexpf(1.0f, max(-100, min(100, 10 - q)));
+    if (v > 0.0f && v < INFINITY) (void)frexpf(v, &q);
+    return ldexpf(1.0f, max(-120, min(126, 10 - q)));
 }
 
 // the columns of the slots [j0, j0 + 8) of an array row (see split_column)
@@ -873,17 +877,17 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     v[e] = e >= lo_e && e < hi_e ? wn[e] - mid[e] : 0.0f;
-                    sq = fmaf(v[e], v[e], sq);
                     vabs = max(vabs, __float_as_uint(v[e]) & 0x7fffffffu);
+                    v[e] *= sw;                            // (squares of scaled numbers neither overflow nor vanish)
+                    sq = fmaf(v[e], v[e], sq);
                 }
             }
             if (MODE != 0) {
                 half8 hi, lo;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    const float y = v[e] * sw;
-                    hi[e] = (_Float16)y;
-                    lo[e] = (_Float16)(y - (float)hi[e]);
+                    hi[e] = (_Float16)v[e];
+                    lo[e] = (_Float16)(v[e] - (float)hi[e]);
                 }
                 half8 *dst = reinterpret_cast<half8 *>(frag + ((((size_t)(c >> 6) * nch + (j0 >> 4)) * 2 + ((c >> 5) & 1)) * 2) * SPLIT_PIECE) +
                              (c & 31) + 32 * ((j0 >> 3) & 1);
@@ -893,7 +897,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
         }
         for (int off = u.g / 2; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
         n2max = max(n2max, __float_as_uint(sq) & 0x7fffffffu);
-        if (MODE != 0 && lane_g == 0) hs[c] = real ? -0.5f * sq * sx * sw : SPLIT_PAD_SCORE;
+        if (MODE != 0 && lane_g == 0) hs[c] = real ? -0.5f * sq * (sx / sw) : SPLIT_PAD_SCORE;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {

@@ -85,3 +85,24 @@ def test_quant_error_with_a_prototype_that_is_not_finite(B, oracle, k, d, N, val
     w[2, d - 1] = value
     q, o = quant_error(B, X, w), oracle.quant_error(X, rest.astype(np.float64))
     assert abs(q - o) <= (d + 3) * 2.0 ** -24 * o
+
+
+# ---- steps ----
+@pytest.mark.parametrize("kernel,k,d,b", [("GENERIC", 20, 13, 150), ("GENERIC", 40, 150, 150), ("MFMA", 64, 32, 600)])
+@pytest.mark.parametrize("scale", [1.0e-36, 1.0e-30, 1.0e-22, 1.0e-20, 1.0e16, 1.0e25, 1.0e34])
+def test_steps_on_small_and_large_numbers(B, oracle, kernel, k, d, b, scale):
+    # squares that vanish or overflow in fp32; the same mixture decides nothing differently at any scale
+    X = make_data(4 * (3 * b + 11), d, k, seed=9) * np.float32(scale)
+    g, _ = run_both(B, oracle, X, k, 4, b, 0.05, 2, 6, kernel=getattr(B, "KERNEL_" + kernel), tune=SPLIT if kernel == "GENERIC" else 0,
+                    check_qe=False)
+    assert g.stats().exact_rechecks < 4 * 6 * b // 20             # (and without taking everything to fp64)
+
+
+@pytest.mark.parametrize("k,d", [(20, 13), (40, 150)])
+@pytest.mark.parametrize("size", [1.0e5, 1.0e10, 1.0e15, 1.0e20])
+def test_steps_from_a_state_far_beyond_the_data(B, oracle, k, d, size):
+    # offsets of the scores beyond that of the rows the state is padded with (k is no multiple of 32)
+    rng = np.random.default_rng(k)
+    X = make_data(4 * 500, d, k, seed=9) * np.float32(1.0e-12)
+    w0 = (size * (1.0 + np.arange(k)[:, None] / k) * rng.choice([-1.0, 1.0], (k, d))).astype(np.float32)
+    run_both(B, oracle, X, k, 4, 150, 0.05, 2, 4, kernel=B.KERNEL_GENERIC, tune=SPLIT, check_qe=False, w0=w0)
