@@ -47,7 +47,8 @@ struct asgd_ctx {
     // Error flag of the kernels (an expired bounded wait), in pinned host memory that the device writes directly: the
     // host clears and reads it around a run without a memset or a copy on the stream (each is a separate operation
     // of several microseconds, which counts when a run is one launch of less than a millisecond).
-    int *flag_host = nullptr;      // [0] error flag, [1] set while loading if a sample is not finite
+    int *flag_host = nullptr;      // [0] error flag; set while loading: [1] a sample is not finite, [2] a column is mostly
+                                   // far smaller than its largest element
     void *split_scratch = nullptr; // matrix-core form of the shape-agnostic kernel, allocated on first use
     size_t split_bytes = 0;
     long long *ncum = nullptr, *counters = nullptr;
@@ -348,7 +349,7 @@ int asgd_create(asgd_ctx **out, int k, int d, int W, int b, float lr)
         e = hipMalloc(a.p, a.bytes);
         if (e != hipSuccess) { fail(e); break; }
     }
-    if (rc == ASGD_OK && (e = hipHostMalloc((void **)&c->flag_host, 2 * sizeof(int), hipHostMallocDefault)) != hipSuccess) fail(e);
+    if (rc == ASGD_OK && (e = hipHostMalloc((void **)&c->flag_host, 3 * sizeof(int), hipHostMallocDefault)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev0)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev1)) != hipSuccess) fail(e);
     if (rc != ASGD_OK) {
@@ -479,8 +480,8 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     HIP_TRY(ctx, hipMemsetAsync(ctx->counters, 0, (size_t)ctx->W * CNT_STRIDE * sizeof(long long), ctx->stream));
     // per-dimension max |x| over the rows the workers own: input of the rounding-error bound
     // that decides when an assignment is recomputed exactly
-    ctx->flag_host[1] = 0;
-    HIP_TRY(ctx, launch_absmax(x_dev, H * ctx->W, ctx->d, ctx->xabsmax, ctx->flag_host + 1, ctx->stream));
+    ctx->flag_host[1] = ctx->flag_host[2] = 0;
+    HIP_TRY(ctx, launch_absmax(x_dev, H * ctx->W, ctx->d, ctx->xabsmax, ctx->flag_host + 1, ctx->flag_host + 2, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     ctx->loaded = true;
     return ASGD_OK;
@@ -657,8 +658,14 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     // time of the fp32 ones).  Free-running mode of the latter stays with the kernel whose workers drift freely.
     // Shape-agnostic: ASGD_OPT_TUNE bit 0 asks for one workgroup per worker, bit 1 for the matrix-core form whatever
     // the size.  A step of the former takes 0.15 us per sample of the mini-batch or more, one of the latter 15 us or more.
+    // The split kernels' gradient sums are in fixed point with one scale per column: exact to 2^-51 of its largest element, which
+    // is more than fp32 sums give unless nearly everything in a column is far smaller (one huge element, a marker for
+    // a missing value): those go to the kernels with fp32 sums.  (More than 256 workers of the matrix-core kernel, two on
+    // a compute unit: its sums are in 32-bit fixed point, the split kernels' are the finer ones.)
     bool split = false;
-    if (ctx->flag_host[1] == 0 && split_kernel_supports(ctx->k, ctx->d, ctx->b) && steps > 0) {
+    const bool wide = ctx->flag_host[2] != 0 &&
+                      !(kernel == ASGD_KERNEL_MFMA && ctx->W > 256 && mfma_kernel_two_per_cu(ctx->k, ctx->d, ctx->b));
+    if (ctx->flag_host[1] == 0 && !wide && split_kernel_supports(ctx->k, ctx->d, ctx->b) && steps > 0) {
         if (kernel == ASGD_KERNEL_GENERIC)
             split = (ctx->tune & 2) || (!(ctx->tune & 1) && (ctx->b >= 96 || (double)ctx->b * ctx->k * ctx->d >= 8192.0));
         else if (kernel == ASGD_KERNEL_MFMA) {

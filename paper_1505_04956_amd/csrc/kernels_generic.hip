@@ -66,63 +66,99 @@ __global__ void init_first_k_kernel(StepParams p)
         p.w[i * kd + e] = p.x[(size_t)i * p.H * p.d + e];
 }
 
-__global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, int d, float *partial, int *nonfinite)
+// partial[block][j] = max |x[row][j]| over the elements this block visits.  The flat array is walked with a stride that is
+// a multiple of d, so a thread always sees one dimension.
+// least (may be null): the smallest, over all groups of eight elements of column j, of a group's largest magnitude, groups of
+// zeros left out (bit patterns, less one).  Far below max |x_j| only if most of the column is: the size of what a single
+// huge element would hide.
+__global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, int d, float *partial, unsigned *least, int *nonfinite)
 {
-    // partial[block][j] = max |x[row][j]| over the elements this block visits.  The flat array
-    // is walked with a stride that is a multiple of d, so a thread always sees one dimension.
-    extern __shared__ float sm[];
-    const long long total = n * d;
-    const long long threads = (long long)gridDim.x * blockDim.x;
-    const long long stride = threads / d * d;          // host guarantees threads >= d
+    const long long total = n * (long long)d;
     const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-    for (int j = threadIdx.x; j < d; j += blockDim.x) sm[j] = 0.0f;
+    const long long nthreads = (long long)gridDim.x * blockDim.x;
+    const long long stride = nthreads - nthreads % d;
+    extern __shared__ float sm[];
+    unsigned *sl = reinterpret_cast<unsigned *>(sm + d);
+    for (int j = threadIdx.x; j < d; j += blockDim.x) {
+        sm[j] = 0.0f;
+        if (least) sl[j] = 0xffffffffu;
+    }
     __syncthreads();
     if (g < stride) {
         float m = 0.0f;
         unsigned bits = 0;            // (the maximum of two floats drops a NaN, that of their bit patterns does not)
+        unsigned low = 0xffffffffu;
         long long e = g;
         for (; e + 7 * stride < total; e += 8 * stride) {      // eight independent loads in flight per thread
             float v[8];
+            unsigned group = 0;
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = x[e + q * stride];
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 m = fmaxf(m, fabsf(v[q]));
-                bits = max(bits, __float_as_uint(v[q]) & 0x7fffffffu);
+                group = max(group, __float_as_uint(v[q]) & 0x7fffffffu);
             }
+            bits = max(bits, group);
+            low = min(low, group - 1u);
         }
+        unsigned group = 0;
         for (; e < total; e += stride) {
             m = fmaxf(m, fabsf(x[e]));
-            bits = max(bits, __float_as_uint(x[e]) & 0x7fffffffu);
+            group = max(group, __float_as_uint(x[e]) & 0x7fffffffu);
         }
+        bits = max(bits, group);
+        low = min(low, group - 1u);
         if (bits >= 0x7f800000u) __hip_atomic_store(nonfinite, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         // max is order independent; |x| >= 0, so the integer order of the bit patterns is the
         // floating-point order and an integer atomic is exact
         atomicMax((unsigned int *)&sm[g % d], __float_as_uint(m));
+        if (least) atomicMin(&sl[g % d], low);
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < d; j += blockDim.x) partial[(size_t)blockIdx.x * d + j] = sm[j];
+    for (int j = threadIdx.x; j < d; j += blockDim.x) {
+        partial[(size_t)blockIdx.x * d + j] = sm[j];
+        if (least) least[(size_t)blockIdx.x * d + j] = sl[j];
+    }
 }
 
 // A workgroup of 16 waves takes 64 columns, a wave every 16th block's maxima, eight of them in flight (one thread per
 // column walking all the blocks took 0.1 to 0.5 ms, 1024 dependent steps and more than once around for d > 256).
-__global__ __launch_bounds__(1024) void absmax_final_kernel(const float *partial, int nblocks, int d, float *out)
+// wide is set if a column's elements are mostly smaller than 2^-26 of its largest.
+__global__ __launch_bounds__(1024) void absmax_final_kernel(const float *partial, const unsigned *least, int nblocks, int d, float *out, int *wide)
 {
     __shared__ float red[16][64];
+    __shared__ unsigned redl[16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
     float m = 0.0f;
+    unsigned low = 0xffffffffu;
+    const unsigned *src = least ? least : reinterpret_cast<const unsigned *>(partial), off = least ? 0u : 0xffffffffu;    // (loads without a branch)
     for (int q0 = wave; q0 < nblocks; q0 += 128) {
         float v[8];
+        unsigned l[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = partial[(size_t)min(q0 + 16 * u, nblocks - 1) * d + (j < d ? j : 0)];
+        for (int u = 0; u < 8; ++u) {
+            const size_t at = (size_t)min(q0 + 16 * u, nblocks - 1) * d + (j < d ? j : 0);
+            v[u] = partial[at];
+            l[u] = src[at] | off;
+        }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) m = fmaxf(m, v[u]);
+        for (int u = 0; u < 8; ++u) {
+            m = fmaxf(m, v[u]);
+            low = min(low, l[u]);
+        }
     }
     red[wave][lane] = m;
+    redl[wave][lane] = low;
     __syncthreads();
     if (wave == 0 && j < d) {
-        for (int q = 0; q < 16; ++q) m = fmaxf(m, red[q][lane]);
+        for (int q = 0; q < 16; ++q) {
+            m = fmaxf(m, red[q][lane]);
+            low = min(low, redl[q][lane]);
+        }
         out[j] = m;
+        if (low != 0xffffffffu && __uint_as_float(low + 1u) < m * 1.4901161e-8f)
+            __hip_atomic_store(wide, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
 
@@ -454,15 +490,17 @@ hipError_t launch_init_first_k(const StepParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, hipStream_t s)
+hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, int *wide, hipStream_t s)
 {
-    // out: d floats; uses a temporary of nblocks*d floats that is freed before returning
+    // out: d floats; uses a temporary of 2 * nblocks * d numbers that is freed before returning
     const int nblocks = 1024;
+    const bool track = d <= 8192;         // (both arrays fit the LDS, and no kernel that takes longer rows asks)
     float *partial = nullptr;
-    hipError_t e = hipMalloc((void **)&partial, (size_t)nblocks * d * sizeof(float));
+    hipError_t e = hipMalloc((void **)&partial, (size_t)nblocks * d * (track ? 2 : 1) * sizeof(float));
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(absmax_partial_kernel, dim3(nblocks), dim3(256), (size_t)d * sizeof(float), s, x, rows, d, partial, nonfinite);
-    hipLaunchKernelGGL(absmax_final_kernel, dim3((d + 63) / 64), dim3(1024), 0, s, partial, nblocks, d, out);
+    unsigned *least = track ? reinterpret_cast<unsigned *>(partial + (size_t)nblocks * d) : nullptr;
+    hipLaunchKernelGGL(absmax_partial_kernel, dim3(nblocks), dim3(256), (size_t)d * (track ? 2 : 1) * sizeof(float), s, x, rows, d, partial, least, nonfinite);
+    hipLaunchKernelGGL(absmax_final_kernel, dim3((d + 63) / 64), dim3(1024), 0, s, partial, least, nblocks, d, out, wide);
     e = hipGetLastError();
     hipError_t e2 = hipStreamSynchronize(s);
     (void)hipFree(partial);

@@ -4,6 +4,7 @@ direct form."""
 import numpy as np
 import pytest
 
+from tests.parity_rules import rel_fro
 from tests.test_parity_gpu import B, make_data, run_both, to_dev  # noqa: F401  (fixtures)
 from tests.test_split_kernel_gpu import SPLIT, quant_error
 
@@ -106,3 +107,21 @@ def test_steps_from_a_state_far_beyond_the_data(B, oracle, k, d, size):
     X = make_data(4 * 500, d, k, seed=9) * np.float32(1.0e-12)
     w0 = (size * (1.0 + np.arange(k)[:, None] / k) * rng.choice([-1.0, 1.0], (k, d))).astype(np.float32)
     run_both(B, oracle, X, k, 4, 150, 0.05, 2, 4, kernel=B.KERNEL_GENERIC, tune=SPLIT, check_qe=False, w0=w0)
+
+
+@pytest.mark.parametrize("kernel,tune,k,d,W,b", [("GENERIC", SPLIT, 20, 13, 4, 150), ("GENERIC", 0, 40, 150, 4, 150), ("GENERIC", 0, 12, 8, 200, 100),
+                                                 ("MFMA", 0, 64, 32, 4, 600), ("MFMA", 0, 300, 32, 4, 600)])
+@pytest.mark.parametrize("value", [1.0e9, 1.0e12, 1.0e20, -3.0e38])
+def test_one_huge_element_does_not_touch_the_other_workers(B, oracle, kernel, tune, k, d, W, b, value):
+    # sums in fixed point scaled by the largest element of a column would lose everything else in it
+    H = max(3 * b + 11, k)
+    X = make_data(W * H, d, k, seed=9)
+    X[2 * H + b // 2, 1] = value
+    g = B.ASGD(k, d, W, b, 0.05, E=0, kernel=getattr(B, "KERNEL_" + kernel), tune=tune)
+    g.load_shards(to_dev(X))
+    g.run_steps(6)
+    o = oracle.OracleASGD(X, k=k, W=W, b=b, lr=0.05, E=0)
+    o.run_steps(6)
+    err = rel_fro(g.get_state(), o.w)
+    # rounding of sums and updates (a few 2^-24 per step), and the odd near-tie of an fp32 state
+    assert np.delete(err, 2).max() <= 1e-5
