@@ -51,7 +51,9 @@ struct StepParams {
 hipError_t launch_init_first_k(const StepParams &p, hipStream_t s);
 // nonfinite, wide: pinned host memory, set to 1 if an element is infinite or not a number; if most elements of a column are
 // smaller than 2^-26 of its largest (d <= 8192)
-hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, int *wide, hipStream_t s);
+// scratch: absmax_scratch_bytes() of device memory (none needed if that is 0).  Enqueued only.
+size_t absmax_scratch_bytes(int d);
+hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, int *wide, void *scratch, hipStream_t s);
 hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1, hipStream_t s);
 // Step kernels with fp16-split operands (any row length; finite samples), all on `scratch` (split_scratch_bytes() of device
 // memory, nothing in it is kept between calls).  Local form: one launch whose workers wait for each other's messages, as

@@ -490,21 +490,30 @@ hipError_t launch_init_first_k(const StepParams &p, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, int *wide, hipStream_t s)
+constexpr int ABSMAX_BLOCKS = 1024;
+constexpr int ABSMAX_TRACK = 8192;        // longest rows whose `least` is tracked (both arrays fit the LDS; no kernel that takes longer ones asks)
+
+size_t absmax_scratch_bytes(int d) { return d <= ABSMAX_TRACK ? (size_t)2 * ABSMAX_BLOCKS * d * sizeof(float) : 0; }
+
+hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, int *wide, void *scratch, hipStream_t s)
 {
-    // out: d floats; uses a temporary of 2 * nblocks * d numbers that is freed before returning
-    const int nblocks = 1024;
-    const bool track = d <= 8192;         // (both arrays fit the LDS, and no kernel that takes longer rows asks)
-    float *partial = nullptr;
-    hipError_t e = hipMalloc((void **)&partial, (size_t)nblocks * d * (track ? 2 : 1) * sizeof(float));
-    if (e != hipSuccess) return e;
-    unsigned *least = track ? reinterpret_cast<unsigned *>(partial + (size_t)nblocks * d) : nullptr;
-    hipLaunchKernelGGL(absmax_partial_kernel, dim3(nblocks), dim3(256), (size_t)d * (track ? 2 : 1) * sizeof(float), s, x, rows, d, partial, least, nonfinite);
-    hipLaunchKernelGGL(absmax_final_kernel, dim3((d + 63) / 64), dim3(1024), 0, s, partial, least, nblocks, d, out, wide);
-    e = hipGetLastError();
-    hipError_t e2 = hipStreamSynchronize(s);
-    (void)hipFree(partial);
-    return e != hipSuccess ? e : e2;
+    const bool track = d <= ABSMAX_TRACK;
+    float *partial = static_cast<float *>(scratch);
+    if (!track) {
+        // (up to 256 MB: not kept, given back before returning)
+        const hipError_t e = hipMalloc((void **)&partial, (size_t)ABSMAX_BLOCKS * d * sizeof(float));
+        if (e != hipSuccess) return e;
+    }
+    unsigned *least = track ? reinterpret_cast<unsigned *>(partial + (size_t)ABSMAX_BLOCKS * d) : nullptr;
+    hipLaunchKernelGGL(absmax_partial_kernel, dim3(ABSMAX_BLOCKS), dim3(256), (size_t)d * (track ? 2 : 1) * sizeof(float), s, x, rows, d, partial, least, nonfinite);
+    hipLaunchKernelGGL(absmax_final_kernel, dim3((d + 63) / 64), dim3(1024), 0, s, partial, least, ABSMAX_BLOCKS, d, out, wide);
+    hipError_t e = hipGetLastError();
+    if (!track) {
+        const hipError_t e2 = hipStreamSynchronize(s);
+        (void)hipFree(partial);
+        if (e == hipSuccess) e = e2;
+    }
+    return e;
 }
 
 hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1, hipStream_t s)
