@@ -641,9 +641,16 @@ __device__ __forceinline__ int split_count(SPLIT_ARG SplitUpdate &u, int W, int 
     }
     return n;
 }
+// (The shares are rounded to fp32, added in fp64 and rounded once more: 2^-23 of the sum at worst, however many they are, and
+// as their roundings are independent about 2^-24.  Added in fp32, 64 shares of a column far from the origin were several times
+// that off.  Their 64-bit integers instead cost 11 % of a step, k = 64, d = 32, b = 500, W = 256, for twice the bytes.)
 __device__ __forceinline__ void split_sums8(float (&sm)[8], SPLIT_ARG SplitUpdate &u, int W, int k, int i, int c, int j0, int d)
 {
     split_row8(sm, u.part + ((size_t)i * k + c) * d, j0, d);
+    if (u.shares == 1) return;
+    double total[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) total[e] = (double)sm[e];
     for (int s0 = 1; s0 < u.shares; s0 += 4) {
         float v[4][8];
 #pragma unroll
@@ -651,8 +658,10 @@ __device__ __forceinline__ void split_sums8(float (&sm)[8], SPLIT_ARG SplitUpdat
 #pragma unroll
         for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sm[e] += s0 + q < u.shares ? v[q][e] : 0.0f;
+            for (int e = 0; e < 8; ++e) total[e] += s0 + q < u.shares ? (double)v[q][e] : 0.0;
     }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sm[e] = (float)total[e];
 }
 
 __device__ double split_block_sum(double v, double *red)

@@ -125,3 +125,23 @@ def test_one_huge_element_does_not_touch_the_other_workers(B, oracle, kernel, tu
     err = rel_fro(g.get_state(), o.w)
     # rounding of sums and updates (a few 2^-24 per step), and the odd near-tie of an fp32 state
     assert np.delete(err, 2).max() <= 1e-5
+
+
+@pytest.mark.parametrize("kernel,d,W,b", [("GENERIC", 75, 2, 20000), ("GENERIC", 13, 1, 8192), ("GENERIC", 5, 3, 6000), ("GENERIC", 300, 1, 40000),
+                                          ("MFMA", 96, 2, 20000)])
+def test_a_sum_over_many_shares_is_rounded_once(B, kernel, d, W, b):
+    # One step of two centroids, all samples at the first, far from the origin, where c w - S cancels.  In units of the last
+    # place of w: S is rounded by half a unit, its up to 64 shares by half a unit of THEIRS each (independently: an eighth of a
+    # unit of S together), 0.75 of that reaches w, doubled where S and w lie differently in their binades; the update itself
+    # rounds by half a unit and little more.
+    rng = np.random.default_rng(d)
+    X = (1.0e4 + rng.uniform(0.0, 6.0e3, (W * b, d))).astype(np.float32)
+    w0 = np.stack([X[:b].mean(0, dtype=np.float64), np.full(d, 3.0e5)]).astype(np.float32)
+    g = B.ASGD(2, d, W, b, 0.75, E=0, kernel=getattr(B, "KERNEL_" + kernel), tune=SPLIT if kernel == "GENERIC" else 0)
+    g.load_shards(to_dev(X))
+    g.set_state(-1, w0)
+    g.run_steps(1)
+    S = X.reshape(W, b, d).sum(1, dtype=np.float64)
+    exact = w0[0].astype(np.float64) - 0.75 * (b * w0[0].astype(np.float64) - S) / b
+    off = np.abs(g.get_state()[:, 0] - exact) / np.spacing(exact.astype(np.float32))
+    assert off.max() <= 1.6, off.max()
