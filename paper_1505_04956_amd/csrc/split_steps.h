@@ -779,9 +779,10 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
                     cnp[CNT_ACCEPTED] += __builtin_popcount(delta_mask);
                     cnp[CNT_PARZEN_NEAR] += near;
                 }
-                // (deterministic mode tests for the round and need not clear; a plain store could overtake the sender's next stamp)
-                for (int n = 0; n < p.nb && p.mode != ASGD_MODE_DETERMINISTIC; ++n)
-                    p.stamp[exchange_buffer(now.read_parity, p.nb, n, p.W, i)] = -1;
+                // A buffer is emptied when it is looked at, in either mode: mode and interval may change between two runs.
+                // (Deterministic mode: the sender's next stamp goes into this buffer two rounds on.)
+                for (int n = 0; n < p.nb; ++n)
+                    __hip_atomic_store(p.stamp + exchange_buffer(now.read_parity, p.nb, n, p.W, i), -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
         __syncthreads();
@@ -1148,6 +1149,8 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             else split_update_call<2>(run, i, 0);
             if (r->sync && now.merge) {
                 __syncthreads();
+                // (thread 0 has emptied the stamps: they have arrived before the sender may write them again)
+                if (threadIdx.x == 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                 if (threadIdx.x == 0) __hip_atomic_store(r->p.consumed + i, now.round, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
