@@ -63,8 +63,9 @@ enum {
                                     Default auto.  All give the same results to rounding.  The kernels keep
                                     messages in flight in different formats; when the kernel changes between
                                     two runs the library carries them over (see asgd_get_exchange). */
-    ASGD_OPT_TUNE = 8,           /* launch-shape variant of the chosen kernel (0 = default; shape-agnostic kernel: 1 one
-                                    workgroup per worker, 2 matrix cores, whatever the size); for
+    ASGD_OPT_TUNE = 8,           /* launch-shape variant of the chosen kernel (0 = default; shape-agnostic kernel: bits 1 one
+                                    workgroup per worker, 2 matrix cores, whatever the size, 4 several launches
+                                    per step also where one launch would do); for
                                     performance experiments: the variants compute the same thing and may
                                     differ in the rounding of their sums */
     ASGD_OPT_COOPERATIVE = 9,    /* 1 (default): a run that needs all its workgroups resident at the
@@ -103,10 +104,13 @@ enum { ASGD_MFMA_PARTS_MAX_STATE = 1 << 18 };
 enum {
     ASGD_OPT_WAIT_POLLS = 12,       /* test hook: polls a workgroup may spend, in total, on the waits of one launch
                                        (0 = the library's default of some 10^5, i.e. a fraction of a second) */
-    ASGD_OPT_DROP_UNANNOUNCED = 13  /* test hook: 1 = the recipient does not know which messages ASGD_OPT_DROP_RATE
+    ASGD_OPT_DROP_UNANNOUNCED = 13, /* test hook: 1 = the recipient does not know which messages ASGD_OPT_DROP_RATE
                                        loses, so a run that is one launch waits for them until its poll budget is
                                        gone and then returns ASGD_ESYNC (every kernel still ends normally); 0 (default):
                                        a lost message is skipped at once */
+    ASGD_OPT_REFUSE_ONE_LAUNCH = 14 /* test hook: 1 = runs that would be one launch of workgroups which wait for each other
+                                       behave as if the runtime refused it: the run is then done with more
+                                       launches and no waits inside them.  Default 0. */
 };
 enum { ASGD_MODE_DETERMINISTIC = 0, ASGD_MODE_FREE_RUNNING = 1 };
 enum { ASGD_LR_CONST = 0, ASGD_LR_INV_COUNT = 1 };

@@ -26,6 +26,7 @@ struct asgd_ctx {
     int cooperative = 1;
     int wait_polls = 0;
     int drop_unannounced = 0;
+    int refuse_one_launch = 0;
 
     int device = 0;
     hipStream_t stream = nullptr;
@@ -116,7 +117,6 @@ StepParams make_params(const asgd_ctx *c)
     p.cooperative = c->cooperative;
     p.wait_polls = c->wait_polls;
     p.drop_unannounced = c->drop_unannounced;
-    p.one_launch = 0;
     return p;
 }
 
@@ -448,6 +448,10 @@ int asgd_set_option(asgd_ctx *ctx, int key, double value)
             if (value != 0 && value != 1) return ASGD_EINVAL;
             ctx->drop_unannounced = (int)value;
             return ASGD_OK;
+        case ASGD_OPT_REFUSE_ONE_LAUNCH:
+            if (value != 0 && value != 1) return ASGD_EINVAL;
+            ctx->refuse_one_launch = (int)value;
+            return ASGD_OK;
         case ASGD_OPT_TUNE:
             if (value < 0 || value > 1000 || value != floor(value)) return ASGD_EINVAL;
             ctx->tune = (int)value;
@@ -677,29 +681,33 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             p.one_launch = 1;
         }
     }
-    if (split) {
+    p.phases_only = kernel == ASGD_KERNEL_GENERIC && (ctx->tune & 4);
+    // device memory of the split kernels' launches; none: the kernels that need none
+    auto take_scratch = [&]() -> bool {
         const size_t need = split_scratch_bytes(p);
-        if (need > SPLIT_SCRATCH_MAX) {
-            split = false;
-        } else if (need > ctx->split_bytes) {
-            if (ctx->split_scratch) (void)hipFree(ctx->split_scratch);
-            ctx->split_scratch = nullptr;
-            ctx->split_bytes = 0;
-            if (hipMalloc(&ctx->split_scratch, need) == hipSuccess) {
-                ctx->split_bytes = need;
-            } else {
-                (void)hipGetLastError();         // no room: the form that needs no scratch
-                split = false;
-            }
+        if (need > SPLIT_SCRATCH_MAX) return false;
+        if (need <= ctx->split_bytes) return true;
+        if (ctx->split_scratch) (void)hipFree(ctx->split_scratch);
+        ctx->split_scratch = nullptr;
+        ctx->split_bytes = 0;
+        if (hipMalloc(&ctx->split_scratch, need) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
         }
-    }
-    if (kernel == ASGD_KERNEL_MFMA && !split) {
-        if (!ctx->xnorm2max) HIP_TRY(ctx, hipMalloc((void **)&ctx->xnorm2max, sizeof(float)));
-        if (!ctx->xnorm2max_valid) {
-            HIP_TRY(ctx, launch_rownorm2max(ctx->x, ctx->H * ctx->W, ctx->d, ctx->xnorm2max, ctx->stream));
-            ctx->xnorm2max_valid = true;
+        ctx->split_bytes = need;
+        return true;
+    };
+    auto take_norms = [&]() -> hipError_t {
+        hipError_t e = hipSuccess;
+        if (!ctx->xnorm2max) e = hipMalloc((void **)&ctx->xnorm2max, sizeof(float));
+        if (e == hipSuccess && !ctx->xnorm2max_valid) {
+            e = launch_rownorm2max(ctx->x, ctx->H * ctx->W, ctx->d, ctx->xnorm2max, ctx->stream);
+            ctx->xnorm2max_valid = e == hipSuccess;
         }
-    }
+        return e;
+    };
+    if (split) split = take_scratch();
+    if (kernel == ASGD_KERNEL_MFMA && !split) HIP_TRY(ctx, take_norms());
     // Deterministic mode: a worker may only read the message of round r-1 once its sender has
     // finished that round.  Either the whole run is one launch of co-resident workgroups that wait
     // for each other's stamps (small-state and matrix-core kernels, when the workers all fit the
@@ -726,15 +734,22 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             long long tb = (t_done / ctx->E + ONE_LAUNCH_MAX_ROUNDS) * (long long)ctx->E;
             if (tb > t_end) tb = t_end;
             int one = 0;
-            hipError_t e = split_local ? launch_split_steps(p, t_done, tb, ctx->split_scratch, ctx->stream, &one)
+            hipError_t e = ctx->refuse_one_launch ? hipErrorCooperativeLaunchTooLarge
+                           : split_local ? launch_split_steps(p, t_done, tb, ctx->split_scratch, ctx->stream, &one)
                            : (kernel == ASGD_KERNEL_SMALL) ? launch_small_steps(p, t_done, tb, ctx->stream, true)
                                                          : launch_mfma_steps(p, t_done, tb, ctx->xnorm2max, ctx->stream, true);
             if (e == hipSuccess) {
                 ++launches;
                 t_done = tb;
                 ctx->passed_t = tb;
-            } else if (!split_local && (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported)) {
-                (void)hipGetLastError();     // the rest (or all of it): one launch per round
+            } else if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
+                // The rest (or all of it) without waits inside a launch: one launch per round, of the split kernels the phases.
+                (void)hipGetLastError();
+                if (split) {
+                    p.phases_only = 1;
+                    split = take_scratch();
+                    if (kernel == ASGD_KERNEL_MFMA && !split) HIP_TRY(ctx, take_norms());
+                }
                 break;
             } else {
                 HIP_TRY(ctx, e);

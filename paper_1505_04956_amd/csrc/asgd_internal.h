@@ -44,6 +44,7 @@ struct StepParams {
     int cooperative;       // use the cooperative launch API for single-launch runs
     int wait_polls;        // polls a workgroup may spend on all the waits of a launch (test hook; 0 = the kernel's default)
     int one_launch;        // fp16-split step kernels: one launch per call also where phases are a little faster
+    int phases_only;       // fp16-split step kernels: no launch whose workgroups wait for each other
     int drop_unannounced;  // test hook: the recipient does not know which messages the loss hook drops and waits for them
 };
 

@@ -246,7 +246,7 @@ bool split_local_form(const StepParams &p)
     const int rounds = (p.W + SPLIT_CUS - 1) / SPLIT_CUS;
     int dev = 0, cus = 0;                  // (a partition of a device may have fewer compute units: not resident at once)
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-    return cus >= SPLIT_CUS && p.parts == 1 && 4LL * p.W >= 3LL * rounds * SPLIT_CUS && (rounds == 1 || p.one_launch) && (p.E == 0 || p.W < 2 || (p.mode == ASGD_MODE_DETERMINISTIC && p.E >= 4));
+    return !p.phases_only && cus >= SPLIT_CUS && p.parts == 1 && 4LL * p.W >= 3LL * rounds * SPLIT_CUS && (rounds == 1 || p.one_launch) && (p.E == 0 || p.W < 2 || (p.mode == ASGD_MODE_DETERMINISTIC && p.E >= 4));
 }
 
 size_t split_scratch_bytes(const StepParams &p) { return scratch_layout(p, make_plan(p, split_local_form(p))).bytes; }
