@@ -40,9 +40,11 @@ enum {
     ASGD_EHIP = -4,     /* a HIP runtime call failed; asgd_last_hip_error() has its code */
     ASGD_ESYNC = -5     /* a bounded wait inside a kernel expired (runs that are one launch of workgroups
                            which wait for each other's messages; all the waits of a workgroup draw on one
-                           budget of polls that grows with the rounds of the launch, and a launch covers
-                           at most 1024 rounds, so such a launch ends within a second plus a few
-                           milliseconds per round of waiting).  The run is lost: the step counter is not advanced and later runs
+                           budget of polls that grows with the rounds of the launch, or, in the kernels
+                           with fp16-split operands, every wait has a budget that covers the longest a
+                           round can take, and after one expired wait there are no more; a launch covers
+                           at most 1024 rounds, so it ends within a second plus a few milliseconds per
+                           round of waiting, or plus a few such rounds).  The run is lost: the step counter is not advanced and later runs
                            fail with ASGD_ESTATE until asgd_load_shards(), or asgd_set_state() followed by
                            asgd_set_step(), have put the context back on a known footing. */
 };
@@ -109,8 +111,9 @@ enum {
                                        gone and then returns ASGD_ESYNC (every kernel still ends normally); 0 (default):
                                        a lost message is skipped at once */
     ASGD_OPT_REFUSE_ONE_LAUNCH = 14 /* test hook: 1 = runs that would be one launch of workgroups which wait for each other
-                                       behave as if the runtime refused it: the run is then done with more
-                                       launches and no waits inside them.  Default 0. */
+                                       behave as if the runtime refused it; 2 (split kernels): as if one of its
+                                       workgroups found no place on the device.  Either way the run is done with
+                                       more launches and no waits inside them.  Default 0. */
 };
 enum { ASGD_MODE_DETERMINISTIC = 0, ASGD_MODE_FREE_RUNNING = 1 };
 enum { ASGD_LR_CONST = 0, ASGD_LR_INV_COUNT = 1 };

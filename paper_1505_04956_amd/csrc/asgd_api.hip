@@ -117,6 +117,7 @@ StepParams make_params(const asgd_ctx *c)
     p.cooperative = c->cooperative;
     p.wait_polls = c->wait_polls;
     p.drop_unannounced = c->drop_unannounced;
+    p.refuse_one_launch = c->refuse_one_launch;
     return p;
 }
 
@@ -449,7 +450,7 @@ int asgd_set_option(asgd_ctx *ctx, int key, double value)
             ctx->drop_unannounced = (int)value;
             return ASGD_OK;
         case ASGD_OPT_REFUSE_ONE_LAUNCH:
-            if (value != 0 && value != 1) return ASGD_EINVAL;
+            if (value < 0 || value > 2 || value != floor(value)) return ASGD_EINVAL;
             ctx->refuse_one_launch = (int)value;
             return ASGD_OK;
         case ASGD_OPT_TUNE:
@@ -676,8 +677,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         if (kernel == ASGD_KERNEL_GENERIC)
             split = (ctx->tune & 2) || (!(ctx->tune & 1) && (ctx->b >= 96 || (double)ctx->b * ctx->k * ctx->d >= 8192.0));
         else if (kernel == ASGD_KERNEL_MFMA) {
-            split = ctx->tune == 0 && !ctx->drop_unannounced && ctx->wait_polls == 0 && ctx->parts == 1 &&
-                    (ctx->mode == ASGD_MODE_DETERMINISTIC || ctx->E == 0 || ctx->W < 2) && mfma_split_pays(ctx);
+            split = ctx->tune == 0 && ctx->parts == 1 && (ctx->mode == ASGD_MODE_DETERMINISTIC || ctx->E == 0 || ctx->W < 2) && mfma_split_pays(ctx);
             p.one_launch = 1;
         }
     }
@@ -734,14 +734,23 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             long long tb = (t_done / ctx->E + ONE_LAUNCH_MAX_ROUNDS) * (long long)ctx->E;
             if (tb > t_end) tb = t_end;
             int one = 0;
-            hipError_t e = ctx->refuse_one_launch ? hipErrorCooperativeLaunchTooLarge
+            hipError_t e = ctx->refuse_one_launch == 1 ? hipErrorCooperativeLaunchTooLarge
                            : split_local ? launch_split_steps(p, t_done, tb, ctx->split_scratch, ctx->stream, &one)
                            : (kernel == ASGD_KERNEL_SMALL) ? launch_small_steps(p, t_done, tb, ctx->stream, true)
                                                          : launch_mfma_steps(p, t_done, tb, ctx->xnorm2max, ctx->stream, true);
+            if (e == hipSuccess && split_local) {
+                // (the next launch may only begin if this one has not been called off)
+                HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+                if (*ctx->flag_host == 2) {
+                    *ctx->flag_host = 0;
+                    e = hipErrorCooperativeLaunchTooLarge;
+                }
+            }
             if (e == hipSuccess) {
                 ++launches;
                 t_done = tb;
                 ctx->passed_t = tb;
+                if (split_local && *ctx->flag_host) break;       // an expired wait: nothing more may run on these states
             } else if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
                 // The rest (or all of it) without waits inside a launch: one launch per round, of the split kernels the phases.
                 (void)hipGetLastError();
@@ -756,6 +765,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             }
         }
     }
+    if (*ctx->flag_host) t_done = t_end;
     if (split && t_done < t_end) {
         HIP_TRY(ctx, launch_split_steps(p, t_done, t_end, ctx->split_scratch, ctx->stream, &launches));
         ctx->passed_t = -1;

@@ -211,7 +211,7 @@ SplitPlan make_plan(const StepParams &p, bool local)
     return q;
 }
 
-struct Scratch { size_t frag, hs, state, gate, mail, m, ms, xmeta, colscale, part, cntpart, idx, bytes; };
+struct Scratch { size_t frag, hs, state, arrived, gate, mail, m, ms, xmeta, colscale, part, cntpart, idx, bytes; };
 Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
 {
     Scratch s;
@@ -220,6 +220,7 @@ Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
     s.frag = take(q.frag_bytes * p.W);
     s.hs = take((size_t)q.kpad * p.W * 4);
     s.state = take((size_t)3 * p.W * sizeof(SplitState));
+    s.arrived = take(sizeof(int));            // (cleared with the states before it)
     s.gate = take((size_t)p.W * p.nb * q.upd_blocks * sizeof(SplitGate));
     s.mail = take((size_t)p.W * sizeof(SplitMail));
     s.m = take((size_t)p.d * 4);
@@ -281,7 +282,7 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, v
     hipLaunchKernelGGL(split_scales_kernel, dim3(1), dim3(256), 0, s, p.xabsmax, (float *)(base + l.m), p.d, q.dpad, p.b,
                        (float *)(base + l.ms), (float *)(base + l.xmeta), (double *)(base + l.colscale));
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemsetAsync(base + l.state, 0, (size_t)3 * p.W * sizeof(SplitState), s);
+    if (e == hipSuccess) e = hipMemsetAsync(base + l.state, 0, l.gate - l.state, s);
     if (e != hipSuccess) return e;
     SplitLaunch l2;
     memset(&l2, 0, sizeof(l2));
@@ -293,6 +294,14 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, v
         r.round0 = p.E > 0 ? t0 / p.E : 0;
         r.te0 = p.E > 0 ? (int)(t0 % p.E) : 0;
         r.sync = det && p.E > 0 && p.W > 1;
+        r.arrived = (int *)(base + l.arrived);
+        r.expected = q.grid + (p.refuse_one_launch == 2 ? 1 : 0);            // (test hook: one that never comes)
+        // A round of a neighbour: E steps of all its workers, of which every sample may have to be decided in fp64 against all
+        // centroids.  That was measured at up to 0.3 ns per element of b k d (1.2 where k d is small next to the 8 us of
+        // a step); four times as much is allowed.
+        const double step = 4e-3 * p.b * (double)p.k * p.d + 4096.0;
+        const double polls = (double)(1 << 18) + step * (double)p.E * ((p.W + q.grid - 1) / q.grid);
+        r.wait_polls = (int)(polls < (double)(1 << 29) ? polls : (double)(1 << 29));
         switch (q.longrow ? 0 : q.nch) {
             case 0: e = launch_split_local_0(r, q.grid, q.lds, s); break;
             case 1: e = launch_split_local_1(r, q.grid, q.lds, s); break;

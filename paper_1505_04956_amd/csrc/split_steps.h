@@ -961,7 +961,12 @@ struct SplitRun {
     long long t0, t1, round0;              // local form: steps of the launch, round of the first
     int te0;                               // first step's place in its round
     int sync;                              // workers wait for each other's messages (deterministic exchange)
+    int *arrived;                          // workgroups that have started (zero before the launch), SPLIT_NOBODY or'ed in to call it off
+    int expected;                          // workgroups that have to have started before any begins
+    int wait_polls;                        // polls a workgroup may spend on one wait
 };
+constexpr int SPLIT_NOBODY = 1 << 30;
+constexpr int SPLIT_ARRIVAL_POLLS = 1 << 20;       // polls until the launch is called off (half a second and more)
 struct SplitLaunch {                       // arguments of a phase
     SplitRun run;
     SplitStep now;
@@ -1048,9 +1053,10 @@ hipError_t split_launch_phase(const SplitLaunch &l, int blocks, int threads, uns
     return hipGetLastError();
 }
 
-// Bounded wait for a flag another workgroup writes, by one thread.  All the waits of a workgroup draw on one budget of polls
-// (about half a microsecond each) that grows with the rounds of the launch; when it is used up it waits for nothing any
-// more, so a launch outlasts its normal duration by a fraction of a second at most.
+// Bounded wait for a flag another workgroup writes, by one thread; about half a microsecond per poll.  What a workgroup may
+// spend on one wait follows the longest a round of its neighbour can take (SplitRun::wait_polls), and once a wait has
+// expired it waits for nothing any more.  (A budget for all the waits of a launch ran out where one worker's samples all
+// had to be decided in fp64.)
 __device__ inline bool split_wait_flag(const int *flag, int want, bool at_least, int &budget)
 {
     while (budget > 0) {
@@ -1060,6 +1066,23 @@ __device__ inline bool split_wait_flag(const int *flag, int want, bool at_least,
         --budget;
     }
     return false;
+}
+
+// Whether all the workgroups of a launch have a place on the device, by one thread of each: they wait for each other's messages
+// later, and one that finds no place (another stream's kernel holds it) would let the others' waits expire.  All of them
+// or none: the word ends as `expected` or with SPLIT_NOBODY in it, whichever comes first, and nothing has been touched yet.
+__device__ inline bool split_all_arrived(int *word, int expected, int polls)
+{
+    int v = __hip_atomic_fetch_add(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1;
+    while (v < expected) {
+        if (polls-- > 0) {
+            __builtin_amdgcn_s_sleep(8);
+            v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else if (__hip_atomic_compare_exchange_strong(word, &v, v | SPLIT_NOBODY, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+            return false;
+        }
+    }
+    return v == expected;
 }
 
 // Local form.  NC: chunks of 16 columns of a row, 0: long rows.  Workgroup g has the workers g, g + grid, ...; every wait
@@ -1080,16 +1103,23 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
     for (int n = 0; n < MAX_BUFFERS; ++n) now.shift[n] = 0;
     const int W = r->p.W;
     const bool det = r->p.mode == ASGD_MODE_DETERMINISTIC;
-    int budget = 0;
-    if (threadIdx.x == 0) {
-        const long long rounds = r->p.E > 0 ? (r->t1 - r->t0) / r->p.E + 1 : 0;
-        budget = r->p.wait_polls > 0 ? r->p.wait_polls : (1 << 18) + 4096 * (int)min(rounds, 65536LL);
-        sh.now = now;
-    }
+    // (the test hook is a budget for all the waits of the launch)
+    int budget = r->p.wait_polls > 0 ? r->p.wait_polls : r->wait_polls;
     auto wait = [&](const int *flag, int want, bool at_least) {            // (thread 0)
-        if (budget > 0 && !split_wait_flag(flag, want, at_least, budget))
+        if (budget <= 0) return;
+        if (!split_wait_flag(flag, want, at_least, budget))
             __hip_atomic_store(r->p.error_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        else if (r->p.wait_polls == 0) budget = r->wait_polls;
     };
+    if (r->sync) {
+        if (threadIdx.x == 0) {
+            sh.delta = split_all_arrived(r->arrived, r->expected, SPLIT_ARRIVAL_POLLS);
+            if (!sh.delta) __hip_atomic_store(r->p.error_flag, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        __syncthreads();
+        if (!sh.delta) return;
+    }
+    if (threadIdx.x == 0) sh.now = now;
     __syncthreads();
     for (int i = blockIdx.x; i < W; i += gridDim.x) {
         split_update_call<0>(run, i, 0);
