@@ -183,10 +183,9 @@ def main():
     algo_flops = samples * (2.0 * wl.k * wl.d + wl.k + wl.d)   # expanded-form scores, compares, accumulation
     kname = KERNEL_NAMES.get(int(st.kernel), "?")
     if int(st.kernel) == B.KERNEL_MFMA:
-        # the default variant of the matrix-core kernel takes the fp16-split kernels where messages are not racing
-        split = args.tune == 0 and args.parts == 1 and args.mode != "free"
-        peak = FP16_SPLIT_PEAK_TFLOPS if split else FP32_MATRIX_PEAK_TFLOPS
-        kname = "split_local_kernel" if split else kname
+        form = g.last_run_form()
+        peak = FP32_MATRIX_PEAK_TFLOPS if form == B.FORM_FP32 else FP16_SPLIT_PEAK_TFLOPS
+        kname = {B.FORM_SPLIT_LAUNCH: "split_local_kernel", B.FORM_SPLIT_PHASES: "split_phase_kernel"}.get(form, kname)
         achieved = algo_flops / (avg_kernel_ms * 1e-3) / 1e12
         roofline = {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                     "frac": achieved / peak, "algorithmic_flops_per_step": algo_flops,

@@ -18,6 +18,7 @@ OPT_EXCHANGE_EVERY, OPT_SEED, OPT_MODE, OPT_PARZEN, OPT_LR_MODE, OPT_DROP_RATE, 
 MODE_DETERMINISTIC, MODE_FREE_RUNNING = 0, 1
 LR_CONST, LR_INV_COUNT = 0, 1
 KERNEL_AUTO, KERNEL_GENERIC, KERNEL_SMALL, KERNEL_MFMA = 0, 1, 2, 3
+FORM_NONE, FORM_FP32, FORM_SPLIT_LAUNCH, FORM_SPLIT_PHASES = range(4)
 
 # every symbol include/asgd.h declares
 SYMBOLS = (
@@ -25,7 +26,7 @@ SYMBOLS = (
     "asgd_run_epochs", "asgd_run_steps", "asgd_set_assign_dump", "asgd_get_state",
     "asgd_get_mean_state", "asgd_quant_error", "asgd_last_run_ms", "asgd_get_stats", "asgd_get_worker_counters",
     "asgd_schedule_peer", "asgd_schedule_peer_n", "asgd_last_hip_error", "asgd_destroy", "asgd_strerror",
-    "asgd_quant_error_noalloc", "asgd_get_exchange", "asgd_set_exchange",
+    "asgd_quant_error_noalloc", "asgd_get_exchange", "asgd_set_exchange", "asgd_last_run_form",
 )
 
 
@@ -79,6 +80,7 @@ def lib():
             "asgd_get_mean_state": (C.c_int, [vp, vp, C.c_size_t]),
             "asgd_quant_error": (C.c_int, [vp, C.c_int, C.POINTER(dbl)]),
             "asgd_last_run_ms": (C.c_int, [vp, C.POINTER(dbl)]),
+            "asgd_last_run_form": (C.c_int, [vp, C.POINTER(C.c_int32)]),
             "asgd_get_stats": (C.c_int, [vp, C.POINTER(asgd_stats)]),
             "asgd_get_worker_counters": (C.c_int, [vp, vp, vp, vp]),
             "asgd_schedule_peer": (i64, [u64, i64, i64, i64]),
@@ -177,6 +179,12 @@ def asgd_quant_error_noalloc(x_dev_ptr, N, k, d, w_dev_ptr, out_dev_ptr, stream=
 def asgd_last_run_ms(h) -> float:
     v = C.c_double()
     _check(lib().asgd_last_run_ms(h, C.byref(v)), "asgd_last_run_ms")
+    return v.value
+
+
+def asgd_last_run_form(h) -> int:
+    v = C.c_int32()
+    _check(lib().asgd_last_run_form(h, C.byref(v)), "asgd_last_run_form")
     return v.value
 
 
@@ -282,6 +290,9 @@ class ASGD:
 
     def last_run_ms(self):
         return asgd_last_run_ms(self.h)
+
+    def last_run_form(self):
+        return asgd_last_run_form(self.h)
 
     def stats(self):
         return asgd_get_stats(self.h)

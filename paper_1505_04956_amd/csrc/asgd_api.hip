@@ -60,7 +60,7 @@ struct asgd_ctx {
 
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     double last_ms = 0.0;
-    int last_kernel = 0, last_launches = 0;
+    int last_kernel = 0, last_launches = 0, last_form = ASGD_FORM_NONE;
     long long passed_t = -1;    // step up to which `consumed` holds what a one-launch run needs (-1: unknown)
     int fill_kernel = 0;        // kernel whose message format the exchange buffers were last emptied for
     bool desynced = false;      // a bounded wait expired in the last run: states and buffers are not those of any step
@@ -765,13 +765,16 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             }
         }
     }
+    int form = split_local && t_done > ctx->t ? ASGD_FORM_SPLIT_LAUNCH : ASGD_FORM_FP32;
     if (*ctx->flag_host) t_done = t_end;
     if (split && t_done < t_end) {
+        form = !rounds && split_local ? ASGD_FORM_SPLIT_LAUNCH : ASGD_FORM_SPLIT_PHASES;      // (nothing to wait for: one launch as well)
         HIP_TRY(ctx, launch_split_steps(p, t_done, t_end, ctx->split_scratch, ctx->stream, &launches));
         ctx->passed_t = -1;
         t_done = t_end;
     }
     for (long long ta = t_done; ta < t_end;) {
+        form = ASGD_FORM_FP32;
         long long tb = t_end;
         if (rounds) {
             const long long next = (ta / ctx->E + 1) * (long long)ctx->E;
@@ -793,6 +796,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     ctx->last_ms = ms;
     ctx->last_kernel = kernel;
     ctx->last_launches = launches;
+    if (steps > 0) ctx->last_form = form;
     if (*ctx->flag_host) {
         // A bounded wait inside a kernel expired: some worker went on without a message it was owed, so the states are
         // not those of any step of the deterministic run.  The step counter stays where it was and the context refuses
@@ -880,6 +884,13 @@ int asgd_last_run_ms(asgd_ctx *ctx, double *out)
 {
     if (!ctx || !out) return ASGD_EINVAL;
     *out = ctx->last_ms;
+    return ASGD_OK;
+}
+
+int asgd_last_run_form(asgd_ctx *ctx, int32_t *out)
+{
+    if (!ctx || !out) return ASGD_EINVAL;
+    *out = ctx->last_form;
     return ASGD_OK;
 }
 

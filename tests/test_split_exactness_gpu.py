@@ -96,7 +96,7 @@ def test_steps_on_small_and_large_numbers(B, oracle, kernel, k, d, b, scale):
     X = make_data(4 * (3 * b + 11), d, k, seed=9) * np.float32(scale)
     g, _ = run_both(B, oracle, X, k, 4, b, 0.05, 2, 6, kernel=getattr(B, "KERNEL_" + kernel), tune=SPLIT if kernel == "GENERIC" else 0,
                     check_qe=False)
-    assert g.stats().exact_rechecks < 4 * 6 * b // 20             # (and without taking everything to fp64)
+    assert g.last_run_form() == B.FORM_SPLIT_PHASES and g.stats().exact_rechecks < 4 * 6 * b // 20             # (and without taking everything to fp64)
 
 
 @pytest.mark.parametrize("k,d", [(20, 13), (40, 150)])
@@ -123,6 +123,8 @@ def test_one_huge_element_does_not_touch_the_other_workers(B, oracle, kernel, tu
     o = oracle.OracleASGD(X, k=k, W=W, b=b, lr=0.05, E=0)
     o.run_steps(6)
     err = rel_fro(g.get_state(), o.w)
+    if abs(value) > 1.0e10:
+        assert g.last_run_form() == B.FORM_FP32
     # rounding of sums and updates (a few 2^-24 per step), and the odd near-tie of an fp32 state
     assert np.delete(err, 2).max() <= 1e-5
 
@@ -143,5 +145,6 @@ def test_a_sum_over_many_shares_is_rounded_once(B, kernel, d, W, b):
     g.run_steps(1)
     S = X.reshape(W, b, d).sum(1, dtype=np.float64)
     exact = w0[0].astype(np.float64) - 0.75 * (b * w0[0].astype(np.float64) - S) / b
+    assert g.last_run_form() == B.FORM_SPLIT_PHASES
     off = np.abs(g.get_state()[:, 0] - exact) / np.spacing(exact.astype(np.float32))
     assert off.max() <= 1.6, off.max()

@@ -56,9 +56,10 @@ def test_a_refused_launch_becomes_several(B, kernel, k, d, W, b, E, refuse):
         g.load_shards(to_dev(X))
         g.run_steps(2 * E + 2)
         g.run_steps(1)
-        res.append((g.get_state(), g.worker_counters(), g.stats()))
-    (wa, ca, sa), (wb, cb, sb) = res
+        res.append((g.get_state(), g.worker_counters(), g.stats(), g.last_run_form()))
+    (wa, ca, sa, _), (wb, cb, sb, _) = res
     assert sa.launches == 1 and sb.launches > 1 and sb.steps == 2 * E + 3
+    assert res[0][3] == B.FORM_SPLIT_LAUNCH and res[1][3] == B.FORM_SPLIT_PHASES
     assert np.array_equal(ca[:, :2], cb[:, :2])
     # the same assignments; sums of several shares are rounded a few times more, the sums of Eq. 4 in another order
     assert np.abs(wa - wb).max() <= 1e-5 * np.abs(wa).max()
@@ -76,7 +77,8 @@ def test_a_slow_neighbour_is_waited_for(B):
     for tune in (0, 4):                                 # one launch, phases (no waits)
         g = context(B, X, k, W, b, E, tune=tune)
         g.run_steps(3 * E + 1)
-        res.append((g.get_state(), g.worker_counters()))
+        res.append((g.get_state(), g.worker_counters(), g.last_run_form()))
+    assert res[0][2] == B.FORM_SPLIT_LAUNCH and res[1][2] == B.FORM_SPLIT_PHASES
     assert np.array_equal(res[0][1][:, :2], res[1][1][:, :2])
     assert np.abs(res[0][0] - res[1][0]).max() <= 1e-5
 
@@ -91,7 +93,7 @@ def test_lost_messages_cuts_and_many_buffers_in_one_launch(B, oracle, kernel, k,
     whole = B.ASGD(k, d, W, b, 0.05, E=E, kernel=id, buffers=2, drop_rate=0.3)
     whole.load_shards(to_dev(X))
     whole.run_steps(steps)
-    assert whole.stats().launches == 1
+    assert whole.stats().launches == 1 and whole.last_run_form() == B.FORM_SPLIT_LAUNCH
     cut = B.ASGD(k, d, W, b, 0.05, E=E, kernel=id, buffers=2, drop_rate=0.3)
     cut.load_shards(to_dev(X))
     for n in (1, 1, E - 2, E - 1, 1, steps - 2 * E):
@@ -115,6 +117,7 @@ def test_a_long_call_is_cut_into_launches(B, kernel, k, d, W, b, E):
         for n in cuts:
             g.run_steps(n)
         res.append((g.get_state(), g.worker_counters(), g.stats().launches))
+        assert g.last_run_form() == B.FORM_SPLIT_LAUNCH
     assert res[0][2] == 3
     assert np.array_equal(res[0][0], res[1][0]) and np.array_equal(res[0][1], res[1][1])
 
@@ -132,6 +135,7 @@ def test_an_expired_wait_is_reported_and_the_context_recovers(B, kernel, k, d, W
     with pytest.raises(B.AsgdError) as e:
         g.run_steps(2 * E + 1)
     assert e.value.code == B.ESYNC and g.stats().steps == 0 and g.stats().launches == 1
+    assert g.last_run_form() == B.FORM_SPLIT_LAUNCH
     with pytest.raises(B.AsgdError) as e:
         g.run_steps(1)
     assert e.value.code == B.ESTATE

@@ -24,6 +24,7 @@ def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
     X = make_data(W * H + 1, d, k, seed=100 + d)
     g, _ = run_both(B, oracle, X, k, W, b, 0.05, E, 7, kernel=B.KERNEL_GENERIC, tune=SPLIT, buffers=buffers,
                     parts=parts)
+    assert g.last_run_form() == B.FORM_SPLIT_PHASES
     again = B.ASGD(k, d, W, b, 0.05, E=E, kernel=B.KERNEL_GENERIC, tune=SPLIT, buffers=buffers, parts=parts)
     again.load_shards(to_dev(X))
     again.run_steps(3)
@@ -33,6 +34,15 @@ def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
 
 # both sides of the rules that choose between the kernels and between the one launch and the phases: mini-batches of 512,
 # k of 256, exchange at every step from 100 workers on, workers beyond one and two per compute unit
+# (what runs: F the fp32 kernel, L one launch, P phases - of the matrix-core kernel, of the shape-agnostic one)
+DISPATCH = {
+    (64, 32, 8, 511, 4, 1): "FP", (64, 32, 8, 512, 4, 2): "PP", (256, 16, 4, 100, 4, 1): "FP", (257, 16, 4, 100, 4, 1): "PP",
+    (12, 8, 99, 100, 1, 1): "FP", (12, 8, 100, 100, 1, 1): "PP", (32, 16, 191, 97, 4, 1): "FP", (32, 16, 192, 520, 4, 1): "LL",
+    (40, 8, 256, 512, 4, 2): "LL", (32, 16, 257, 97, 4, 1): "FP", (500, 24, 300, 64, 4, 1): "PP", (32, 16, 384, 97, 3, 1): "PP",
+    (24, 8, 600, 100, 0, 1): "FP",
+}
+
+
 @pytest.mark.parametrize("kernel", ["MFMA", "GENERIC"])
 @pytest.mark.parametrize("k,d,W,b,E,buffers", [
     (64, 32, 8, 511, 4, 1), (64, 32, 8, 512, 4, 2), (256, 16, 4, 100, 4, 1), (257, 16, 4, 100, 4, 1),
@@ -41,13 +51,24 @@ def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
 ])
 def test_split_kernel_dispatch(B, oracle, k, d, W, b, E, buffers, kernel):
     X = make_data(W * max(2 * b + 5, k), d, k, seed=200 + W)
-    run_both(B, oracle, X, k, W, b, 0.05, E, 9, kernel=getattr(B, "KERNEL_" + kernel), buffers=buffers)
+    g, _ = run_both(B, oracle, X, k, W, b, 0.05, E, 9, kernel=getattr(B, "KERNEL_" + kernel), buffers=buffers)
+    form = {B.FORM_FP32: "F", B.FORM_SPLIT_LAUNCH: "L", B.FORM_SPLIT_PHASES: "P"}[g.last_run_form()]
+    assert form == DISPATCH[(k, d, W, b, E, buffers)][0 if kernel == "MFMA" else 1]
+
+
+# the shape-agnostic kernel takes one workgroup per worker where a step is tiny
+@pytest.mark.parametrize("k,d,b,form", [(3, 2, 95, "FP32"), (3, 2, 96, "SPLIT_PHASES"), (10, 9, 91, "FP32"), (10, 9, 92, "SPLIT_PHASES")])
+def test_split_kernel_dispatch_of_tiny_steps(B, oracle, k, d, b, form):
+    X = make_data(4 * (2 * b + 3), d, k, seed=b)
+    g, _ = run_both(B, oracle, X, k, 4, b, 0.05, 2, 5, kernel=B.KERNEL_GENERIC)
+    assert g.last_run_form() == getattr(B, "FORM_" + form)
 
 
 @pytest.mark.parametrize("k,d,b", [(7, 5, 200), (40, 77, 333), (12, 140, 90)])
 def test_split_kernel_running_mean(B, oracle, k, d, b):
     X = make_data(4 * (5 * b + 3), d, k, seed=5)
-    run_both(B, oracle, X, k, 4, b, 0.1, 0, 9, lr_mode=1, kernel=B.KERNEL_GENERIC)
+    g, _ = run_both(B, oracle, X, k, 4, b, 0.1, 0, 9, lr_mode=1, kernel=B.KERNEL_GENERIC)
+    assert g.last_run_form() == B.FORM_SPLIT_PHASES
 
 
 def pair(B, X, k, W, b, steps, w0=None, **kw):
@@ -59,7 +80,7 @@ def pair(B, X, k, W, b, steps, w0=None, **kw):
         if w0 is not None:
             g.set_state(-1, w0)
         g.run_steps(steps)
-        out.append((g.get_state(), g.stats()))
+        out.append((g.get_state(), g.stats(), g.last_run_form()))
     return out
 
 
@@ -81,11 +102,12 @@ def test_split_kernel_awkward_data(B, k, d, what):
         w0 = np.float32(3.0e5) * make_data(k, d, k, seed=3)
     elif what == "w0_zero":
         w0 = np.zeros((k, d), dtype=np.float32)
-    (wa, sa), (wb, sb) = pair(B, np.ascontiguousarray(X, dtype=np.float32), k, W, b, steps, w0)
+    (wa, sa, fa), (wb, sb, fb) = pair(B, np.ascontiguousarray(X, dtype=np.float32), k, W, b, steps, w0)
     scale = np.abs(wb).max(axis=(0, 1)) + np.float32(1e-30)
     # (identical samples: w - c G ties in Eq. 4 and equal distances are decided the same way in both forms)
     assert np.all(np.abs(wa - wb).max(axis=(0, 1)) <= 1e-6 * scale), what
     assert sa.sent == sb.sent and sa.received == sb.received
+    assert fa == B.FORM_SPLIT_PHASES and fb == B.FORM_FP32
 
 
 @pytest.mark.parametrize("value", [np.inf, np.nan])
@@ -93,7 +115,8 @@ def test_split_kernel_leaves_non_finite_samples_to_the_other_form(B, value):
     k, d, W, b = 20, 13, 4, 100
     X = make_data(W * 500, d, k, seed=9)
     X[777, 5] = value
-    (wa, sa), (wb, sb) = pair(B, X, k, W, b, 6)
+    (wa, sa, fa), (wb, sb, fb) = pair(B, X, k, W, b, 6)
+    assert fa == fb == B.FORM_FP32
     assert np.array_equal(wa, wb, equal_nan=True) and sa.launches == sb.launches
 
 
