@@ -52,6 +52,8 @@ struct asgd_ctx {
                                    // far smaller than its largest element
     void *split_scratch = nullptr; // matrix-core form of the shape-agnostic kernel, allocated on first use
     size_t split_bytes = 0;
+    void *split_data = nullptr;    // what its kernels need to know of the samples, allocated on first use
+    bool split_data_valid = false;
     void *load_scratch = nullptr;  // partial maxima of asgd_load_shards(), kept: taking 3 MB and giving them back was 80 us a call
     long long *ncum = nullptr, *counters = nullptr;
     double *qpart = nullptr, *qout = nullptr;
@@ -94,7 +96,7 @@ size_t kd_of(const asgd_ctx *c) { return (size_t)c->k * c->d; }
 void free_all(asgd_ctx *c)
 {
     void *ptrs[] = {c->w, c->slot, c->acc, c->xabsmax, c->mean, c->stamp, c->consumed, c->cnt, c->assign_tmp,
-                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->load_scratch};
+                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->split_data, c->load_scratch};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (c->flag_host) (void)hipHostFree(c->flag_host);
@@ -479,6 +481,7 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     ctx->pending = false;
     ctx->loaded = false;
     ctx->xnorm2max_valid = false;
+    ctx->split_data_valid = false;
     StepParams p = make_params(ctx);
     HIP_TRY(ctx, launch_init_first_k(p, ctx->stream));
     int rc = clear_exchange(ctx, ASGD_KERNEL_SMALL);
@@ -697,6 +700,15 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         ctx->split_bytes = need;
         return true;
     };
+    auto take_data = [&]() -> hipError_t {
+        hipError_t e = hipSuccess;
+        if (!ctx->split_data) e = hipMalloc(&ctx->split_data, split_data_bytes(ctx->d));
+        if (e == hipSuccess && !ctx->split_data_valid) {
+            e = launch_split_data(p, ctx->split_data, ctx->stream);
+            ctx->split_data_valid = e == hipSuccess;
+        }
+        return e;
+    };
     auto take_norms = [&]() -> hipError_t {
         hipError_t e = hipSuccess;
         if (!ctx->xnorm2max) e = hipMalloc((void **)&ctx->xnorm2max, sizeof(float));
@@ -707,6 +719,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         return e;
     };
     if (split) split = take_scratch();
+    if (split) HIP_TRY(ctx, take_data());
     if (kernel == ASGD_KERNEL_MFMA && !split) HIP_TRY(ctx, take_norms());
     // Deterministic mode: a worker may only read the message of round r-1 once its sender has
     // finished that round.  Either the whole run is one launch of co-resident workgroups that wait
@@ -735,7 +748,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             if (tb > t_end) tb = t_end;
             int one = 0;
             hipError_t e = ctx->refuse_one_launch == 1 ? hipErrorCooperativeLaunchTooLarge
-                           : split_local ? launch_split_steps(p, t_done, tb, ctx->split_scratch, ctx->stream, &one)
+                           : split_local ? launch_split_steps(p, t_done, tb, ctx->split_data, ctx->split_scratch, ctx->stream, &one)
                            : (kernel == ASGD_KERNEL_SMALL) ? launch_small_steps(p, t_done, tb, ctx->stream, true)
                                                          : launch_mfma_steps(p, t_done, tb, ctx->xnorm2max, ctx->stream, true);
             if (e == hipSuccess && split_local) {
@@ -769,7 +782,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     if (*ctx->flag_host) t_done = t_end;
     if (split && t_done < t_end) {
         form = !rounds && split_local ? ASGD_FORM_SPLIT_LAUNCH : ASGD_FORM_SPLIT_PHASES;      // (nothing to wait for: one launch as well)
-        HIP_TRY(ctx, launch_split_steps(p, t_done, t_end, ctx->split_scratch, ctx->stream, &launches));
+        HIP_TRY(ctx, launch_split_steps(p, t_done, t_end, ctx->split_data, ctx->split_scratch, ctx->stream, &launches));
         ctx->passed_t = -1;
         t_done = t_end;
     }

@@ -64,7 +64,10 @@ hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1,
 bool split_kernel_supports(int k, int d, int b);
 bool split_local_form(const StepParams &p);
 size_t split_scratch_bytes(const StepParams &p);
-hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, void *scratch, hipStream_t s, int *launches);
+// data: split_data_bytes() of device memory that launch_split_data() has filled for these samples
+size_t split_data_bytes(int d);
+hipError_t launch_split_data(const StepParams &p, void *data, hipStream_t s);
+hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, const void *data, void *scratch, hipStream_t s, int *launches);
 bool small_kernel_supports(int k, int d, int b);
 // bytes of one exchange buffer in the small-state kernel's own message format (0: kernel not applicable)
 size_t small_kernel_message_bytes(int k, int d);

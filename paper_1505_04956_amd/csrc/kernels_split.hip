@@ -41,7 +41,7 @@ constexpr int SPLIT_SAMPLE_ROWS = 1024;     // rows looked at for the middle of 
 constexpr unsigned SPLIT_LDS = 150 * 1024;
 constexpr int SPLIT_CUS = 256;
 
-// ---- once per call of the library: middle of the data, scale of the samples, scales of the fixed-point sums ----
+// ---- once per set of samples: middle of the data, scale of the samples, scales of the fixed-point sums ----
 // m_j: mean of up to SPLIT_SAMPLE_ROWS rows spread over the data (any value is a valid reference; one near the middle
 // keeps |x - m| small).  One workgroup of 16 waves per 64 columns, eight rows per wave in flight.
 __global__ __launch_bounds__(1024) void split_middle_kernel(const float *x, long long rows, int d, float *m)
@@ -114,6 +114,7 @@ struct SplitPlan {
     int g, upd_blocks;             // update: lanes per row, workgroups per worker
 };
 
+int padded_row(int d) { return d > 128 ? (d + 127) / 128 * 128 : (d + 15) / 16 * 16; }
 unsigned round16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
 
 SplitPlan make_plan(const StepParams &p, bool local)
@@ -121,7 +122,7 @@ SplitPlan make_plan(const StepParams &p, bool local)
     SplitPlan q;
     memset(&q, 0, sizeof(q));
     q.longrow = p.d > 128;
-    q.dpad = q.longrow ? (p.d + 127) / 128 * 128 : (p.d + 15) / 16 * 16;
+    q.dpad = padded_row(p.d);
     q.nch = q.dpad / 16;
     q.nblk = (p.k + 31) / 32;
     q.npair = (q.nblk + 1) / 2;
@@ -211,7 +212,22 @@ SplitPlan make_plan(const StepParams &p, bool local)
     return q;
 }
 
-struct Scratch { size_t frag, hs, state, arrived, gate, mail, m, ms, xmeta, colscale, part, cntpart, idx, bytes; };
+// What depends on the samples only, computed once after they are loaded.
+struct Data { size_t m, ms, xmeta, colscale, bytes; };
+Data data_layout(int d)
+{
+    Data s;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { const size_t at = o; o += (bytes + 255) / 256 * 256; return at; };
+    s.m = take((size_t)d * 4);
+    s.ms = take((size_t)padded_row(d) * 4);
+    s.xmeta = take(16);
+    s.colscale = take((size_t)d * 16);
+    s.bytes = o;
+    return s;
+}
+
+struct Scratch { size_t frag, hs, state, arrived, gate, mail, part, cntpart, idx, bytes; };
 Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
 {
     Scratch s;
@@ -223,10 +239,6 @@ Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
     s.arrived = take(sizeof(int));            // (cleared with the states before it)
     s.gate = take((size_t)p.W * p.nb * q.upd_blocks * sizeof(SplitGate));
     s.mail = take((size_t)p.W * sizeof(SplitMail));
-    s.m = take((size_t)p.d * 4);
-    s.ms = take((size_t)q.dpad * 4);
-    s.xmeta = take(16);
-    s.colscale = take((size_t)p.d * 16);
     s.part = take((size_t)q.sum_shares * p.W * p.k * p.d * 4);
     s.cntpart = take((size_t)q.sum_shares * p.W * p.k * 4);
     s.idx = take(q.fused ? 0 : (size_t)p.W * p.b * 4);
@@ -252,7 +264,19 @@ bool split_local_form(const StepParams &p)
 
 size_t split_scratch_bytes(const StepParams &p) { return scratch_layout(p, make_plan(p, split_local_form(p))).bytes; }
 
-hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, void *scratch, hipStream_t s, int *launches)
+size_t split_data_bytes(int d) { return data_layout(d).bytes; }
+
+hipError_t launch_split_data(const StepParams &p, void *data, hipStream_t s)
+{
+    const Data l = data_layout(p.d);
+    unsigned char *base = static_cast<unsigned char *>(data);
+    hipLaunchKernelGGL(split_middle_kernel, dim3((p.d + 63) / 64), dim3(1024), 0, s, p.x, p.H * p.W, p.d, (float *)(base + l.m));
+    hipLaunchKernelGGL(split_scales_kernel, dim3(1), dim3(256), 0, s, p.xabsmax, (float *)(base + l.m), p.d, padded_row(p.d), p.b,
+                       (float *)(base + l.ms), (float *)(base + l.xmeta), (double *)(base + l.colscale));
+    return hipGetLastError();
+}
+
+hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, const void *data, void *scratch, hipStream_t s, int *launches)
 {
     const bool local = split_local_form(p);
     const SplitPlan q = make_plan(p, local);
@@ -263,7 +287,9 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, v
     a.x = p.x; a.w = p.w;
     a.frag = base + l.frag; a.frag_bytes = q.frag_bytes;
     a.hs = (float *)(base + l.hs);
-    a.ms = (float *)(base + l.ms); a.xmeta = (float *)(base + l.xmeta); a.colscale = (double *)(base + l.colscale);
+    const Data dl = data_layout(p.d);
+    const unsigned char *from = static_cast<const unsigned char *>(data);
+    a.ms = (const float *)(from + dl.ms); a.xmeta = (const float *)(from + dl.xmeta); a.colscale = (const double *)(from + dl.colscale);
     a.part = (float *)(base + l.part); a.cntpart = (int *)(base + l.cntpart);
     a.idx = q.fused ? nullptr : (int *)(base + l.idx);
     a.counters = p.counters;
@@ -275,14 +301,10 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, v
     SplitUpdate u;
     u.frag = base + l.frag; u.hs = (float *)(base + l.hs);
     u.state = (SplitState *)(base + l.state); u.gate = (SplitGate *)(base + l.gate); u.mail = (SplitMail *)(base + l.mail);
-    u.m = (float *)(base + l.m); u.xmeta = a.xmeta; u.part = a.part; u.cntpart = a.cntpart;
+    u.m = (const float *)(from + dl.m); u.xmeta = a.xmeta; u.part = a.part; u.cntpart = a.cntpart;
     u.frag_bytes = q.frag_bytes; u.kpad = q.kpad; u.dpad = q.dpad; u.shares = q.sum_shares; u.g = q.g; u.blocks = q.upd_blocks;
 
-    hipLaunchKernelGGL(split_middle_kernel, dim3((p.d + 63) / 64), dim3(1024), 0, s, p.x, p.H * p.W, p.d, (float *)(base + l.m));
-    hipLaunchKernelGGL(split_scales_kernel, dim3(1), dim3(256), 0, s, p.xabsmax, (float *)(base + l.m), p.d, q.dpad, p.b,
-                       (float *)(base + l.ms), (float *)(base + l.xmeta), (double *)(base + l.colscale));
-    hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemsetAsync(base + l.state, 0, l.gate - l.state, s);
+    hipError_t e = hipMemsetAsync(base + l.state, 0, l.gate - l.state, s);
     if (e != hipSuccess) return e;
     SplitLaunch l2;
     memset(&l2, 0, sizeof(l2));

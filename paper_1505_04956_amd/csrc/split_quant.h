@@ -261,7 +261,7 @@ __global__ __launch_bounds__(SPLITQ_THREADS) __attribute__((amdgpu_waves_per_eu(
     __shared__ double red[8];
     __shared__ float redf[3][8];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-    const int k = a.k, d = a.d, nch = a.dpad / 16, npair = (a.nblk + 1) / 2;
+    const int k = a.k, d = a.d, npair = (a.nblk + 1) / 2;
     float *hs = reinterpret_cast<float *>(smem + a.off_hs), *m = reinterpret_cast<float *>(smem + a.off_m);
     half8 *frag = reinterpret_cast<half8 *>(smem);
 
