@@ -120,6 +120,7 @@ enum { ASGD_LR_CONST = 0, ASGD_LR_INV_COUNT = 1 };
 enum { ASGD_KERNEL_AUTO = 0, ASGD_KERNEL_GENERIC = 1, ASGD_KERNEL_SMALL = 2, ASGD_KERNEL_MFMA = 3 };
 /* Two of the kernels stand for a pair each, and asgd_last_run_form() says which of the pair ran: the fp32 kernel, or the one
    with fp16-split operands, as one launch or as several launches per step (phases). */
+/* (SPLIT_LAUNCH also where that one launch was refused or the call is short, and one launch per round took its place.) */
 enum { ASGD_FORM_NONE = 0, ASGD_FORM_FP32 = 1, ASGD_FORM_SPLIT_LAUNCH = 2, ASGD_FORM_SPLIT_PHASES = 3 };
 
 typedef struct asgd_stats {
@@ -273,8 +274,7 @@ int asgd_quant_error_noalloc(const float *x_dev, int64_t N, int k, int d, const 
    the context's stream around its kernel launches.  No device access. */
 int asgd_last_run_ms(asgd_ctx *ctx, double *out);
 
-/* ASGD_FORM_* of the last asgd_run_* call (of its last launch, if one launch was refused and several took its place).  No
-   device access. */
+/* ASGD_FORM_* of the last asgd_run_* call.  No device access. */
 int asgd_last_run_form(asgd_ctx *ctx, int32_t *out);
 
 /* Totals since asgd_load_shards(). */

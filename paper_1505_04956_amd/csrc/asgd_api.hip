@@ -733,7 +733,10 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     long long t_done = ctx->t;           // steps [ctx->t, t_done) have been launched
     const bool split_local = split && split_local_form(p);
     const bool one_launch = split_local || (!split && ((kernel == ASGD_KERNEL_SMALL && (ctx->tune & 3) != 3) || (kernel == ASGD_KERNEL_MFMA && !(ctx->tune & 4))));
-    if (rounds && one_launch && steps > 0) {
+    // The split kernels' one launch costs 45 us more than a plain one (cooperative, and its workgroups make sure that all have a
+    // place): a call of less than two rounds is one plain launch per round instead, the same bits (k = 64, d = 32, W = 256,
+    // b = 512, one step: 93 us, 50).
+    if (rounds && one_launch && steps > 0 && !(split_local && steps / ctx->E < 2)) {
         // every worker has passed the merge points before the first step of this run
         const long long r0 = ctx->t / ctx->E;
         const int passed = (int)((ctx->t % ctx->E) != 0 ? r0 : (r0 > 0 ? r0 - 1 : 0));
@@ -765,29 +768,27 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
                 ctx->passed_t = tb;
                 if (split_local && *ctx->flag_host) break;       // an expired wait: nothing more may run on these states
             } else if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
-                // The rest (or all of it) without waits inside a launch: one launch per round, of the split kernels the phases.
-                (void)hipGetLastError();
-                if (split) {
-                    p.phases_only = 1;
-                    split = take_scratch();
-                    if (kernel == ASGD_KERNEL_MFMA && !split) HIP_TRY(ctx, take_norms());
-                }
+                (void)hipGetLastError();     // the rest (or all of it): one launch per round
                 break;
             } else {
                 HIP_TRY(ctx, e);
             }
         }
     }
-    int form = split_local && t_done > ctx->t ? ASGD_FORM_SPLIT_LAUNCH : ASGD_FORM_FP32;
+    const int form = !split ? ASGD_FORM_FP32 : split_local ? ASGD_FORM_SPLIT_LAUNCH : ASGD_FORM_SPLIT_PHASES;
     if (*ctx->flag_host) t_done = t_end;
-    if (split && t_done < t_end) {
-        form = !rounds && split_local ? ASGD_FORM_SPLIT_LAUNCH : ASGD_FORM_SPLIT_PHASES;      // (nothing to wait for: one launch as well)
-        HIP_TRY(ctx, launch_split_steps(p, t_done, t_end, ctx->split_data, ctx->split_scratch, ctx->stream, &launches));
+    p.no_waits = 1;
+    while (split && t_done < t_end) {
+        long long tb = t_end;
+        if (split_local && rounds) {
+            const long long next = (t_done / ctx->E + 1) * (long long)ctx->E;
+            if (next < tb) tb = next;
+        }
+        HIP_TRY(ctx, launch_split_steps(p, t_done, tb, ctx->split_data, ctx->split_scratch, ctx->stream, &launches));
         ctx->passed_t = -1;
-        t_done = t_end;
+        t_done = tb;
     }
     for (long long ta = t_done; ta < t_end;) {
-        form = ASGD_FORM_FP32;
         long long tb = t_end;
         if (rounds) {
             const long long next = (ta / ctx->E + 1) * (long long)ctx->E;

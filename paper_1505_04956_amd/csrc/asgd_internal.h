@@ -44,7 +44,8 @@ struct StepParams {
     int cooperative;       // use the cooperative launch API for single-launch runs
     int wait_polls;        // polls a workgroup may spend on all the waits of a launch (test hook; 0 = the kernel's default)
     int one_launch;        // fp16-split step kernels: one launch per call also where phases are a little faster
-    int phases_only;       // fp16-split step kernels: no launch whose workgroups wait for each other
+    int phases_only;       // fp16-split step kernels: phases also where one launch would do
+    int no_waits;          // fp16-split step kernels, local form: the launch lies within a round
     int refuse_one_launch; // test hook: 1 such launches are refused (by the host), 2 one of their workgroups never starts
     int drop_unannounced;  // test hook: the recipient does not know which messages the loss hook drops and waits for them
 };
@@ -59,8 +60,8 @@ hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int 
 hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1, hipStream_t s);
 // Step kernels with fp16-split operands (any row length; finite samples), all on `scratch` (split_scratch_bytes() of device
 // memory, nothing in it is kept between calls).  Local form: one launch whose workers wait for each other's messages, as
-// with `persistent` below; else a few launches per step.  If the workgroups of the local form do not all find a place on the
-// device it does nothing and sets *p.error_flag to 2.
+// with `persistent` below; else a few launches per step.  If the workgroups of a local form with waits do not all find a
+// place on the device it does nothing and sets *p.error_flag to 2.
 bool split_kernel_supports(int k, int d, int b);
 bool split_local_form(const StepParams &p);
 size_t split_scratch_bytes(const StepParams &p);

@@ -315,7 +315,7 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, c
         r.t0 = t0; r.t1 = t1;
         r.round0 = p.E > 0 ? t0 / p.E : 0;
         r.te0 = p.E > 0 ? (int)(t0 % p.E) : 0;
-        r.sync = det && p.E > 0 && p.W > 1;
+        r.sync = det && p.E > 0 && p.W > 1 && !p.no_waits;
         r.arrived = (int *)(base + l.arrived);
         r.expected = q.grid + (p.refuse_one_launch == 2 ? 1 : 0);            // (test hook: one that never comes)
         // A round of a neighbour: E steps of all its workers, of which every sample may have to be decided in fp64 against all
