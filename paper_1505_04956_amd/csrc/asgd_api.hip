@@ -267,22 +267,28 @@ int import_exchange(asgd_ctx *c, int kernel, const float *values, const int32_t 
 }
 
 // Whether the fp16-split step kernels are faster than the fp32 matrix kernel (the default variant of
-// ASGD_KERNEL_MFMA).  They take 15 to 20 us per step whatever its size, the latter a step of one workgroup per worker,
-// and both sides were measured over k x d from 12 x 8 to 500 x 24 and 4 to 1000 workers (us per step, fp32 -> split):
-//   up to 256 workers: 600 samples 1.02 to 1.9 times as fast (W = 256, k = 64, d = 32: 33.1 -> 32.5; W = 4, k = d = 100:
-//     64 -> 48), 2400 samples 1.3 to 4; 150 samples 0.7 to 0.96 (W = 32, k = 64, d = 32: 14.3 -> 20.8), but k = 500 1.05
-//     to 1.2 (the fp32 kernel streams the state);
-//   exchange at every step, 100 workers and more: always (fp32 waits for messages every step: 31 -> 24, 89 -> 55);
-//   more than 256 workers where the fp32 kernel keeps two of them on a compute unit: only long steps (k = d = 100,
-//     b = 600: 121 -> 155, b = 2000: 270 -> 250; a job of two epochs from loading to states 14.6 -> 11.2 ms; calls of ten
-//     epochs late in a run, when few samples lie between centroids and the fp32 kernel's two workers per compute unit have
-//     drifted apart: 237 -> 241); otherwise always (k = 500, d = 24: 201 -> 133).
+// ASGD_KERNEL_MFMA).  The former take 14 to 20 us per step whatever its size, the latter a step of one workgroup per worker.
+// Microseconds per step of long calls, fp32 and split:
+//   mini-batches of 512 and more: W = 4, k = 12, d = 8: b = 512 20, 17; b = 2000 50, 26; W = 32, k = 64, d = 32, b = 512: 24, 23;
+//     k = d = 100: W = 4 72, 45; W = 256 84, 79 (150 samples: W = 32, k = 64, d = 32: 14, 21).  A call of one step: 0.94 to 1.7
+//     times as fast.  Not where the workers fill the device and exchange (one launch with waits on either side) and steps are
+//     short (W = 256, b = 512, k = 64, d = 32: 34, 37; k = 12, d = 8: 27.6, 28);
+//   k > 256, any mini-batch: a state that does not fit the LDS as fp32 is streamed (k = 1000, d = 64, b = 16, W = 4: 125, 56); one
+//     that does: k = 300, d = 16, b = 64: W = 4 29, 27; W = 200 39, 34; k = 500, d = 24: W = 200 52, 51, but W = 4 42, 48;
+//   exchange at every step, 100 workers and more: always (fp32 waits for messages every step: W = 150, k = 12, d = 8, b = 100: 33,
+//     24; W = 256, k = 64, d = 32, b = 60: 68, 25; calls of one step 1.2 to 1.8 times as fast);
+//   more than 256 workers where the fp32 kernel keeps two of them on a compute unit: only long steps (k = d = 100, W = 512,
+//     b = 600: 121, 155; b = 2000: in milliseconds per epoch of 19 steps, two epochs 5.1, 4.9, a first one 5.5, 5.1, ten late in a run,
+//     when few samples lie between centroids and the two workers of a compute unit have drifted apart, 4.60, 4.65); otherwise
+//     always (k = 500, d = 24, W = 300, E = 1: 200, 83).
 bool mfma_split_pays(const asgd_ctx *c)
 {
-    const bool often = c->E > 0 && c->E < 4 && c->W > 1;
-    if (c->W > 256)
-        return often || !mfma_kernel_two_per_cu(c->k, c->d, c->b) || (double)c->b * c->k * c->d >= 1.5e7;
-    return (often && c->W >= 100) || c->b >= 512 || c->k > 256;
+    const bool exchange = c->E > 0 && c->W > 1, often = exchange && c->E < 4;
+    const double size = (double)c->b * c->k * c->d;
+    if (c->W > 256) return often || !mfma_kernel_two_per_cu(c->k, c->d, c->b) || size >= 1.5e7;
+    if (often && c->W >= 100) return true;
+    if (c->k > 256) return c->W >= 64 || (double)c->k * c->d <= 8192.0 || !mfma_state_resident(c->k, c->d, c->b) || c->b >= 512;
+    return c->b >= 512 && !(exchange && c->W >= 192 && size < 2.0e6);
 }
 
 }  // namespace
@@ -668,7 +674,9 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     // variant also what the matrix-core kernel runs (three products on the fp16 matrix instructions take a fifth of the
     // time of the fp32 ones).  Free-running mode of the latter stays with the kernel whose workers drift freely.
     // Shape-agnostic: ASGD_OPT_TUNE bit 0 asks for one workgroup per worker, bit 1 for the matrix-core form whatever
-    // the size.  A step of the former takes 0.15 us per sample of the mini-batch or more, one of the latter 15 us or more.
+    // the size.  A step of the former takes 0.14 us per sample of the mini-batch or more, one of the latter 14 us or more and a
+    // call 25 us once (W = 4, k = 3, d = 2: b = 96 14.3 and 16.0 us per step, a call of one step 31 and 39; b = 128 18.8 and 15.8,
+    // 38 and 39; k = 12, d = 7: b = 20 10.3 and 13.9, b = 96 19.5 and 15.7, 37 and 39; k = 20, d = 21, b = 20: 34 and 15, 50 and 38).
     // The split kernels' gradient sums are in fixed point with one scale per column: exact to 2^-51 of its largest element, which
     // is more than fp32 sums give unless nearly everything in a column is far smaller (one huge element, a marker for
     // a missing value): those go to the kernels with fp32 sums.  (More than 256 workers of the matrix-core kernel, two on
@@ -678,7 +686,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
                       !(kernel == ASGD_KERNEL_MFMA && ctx->W > 256 && mfma_kernel_two_per_cu(ctx->k, ctx->d, ctx->b));
     if (ctx->flag_host[1] == 0 && !wide && split_kernel_supports(ctx->k, ctx->d, ctx->b) && steps > 0) {
         if (kernel == ASGD_KERNEL_GENERIC)
-            split = (ctx->tune & 2) || (!(ctx->tune & 1) && (ctx->b >= 96 || (double)ctx->b * ctx->k * ctx->d >= 8192.0));
+            split = (ctx->tune & 2) || (!(ctx->tune & 1) && (ctx->b >= 128 || (double)ctx->b * ctx->k * ctx->d >= 6000.0));
         else if (kernel == ASGD_KERNEL_MFMA) {
             split = ctx->tune == 0 && ctx->parts == 1 && (ctx->mode == ASGD_MODE_DETERMINISTIC || ctx->E == 0 || ctx->W < 2) && mfma_split_pays(ctx);
             p.one_launch = 1;

@@ -81,6 +81,8 @@ hipError_t launch_small_steps(const StepParams &p, long long t0, long long t1, h
 bool mfma_kernel_supports(int k, int d, int b, const void *x);
 // the variant with four waves and the state resident in LDS, two workers per compute unit
 bool mfma_kernel_two_per_cu(int k, int d, int b);
+// the variants with eight waves: whether the state stays in LDS
+bool mfma_state_resident(int k, int d, int b);
 hipError_t launch_rownorm2max(const float *x, long long rows, int d, float *out, hipStream_t s);   // max_n |x_n|^2
 // persistent = true: as for the small-state kernel (deterministic mode; hipErrorCooperativeLaunchTooLarge when the
 // workers do not all fit the device at once)

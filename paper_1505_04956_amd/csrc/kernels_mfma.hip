@@ -1677,6 +1677,8 @@ bool mfma_kernel_supports(int k, int d, int b, const void *x)
 
 bool mfma_kernel_two_per_cu(int k, int d, int b) { return mfma_geom(k, b, mfma_chunks(d), true, 4).bytes <= 78 * 1024; }
 
+bool mfma_state_resident(int k, int d, int b) { return mfma_geom(k, b, mfma_chunks(d), true, 8).bytes <= MF_LDS_BUDGET; }
+
 bool mfma_quant_error_supports(int k, int d, const void *x)
 {
     if (d % 4 != 0 || d < 16 || d > 128 || k < 32 || k > 32768 || (((uintptr_t)x) & 15u) != 0) return false;

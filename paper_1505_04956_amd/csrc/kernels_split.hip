@@ -251,9 +251,9 @@ Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
 // Local form: the workers fill the device, one workgroup of eight waves each (three quarters of them at least: fewer are
 // better off with phases, which cut their mini-batches), and exchange every fourth step at most (every message costs its
 // sender a write-back and its recipient an invalidation of the L2, which phases get from the end of a launch: k = 64,
-// d = 32, b = 500, E = 1: 105 us per step local, 33 us in phases).  Two rounds of workers and more take as long as
-// phases or longer (512 workers, E = 8: k = 12, d = 8, b = 600: 47 us per step local, 34 in phases; k = d = 100,
-// b = 2000: 252 and 236): only where the caller wants one launch.
+// d = 32, b = 500, E = 1: 105 us per step local, 33 us in phases).  Two rounds of workers and more take longer than phases
+// (512 workers, E = 8: k = 12, d = 8, b = 600: 47 us per step local, 34 in phases; k = d = 100, b = 2000, ten epochs a call:
+// 245 and 227): only for the caller that promises one launch per call (the matrix-core kernel: asgd_run_epochs()).
 bool split_local_form(const StepParams &p)
 {
     const int rounds = (p.W + SPLIT_CUS - 1) / SPLIT_CUS;

@@ -40,7 +40,7 @@ def test_a_message_is_gone_once_it_was_looked_at(B, W, tune, parts):
 
 
 FORMS = [  # kernel, k, d, W, b, E: shapes of the one launch, one workgroup per worker, and of two rounds of workers
-    ("GENERIC", 20, 13, 200, 100, 4), ("GENERIC", 40, 150, 192, 96, 5), ("MFMA", 40, 20, 256, 512, 4), ("MFMA", 500, 24, 400, 64, 4),
+    ("GENERIC", 20, 13, 200, 100, 4), ("GENERIC", 40, 150, 192, 96, 5), ("MFMA", 64, 64, 192, 512, 4), ("MFMA", 500, 24, 400, 64, 4),
 ]
 
 
@@ -105,9 +105,9 @@ def test_lost_messages_cuts_and_many_buffers_in_one_launch(B, oracle, kernel, k,
     check_counters(whole.worker_counters(), o.counters, o.parzen_near)
 
 
-@pytest.mark.parametrize("kernel,k,d,W,b,E", [("GENERIC", 3, 2, 192, 96, 4), ("MFMA", 5, 4, 256, 512, 4)])
+@pytest.mark.parametrize("kernel,k,d,W,b,E", [("GENERIC", 3, 2, 192, 128, 4), ("MFMA", 500, 24, 400, 64, 4)])
 def test_a_long_call_is_cut_into_launches(B, kernel, k, d, W, b, E):
-    X = make_data(W * (2 * b + 3), d, k, seed=47)
+    X = make_data(W * max(2 * b + 3, k), d, k, seed=47)
     steps = 2060 * E + 3                                # 1024 rounds a launch
     res = []
     for cuts in ((steps,), (1024 * E, 5, 1030 * E + 1, steps - 2054 * E - 6)):

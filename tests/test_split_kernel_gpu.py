@@ -37,8 +37,9 @@ def test_split_kernel_edges(B, oracle, k, d, W, b, E, buffers, parts):
 # (what runs: F the fp32 kernel, L one launch, P phases - of the matrix-core kernel, of the shape-agnostic one)
 DISPATCH = {
     (64, 32, 8, 511, 4, 1): "FP", (64, 32, 8, 512, 4, 2): "PP", (256, 16, 4, 100, 4, 1): "FP", (257, 16, 4, 100, 4, 1): "PP",
-    (12, 8, 99, 100, 1, 1): "FP", (12, 8, 100, 100, 1, 1): "PP", (32, 16, 191, 97, 4, 1): "FP", (32, 16, 192, 520, 4, 1): "LL",
-    (40, 8, 256, 512, 4, 2): "LL", (32, 16, 257, 97, 4, 1): "FP", (500, 24, 300, 64, 4, 1): "PP", (32, 16, 384, 97, 3, 1): "PP",
+    (12, 8, 99, 100, 1, 1): "FP", (12, 8, 100, 100, 1, 1): "PP", (32, 16, 191, 97, 4, 1): "FP", (32, 16, 192, 520, 4, 1): "FL",
+    (40, 8, 256, 512, 4, 2): "FL", (32, 16, 192, 520, 0, 1): "LL", (64, 64, 192, 512, 4, 1): "LL", (500, 24, 4, 64, 4, 1): "FP",
+    (500, 24, 64, 64, 4, 1): "PP", (32, 16, 257, 97, 4, 1): "FP", (500, 24, 300, 64, 4, 1): "PP", (32, 16, 384, 97, 3, 1): "PP",
     (24, 8, 600, 100, 0, 1): "FP",
 }
 
@@ -48,6 +49,7 @@ DISPATCH = {
     (64, 32, 8, 511, 4, 1), (64, 32, 8, 512, 4, 2), (256, 16, 4, 100, 4, 1), (257, 16, 4, 100, 4, 1),
     (12, 8, 99, 100, 1, 1), (12, 8, 100, 100, 1, 1), (32, 16, 191, 97, 4, 1), (32, 16, 192, 520, 4, 1), (40, 8, 256, 512, 4, 2),
     (32, 16, 257, 97, 4, 1), (500, 24, 300, 64, 4, 1), (32, 16, 384, 97, 3, 1), (24, 8, 600, 100, 0, 1),
+    (32, 16, 192, 520, 0, 1), (64, 64, 192, 512, 4, 1), (500, 24, 4, 64, 4, 1), (500, 24, 64, 64, 4, 1),
 ])
 def test_split_kernel_dispatch(B, oracle, k, d, W, b, E, buffers, kernel):
     X = make_data(W * max(2 * b + 5, k), d, k, seed=200 + W)
@@ -57,7 +59,7 @@ def test_split_kernel_dispatch(B, oracle, k, d, W, b, E, buffers, kernel):
 
 
 # the shape-agnostic kernel takes one workgroup per worker where a step is tiny
-@pytest.mark.parametrize("k,d,b,form", [(3, 2, 95, "FP32"), (3, 2, 96, "SPLIT_PHASES"), (10, 9, 91, "FP32"), (10, 9, 92, "SPLIT_PHASES")])
+@pytest.mark.parametrize("k,d,b,form", [(3, 2, 127, "FP32"), (3, 2, 128, "SPLIT_PHASES"), (10, 9, 66, "FP32"), (10, 9, 67, "SPLIT_PHASES")])
 def test_split_kernel_dispatch_of_tiny_steps(B, oracle, k, d, b, form):
     X = make_data(4 * (2 * b + 3), d, k, seed=b)
     g, _ = run_both(B, oracle, X, k, 4, b, 0.05, 2, 5, kernel=B.KERNEL_GENERIC)
