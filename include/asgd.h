@@ -142,7 +142,10 @@ typedef struct asgd_stats {
  * Alg. 5 with W workers ("nodes"), mini-batch size b and step size eps = lr.
  * Requires k, d, W, b >= 1 and lr > 0 (Alg. 5 "Require"; W = 1 is allowed and equals
  * Alg. 4).  Allocates W*k*d floats of state and the exchange buffers on the current
- * device.  *out is set only on success and must be released with asgd_destroy().
+ * device.  More is allocated by the first call that needs it and kept until asgd_destroy():
+ * 8 KB per column at the first asgd_load_shards() (d <= 8192), and the operands and sums of the
+ * kernels with fp16-split operands at a run, several times W*k*d floats and 32 GiB at most
+ * (a kernel that needs none takes over where there is no room).  *out is set only on success and must be released with asgd_destroy().
  */
 int asgd_create(asgd_ctx **out, int k, int d, int W, int b, float lr);
 
