@@ -214,9 +214,10 @@ int asgd_set_exchange(asgd_ctx *ctx, const float *values_host, const int32_t *ro
  * has finished on the device.  The result does not depend on how a run is cut into
  * calls (deterministic mode: bit for bit), the time does: with the streaming kernel, and
  * with the others where the workers fill the device and exchange every fourth step or less
- * often, a call is ONE kernel launch for every 1024 communication rounds it covers, and the
- * start and the tail of a launch are then paid once per launch, not once per epoch
- * (asgd_stats.launches); else every phase of a step is a launch over all workers.
+ * often, a call of two communication rounds or more is ONE kernel launch for every 1024 rounds
+ * it covers, and the start and the tail of a launch are then paid once per launch, not once per
+ * epoch (asgd_stats.launches); else a round, or every phase of a step, is a launch over all
+ * workers.
  */
 int asgd_run_epochs(asgd_ctx *ctx, int epochs);
 
