@@ -48,8 +48,8 @@ struct asgd_ctx {
     // Error flag of the kernels (an expired bounded wait), in pinned host memory that the device writes directly: the
     // host clears and reads it around a run without a memset or a copy on the stream (each is a separate operation
     // of several microseconds, which counts when a run is one launch of less than a millisecond).
-    int *flag_host = nullptr;      // [0] error flag; set while loading: [1] a sample is not finite, [2] a column is mostly
-                                   // far smaller than its largest element
+    int *flag_host = nullptr;      // [0] error flag; set while loading: [1] a sample is not finite, [2] a column's typical
+                                   // element is far smaller than its largest
     void *split_scratch = nullptr; // matrix-core form of the shape-agnostic kernel, allocated on first use
     size_t split_bytes = 0;
     void *split_data = nullptr;    // what its kernels need to know of the samples, allocated on first use
@@ -678,8 +678,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     // call 25 us once (W = 4, k = 3, d = 2: b = 96 14.3 and 16.0 us per step, a call of one step 31 and 39; b = 128 18.8 and 15.8,
     // 38 and 39; k = 12, d = 7: b = 20 10.3 and 13.9, b = 96 19.5 and 15.7, 37 and 39; k = 20, d = 21, b = 20: 34 and 15, 50 and 38).
     // The split kernels' gradient sums are in fixed point with one scale per column: exact to 2^-51 of its largest element, which
-    // is more than fp32 sums give unless nearly everything in a column is far smaller (one huge element, a marker for
-    // a missing value): those go to the kernels with fp32 sums.  (More than 256 workers of the matrix-core kernel, two on
+    // is more than fp32 sums give unless a column's typical element is far smaller (one huge element, a marker for a missing
+    // value): those go to the kernels with fp32 sums.  (More than 256 workers of the matrix-core kernel, two on
     // a compute unit: its sums are in 32-bit fixed point, the split kernels' are the finer ones.)
     bool split = false;
     const bool wide = ctx->flag_host[2] != 0 &&

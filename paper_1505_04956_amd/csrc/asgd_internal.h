@@ -52,8 +52,8 @@ struct StepParams {
 
 // Launchers (each returns the hipError_t of its launch).
 hipError_t launch_init_first_k(const StepParams &p, hipStream_t s);
-// nonfinite, wide: pinned host memory, set to 1 if an element is infinite or not a number; if most elements of a column are
-// smaller than 2^-26 of its largest (d <= 8192)
+// nonfinite, wide: pinned host memory, set to 1 if an element is infinite or not a number; if the typical element of a column
+// is smaller than 2^-26 of its largest (d <= 8192)
 // scratch: absmax_scratch_bytes() of device memory (none needed if that is 0).  Enqueued only.
 size_t absmax_scratch_bytes(int d);
 hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int *nonfinite, int *wide, void *scratch, hipStream_t s);

@@ -68,10 +68,9 @@ __global__ void init_first_k_kernel(StepParams p)
 
 // partial[block][j] = max |x[row][j]| over the elements this block visits.  The flat array is walked with a stride that is
 // a multiple of d, so a thread always sees one dimension.
-// least (may be null): the smallest, over all groups of eight elements of column j, of a group's largest magnitude, groups of
-// zeros left out (bit patterns, less one).  Far below max |x_j| only if most of the column is: the size of what a single
-// huge element would hide.
-__global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, int d, float *partial, unsigned *least, int *nonfinite)
+// size (may be null): how large the elements of column j are typically, from every eighth one that is not zero: the mean
+// exponents of the block's threads added up, and above 20 bits the number of these threads.
+__global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, int d, float *partial, unsigned *size, int *nonfinite)
 {
     const long long total = n * (long long)d;
     const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -81,58 +80,59 @@ __global__ void absmax_partial_kernel(const float *__restrict__ x, long long n, 
     unsigned *sl = reinterpret_cast<unsigned *>(sm + d);
     for (int j = threadIdx.x; j < d; j += blockDim.x) {
         sm[j] = 0.0f;
-        if (least) sl[j] = 0xffffffffu;
+        if (size) sl[j] = 0;
     }
     __syncthreads();
     if (g < stride) {
         float m = 0.0f;
         unsigned bits = 0;            // (the maximum of two floats drops a NaN, that of their bit patterns does not)
-        unsigned low = 0xffffffffu;
+        unsigned count = 0, exponents = 0;       // (2^24 samples of a thread are 3e13 elements)
+        auto sample = [&](unsigned b) {
+            exponents += b >> 23;     // (of a zero: nothing)
+            count += b != 0 ? 1 : 0;
+        };
         long long e = g;
         for (; e + 7 * stride < total; e += 8 * stride) {      // eight independent loads in flight per thread
             float v[8];
-            unsigned group = 0;
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = x[e + q * stride];
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 m = fmaxf(m, fabsf(v[q]));
-                group = max(group, __float_as_uint(v[q]) & 0x7fffffffu);
+                bits = max(bits, __float_as_uint(v[q]) & 0x7fffffffu);
             }
-            bits = max(bits, group);
-            low = min(low, group - 1u);
+            sample(__float_as_uint(v[0]) & 0x7fffffffu);
         }
-        unsigned group = 0;
+        if (e < total) sample(__float_as_uint(x[e]) & 0x7fffffffu);
         for (; e < total; e += stride) {
             m = fmaxf(m, fabsf(x[e]));
-            group = max(group, __float_as_uint(x[e]) & 0x7fffffffu);
+            bits = max(bits, __float_as_uint(x[e]) & 0x7fffffffu);
         }
-        bits = max(bits, group);
-        low = min(low, group - 1u);
         if (bits >= 0x7f800000u) __hip_atomic_store(nonfinite, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         // max is order independent; |x| >= 0, so the integer order of the bit patterns is the
         // floating-point order and an integer atomic is exact
         atomicMax((unsigned int *)&sm[g % d], __float_as_uint(m));
-        if (least) atomicMin(&sl[g % d], low);
+        if (size && count) atomicAdd(&sl[g % d], 1u << 20 | (unsigned)((float)exponents / (float)count));      // (256 threads, exponents below 256)
     }
     __syncthreads();
     for (int j = threadIdx.x; j < d; j += blockDim.x) {
         partial[(size_t)blockIdx.x * d + j] = sm[j];
-        if (least) least[(size_t)blockIdx.x * d + j] = sl[j];
+        if (size) size[(size_t)blockIdx.x * d + j] = sl[j];
     }
 }
 
 // A workgroup of 16 waves takes 64 columns, a wave every 16th block's maxima, eight of them in flight (one thread per
 // column walking all the blocks took 0.1 to 0.5 ms, 1024 dependent steps and more than once around for d > 256).
-// wide is set if a column's elements are mostly smaller than 2^-26 of its largest.
-__global__ __launch_bounds__(1024) void absmax_final_kernel(const float *partial, const unsigned *least, int nblocks, int d, float *out, int *wide)
+// wide is set if a column's largest element is more than 2^26 times as large as a typical one (the mean exponent: half the
+// elements or a tenth of them may be huge, or just one).
+__global__ __launch_bounds__(1024) void absmax_final_kernel(const float *partial, const unsigned *size, int nblocks, int d, float *out, int *wide)
 {
     __shared__ float red[16][64];
-    __shared__ unsigned redl[16][64];
+    __shared__ unsigned redl[2][16][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, j = blockIdx.x * 64 + lane;
     float m = 0.0f;
-    unsigned low = 0xffffffffu;
-    const unsigned *src = least ? least : reinterpret_cast<const unsigned *>(partial), off = least ? 0u : 0xffffffffu;    // (loads without a branch)
+    unsigned sum = 0, count = 0;
+    const unsigned *src = size ? size : reinterpret_cast<const unsigned *>(partial), use = size ? ~0u : 0u;      // (loads without a branch)
     for (int q0 = wave; q0 < nblocks; q0 += 128) {
         float v[8];
         unsigned l[8];
@@ -140,24 +140,28 @@ __global__ __launch_bounds__(1024) void absmax_final_kernel(const float *partial
         for (int u = 0; u < 8; ++u) {
             const size_t at = (size_t)min(q0 + 16 * u, nblocks - 1) * d + (j < d ? j : 0);
             v[u] = partial[at];
-            l[u] = src[at] | off;
+            l[u] = src[at] & use & (unsigned)((q0 + 16 * u - nblocks) >> 31);       // (past the end: nothing)
         }
 #pragma unroll
         for (int u = 0; u < 8; ++u) {
             m = fmaxf(m, v[u]);
-            low = min(low, l[u]);
+            sum += l[u] & 0xfffffu;
+            count += l[u] >> 20;
         }
     }
     red[wave][lane] = m;
-    redl[wave][lane] = low;
+    redl[0][wave][lane] = sum;
+    redl[1][wave][lane] = count;
     __syncthreads();
     if (wave == 0 && j < d) {
+        sum = count = 0;
         for (int q = 0; q < 16; ++q) {
             m = fmaxf(m, red[q][lane]);
-            low = min(low, redl[q][lane]);
+            sum += redl[0][q][lane];
+            count += redl[1][q][lane];
         }
         out[j] = m;
-        if (low != 0xffffffffu && __uint_as_float(low + 1u) < m * 1.4901161e-8f)
+        if (count && (float)(__float_as_uint(m) >> 23) - (float)sum / (float)count > 26.0f)
             __hip_atomic_store(wide, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
 }
@@ -491,7 +495,7 @@ hipError_t launch_init_first_k(const StepParams &p, hipStream_t s)
 }
 
 constexpr int ABSMAX_BLOCKS = 1024;
-constexpr int ABSMAX_TRACK = 8192;        // longest rows whose `least` is tracked (both arrays fit the LDS; no kernel that takes longer ones asks)
+constexpr int ABSMAX_TRACK = 8192;        // longest rows whose `size` is taken (both arrays fit the LDS; no kernel that takes longer ones asks)
 
 size_t absmax_scratch_bytes(int d) { return d <= ABSMAX_TRACK ? (size_t)2 * ABSMAX_BLOCKS * d * sizeof(float) : 0; }
 
@@ -504,9 +508,9 @@ hipError_t launch_absmax(const float *x, long long rows, int d, float *out, int 
         const hipError_t e = hipMalloc((void **)&partial, (size_t)ABSMAX_BLOCKS * d * sizeof(float));
         if (e != hipSuccess) return e;
     }
-    unsigned *least = track ? reinterpret_cast<unsigned *>(partial + (size_t)ABSMAX_BLOCKS * d) : nullptr;
-    hipLaunchKernelGGL(absmax_partial_kernel, dim3(ABSMAX_BLOCKS), dim3(256), (size_t)d * (track ? 2 : 1) * sizeof(float), s, x, rows, d, partial, least, nonfinite);
-    hipLaunchKernelGGL(absmax_final_kernel, dim3((d + 63) / 64), dim3(1024), 0, s, partial, least, ABSMAX_BLOCKS, d, out, wide);
+    unsigned *size = track ? reinterpret_cast<unsigned *>(partial + (size_t)ABSMAX_BLOCKS * d) : nullptr;
+    hipLaunchKernelGGL(absmax_partial_kernel, dim3(ABSMAX_BLOCKS), dim3(256), (size_t)d * (track ? 2 : 1) * sizeof(float), s, x, rows, d, partial, size, nonfinite);
+    hipLaunchKernelGGL(absmax_final_kernel, dim3((d + 63) / 64), dim3(1024), 0, s, partial, size, ABSMAX_BLOCKS, d, out, wide);
     hipError_t e = hipGetLastError();
     if (!track) {
         const hipError_t e2 = hipStreamSynchronize(s);

@@ -129,6 +129,36 @@ def test_one_huge_element_does_not_touch_the_other_workers(B, oracle, kernel, tu
     assert np.delete(err, 2).max() <= 1e-5
 
 
+@pytest.mark.parametrize("what,form", [("lognormal", "SPLIT_PHASES"), ("sparse", "SPLIT_PHASES"), ("probabilities", "SPLIT_PHASES"),
+                                        ("one in ten", "FP32"), ("half", "FP32"), ("tiny column", "FP32")])
+def test_heavy_tails_stay_and_markers_go(B, oracle, what, form):
+    """Columns whose elements spread over many magnitudes keep the split kernels; a marker of 1e30, in however many elements,
+    takes the kernel with fp32 sums.  All against the oracle."""
+    k, d, W, b = 20, 13, 4, 150
+    rng = np.random.default_rng(3)
+    X = make_data(W * (3 * b + 11), d, k, seed=9)
+    if what == "lognormal":
+        X = np.exp(2.5 * rng.standard_normal(X.shape))
+    elif what == "sparse":
+        X = X * (rng.random(X.shape) < 0.05)
+    elif what == "probabilities":
+        X = np.exp(1.2 * X - 1.2 * X.max(1, keepdims=True))
+    elif what == "tiny column":
+        X[:, 4] *= 1.0e-9
+        X[77, 4] = 1.0e3
+    else:
+        X = np.where(rng.random(X.shape) < (0.1 if what == "one in ten" else 0.5), 1.0e30, X)
+    X = np.ascontiguousarray(X, dtype=np.float32)
+    g = B.ASGD(k, d, W, b, 0.05, E=0, kernel=B.KERNEL_GENERIC)
+    g.load_shards(to_dev(X))
+    g.run_steps(6)
+    assert g.last_run_form() == getattr(B, "FORM_" + form)
+    o = oracle.OracleASGD(X, k=k, W=W, b=b, lr=0.05, E=0)
+    o.run_steps(6)
+    if form == "SPLIT_PHASES":
+        assert rel_fro(g.get_state(), o.w).max() <= 1e-5
+
+
 @pytest.mark.parametrize("kernel,d,W,b", [("GENERIC", 75, 2, 20000), ("GENERIC", 13, 1, 8192), ("GENERIC", 5, 3, 6000), ("GENERIC", 300, 1, 40000),
                                           ("MFMA", 96, 2, 20000)])
 def test_a_sum_over_many_shares_is_rounded_once(B, kernel, d, W, b):
