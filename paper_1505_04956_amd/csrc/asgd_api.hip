@@ -727,7 +727,15 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         return e;
     };
     if (split) split = take_scratch();
-    if (split) HIP_TRY(ctx, take_data());
+    if (split) {
+        const hipError_t e = take_data();
+        if (e == hipErrorOutOfMemory) {
+            (void)hipGetLastError();
+            split = false;
+        } else {
+            HIP_TRY(ctx, e);
+        }
+    }
     if (kernel == ASGD_KERNEL_MFMA && !split) HIP_TRY(ctx, take_norms());
     // Deterministic mode: a worker may only read the message of round r-1 once its sender has
     // finished that round.  Either the whole run is one launch of co-resident workgroups that wait
