@@ -143,7 +143,7 @@ typedef struct asgd_stats {
  * Requires k, d, W, b >= 1 and lr > 0 (Alg. 5 "Require"; W = 1 is allowed and equals
  * Alg. 4).  Allocates W*k*d floats of state and the exchange buffers on the current
  * device.  More is allocated by the first call that needs it and kept until asgd_destroy():
- * 8 KB per column at the first asgd_load_shards() (d <= 8192), and the operands and sums of the
+ * 8 KB per column at the first asgd_load_shards() (d <= 8192; where the streaming kernel runs: at the first run of another), and the operands and sums of the
  * kernels with fp16-split operands at a run, several times W*k*d floats and 32 GiB at most
  * (a kernel that needs none takes over where there is no room).  *out is set only on success and must be released with asgd_destroy().
  */
@@ -164,6 +164,8 @@ int asgd_set_option(asgd_ctx *ctx, int key, double value);
  *               the context enqueue their work.
  * Effects: every worker's state is set to the first k rows of its own shard, exchange
  * buffers, counters and the step counter are cleared.  Synchronises the stream.
+ * Column maxima are formed over all rows, where the streaming kernel runs over a part of them: it looks out for larger elements
+ * in the first epoch.
  */
 int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_stream);
 
@@ -215,8 +217,8 @@ int asgd_set_exchange(asgd_ctx *ctx, const float *values_host, const int32_t *ro
  * calls (deterministic mode: bit for bit), the time does: with the streaming kernel, and
  * with the others where the workers fill the device and exchange every fourth step or less
  * often, a call of two communication rounds or more is ONE kernel launch for every 1024 rounds
- * it covers, and the start and the tail of a launch are then paid once per launch, not once per
- * epoch (asgd_stats.launches); else a round, or every phase of a step, is a launch over all
+ * it covers (the streaming kernel: a call of more than sixteen epochs that begins with the first after loading, one more),
+ * and the start and the tail of a launch are then paid once per launch, not once per epoch (asgd_stats.launches); else a round, or every phase of a step, is a launch over all
  * workers.
  */
 int asgd_run_epochs(asgd_ctx *ctx, int epochs);

@@ -36,6 +36,10 @@ struct asgd_ctx {
     long long t = 0;
 
     float *w = nullptr, *slot = nullptr, *acc = nullptr, *xabsmax = nullptr, *mean = nullptr;
+    long long seen = 0;            // streaming kernel: it has looked at the mini-batches [0, seen) (flag_host[3]: and met an element
+                                   // beyond the limits it forms of xsample)
+    bool xabsmax_valid = false;    // xabsmax and flag_host[1], [2] are those of the loaded samples
+    float *xsample = nullptr;      // streaming kernel only: column maxima over a part of the samples, and scratch
     float *xnorm2max = nullptr;    // matrix-core kernel only, allocated on first use
     size_t slot_bytes = 0;         // size of the exchange buffers (both parities, all workers)
     int *shift_tab = nullptr;      // schedule table of the small-state kernel, grown on demand
@@ -96,7 +100,7 @@ size_t kd_of(const asgd_ctx *c) { return (size_t)c->k * c->d; }
 void free_all(asgd_ctx *c)
 {
     void *ptrs[] = {c->w, c->slot, c->acc, c->xabsmax, c->mean, c->stamp, c->consumed, c->cnt, c->assign_tmp,
-                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->split_data, c->load_scratch};
+                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->split_data, c->load_scratch, c->xsample};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (c->flag_host) (void)hipHostFree(c->flag_host);
@@ -129,7 +133,7 @@ StepParams make_params(const asgd_ctx *c)
 int clear_exchange(asgd_ctx *c, int kernel)
 {
     const int fill = (c->parts > 1 && kernel != ASGD_KERNEL_SMALL) ? 0 : 0xFF;
-    HIP_TRY(c, hipMemsetAsync(c->slot, fill, c->slot_bytes, c->stream));
+    if (fill == 0 || small_kernel_supports(c->k, c->d, c->b)) HIP_TRY(c, hipMemsetAsync(c->slot, fill, c->slot_bytes, c->stream));
     HIP_TRY(c, hipMemsetAsync(c->stamp, 0xFF, exchange_buffers_total(c->nb, c->W) * sizeof(int), c->stream));   // -1
     c->fill_kernel = kernel;
     return ASGD_OK;
@@ -266,6 +270,20 @@ int import_exchange(asgd_ctx *c, int kernel, const float *values, const int32_t 
     return ASGD_OK;
 }
 
+// Per-dimension max |x| over the rows the workers own (inputs of the rounding-error bounds that decide when an assignment is
+// recomputed exactly, and of the scales of fixed-point sums), and whether they are finite and of ordinary size.
+// Synchronises the stream.
+int take_absmax(asgd_ctx *c)
+{
+    const size_t bytes = absmax_scratch_bytes(c->d);
+    if (bytes && !c->load_scratch) HIP_TRY(c, hipMalloc(&c->load_scratch, bytes));
+    c->flag_host[1] = c->flag_host[2] = 0;
+    HIP_TRY(c, launch_absmax(c->x, c->H * c->W, c->d, c->xabsmax, c->flag_host + 1, c->flag_host + 2, c->load_scratch, c->stream));
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    c->xabsmax_valid = true;
+    return ASGD_OK;
+}
+
 // Whether the fp16-split step kernels are faster than the fp32 matrix kernel (the default variant of
 // ASGD_KERNEL_MFMA).  The former take 14 to 20 us per step whatever its size, the latter a step of one workgroup per worker.
 // Microseconds per step of long calls, fp32 and split:
@@ -359,7 +377,12 @@ int asgd_create(asgd_ctx **out, int k, int d, int W, int b, float lr)
         e = hipMalloc(a.p, a.bytes);
         if (e != hipSuccess) { fail(e); break; }
     }
-    if (rc == ASGD_OK && (e = hipHostMalloc((void **)&c->flag_host, 3 * sizeof(int), hipHostMallocDefault)) != hipSuccess) fail(e);
+    if (rc == ASGD_OK && small_kernel_supports(k, d, b)) {
+        e = hipMalloc((void **)&c->xsample, sample_scratch_bytes(d));
+        if (e == hipSuccess) e = hipMemset(c->xsample, 0, sample_scratch_bytes(d));
+        if (e != hipSuccess) fail(e);
+    }
+    if (rc == ASGD_OK && (e = hipHostMalloc((void **)&c->flag_host, 4 * sizeof(int), hipHostMallocDefault)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev0)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev1)) != hipSuccess) fail(e);
     if (rc != ASGD_OK) {
@@ -477,8 +500,6 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     const long long H = N / ctx->W;
     if (H < ctx->k || H < ctx->b) return ASGD_EINVAL;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
-    const size_t load_bytes = absmax_scratch_bytes(ctx->d);
-    if (load_bytes && !ctx->load_scratch) HIP_TRY(ctx, hipMalloc(&ctx->load_scratch, load_bytes));
     ctx->x = x_dev; ctx->N = N; ctx->H = H; ctx->S = H / ctx->b;
     ctx->stream = (hipStream_t)hip_stream;
     ctx->t = 0;
@@ -488,17 +509,26 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     ctx->loaded = false;
     ctx->xnorm2max_valid = false;
     ctx->split_data_valid = false;
-    StepParams p = make_params(ctx);
-    HIP_TRY(ctx, launch_init_first_k(p, ctx->stream));
-    int rc = clear_exchange(ctx, ASGD_KERNEL_SMALL);
-    if (rc != ASGD_OK) return rc;
+    ctx->xabsmax_valid = false;
+    ctx->seen = 0;
+    ctx->flag_host[3] = 0;
+    LoadParams l;
+    memset(&l, 0, sizeof(l));
+    l.x = ctx->x; l.w = ctx->w; l.stamp = ctx->stamp; l.ncum = ctx->ncum; l.counters = ctx->counters;
+    l.H = H; l.k = ctx->k; l.d = ctx->d; l.W = ctx->W;
+    l.stamps = exchange_buffers_total(ctx->nb, ctx->W);
+    if (small_kernel_supports(ctx->k, ctx->d, ctx->b)) {             // (the other kernels look at the stamps first)
+        l.slot = reinterpret_cast<unsigned *>(ctx->slot);
+        l.slot_words = ctx->slot_bytes / sizeof(unsigned);
+    }
+    HIP_TRY(ctx, launch_load(l, ctx->xsample, ctx->stream));
     ctx->fill_kernel = 0;
-    HIP_TRY(ctx, hipMemsetAsync(ctx->ncum, 0, (size_t)ctx->W * ctx->k * sizeof(long long), ctx->stream));
-    HIP_TRY(ctx, hipMemsetAsync(ctx->counters, 0, (size_t)ctx->W * CNT_STRIDE * sizeof(long long), ctx->stream));
-    // per-dimension max |x| over the rows the workers own: input of the rounding-error bound
-    // that decides when an assignment is recomputed exactly
-    ctx->flag_host[1] = ctx->flag_host[2] = 0;
-    HIP_TRY(ctx, launch_absmax(x_dev, H * ctx->W, ctx->d, ctx->xabsmax, ctx->flag_host + 1, ctx->flag_host + 2, ctx->load_scratch, ctx->stream));
+    // The streaming kernel makes do with maxima over a part of the samples; those over all of them are formed by the first run
+    // of another kernel.
+    if (!(ctx->xsample && ctx->lr_mode == ASGD_LR_CONST && (ctx->kernel_opt == ASGD_KERNEL_AUTO || ctx->kernel_opt == ASGD_KERNEL_SMALL))) {
+        const int rc = take_absmax(ctx);
+        if (rc != ASGD_OK) return rc;
+    }
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     ctx->loaded = true;
     return ASGD_OK;
@@ -643,7 +673,16 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         if (rc != ASGD_OK) return rc;
     }
 
+    if (kernel != ASGD_KERNEL_SMALL && !ctx->xabsmax_valid && steps > 0) {
+        const int rc = take_absmax(ctx);
+        if (rc != ASGD_OK) return rc;
+    }
     StepParams p = make_params(ctx);
+    if (kernel == ASGD_KERNEL_SMALL) {
+        p.xabsmax = ctx->xsample;
+        p.beyond_flag = ctx->flag_host + 3;
+        p.within_limits = sample_is_all(ctx->H * ctx->W, ctx->d) || (ctx->seen >= ctx->S && ctx->flag_host[3] == 0);
+    }
     const long long t_end = ctx->t + steps;
     if (kernel == ASGD_KERNEL_SMALL && ctx->mode == ASGD_MODE_DETERMINISTIC && ctx->E > 0 && ctx->W > 1 && steps > 0) {
         // cyclic shifts of the rounds this call touches: the round before the first step up to the last step's
@@ -743,6 +782,21 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     // device), or a launch never crosses a multiple of E, so that the message was written by an
     // earlier launch on the same stream.
     const bool rounds = (ctx->mode == ASGD_MODE_DETERMINISTIC && ctx->E > 0 && ctx->W > 1);
+    // The streaming kernel looks out for elements beyond its limits in the first epoch after loading (6 % of the time of an epoch;
+    // looking at all samples while loading took as long as an epoch).  A call that begins with that epoch and goes on for more
+    // than sixteen is cut after it.
+    auto first_epoch_end = [&](long long from) -> long long {        // step at which a launch from `from` on is cut, or t_end
+        if (kernel != ASGD_KERNEL_SMALL || p.within_limits || from > ctx->seen || from >= ctx->S || t_end - from <= 16 * ctx->S) return t_end;
+        return rounds ? (ctx->S + ctx->E - 1) / ctx->E * ctx->E : ctx->S;
+    };
+    auto looked_at = [&](long long from, long long to) -> int {       // steps [from, to) have been launched
+        if (kernel != ASGD_KERNEL_SMALL || from > ctx->seen) return ASGD_OK;
+        if (to < t_end) {
+            HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+            p.within_limits = p.within_limits || (to >= ctx->S && ctx->flag_host[3] == 0);
+        }
+        return ASGD_OK;
+    };
     int launches = 0;
     *ctx->flag_host = 0;         // (no kernel of this context is in flight: every run ends with a wait for the stream)
     HIP_TRY(ctx, hipEventRecord(ctx->ev0, ctx->stream));
@@ -764,7 +818,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         // the call is.
         while (t_done < t_end) {
             long long tb = (t_done / ctx->E + ONE_LAUNCH_MAX_ROUNDS) * (long long)ctx->E;
-            if (tb > t_end) tb = t_end;
+            const long long cut = first_epoch_end(t_done);
+            if (tb > cut) tb = cut;
             int one = 0;
             hipError_t e = ctx->refuse_one_launch == 1 ? hipErrorCooperativeLaunchTooLarge
                            : split_local ? launch_split_steps(p, t_done, tb, ctx->split_data, ctx->split_scratch, ctx->stream, &one)
@@ -780,6 +835,10 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             }
             if (e == hipSuccess) {
                 ++launches;
+                if (tb == cut && cut < t_end) {
+                    const int rc = looked_at(t_done, tb);
+                    if (rc != ASGD_OK) return rc;
+                }
                 t_done = tb;
                 ctx->passed_t = tb;
                 if (split_local && *ctx->flag_host) break;       // an expired wait: nothing more may run on these states
@@ -809,6 +868,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         if (rounds) {
             const long long next = (ta / ctx->E + 1) * (long long)ctx->E;
             if (next < tb) tb = next;
+        } else {
+            tb = first_epoch_end(ta);
         }
         hipError_t e = (kernel == ASGD_KERNEL_SMALL) ? launch_small_steps(p, ta, tb, ctx->stream, false)
                        : (kernel == ASGD_KERNEL_MFMA)
@@ -816,6 +877,10 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
                            : launch_generic_steps(p, ta, tb, ctx->stream);
         HIP_TRY(ctx, e);
         ++launches;
+        if (!rounds && tb < t_end) {
+            const int rc = looked_at(ta, tb);
+            if (rc != ASGD_OK) return rc;
+        }
         ta = tb;
         ctx->passed_t = -1;
     }
@@ -835,6 +900,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         ctx->desynced = true;
         return ASGD_ESYNC;
     }
+    if (kernel == ASGD_KERNEL_SMALL && ctx->t <= ctx->seen && t_end > ctx->seen) ctx->seen = t_end;
     ctx->t = t_end;
     return ASGD_OK;
 }

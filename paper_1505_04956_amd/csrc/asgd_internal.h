@@ -27,7 +27,9 @@ struct StepParams {
     int *cnt;              // W x k count scratch
     int *assign_tmp;       // W x b assignment scratch
     int32_t *dump;         // optional assignment dump (step-major), or nullptr
-    const float *xabsmax;  // d per-dimension max |x| over the loaded samples
+    const float *xabsmax;  // d per-dimension max |x| over the loaded samples (small-state kernel: over a part of them)
+    int within_limits;     // small-state kernel: it is known that no element is beyond the limits that go with xabsmax
+    int *beyond_flag;      // pinned host memory, set to 1 by the small-state kernel when it meets one
     int *error_flag;       // pinned host memory, set to 1 by a kernel whose bounded wait expired
     const int *shift_tab;  // deterministic schedule: cyclic shift of round r at [r - shift_r0] (small-state kernel)
     long long shift_r0;
@@ -51,7 +53,23 @@ struct StepParams {
 };
 
 // Launchers (each returns the hipError_t of its launch).
-hipError_t launch_init_first_k(const StepParams &p, hipStream_t s);
+struct LoadParams {
+    const float *x;
+    float *w;
+    unsigned *slot;
+    int *stamp;
+    long long *ncum, *counters;
+    size_t slot_words, stamps;
+    long long H;
+    int k, d, W;
+    float *sample, *sample_part;      // (set by launch_load)
+    int *arrived;
+};
+// What asgd_load_shards() begins with.  sample_scratch (may be null; d <= 16): sample_scratch_bytes() of device memory, zero before the
+// first use; its first d floats become maxima of |x_j| over a part of the samples.
+size_t sample_scratch_bytes(int d);
+bool sample_is_all(long long rows, int d);       // whether that part is all of them
+hipError_t launch_load(LoadParams l, void *sample_scratch, hipStream_t s);
 // nonfinite, wide: pinned host memory, set to 1 if an element is infinite or not a number; if the typical element of a column
 // is smaller than 2^-26 of its largest (d <= 8192)
 // scratch: absmax_scratch_bytes() of device memory (none needed if that is 0).  Enqueued only.

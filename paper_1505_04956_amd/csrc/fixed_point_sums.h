@@ -39,6 +39,28 @@ ASGD_HD inline bool fx_scale_exponent(int b, float xmax, bool term_cap, int *e)
     return true;
 }
 
+// The scale itself for sums whose terms are checked (below): a column that is zero as far as it was looked at gets the largest
+// scale there is, so that an element that is not is found; one that is not finite, or too large, none.
+ASGD_HD inline float fx_column_scale(int b, float xmax)
+{
+    int e = 0;
+    if (fx_scale_exponent(b, xmax, true, &e)) return ldexpf(1.0f, e);
+    return xmax == 0.0f ? ldexpf(1.0f, 96) : 0.0f;
+}
+constexpr float FX_DENORM_UNIT = 1.40129846e-45f;      // 2^-149, the smallest denormal number
+
+// Largest magnitude of a term (an integer) that sums of b terms may hold where the column maxima are known from a part of the
+// samples only.  most: the largest max|x_j| * scale over the columns.  A sixteenth above it, so that a largest element that was
+// not looked at seldom passes it; b terms stay below 2^31 (b * most < 2^30), and a term keeps to a float's integers.
+// (Even: a term that lies between two integers is rounded to the even one, of the sum with the limit where that is the offset.)
+ASGD_HD inline int fx_term_limit(int b, float most)
+{
+    const double room = 2147483647.0 / (double)b, cap = 4194303.0;
+    double limit = 1.0625 * (double)most + 1.0;
+    if (limit > room) limit = room;
+    return (int)(limit < cap ? limit : cap) & ~1;
+}
+
 // what is added to a cell for the value x of a column with the given scale (magic-constant form)
 ASGD_HD inline uint32_t fx_term_bits(float x, float scale)
 {

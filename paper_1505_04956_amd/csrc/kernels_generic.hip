@@ -57,13 +57,101 @@ __device__ __forceinline__ double gen_wave_sum(double v)
     return v;
 }
 
-__global__ void init_first_k_kernel(StepParams p)
+// Everything a load begins with, in one launch (seven took 40 us together, most of it between them): the states (worker i
+// starts from the first k rows of its own shard), the exchange buffers emptied (all bits set; slot_words 0: left alone),
+// the counters, and, for the streaming kernel, column maxima over a part of the samples.
+constexpr int LOAD_BLOCKS = 1024;
+// Maxima over a part: pieces of 16 sweeps of a workgroup, a thread always in one column (d <= 16).  All of them up to
+// 4096 pieces (64 MB), then evenly spread ones, 1 in 128 at the least; whoever uses the maxima looks out for elements
+// beyond them.  (All samples of N = 1e8, d = 10: 675 us, as long as an epoch over them.)
+__host__ __device__ inline long long sample_pieces(long long total, int d)
 {
-    // Worker i starts from the first k rows of its own shard; gridDim.y workgroups per worker.
-    const size_t kd = (size_t)p.k * p.d;
-    const int i = blockIdx.x;
-    for (size_t e = (size_t)blockIdx.y * blockDim.x + threadIdx.x; e < kd; e += (size_t)gridDim.y * blockDim.x)
-        p.w[i * kd + e] = p.x[(size_t)i * p.H * p.d + e];
+    const long long piece = 16LL * (256 - 256 % d);
+    return (total + piece - 1) / piece;
+}
+__host__ __device__ inline long long sample_every(long long pieces)
+{
+    const long long n = pieces / 4096;
+    return n < 1 ? 1 : n > 128 ? 128 : n;
+}
+__device__ void sample_columns(const LoadParams &l, float *red)
+{
+    const int d = l.d, T = 256 - 256 % d, t = threadIdx.x;
+    const long long total = l.H * l.W * d, piece = 16LL * T, pieces = sample_pieces(total, d), every = sample_every(pieces);
+    float m = 0.0f;
+    if (t < T)
+        for (long long q = (long long)blockIdx.x * every; q < pieces; q += (long long)LOAD_BLOCKS * every) {
+            const long long e = q * piece + t;
+            float v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) v[u] = l.x[e + u * T < total ? e + u * T : t];
+#pragma unroll
+            for (int u = 0; u < 16; ++u) m = fmaxf(m, fabsf(v[u]));
+        }
+    red[t] = t < T ? m : 0.0f;
+    __syncthreads();
+    if (t < d) {
+        for (int q = t + d; q < T; q += d) m = fmaxf(m, red[q]);
+        __hip_atomic_store(l.sample_part + blockIdx.x * d + t, m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+__global__ __launch_bounds__(256) void load_kernel(LoadParams l)
+{
+    __shared__ float red[256];
+    __shared__ int last;
+    const size_t kd = (size_t)l.k * l.d, states = kd * l.W, n = (size_t)gridDim.x * blockDim.x, g = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const size_t shard = (size_t)l.H * l.d;
+    if (kd < 4096) {
+        for (size_t e = g; e < states; e += n) l.w[e] = l.x[e / kd * shard + e % kd];
+    } else {
+        // (a workgroup stays in one state: no division per element)
+        const int per = max(1, (int)gridDim.x / l.W);
+        for (size_t i = blockIdx.x / per; i < (size_t)l.W; i += max(1, (int)gridDim.x / per))
+            for (size_t e0 = (size_t)(blockIdx.x % per) * blockDim.x + threadIdx.x; e0 < kd; e0 += (size_t)8 * per * blockDim.x) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const size_t e = e0 + (size_t)u * per * blockDim.x;
+                    v[u] = l.x[i * shard + (e < kd ? e : 0)];
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const size_t e = e0 + (size_t)u * per * blockDim.x;
+                    if (e < kd) l.w[i * kd + e] = v[u];
+                }
+            }
+    }
+    for (size_t e = g; e < l.slot_words; e += n) l.slot[e] = ~0u;
+    for (size_t e = g; e < l.stamps; e += n) l.stamp[e] = -1;
+    for (size_t e = g; e < (size_t)l.W * l.k; e += n) l.ncum[e] = 0;
+    for (size_t e = g; e < (size_t)l.W * CNT_STRIDE; e += n) l.counters[e] = 0;
+    if (!l.sample_part) return;
+    sample_columns(l, red);
+    // The last workgroup to get here forms the maxima of all.  (The parts are written past the caches and have arrived before
+    // the workgroup counts itself: no fence, which would write back a cache full of states.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) last = __hip_atomic_fetch_add(l.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == LOAD_BLOCKS - 1;
+    __syncthreads();
+    if (!last) return;
+    const int T = 256 - 256 % l.d, t = threadIdx.x;
+    float m = 0.0f;
+    if (t < T)
+        for (int q0 = t; q0 < LOAD_BLOCKS * l.d; q0 += 16 * T) {
+            float v[16];
+#pragma unroll
+            for (int u = 0; u < 16; ++u)
+                v[u] = __hip_atomic_load(l.sample_part + (q0 + u * T < LOAD_BLOCKS * l.d ? q0 + u * T : t), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+            for (int u = 0; u < 16; ++u) m = fmaxf(m, v[u]);
+        }
+    red[t] = m;
+    __syncthreads();
+    if (t < l.d) {
+        for (int q = t + l.d; q < T; q += l.d) m = fmaxf(m, red[q]);
+        l.sample[t] = m;
+    }
+    if (t == 0) *l.arrived = 0;          // (for the next load)
 }
 
 // partial[block][j] = max |x[row][j]| over the elements this block visits.  The flat array is walked with a stride that is
@@ -455,7 +543,13 @@ __global__ void quant_error_final_kernel(const double *partials, int n, double *
     // order.  The result does not depend on scheduling.
     __shared__ double red[64];
     double s = 0.0;
-    for (int q = threadIdx.x; q < n; q += 64) s += partials[q];
+    for (int q0 = threadIdx.x; q0 < n; q0 += 512) {              // (eight in flight: one after the other took 9 us)
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = partials[q0 + 64 * u < n ? q0 + 64 * u : 0];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += q0 + 64 * u < n ? v[u] : 0.0;
+    }
     red[threadIdx.x] = s;
     __syncthreads();
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -485,12 +579,18 @@ __global__ void mean_state_kernel(const float *w, int W, int kd, float *out)
 }  // namespace
 
 // ------------------------------------------------------------------------------------------
-hipError_t launch_init_first_k(const StepParams &p, hipStream_t s)
+bool sample_is_all(long long rows, int d) { return sample_every(sample_pieces(rows * d, d)) == 1; }
+size_t sample_scratch_bytes(int d) { return ((size_t)(LOAD_BLOCKS + 1) * d + 1) * sizeof(float); }
+
+hipError_t launch_load(LoadParams l, void *sample_scratch, hipStream_t s)
 {
-    // four elements per thread, as long as that is at most 64 workgroups per worker (one per worker took 0.15 ms for 64
-    // states of 98304 floats and 0.22 ms for 256 of 131072)
-    const size_t per = ((size_t)p.k * p.d + 1023) / 1024;
-    hipLaunchKernelGGL(init_first_k_kernel, dim3(p.W, (unsigned)(per < 64 ? per : 64)), dim3(256), 0, s, p);
+    l.sample_part = nullptr;
+    if (sample_scratch) {
+        l.sample = static_cast<float *>(sample_scratch);
+        l.arrived = reinterpret_cast<int *>(l.sample + l.d);
+        l.sample_part = l.sample + l.d + 1;
+    }
+    hipLaunchKernelGGL(load_kernel, dim3(LOAD_BLOCKS), dim3(256), 0, s, l);
     return hipGetLastError();
 }
 

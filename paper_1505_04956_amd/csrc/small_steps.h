@@ -139,6 +139,18 @@ __device__ __forceinline__ void top2(const float (&t)[N], float &best, float &se
     second = M;
 }
 
+// The lane number as a value of its own: the addresses that are derived from it once per step are formed there instead of
+// being registers held across the streaming part.  Only where there are too few of them (LEAN): it costs a step some forty
+// instructions (W = 4, b = 500: 0.14 us per step).
+template <bool LEAN>
+__device__ __forceinline__ int fresh_lane(int lane)
+{
+    if constexpr (LEAN) asm volatile("" : "+v"(lane));
+    return lane;
+}
+// a value that is the same in all lanes, in a scalar register
+__device__ __forceinline__ float uniform_float(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
+
 // The lanes of a wave hand values to each other through LDS (the copies of the state, the accumulator cells).  The
 // hardware executes the LDS accesses of a wave in program order; this keeps the compiler from moving a read above
 // the write or atomic of another lane that it has to see (to a single lane the two look unrelated).
@@ -375,7 +387,7 @@ struct SmallWalk {
 // its rows padded to 4*NQ floats.
 //   NB     external buffers per worker = recipients per message (Eq. 3 / Eq. 6); NB = p.nb
 //   PARTS  partial messages (Sec. 4.4) compiled in; p.parts > 1 needs it
-template <int K, int D, int NB, bool PARTS>
+template <int K, int D, int NB, bool PARTS, bool LEAN>
 struct SmallKeeper {
     using G = SmallGeo<K, D>;
     static constexpr int NQ = G::NQ, NT = G::NT, CQ = G::CQ, CI = G::CI, KD = G::KD;
@@ -404,8 +416,6 @@ struct SmallKeeper {
         bp_row = (lane - tq) * 4;                   // lane_read address of the first lane of this lane's centroid
         bp_w0 = tq * 4;                             // ... of the lane that holds the same float4 of centroid 0
         sum_xmax = 0.0f;
-#pragma unroll
-        for (int j = 0; j < D; ++j) sum_xmax += p.xabsmax[j];
         inv_b = 1.0f / (float)p.b;
         eps = p.eps;
         wait_failed = 0;
@@ -420,7 +430,7 @@ struct SmallKeeper {
     __device__ __forceinline__ void load_state(const StepParams &p, int i)
     {
 #pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4) w4[c4] = tv[c4] ? p.w[(size_t)i * KD + elem0 + c4] : 0.0f;
+        for (int c4 = 0; c4 < 4; ++c4) w4[c4] = tv[c4] ? p.w[(size_t)i * KD + fresh_lane<LEAN>(elem0) + c4] : 0.0f;
         // wait for the state here, once, not at the head of the step loop, where the wait would also cover the
         // samples fetched ahead
 #pragma unroll
@@ -430,7 +440,7 @@ struct SmallKeeper {
     {
 #pragma unroll
         for (int c4 = 0; c4 < 4; ++c4) {
-            if (tv[c4]) p.w[(size_t)i * KD + elem0 + c4] = w4[c4];
+            if (tv[c4]) p.w[(size_t)i * KD + fresh_lane<LEAN>(elem0) + c4] = w4[c4];
         }
     }
 
@@ -457,9 +467,10 @@ struct SmallKeeper {
             dabs = fmaxf(dabs, fabsf(wdv[c4]));
         }
         if (tq == CQ) wdv[CI] = hol;
-        if (has_task) {
-            wst[lane] = make_float4(w4[0], w4[1], w4[2], w4[3]);
-            wdt[lane] = make_float4(wdv[0], wdv[1], wdv[2], wdv[3]);
+        const int at = fresh_lane<LEAN>(lane);
+        if (at < NT) {
+            wst[at] = make_float4(w4[0], w4[1], w4[2], w4[3]);
+            wdt[at] = make_float4(wdv[0], wdv[1], wdv[2], wdv[3]);
         }
         // max_k |h_k| bounds max_k |h_k - h_0| up to a factor 2; one wave-wide max serves both
         const float hmax = wave_max_nonneg(has_task ? fabsf(hl) : 0.0f);
@@ -475,6 +486,16 @@ struct SmallKeeper {
         const float Abound = wave_max_nonneg(dabs) * sum_xmax;
         return 3.0f * 5.9604645e-8f *
                ((float)(D + 33) * Abound + (float)(D + 34) * (hdmax + 1.0f) + (float)(2 * D + 2) * hmax);
+    }
+
+    // The state again, from the copy that publish() wrote: four registers that are not held across the streaming part.
+    __device__ __forceinline__ void take_back(const float4 *wst)
+    {
+        if constexpr (!LEAN) return;
+        const int at = fresh_lane<LEAN>(lane);
+        const float4 v = wst[at < NT ? at : 0];
+        w4[0] = at < NT ? v.x : 0.0f; w4[1] = at < NT ? v.y : 0.0f;
+        w4[2] = at < NT ? v.z : 0.0f; w4[3] = at < NT ? v.w : 0.0f;
     }
 
     // cyclic shift of copy n in round r: 1 + (shift of copy 0 - 1 + n) mod (W - 1)
@@ -507,12 +528,12 @@ struct SmallKeeper {
     {
         const int W = p.W;
         if (merge_point) {
-            const int rpar = det ? ((round - 1) & 1) : 0;
+            const int rpar = det ? ((round - 1) & 1) : 0, here = fresh_lane<LEAN>(lane);
             // buffer n of this worker (parity rpar): NT lanes x 4 pairs each; copy n of a message goes to buffer n
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
                 mslot[n] = reinterpret_cast<const unsigned long long *>(p.slot) +
-                           (((size_t)(rpar * NB + n) * W + i) * NT + (has_task ? lane : 0)) * 4;
+                           (((size_t)(rpar * NB + n) * W + i) * NT + (here < NT ? here : 0)) * 4;
 #pragma unroll
                 for (int c4 = 0; c4 < 4; ++c4) mp[n][c4] = load_pair(mslot[n] + c4);
             }
@@ -720,14 +741,14 @@ struct SmallKeeper {
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
                 if (p.drop_thr != 0 && message_dropped(p.seed, round, i, p.drop_thr, n)) continue;
-                const int spar = det ? (round & 1) : 0;
+                const int spar = det ? (round & 1) : 0, here = fresh_lane<LEAN>(lane);
                 if (sync && det && round >= 2 && !wait_failed && ackv[n] < round - 1) {
                     // the buffer still holds the message of round-2 until the recipient has passed
                     // the merge point of round-1 (it had not when this step began: look again)
                     if (!wait_at_least(p.consumed + peer[n], round - 1, budget)) wait_failed = 1;
                 }
                 unsigned long long *dst = reinterpret_cast<unsigned long long *>(p.slot) +
-                                          (((size_t)(spar * NB + n) * W + peer[n]) * NT + (has_task ? lane : 0)) * 4;
+                                          (((size_t)(spar * NB + n) * W + peer[n]) * NT + (here < NT ? here : 0)) * 4;
                 bool mine = has_task;
                 if constexpr (PARTS) {
                     if (p.parts > 1) mine = has_task && tc % p.parts == (round + peer[n] + n) % p.parts;
@@ -790,13 +811,14 @@ constexpr int small_waves_per_simd()
     return (K - 1) * SmallGeo<K, D>::RW + PF * D + 96 <= 256 ? RS : 1;
 }
 
-template <int K, int D, int PF, int NW, int RS, int NB, bool PARTS>
+template <int K, int D, int PF, int NW, int RS, int NB, bool PARTS, bool AHEAD, bool CHECK>
 __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(small_waves_per_simd<K, D, PF, RS>(), small_waves_per_simd<K, D, PF, RS>())))
 void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
 {
     using G = SmallGeo<K, D>;
     constexpr int NQ = G::NQ, RW = G::RW, NT = G::NT, NPART = G::NPART;
+    constexpr bool LEAN = CHECK && (K - 1) * RW + PF * D + 96 > 230;
     // copies of an accumulator cell per wave: one per lane, or sixteen (lanes r, r + 16, r + 32, r + 48 share one; 32 where
     // the once-per-step sums need that many to give every lane of a task four)
     constexpr int RL = RS == 1 ? 64 : (16 >= 4 * NPART ? 16 : 32);
@@ -819,6 +841,8 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
     __shared__ float4 wst[NW][NT];                  // state, rows padded to RW floats; one copy per wave
     __shared__ float4 wdt[NW][NT];                  // row k: w_k - w_0 in elements < D, (h_k - h_0) + 1 in element D
     __shared__ int4 part[2][NW][NPART][NT];         // per-wave totals, double-buffered by step parity
+    __shared__ float4 inverse_scales[NW][NQ];       // inverse scale of every column, zero past the last
+    __shared__ unsigned cmax[NW][D];                // column maxima of one mini-batch, a copy per wave
 
     const int wave = NW == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63;
@@ -837,7 +861,7 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
         return reinterpret_cast<const float *>(reinterpret_cast<const char *>(batch) + off);
     };
 
-    SmallKeeper<K, D, NB, PARTS> kp;
+    SmallKeeper<K, D, NB, PARTS, LEAN> kp;
     kp.init(p, lane);
     // the budget of polls grows with the rounds the launch covers: a healthy run of the streaming workload spends up
     // to ~30 polls per round on the workgroup that waits most
@@ -845,23 +869,45 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
     for (int q = lane; q < ((K + 1) * CE + 4) * RL; q += 64) (&acc[wave][0][0])[q] = 0u;
     if (lane < NT) before[wave][lane] = make_int4(0, 0, 0, 0);
 
-    // Fixed-point sums: the scale of every column (2^e with b * max|x_j| * 2^e < 2^30 and max|x_j| * 2^e < 2^22; 0 for a
-    // column of zeros), the inverse scales of this lane's four elements in the task layout (the count needs none),
-    // and the LDS byte address of this lane's copy of element 0 of centroid 0
+    // Fixed-point sums: the scale of every column, the inverse scales of this lane's four elements in the task layout
+    // (the count needs none), and the LDS byte address of this lane's copy of element 0 of centroid 0.
+    // p.xabsmax are maxima over a part of the samples only (launch_load), so every term is compared with the
+    // limit of fx_term_limit(); the sums of a step whose mini-batch holds an element beyond it are dropped and the step is
+    // formed again with the maxima of that mini-batch (`column_maxima`).  CHECK = false: it is known that no element is beyond
+    // its limit (fx_term_limit() of the same maxima: the terms and with them the results are the same), nothing is compared.
     constexpr unsigned ELEM_BYTES = RL * 4u, CENT_BYTES = (unsigned)CE * ELEM_BYTES;
-    float scl[D], inv4[4];
+    // A term is the bit pattern of fma(x, scale, magic).  With scales of one and more (ordinary data) the terms are formed
+    // among the denormal numbers, where the bit pattern counts on linearly from zero: magic = limit * 2^-149, what
+    // lies below -limit is negative and as an unsigned number beyond every limit, so one running maximum looks after both
+    // sides (W = 1024, b = 1000, an epoch of 1e8 samples: maximum and minimum 757 us, the maximum alone 733, nothing compared 688).
+    float scl[D], magic;
+    float4 inverse = make_float4(0.0f, 0.0f, 0.0f, 0.0f);        // of this lane's four elements (CHECK: read again every step)
+    unsigned bias, term_lo, term_hi;                // of a term; the smallest and the largest that count
+    bool two_sided;
+    // maxima: of all columns; exact: they are the maxima of all samples that are looked at.  A lane per column.
+    auto set_scales = [&](const float *maxima, bool exact) {
+        const int j0 = fresh_lane<LEAN>(lane);
+        const float m = j0 < D ? maxima[j0] : 0.0f, s = j0 < D ? fx_column_scale(b, m) : 0.0f;
+        if (j0 < RW) (&inverse_scales[wave][0].x)[j0] = s > 0.0f ? 1.0f / s : 0.0f;
+        const int limit = __builtin_amdgcn_readfirstlane(fx_term_limit(b, wave_max_nonneg(s > 0.0f ? m * s : 0.0f)));
+        const float bound = exact || !(s > 0.0f) ? m : (float)(limit + 1) / s;       // of |x_j| where no term is beyond the limit
+        two_sided = exact || !CHECK || __ballot(s > 0.0f && s < 1.0f) != 0ull;
+        magic = two_sided ? FX_MAGIC : __int_as_float(limit);
+        bias = two_sided ? FX_BIAS : (unsigned)limit;
+        term_lo = exact || !two_sided ? 0u : FX_BIAS - (unsigned)limit;
+        term_hi = exact ? ~0u : bias + (unsigned)limit;
+        const float unit = two_sided ? s : s * FX_DENORM_UNIT;
+        float sum = 0.0f;
 #pragma unroll
-    for (int c4 = 0; c4 < 4; ++c4) inv4[c4] = 0.0f;
-#pragma unroll
-    for (int j = 0; j < D; ++j) {
-        int e = 0;
-        const bool okj = fx_scale_exponent(b, p.xabsmax[j], true, &e);
-        scl[j] = okj ? ldexpf(1.0f, e) : 0.0f;
-        const float iv = okj ? ldexpf(1.0f, -e) : 0.0f;
-#pragma unroll
-        for (int c4 = 0; c4 < 4; ++c4)
-            if (kp.has_task && 4 * kp.tq + c4 == j) inv4[c4] = iv;
-    }
+        for (int j = 0; j < D; ++j) {
+            scl[j] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(unit), j));
+            sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(bound), j));
+        }
+        kp.sum_xmax = uniform_float(sum);
+        phase_fence();
+        if constexpr (!CHECK) inverse = inverse_scales[wave][kp.tq];
+    };
+    set_scales(p.xabsmax, false);
     const unsigned wave_cells = (unsigned)(size_t)(lds_u32_ptr)&acc[wave][0][0];
     const unsigned lane_cell = wave_cells + (unsigned)(lane % RL) * 4u;
     unsigned scratch_cell = lane_cell + (unsigned)K * CENT_BYTES;
@@ -872,30 +918,40 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
 
     int rechecks = 0;
     int parity = 0;
-    // LDS byte address of the totals of this lane's four elements over all copies after the previous step
-    const unsigned before_cell = (unsigned)(size_t)(lds_u32_ptr)(unsigned *)&before[wave][kp.has_task ? lane : 0];
     SmallWalk wk(p, t0, t1);
 
     // ring of sample buffers: buffer u holds this wave's group m with m % PF == u
-    float xr[PF][D];
+    // AHEAD (the mini-batch has no more groups than there are buffers, ngw = PF): instead of a ring, the whole of the next
+    // mini-batch is fetched into a second set of registers when a step begins and handed over when it ends.  (With the ring of
+    // two a group was fetched one group ahead of its use, less than the latency of the memory.)
+    float xr[PF][D], xn[AHEAD ? PF : 1][D];
 #pragma unroll
     for (int u = 0; u < PF; ++u) {
 #pragma unroll
         for (int j = 0; j < D; ++j) xr[u][j] = 0.0f;
     }
-    {
-        const float *x0 = wk.first_batch(p.x + (size_t)blockIdx.x * (size_t)p.H * D, D);
+    auto refill = [&](const float *x0) {
 #pragma unroll
-        for (int u = 0; u + 1 < PF; ++u) load_row<D>(xr[u], sample_ptr(x0, wave + u * NW));
+        for (int u = 0; u + (AHEAD ? 0 : 1) < PF; ++u) load_row<D>(xr[u], sample_ptr(x0, wave + u * NW));
         // Wait for them here, once per launch.  The compiler may issue these loads in any order, and a loop entered
         // with buffer 0 as the youngest load outstanding would make it wait, at the head of EVERY turn of the ring,
         // until no load at all is outstanding (the count it waits for has to hold on every path into the loop).
 #pragma unroll
-        for (int u = 0; u + 1 < PF; ++u) {
+        for (int u = 0; u + (AHEAD ? 0 : 1) < PF; ++u) {
 #pragma unroll
             for (int j = 0; j < D; ++j) asm volatile("" : "+v"(xr[u][j]));
         }
-    }
+    };
+    refill(wk.first_batch(p.x + (size_t)blockIdx.x * (size_t)p.H * D, D));
+    // largest |x_j| of a mini-batch to cmax, by every wave for itself (a NaN does not count, as in the maxima over all samples)
+    auto column_maxima = [&](const float *batch) {
+        const int j0 = fresh_lane<LEAN>(lane);
+        if (j0 < D) cmax[wave][j0] = 0u;
+        phase_fence();
+#pragma unroll 1
+        for (unsigned e = (unsigned)j0; e < (unsigned)b * D; e += 64) atomicMax(&cmax[wave][e % D], __float_as_uint(fmaxf(fabsf(batch[e]), 0.0f)));
+        phase_fence();
+    };
 
     // A workgroup with one worker keeps its state in registers from segment to segment (every wave holds the same
     // values); one that takes several workers in turn stores and reloads it.
@@ -911,7 +967,8 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
             if (!one_worker || wk.done == 0) kp.load_state(p, i);
             int s_epoch = wk.s_seg, te = wk.te_seg, round = wk.round_seg;
 
-            for (int ls = 0; ls < wk.seg; ++ls) {
+            bool again = false;         // this step is formed a second time, with the maxima of its own mini-batch
+            for (int ls = 0; ls < wk.seg;) {
                 // ---- wave-uniform copies of the state: every lane gets w_k - w_0 and (h_k - h_0) + 1 ----
                 const float thr = kp.publish(wst[wave], wdt[wave]);
                 phase_fence();      // the copies are per wave: the lanes of this wave only have to see each other's writes
@@ -939,7 +996,8 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
                 const bool send_point = wk.xchg && te + 1 == E;
                 // what the first step of a launch finds in the buffers was sent before the launch: nothing to wait for
                 const int sync_now = (wk.done + ls) > 0 ? sync : 0;
-                kp.fetch(p, i, round, merge_point, send_point, det, sync_now, wave == 0);
+                if (!CHECK || !again) kp.fetch(p, i, round, merge_point, send_point, det, sync_now, wave == 0);
+                unsigned most = 0u, least = ~0u;                // the largest and the smallest term (two_sided only)
 
                 const bool last_step = ls + 1 == wk.seg;
                 const int s_next = (s_epoch + 1 == wk.S) ? 0 : s_epoch + 1;
@@ -947,6 +1005,12 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
                 const float *xbn = last_step ? x_after : (s_next == 0 ? xs : xb + (size_t)b * D);
                 int32_t *dump = p.dump ? p.dump + ((size_t)(wk.dump0 + wk.done + ls) * W + i) * b : nullptr;
                 const float tk0 = __uint_as_float(0x3F800000u | 15u);     // t_0 = 1 with the index of centroid 0
+
+                if constexpr (AHEAD) {
+#pragma unroll
+                    for (int u = 0; u < PF; ++u) load_row<D>(xn[u], sample_ptr(xbn, wave + u * NW));
+                    __builtin_amdgcn_sched_barrier(0);
+                }
 
                 int m0 = 0;
                 do {        // (ngw >= PF: at least one turn, which the compiler has to know for settle_fetched)
@@ -980,7 +1044,7 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
                         top2<K>(tk, best, second);
                         __builtin_amdgcn_sched_barrier(0);
                         // buffer `up` is free now: refill it with the group PF-1 turns ahead
-                        {
+                        if constexpr (!AHEAD) {
                             const unsigned off = u == 0 ? own_off : turn_off + (unsigned)(NW * (u - 1)) * GROUP_BYTES;
                             load_row<D>(xr[up], reinterpret_cast<const float *>(
                                                     reinterpret_cast<const char *>(u == 0 ? xb : pbase) + min(off, max_off)));
@@ -994,31 +1058,49 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
                         // this group's row update: D fixed-point terms and a one for the count, added to the lane's
                         // cells of the centroid (masked lanes: the scratch row)
                         const unsigned cell = valid ? (__umul24((unsigned)arg, CENT_BYTES) + lane_cell) : scratch_cell;
+                        unsigned term[D];
 #pragma unroll
-                        for (int j = 0; j < D; ++j) lds_add_u32(cell + (unsigned)j * ELEM_BYTES, fx_term_bits(xc[j], scl[j]));
+                        for (int j = 0; j < D; ++j) {
+                            term[j] = __float_as_uint(fmaf(xc[j], scl[j], magic));
+                            lds_add_u32(cell + (unsigned)j * ELEM_BYTES, term[j]);
+                        }
+                        // (bit patterns as integers: a NaN counts as large, -infinity too)
+                        if constexpr (CHECK) {
+#pragma unroll
+                            for (int j = 0; j < D; j += 2) most = max(max(term[j], term[j + 1]), most);
+                            if (two_sided) {
+#pragma unroll
+                                for (int j = 0; j < D; j += 2) least = min(min(term[j], term[j + 1]), least);
+                            }
+                        }
                         lds_add_u32(cell + (unsigned)D * ELEM_BYTES, 1u);
                     }
                     kp.settle_fetched();
                     m0 += PF;
-                } while (m0 < ngw);
+                } while (!AHEAD && m0 < ngw);       // (AHEAD: not a loop, before which the compiler would wait for all loads)
                 // the part of the step that does not stream is on the worker's critical path: it goes first on its SIMD
                 // until the next step sets the streaming priority again
                 __builtin_amdgcn_s_setprio(3);
                 phase_fence();      // a wave sums its own cells: its atomics have to be done
+                const int here = fresh_lane<LEAN>(lane);
 
                 // ---- sum the copies of every cell ----
                 // lane = (part, task): task = four elements of a centroid (centroid, float4 number); part = its share of
                 // the copies
                 {
-                    const int task = lane % NT, prt = lane / NT;
+                    const int task = here % NT, prt = here / NT;
+                    // (the last of a centroid's four-element groups ends with padding: the flag travels there)
+                    const bool out = CHECK && __ballot(most > term_hi || (two_sided && least < term_lo)) != 0ull;
                     if (prt < NPART) {
                         int si[4];
                         sum_cells<RPP>(wave_cells + (unsigned)(task / NQ) * CENT_BYTES +
                                                      (unsigned)(4 * (task % NQ)) * ELEM_BYTES + (unsigned)(prt * RPP) * 4u,
                                                  ELEM_BYTES, task, si);
-                        part[parity][wave][prt][task] = make_int4(si[0], si[1], si[2], si[3]);
+                        part[parity][wave][prt][task] = make_int4(si[0], si[1], si[2], CHECK && task % NQ == NQ - 1 ? (int)out : si[3]);
                     }
                 }
+                kp.take_back(wst[wave]);
+                const float4 iv = CHECK ? inverse_scales[wave][here < NT ? here % NQ : 0] : inverse;
                 if constexpr (NW > 1) __syncthreads(); else phase_fence();
                 // Totals of this lane's four elements over waves and parts, as integers.  The count of the centroid
                 // (element D) times the rounding constant comes off the sums (modulo 2^32, like the additions), then
@@ -1027,15 +1109,16 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
                 if (kp.has_task) {
 #pragma unroll
                     for (int v = 0; v < NW * NPART; ++v) {
-                        const int4 sv = (&part[parity][0][0][0])[v * NT + lane];
+                        const int4 sv = (&part[parity][0][0][0])[v * NT + here];
                         Si[0] += sv.x; Si[1] += sv.y; Si[2] += sv.z; Si[3] += sv.w;
                     }
                 }
+                const int out = CHECK ? __builtin_amdgcn_readlane(Si[3], NQ - 1) : 0;      // waves whose samples hold an element beyond a limit
                 // the cells are never cleared: they run on, modulo 2^32, and a step's sums are the totals now minus the
                 // totals a step ago (exact, since a step's sums are below 2^30 in magnitude)
                 // (every wave keeps its own copy of the totals a step ago, the values are the same)
                 if (kp.has_task) {
-                    const lds_ivec4_ptr bq = (lds_ivec4_ptr)(size_t)before_cell;
+                    const lds_ivec4_ptr bq = (lds_ivec4_ptr)(size_t)(unsigned)(size_t)(lds_u32_ptr)(unsigned *)&before[wave][here];
                     const lds_ivec4 bv = *bq;
                     const lds_ivec4 nv = {Si[0], Si[1], Si[2], Si[3]};
                     *bq = nv;
@@ -1043,16 +1126,42 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
                     Si[2] = (int)((unsigned)Si[2] - (unsigned)bv.z); Si[3] = (int)((unsigned)Si[3] - (unsigned)bv.w);
                 }
                 const int cnt_i = __float_as_int(lane_read(kp.bp_row + 4 * G::CQ, __int_as_float(Si[G::CI])));
-                // (inv4 is zero where the lane has no column: no select for those)
+                // (the inverse scale is zero where the lane has no column: no select for those)
                 float S4[4];
-                const unsigned bias_off = (unsigned)cnt_i * FX_BIAS;
+                const float inv4[4] = {iv.x, iv.y, iv.z, iv.w};
+                const unsigned bias_off = (unsigned)cnt_i * bias;
 #pragma unroll
                 for (int c4 = 0; c4 < 4; ++c4) S4[c4] = (float)(int)((unsigned)Si[c4] - bias_off) * inv4[c4];
                 if (kp.tq == G::CQ) S4[G::CI] = (float)cnt_i;
                 parity ^= 1;
+                if (CHECK && out) {
+                    if (lane == 0) __hip_atomic_store(p.beyond_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                    // `before` holds the totals with this attempt's terms in them: they are out of the next difference
+                    column_maxima(xb);
+                    set_scales(reinterpret_cast<const float *>(&cmax[wave][0]), true);
+                    again = true;
+                    refill(xb);
+                    continue;
+                }
+                if (CHECK && again) {
+                    set_scales(p.xabsmax, false);
+                    again = false;
+                }
+                if constexpr (AHEAD) {
+                    // (before the step's messages and counters are written: stores count like loads, and would be waited for)
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int u = 0; u < PF; ++u)
+#pragma unroll
+                        for (int j = 0; j < D; ++j) {
+                            xr[u][j] = xn[u][j];
+                            asm volatile("" : "+v"(xr[u][j]));
+                        }
+                }
                 kp.template finish<(NW > 1)>(p, i, round, S4, (float)cnt_i, merge_point, send_point, det, sync_now, wave == 0);
 
                 // advance the clock
+                ++ls;
                 xb = xbn;
                 s_epoch = s_next;
                 if (wk.xchg && ++te == E) { te = 0; ++round; }
@@ -1120,20 +1229,32 @@ hipError_t launch_kernel(int threads, const StepParams &p, long long t0, long lo
 // Like waves.  Several buffers: the message pairs of all buffers sit in registers during a step, so the ring depth is
 // at most 4, and 2 for four buffers; the caller limits it.  Several buffers and partial messages are only built for
 // the shapes with shared rows.
+template <int K, int D, int PF, int NW, int RS, bool CHECK>
+hipError_t launch_variant_of(const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
+{
+    // (two groups per wave: 256 < b <= 512)
+    if constexpr (PF == 2 && NW == 4) {
+        if (p.nb == 1 && p.parts == 1 && (p.b + 63) / 64 <= 2 * NW)
+            return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, true, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+    }
+    if (p.nb == 1 && p.parts == 1)
+        return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+    if constexpr (PF <= 4 && RS == 2 && NW <= 2) {
+        if (p.nb == 1) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 2) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 2, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 3) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 3, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+    }
+    if constexpr (PF == 2 && RS == 2 && NW <= 2) {
+        if (p.nb == 4) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 4, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+    }
+    return hipErrorInvalidValue;
+}
+
 template <int K, int D, int PF, int NW, int RS>
 hipError_t launch_variant(const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
 {
-    if (p.nb == 1 && p.parts == 1)
-        return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false>>(64 * NW, p, t0, t1, s, persistent);
-    if constexpr (PF <= 4 && RS == 2 && NW <= 2) {
-        if (p.nb == 1) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, true>>(64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 2) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 2, true>>(64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 3) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 3, true>>(64 * NW, p, t0, t1, s, persistent);
-    }
-    if constexpr (PF == 2 && RS == 2 && NW <= 2) {
-        if (p.nb == 4) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 4, true>>(64 * NW, p, t0, t1, s, persistent);
-    }
-    return hipErrorInvalidValue;
+    return p.within_limits ? launch_variant_of<K, D, PF, NW, RS, false>(p, t0, t1, s, persistent)
+                           : launch_variant_of<K, D, PF, NW, RS, true>(p, t0, t1, s, persistent);
 }
 
 // ring depth the registers of a shape leave room for: the wave-uniform copy of w_k - w_0 takes (K - 1) * RW registers,

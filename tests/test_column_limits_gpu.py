@@ -1,0 +1,94 @@
+"""Streaming kernel: its fixed-point sums are scaled by column maxima over a part of the samples (16 sweeps of 250 elements in
+turn taken and left, for the data of these tests every second piece of 4000 elements).  Elements beyond the limits that go
+with them, where nothing was looked at, are met in a step, which is then formed again with the maxima of its own mini-batch."""
+import numpy as np
+import pytest
+
+from tests.parity_rules import check_counters, rel_fro
+
+pytestmark = pytest.mark.gpu
+
+K = D = 10
+PIECE = 400            # rows of ten columns
+N = 3_400_000          # 8500 pieces: one in two is looked at
+TOL = 1e-4
+
+
+@pytest.fixture(scope="module")
+def B():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device; there is no CPU fallback")
+    from paper_1505_04956_amd import binding
+    binding.lib()
+    return binding
+
+
+@pytest.fixture(scope="module")
+def samples():
+    rng = np.random.default_rng(5)
+    centres = rng.uniform(0.0, 10.0, (K, D))
+    X = (centres[rng.integers(0, K, N)] + rng.standard_normal((N, D))).astype(np.float32)
+    X[:, 8] = 0.0
+    return X
+
+
+def unseen_rows(rng, n, last):
+    """n rows below `last` in pieces that are not looked at."""
+    piece = 2 * rng.integers(0, last // (2 * PIECE), n) + 1
+    return piece * PIECE + rng.integers(0, PIECE, n)
+
+
+def load(B, X, **kw):
+    import torch
+    g = B.ASGD(K, D, kw.pop("W"), kw.pop("b"), 0.05, kernel=2, **kw)
+    g.load_shards(torch.from_numpy(X).to("cuda:0"))
+    return g
+
+
+# factor 1: scales above one, the maximum alone is compared; 1e8: below one, the minimum too.  W = 4 has four waves per worker,
+# W = 300 two, W = 1100 one; b = 300 is two groups per wave of four
+@pytest.mark.parametrize("W,b,factor", [(4, 1000, 1.0), (4, 300, 1.0), (4, 1000, 1e8), (300, 500, 1.0), (300, 500, 1e8), (1100, 700, 1.0)])
+def test_elements_beyond_the_limits(B, oracle, samples, W, b, factor):
+    X = samples.copy()
+    H, steps = N // W, 9 if W > 4 else 60
+    rng = np.random.default_rng(W + b)
+    for i in range(min(W, 12)):                    # some steps of some workers
+        rows = unseen_rows(rng, 40, N)
+        rows = rows[(rows >= i * H) & (rows < i * H + steps * b)] if W > 300 else i * H + (unseen_rows(rng, 3, steps * b) if steps * b > 800 else [0])
+        X[rows, rng.integers(0, 8, len(rows))] *= np.float32(40.0)
+        X[rows[:1], 9] = np.float32(-300.0)
+        X[rows[-1:], 8] = np.float32(0.25)
+    X *= np.float32(factor)
+    whole, cut = load(B, X, W=W, b=b, E=3), load(B, X, W=W, b=b, E=3)
+    whole.run_steps(steps)
+    for n in (1, 4, steps - 5):
+        cut.run_steps(n)
+    assert np.array_equal(whole.get_state(), cut.get_state())
+    o = oracle.OracleASGD(X, k=K, W=W, b=b, lr=0.05, E=3, seed=1)
+    o.run_steps(steps)
+    wg, wo = whole.get_state().astype(np.float64), np.asarray(o.w)
+    assert rel_fro(wg, wo).max() <= TOL
+    check_counters(whole.worker_counters(), o.counters, o.parzen_near)
+    for j in range(D):                             # every column on its own
+        den = np.linalg.norm(wo[:, :, j], axis=1)
+        assert np.all(np.linalg.norm((wg - wo)[:, :, j], axis=1) <= TOL * den + 1e-30), j
+
+
+# a second epoch, and all but the first of a call of more than sixteen, are not compared with the limits any more
+@pytest.mark.parametrize("W,b,beyond", [(4, 4000, False), (300, 3000, False), (1100, 700, False), (300, 3000, True)])
+def test_later_epochs_give_the_same_bits(B, samples, W, b, beyond):
+    X = samples
+    if beyond:
+        X = samples.copy()
+        X[3 * (N // W) + 500: 3 * (N // W) + 1500, 3] *= np.float32(50.0)
+    S = N // W // b
+    one, two, many = (load(B, X, W=W, b=b, E=2) for _ in range(3))
+    one.run_epochs(2)
+    two.run_epochs(1)
+    two.run_epochs(1)
+    assert one.stats().launches == 1 and np.array_equal(one.get_state(), two.get_state())
+    one.run_steps(16 * S + 3)
+    many.run_steps(18 * S + 3)
+    assert np.array_equal(one.get_state(), many.get_state())
+    assert many.stats().launches <= 2 + (18 * S + 3) // 2 // 1024
