@@ -15,23 +15,23 @@ hipError_t launch_split_quant_5(const SplitQuant &a, int blocks, unsigned lds, h
 hipError_t launch_split_quant_6(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_quant_7(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_quant_8(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_0(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_0(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_0(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_1(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_1(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_1(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_2(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_2(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_2(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_3(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_3(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_3(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_4(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_4(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_4(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_5(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_5(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_5(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_6(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_6(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_6(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_7(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_7(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_7(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
-hipError_t launch_split_local_8(const SplitRun &r, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_local_8(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_8(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
 
 
@@ -106,9 +106,9 @@ namespace {
 struct SplitPlan {
     int nch, dpad, nblk, kpad, npair;
     size_t frag_bytes;
-    bool longrow, fused, resident;
+    bool longrow, fused, resident, kept;
     int waves, shares, share_len, grid;
-    unsigned off_cells, off_cnt, off_hs, off_ms, off_args, lds;
+    unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes, lds;
     int dc, ncol, sum_shares, sum_len;      // sums in a launch of their own: columns per workgroup, shares
     unsigned lds_sums;
     int g, upd_blocks;             // update: lanes per row, workgroups per worker
@@ -150,6 +150,12 @@ SplitPlan make_plan(const StepParams &p, bool local)
     q.off_hs = o;  o += round16((size_t)q.kpad * 4);
     q.off_ms = o;  o += round16((size_t)q.dpad * 4);
     q.off_args = o; o += 8 * 64 * 4 * (q.longrow ? 5 : 1);
+    // (two mini-batches of a kept worker: the next one arrives while the current one is worked on)
+    q.batch_bytes = (unsigned)(((size_t)(p.b < 16384 ? p.b : 16384) * p.d * 4 + 1023) / 1024 * 1024);
+    q.kept = local && q.fused && q.resident && q.nch <= SPLIT_KEPT_CHUNKS && p.W <= SPLIT_CUS && p.b <= 16384 && (size_t)o + 2 * (size_t)q.batch_bytes + SPLIT_LDS_SHARED <= 160 * 1024;
+    o = (o + 1023) / 1024 * 1024;
+    q.off_batch = o;
+    if (q.kept) o += 2 * q.batch_bytes;
     q.lds = o;
     // Phases: waves of a workgroup and shares of a mini-batch - enough workgroups for the compute units first, then as many
     // waves per workgroup as share the staged operands, and as many workgroups as are resident at once (three waves per
@@ -248,18 +254,30 @@ Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
 
 }  // namespace
 
-// Local form: the workers fill the device, one workgroup of eight waves each (three quarters of them at least: fewer are
-// better off with phases, which cut their mini-batches), and exchange every fourth step at most (every message costs its
-// sender a write-back and its recipient an invalidation of the L2, which phases get from the end of a launch: k = 64,
-// d = 32, b = 500, E = 1: 105 us per step local, 33 us in phases).  Two rounds of workers and more take longer than phases
-// (512 workers, E = 8: k = 12, d = 8, b = 600: 47 us per step local, 34 in phases; k = d = 100, b = 2000, ten epochs a call:
-// 245 and 227): only for the caller that promises one launch per call (the matrix-core kernel: asgd_run_epochs()).
+// Kept workers: what a step needs besides messages is in the LDS when it begins, so it takes 11 to 25 us and never a launch, also
+// with a message every step.  Microseconds per step of long calls, W = 256 (phases where E < 4, else the local form that is not kept; kept): k = 12,
+// d = 7: b = 100, E = 0 15.0, 11.2; b = 500, E = 0 17.5, 13.5; E = 2 26.5, 18.4; b = 2000, E = 4 52.9, 30.7; k = 64, d = 32, b = 500, E = 1 33.4, 24.6;
+// k = 100, d = 60, b = 120, E = 1 45.9, 37.5; k = 500, d = 8, b = 256, E = 1 47.5, 37.0; k = 400, d = 10, b = 1000, E = 2 59.6, 47.5.
+// (Where they do not fill the device, phases cut their mini-batches: k = 12, d = 7, b = 2000, W = 32 24.9, 29.6.)
+static bool split_kept(const StepParams &p)
+{
+    return p.parts == 1 && !p.phases_only && 4LL * p.W >= 3LL * SPLIT_CUS && make_plan(p, true).kept;
+}
+
+// Local form: kept workers, or workers that fill the device, one workgroup of eight waves each
+// (three quarters of them at least: fewer are better off with phases, which cut their mini-batches), and exchange every fourth step
+// at most (every message costs its sender a write-back and its recipient an invalidation of the L2, which phases get from the end
+// of a launch: k = 64, d = 32, b = 500, E = 1: 105 us per step local, 33 us in phases).  Two rounds of workers and more take longer
+// than phases (512 workers, E = 8: k = 12, d = 8, b = 600: 47 us per step local, 34 in phases; k = d = 100, b = 2000, ten epochs a
+// call: 245 and 227): only for the caller that promises one launch per call (the matrix-core kernel: asgd_run_epochs()).
 bool split_local_form(const StepParams &p)
 {
     const int rounds = (p.W + SPLIT_CUS - 1) / SPLIT_CUS;
     int dev = 0, cus = 0;                  // (a partition of a device may have fewer compute units: not resident at once)
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return false;
-    return !p.phases_only && cus >= SPLIT_CUS && p.parts == 1 && 4LL * p.W >= 3LL * rounds * SPLIT_CUS && (rounds == 1 || p.one_launch) && (p.E == 0 || p.W < 2 || (p.mode == ASGD_MODE_DETERMINISTIC && p.E >= 4));
+    const bool exchange = p.E > 0 && p.W > 1;
+    if (p.phases_only || cus < SPLIT_CUS || p.parts > 1 || (exchange && p.mode != ASGD_MODE_DETERMINISTIC)) return false;
+    return split_kept(p) || (4LL * p.W >= 3LL * rounds * SPLIT_CUS && (rounds == 1 || p.one_launch) && (!exchange || p.E >= 4));
 }
 
 size_t split_scratch_bytes(const StepParams &p) { return scratch_layout(p, make_plan(p, split_local_form(p))).bytes; }
@@ -297,6 +315,7 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, c
     a.k = p.k; a.d = p.d; a.b = p.b; a.W = p.W; a.kpad = q.kpad; a.nblk = q.nblk; a.dpad = q.dpad;
     a.shares = q.shares; a.share_len = q.share_len; a.sum_shares = q.sum_shares; a.sum_len = q.sum_len; a.dc = q.dc; a.ncol = q.ncol; a.resident = q.resident; a.fused = q.fused;
     a.vec4 = p.d % 4 == 0 && ((uintptr_t)p.x & 15u) == 0;
+    a.kept = q.kept; a.off_batch = q.off_batch; a.batch_bytes = q.batch_bytes;
     a.off_cells = q.off_cells; a.off_cnt = q.off_cnt; a.off_hs = q.off_hs; a.off_ms = q.off_ms; a.off_args = q.off_args;
     SplitUpdate u;
     u.frag = base + l.frag; u.hs = (float *)(base + l.hs);
@@ -325,15 +344,15 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, c
         const double polls = (double)(1 << 18) + step * (double)p.E * ((p.W + q.grid - 1) / q.grid);
         r.wait_polls = (int)(polls < (double)(1 << 29) ? polls : (double)(1 << 29));
         switch (q.longrow ? 0 : q.nch) {
-            case 0: e = launch_split_local_0(r, q.grid, q.lds, s); break;
-            case 1: e = launch_split_local_1(r, q.grid, q.lds, s); break;
-            case 2: e = launch_split_local_2(r, q.grid, q.lds, s); break;
-            case 3: e = launch_split_local_3(r, q.grid, q.lds, s); break;
-            case 4: e = launch_split_local_4(r, q.grid, q.lds, s); break;
-            case 5: e = launch_split_local_5(r, q.grid, q.lds, s); break;
-            case 6: e = launch_split_local_6(r, q.grid, q.lds, s); break;
-            case 7: e = launch_split_local_7(r, q.grid, q.lds, s); break;
-            default: e = launch_split_local_8(r, q.grid, q.lds, s); break;
+            case 0: e = launch_split_local_0(r, q.grid, 64 * q.waves, q.lds, s); break;
+            case 1: e = launch_split_local_1(r, q.grid, 64 * q.waves, q.lds, s); break;
+            case 2: e = launch_split_local_2(r, q.grid, 64 * q.waves, q.lds, s); break;
+            case 3: e = launch_split_local_3(r, q.grid, 64 * q.waves, q.lds, s); break;
+            case 4: e = launch_split_local_4(r, q.grid, 64 * q.waves, q.lds, s); break;
+            case 5: e = launch_split_local_5(r, q.grid, 64 * q.waves, q.lds, s); break;
+            case 6: e = launch_split_local_6(r, q.grid, 64 * q.waves, q.lds, s); break;
+            case 7: e = launch_split_local_7(r, q.grid, 64 * q.waves, q.lds, s); break;
+            default: e = launch_split_local_8(r, q.grid, 64 * q.waves, q.lds, s); break;
         }
         *launches += 1;
         return e;

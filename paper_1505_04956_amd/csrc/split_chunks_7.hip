@@ -4,9 +4,9 @@
 
 namespace asgd {
 
-hipError_t launch_split_local_7(const SplitRun &r, int blocks, unsigned lds, hipStream_t s)
+hipError_t launch_split_local_7(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s)
 {
-    return split_launch_local<7>(r, blocks, lds, s);
+    return split_launch_local<7>(r, blocks, threads, lds, s);
 }
 hipError_t launch_split_assign_7(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s)
 {

@@ -191,7 +191,7 @@ __device__ inline int split_scan_own(const float *xl, const float *w, int k, int
 // `xg` (valid or not), `t` its best scores.  Closer than thr: decided in fp64, two candidates by the sign of
 // sum_j (w_aj - w_bj)(w_aj + w_bj - 2 x_j), more by all k distances in direct form; the lowest index wins exact ties.
 // thr may be infinite (then everything is decided in fp64); scores may be NaN.
-__device__ inline int split_settle(const SplitTop &t, float thr, bool valid, const float *xg, const float *w, int k, int d,
+__device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool valid, const float *xg, const float *w, int k, int d,
                                    int &rechecks)
 {
     const int lane = split_lane();

@@ -17,6 +17,7 @@ namespace asgd {
 // chunks of 16; [row pair][chunk][block of the pair][hi, lo] pieces of 1 KB, piece = 64 lanes x 8 fp16, lane l holding row
 // l % 32, columns 8 * (l / 32) .. + 7 of the chunk.
 constexpr int SPLIT_THREADS = 512;
+constexpr int SPLIT_KEPT_CHUNKS = 4;              // longest rows of a kept worker: beyond, its kernel needs more registers than there are
 
 struct SplitState {                // one per worker and step modulo 3
     float sw;                      // scale of the operands
@@ -24,13 +25,16 @@ struct SplitState {                // one per worker and step modulo 3
     unsigned pad[29];              // a cache line each: atomics on one line wait for each other, and that took 15 us
 };
 
+struct SplitSize { float sw; unsigned vabs, n2; };
+
 struct SplitStep {                         // what is the same for all workers in a step
     int slot, slot_next, slot_after;       // step modulo 3
     int merge, send, round;                // merge point, messages go out, round number
     int read_parity, send_parity, local;
+    int batch;                             // which of a kept worker's two buffers holds the mini-batch
     const SplitState *state;               // W, of this step's slot
     int32_t *dump;                         // W x b of this step, or null
-    long long row0;                        // first row of the mini-batch in a shard
+    long long row0, row0_next;             // first row of the mini-batch in a shard, and of the next one (-1: none)
     int shift[MAX_BUFFERS];                // deterministic schedule of the round
 };
 
@@ -55,8 +59,23 @@ struct SplitArgs {
     int shares, share_len;           // share_len: samples of a share, a multiple of 64
     int sum_shares, sum_len, dc, ncol;       // sums in a phase of their own: shares, columns per item, groups of columns
     int resident, fused, vec4;
-    unsigned off_cells, off_cnt, off_hs, off_ms, off_args;
+    int kept;                        // local form, one worker per workgroup: its operands, sums and counts stay in the LDS, and two mini-batches take turns there
+    unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes;
 };
+
+struct SplitShared {                       // start of the LDS: the step, and space of the gate and update phases
+    SplitStep now;
+    double red[8];
+    int delta;
+    unsigned most[2][8];
+    SplitSize size[3];                     // SplitState of a kept worker
+};
+
+// The LDS starts with what all phases share.
+extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
+constexpr unsigned SPLIT_LDS_SHARED = 512;
+static_assert(sizeof(SplitShared) <= SPLIT_LDS_SHARED, "room at the start of the LDS");
+__device__ __forceinline__ SplitShared &split_shared() { return *reinterpret_cast<SplitShared *>(split_lds); }
 
 // A term x * scale is rounded to an integer by adding 1.5 * 2^52 in the fused multiply-add and its bit pattern is added
 // to a 64-bit cell; the count times the bit pattern of 1.5 * 2^52 comes off when the cell is read, modulo 2^64.
@@ -86,7 +105,7 @@ __device__ __forceinline__ int split_cell(SPLIT_ARG SplitArgs &a, int j)
     return a.vec4 ? (j & 3) * (a.d >> 2) + (j >> 2) : (j & 1) * ((a.d + 1) >> 1) + (j >> 1);
 }
 // rows 0 .. nv-1 of xg, their centroids in args
-__device__ inline void split_accumulate(SPLIT_ARG SplitArgs &a, const float *xg, int nv, const int *args, u64 *cells, int *cnt)
+__device__ __forceinline__ void split_accumulate(SPLIT_ARG SplitArgs &a, const float *xg, int nv, const int *args, u64 *cells, int *cnt)
 {
     const int lane = split_lane(), d = a.d;
     if (lane < nv) atomicAdd(&cnt[args[lane]], 1);
@@ -191,6 +210,22 @@ __device__ __forceinline__ void split_stage_wait()
     __syncthreads();
 }
 
+// A mini-batch of a kept worker on its way to the LDS.
+__device__ __forceinline__ void split_batch_fetch(SPLIT_ARG SplitArgs &a, int worker, long long row0, unsigned char *dst)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6, total = a.b * a.d;
+    const float *src = a.x + ((size_t)worker * a.H + (size_t)row0) * a.d;
+    if (a.vec4) {
+        for (int q = wave; q * 256 < total; q += nw)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + min(q * 256 + lane * 4, total - 4)),
+                                             (__attribute__((address_space(3))) void *)(dst + q * 1024), 16, 0, 0);
+    } else {
+        for (int q = wave; q * 64 < total; q += nw)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + min(q * 64 + lane, total - 1)),
+                                             (__attribute__((address_space(3))) void *)(dst + q * 256), 4, 0, 0);
+    }
+}
+
 __device__ __forceinline__ void split_init_acc(sfloatx16 &acc, const float *hs, int block, int half)
 {
     const float4 *hp = reinterpret_cast<const float4 *>(hs + block * 32 + 4 * half);
@@ -202,12 +237,15 @@ __device__ __forceinline__ void split_init_acc(sfloatx16 &acc, const float *hs, 
 }
 
 // What a wave does once the best scores of its 64 samples are known (lane l: sample l), the same in both assignment items.
+template <bool KEPT>
 __device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const SplitStep &now, const SplitTop &t, float n2, int worker, int g,
                                                    int n_hi, const float *xb, int *args, u64 *cells, int *cnt, int &rechecks)
 {
     const int lane = split_lane();
     const float yn = sqrtf(n2) * 1.0001f;
-    const SplitState st = now.state[worker];
+    SplitSize st;
+    if constexpr (KEPT) st = split_shared().size[now.slot];
+    else st = SplitSize{now.state[worker].sw, now.state[worker].vabs, now.state[worker].n2};
     const float sw = st.sw, n2max = __uint_as_float(st.n2), vmax = sqrtf(n2max) * 1.0001f, ratio = a.xmeta[0] / sw;
     const float offset = 0.5f * vmax * vmax * ratio;
     float thr = split_c1(a.dpad) * (yn * vmax + offset) + split_c2(a.dpad) * (yn + vmax);
@@ -227,7 +265,11 @@ __device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const
         args[lane] = valid ? arg : 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        split_accumulate(a, xg, min(64, n_hi - g), args, cells, cnt);
+        if (KEPT)
+            split_accumulate(a, reinterpret_cast<const float *>(split_lds + SPLIT_LDS_SHARED + a.off_batch + now.batch * a.batch_bytes) + g * a.d,
+                             min(64, n_hi - g), args, cells, cnt);
+        else
+            split_accumulate(a, xg, min(64, n_hi - g), args, cells, cnt);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
     }
@@ -245,7 +287,7 @@ __device__ __forceinline__ void split_count_rechecks(SPLIT_ARG SplitArgs &a, int
 // registers (NC * 16 registers); the state's operands come from LDS, resident when they fit, else one row pair at a time
 // through two stages.  fused: the gradient sums are formed right away from a second, coalesced read of the wave's
 // samples (in a cache still), in 64-bit fixed-point cells in LDS.
-template <int NC>
+template <int NC, bool KEPT>
 __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
 {
     const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len);
@@ -259,23 +301,32 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
     const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
     const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * a.d;
     const float sx = a.xmeta[0];
+    const float *batch = reinterpret_cast<const float *>(smem + a.off_batch + now.batch * a.batch_bytes);
 
+    // (this wave's rows of the new state, for the exact decisions, and its part of the mini-batch)
+    if constexpr (KEPT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();                            // (the item before this one is done with the LDS)
-    if (a.resident) split_stage(frag, smem, npair * NC * 4);
-    for (int c = tid; c < a.kpad; c += blockDim.x) hs[c] = a.hs[(size_t)worker * a.kpad + c];
-    for (int j = tid; j < a.dpad; j += blockDim.x) ms[j] = a.ms[j];
-    if (a.fused) {
-        for (int e = tid; e < a.k * split_cell_stride(a); e += blockDim.x) cells[e] = 0;
-        for (int c = tid; c < a.k; c += blockDim.x) cnt[c] = 0;
+    if constexpr (KEPT) {
+        if (now.row0_next >= 0) split_batch_fetch(a, worker, now.row0_next, smem + a.off_batch + (now.batch ^ 1) * a.batch_bytes);
     }
-    split_stage_wait();
+    if constexpr (!KEPT) {
+        if (a.resident) split_stage(frag, smem, npair * NC * 4);
+        for (int c = tid; c < a.kpad; c += blockDim.x) hs[c] = a.hs[(size_t)worker * a.kpad + c];
+        for (int j = tid; j < a.dpad; j += blockDim.x) ms[j] = a.ms[j];
+        if (a.fused) {
+            for (int e = tid; e < a.k * split_cell_stride(a); e += blockDim.x) cells[e] = 0;
+            for (int c = tid; c < a.k; c += blockDim.x) cnt[c] = 0;
+        }
+        split_stage_wait();
+    }
+    const bool resident = KEPT || a.resident;
 
     int rechecks = 0;
     const int span = nw * 64;
     for (int g0 = n_lo; g0 < n_hi; g0 += span) {
         const int g = g0 + wave * 64;
         const bool active = g < n_hi;
-        if (a.resident && !active) break;
+        if (resident && !active) break;
         half8 bh[2][NC], bl[2][NC];
         float n2[2] = {0.0f, 0.0f};
         // (Fetching a group's columns while the group before it is finished changed nothing where there are registers for
@@ -283,12 +334,32 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
         if (active) {
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                const int n = g + 32 * m + l32;
-                const float *row = xb + (size_t)(n < n_hi ? n : n_lo) * a.d;
                 float v[NC][8];
+                const int n = g + 32 * m + l32;
+                if (KEPT) {
+                    const float *row = batch + (n < n_hi ? n : n_lo) * a.d;
+                    if (a.vec4 && a.d >= 8) {
 #pragma unroll
-                for (int ch = 0; ch + 1 < NC; ++ch) split_load8<false>(v[ch], row, ch * 16 + 8 * half, a.d);
-                split_load8<true>(v[NC - 1], row, (NC - 1) * 16 + 8 * half, a.d);
+                        for (int ch = 0; ch < NC; ++ch) {
+                            const int slot = ch * 16 + 8 * half;
+                            const float *q = row + (ch + 1 < NC ? slot : min(slot, a.d - 8));
+                            const float4 p0 = *reinterpret_cast<const float4 *>(q), p1 = *reinterpret_cast<const float4 *>(q + 4);
+                            v[ch][0] = p0.x; v[ch][1] = p0.y; v[ch][2] = p0.z; v[ch][3] = p0.w;
+                            v[ch][4] = p1.x; v[ch][5] = p1.y; v[ch][6] = p1.z; v[ch][7] = p1.w;
+                        }
+                    } else {
+#pragma unroll
+                        for (int ch = 0; ch < NC; ++ch)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e)
+                                v[ch][e] = row[min(split_column(ch * 16 + 8 * half < a.d ? ch * 16 + 8 * half + e : e, a.d), a.d - 1)];
+                    }
+                } else {
+                    const float *row = xb + (size_t)(n < n_hi ? n : n_lo) * a.d;
+#pragma unroll
+                    for (int ch = 0; ch + 1 < NC; ++ch) split_load8<false>(v[ch], row, ch * 16 + 8 * half, a.d);
+                    split_load8<true>(v[NC - 1], row, (NC - 1) * 16 + 8 * half, a.d);
+                }
 #pragma unroll
                 for (int ch = 0; ch + 1 < NC; ++ch) {
                     split_convert<false>(v[ch], sx, ms, ch * 16 + 8 * half, a.d, bh[m][ch], bl[m][ch], n2[m]);
@@ -305,13 +376,13 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
             top[m].i1 = top[m].i2 = 0;
         }
         const float big = split_opaque_infinity();
-        if (!a.resident) {
+        if (!resident) {
             __syncthreads();                    // nobody still reads the first stage
             split_stage(frag, smem, NC * 4);
         }
         for (int rp = 0; rp < npair; ++rp) {
-            const unsigned char *st = smem + (size_t)(a.resident ? rp : (rp & 1)) * NC * 4 * SPLIT_PIECE;
-            if (!a.resident) {
+            const unsigned char *st = smem + (size_t)(resident ? rp : (rp & 1)) * NC * 4 * SPLIT_PIECE;
+            if (!resident) {
                 split_stage_wait();
                 if (rp + 1 < npair)
                     split_stage(frag + (size_t)(rp + 1) * NC * 4 * SPLIT_PIECE, smem + ((rp + 1) & 1) * NC * 4 * SPLIT_PIECE, NC * 4);
@@ -348,11 +419,11 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
             SplitTop t;
             split_combine(top, t, half);
             swap2(n2[0], n2[1]);
-            split_finish_group(a, now, t, n2[0] + n2[1], worker, g, n_hi, xb, args, cells, cnt, rechecks);
+            split_finish_group<KEPT>(a, now, t, n2[0] + n2[1], worker, g, n_hi, xb, args, cells, cnt, rechecks);
         }
     }
     split_count_rechecks(a, worker, rechecks);
-    if (a.fused) {
+    if (!KEPT && a.fused) {
         __syncthreads();
         split_flush(a, worker, share, cells, cnt);
     }
@@ -477,7 +548,7 @@ __device__ inline void split_assign_long_item(SPLIT_ARG SplitArgs &a, const Spli
                 t.v3 = fmaxf(t.v3, o[128]);
             }
             swap2(n2[0], n2[1]);
-            split_finish_group(a, now, t, n2[0] + n2[1], worker, g, n_hi, xb, nullptr, nullptr, nullptr, rechecks);
+            split_finish_group<false>(a, now, t, n2[0] + n2[1], worker, g, n_hi, xb, nullptr, nullptr, nullptr, rechecks);
         }
         __syncthreads();                          // (tops are written again)
     }
@@ -582,12 +653,6 @@ __device__ inline void split_sums_item(SPLIT_ARG SplitArgs &a, const SplitStep &
 // memory between phases: the three sums of Eq. 4 (partial sums per workgroup, added in order), the largest |v| and
 // row norm (integer maxima of bit patterns, which do not depend on the order), and the power of two the fp16 operands
 // are scaled with, which follows the state one step behind.
-struct SplitShared {                       // start of the LDS: the step, and space of the gate and update phases
-    SplitStep now;
-    double red[8];
-    int delta;
-    unsigned most[2][8];
-};
 struct SplitGate { double lhs, rhs, nrm; };
 struct SplitMail { int has, round[MAX_BUFFERS]; };     // messages of a merge point: buffers that hold one, their rounds
 
@@ -664,6 +729,63 @@ __device__ __forceinline__ void split_sums8(float (&sm)[8], SPLIT_ARG SplitUpdat
     for (int e = 0; e < 8; ++e) sm[e] = (float)total[e];
 }
 
+// The same of a kept worker, from the cells themselves.
+__device__ __forceinline__ void split_kept_sums8(float (&sm)[8], SPLIT_ARG SplitArgs &a, const unsigned char *smem, int c, int cn, int j0, int d)
+{
+    const u64 *cells = reinterpret_cast<const u64 *>(smem + a.off_cells) + c * split_cell_stride(a);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const int j = min(split_column(j0 + e, d), d - 1);
+        sm[e] = split_sum(cells[split_cell(a, j)], cn, a.colscale[d + j]);
+    }
+}
+__device__ __forceinline__ void split_kept_clear8(SPLIT_ARG SplitArgs &a, unsigned char *smem, int c, int j0, int d)
+{
+    u64 *cells = reinterpret_cast<u64 *>(smem + a.off_cells) + c * split_cell_stride(a);
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (split_slot_used(j0 + e, d)) cells[split_cell(a, split_column(j0 + e, d))] = 0;
+}
+
+// Messages between workgroups of one launch: written and read past the caches that are not shared, element by element, so that
+// neither side needs a fence (which writes back or invalidates a whole L2: k = 64, d = 32, b = 500, a message every step, 105 us
+// per step with fences).
+// (sixteen bytes with the scope bit of an agent-scope access; a load waits in the same block)
+__device__ __forceinline__ void split_message_put16(float *row, const float (&v)[8])
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    const f4 a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\tglobal_store_dwordx4 %0, %2, off offset:16 sc1" ::"v"(row), "v"(a), "v"(b) : "memory");
+}
+__device__ __forceinline__ void split_message_row16(float (&v)[8], const float *row)
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    f4 a, b;
+    asm volatile("global_load_dwordx4 %0, %2, off sc1\n\tglobal_load_dwordx4 %1, %2, off offset:16 sc1\n\ts_waitcnt vmcnt(0)"
+                 : "=&v"(a), "=&v"(b) : "v"(row) : "memory");
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+}
+__device__ __forceinline__ void split_message_put8(float *row, const float (&v)[8], int j0, int d)
+{
+    if (j0 + 8 <= d) {
+        split_message_put16(row + j0, v);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        if (split_slot_used(j0 + e, d)) __hip_atomic_store(row + split_column(j0 + e, d), v[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void split_message_row8(float (&v)[8], const float *row, int j0, int d)
+{
+    if (d >= 8) {
+        split_message_row16(v, row + min(j0, d - 8));
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = __hip_atomic_load(row + min(split_column(j0 + e, d), d - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ double split_block_sum(double v, double *red)
 {
     v = split_wave_sum(v);
@@ -691,8 +813,10 @@ __device__ __forceinline__ void split_gate8(const float (&wv)[8], const float (&
 }
 
 // Eq. 4 at a merge point: which buffers hold a message, and (whole states) the sums over a workgroup's rows, in fp64.
-__device__ inline void split_gate_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, const SplitStep &now, int i, int blk, double *red)
+template <bool KEPT>
+__device__ inline void split_gate_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, SPLIT_ARG SplitArgs &a, const SplitStep &now, int i, int blk, double *red)
 {
+    unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
     __syncthreads();
     const int k = p.k, d = p.d;
     const int lane_g = threadIdx.x & (u.g - 1), ngrp = (int)blockDim.x / u.g, grp = threadIdx.x / u.g;
@@ -715,12 +839,17 @@ __device__ inline void split_gate_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitU
         if (mail.has >> n & 1) {
             const float *ext = p.slot + exchange_buffer(now.read_parity, p.nb, n, p.W, i) * kd;
             for (int c = blk * ngrp + grp; c < k; c += u.blocks * ngrp) {
-                const int cn = split_count(u, p.W, k, i, c);
+                const int cn = KEPT ? reinterpret_cast<const int *>(smem + a.off_cnt)[c] : split_count(u, p.W, k, i, c);
                 for (int j0 = lane_g * 8; j0 < d; j0 += u.g * 8) {
                     float wv[8], sm[8], ev[8];
                     split_row8(wv, w + (size_t)c * d, j0, d);
-                    split_row8(ev, ext + (size_t)c * d, j0, d);
-                    split_sums8(sm, u, p.W, k, i, c, j0, d);
+                    if constexpr (KEPT) {
+                        split_message_row8(ev, ext + (size_t)c * d, j0, d);
+                        split_kept_sums8(sm, a, smem, c, cn, j0, d);
+                    } else {
+                        split_row8(ev, ext + (size_t)c * d, j0, d);
+                        split_sums8(sm, u, p.W, k, i, c, j0, d);
+                    }
                     split_gate8(wv, sm, ev, cn, j0, p, lhs, rhs, nrm);
                 }
             }
@@ -730,30 +859,95 @@ __device__ inline void split_gate_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitU
     }
 }
 
+__device__ __forceinline__ bool split_gate_at_once(SPLIT_ARG SplitArgs &a, SPLIT_ARG SplitUpdate &u)
+{
+    return a.k * u.g <= (int)blockDim.x && u.dpad <= 8 * u.g;
+}
+
 // MODE 0: size of the states; 1: their operands; 2: a step; 3: a step with the 1/count step size (no exchange there);
 // 4: a step with partial messages.
 // (A template: a phase this short is mostly the fetch of its own code.)
-template <int MODE>
-__device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, const SplitStep &now, int i, int blk,
+template <int MODE, bool KEPT>
+__device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, SPLIT_ARG SplitArgs &a, const SplitStep &now, int i, int blk,
                                          SplitShared &sh)
 {
+    unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
+    int *kept_cnt = reinterpret_cast<int *>(smem + a.off_cnt);
     constexpr bool STEP = MODE >= 2, INV_COUNT = MODE == 3, ROWWISE = MODE == 4;
     const int tid = threadIdx.x, k = p.k, d = p.d;
     const int lane_g = tid & (u.g - 1), ngrp = (int)blockDim.x / u.g, grp = tid / u.g;
     const size_t kd = (size_t)k * d;
     float *w = p.w + (size_t)i * kd;
-    unsigned char *frag = u.frag + (size_t)i * u.frag_bytes;
-    float *hs = u.hs + (size_t)i * u.kpad;
+    unsigned char *frag = KEPT ? smem : u.frag + (size_t)i * u.frag_bytes;
+    float *hs = KEPT ? reinterpret_cast<float *>(smem + a.off_hs) : u.hs + (size_t)i * u.kpad;
     SplitState *st_now = u.state + (size_t)now.slot * p.W + i, *st_next = u.state + (size_t)now.slot_next * p.W + i,
                *st_after = u.state + (size_t)now.slot_after * p.W + i;
     const float sx = u.xmeta[0];
-    const float sw = MODE == 0 ? 1.0f : split_state_scale(st_now->vabs);
-
     __syncthreads();                                 // (the item before this one is done with the LDS)
+    const float sw = MODE == 0 ? 1.0f : split_state_scale(KEPT ? sh.size[now.slot].vabs : st_now->vabs);
+
     SplitMail mail;
     mail.has = 0;
     int delta_mask = 0;
-    if (STEP && !INV_COUNT && now.merge) {
+    // A kept state of no more than a unit per thread: Eq. 4 here, its messages are read once and stay in registers.
+    const bool at_once = KEPT && STEP && !INV_COUNT && split_gate_at_once(a, u);
+    float evs[KEPT ? MAX_BUFFERS : 1][8];
+    if (at_once && now.merge) {
+        const bool det = p.mode == ASGD_MODE_DETERMINISTIC;
+        const int j0 = lane_g * 8;
+        double *gred = reinterpret_cast<double *>(smem + a.off_args);            // [wave][buffer][3]
+        int st[MAX_BUFFERS];
+        float wv[8], sm[8];
+        const bool mine = grp < k && j0 < d;
+        const int cn = mine ? kept_cnt[grp] : 0;
+        if (mine) {
+            split_row8(wv, w + (size_t)grp * d, j0, d);
+            split_kept_sums8(sm, a, smem, grp, cn, j0, d);
+        }
+#pragma unroll
+        for (int n = 0; n < MAX_BUFFERS; ++n) {
+            if (n >= p.nb) continue;
+            const size_t buf = exchange_buffer(now.read_parity, p.nb, n, p.W, i);
+            st[n] = __hip_atomic_load(p.stamp + buf, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            double lhs = 0.0, rhs = 0.0, nrm = 0.0;
+            if (mine) {
+                split_message_row8(evs[n], p.slot + buf * kd + (size_t)grp * d, j0, d);
+                split_gate8(wv, sm, evs[n], cn, j0, p, lhs, rhs, nrm);
+            }
+            lhs = split_wave_sum(lhs); rhs = split_wave_sum(rhs); nrm = split_wave_sum(nrm);
+            if ((tid & 63) == 0) {
+                double *at = gred + ((tid >> 6) * MAX_BUFFERS + n) * 3;
+                at[0] = lhs; at[1] = rhs; at[2] = nrm;
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // (the stamps have been read before thread 0 empties them)
+        __syncthreads();
+        int received = 0, near = 0;
+#pragma unroll
+        for (int n = 0; n < MAX_BUFFERS; ++n) {
+            if (n >= p.nb || !(det ? st[n] == now.round - 1 : st[n] >= 0)) continue;
+            double lhs = 0.0, rhs = 0.0, nrm = 0.0;
+            for (int q = 0; q < (int)(blockDim.x >> 6); ++q) {
+                const double *at = gred + (q * MAX_BUFFERS + n) * 3;
+                lhs += at[0]; rhs += at[1]; nrm += at[2];
+            }
+            if (nrm > 0.0) {                               // lambda of Eq. 3: an all-zero buffer is empty
+                received += 1;
+                if (p.parzen ? (lhs < rhs) : 1) delta_mask |= 1 << n;
+                if (rhs > 0.0 && fabs(lhs - rhs) / rhs < 1e-6) near += 1;
+            }
+        }
+        if (tid == 0) {
+            long long *cnp = p.counters + (size_t)i * CNT_STRIDE;
+            if (received) {
+                cnp[CNT_RECEIVED] += received;
+                cnp[CNT_ACCEPTED] += __builtin_popcount(delta_mask);
+                cnp[CNT_PARZEN_NEAR] += near;
+            }
+            for (int n = 0; n < p.nb; ++n)                 // (emptied when it was looked at, as below)
+                __hip_atomic_store(p.stamp + exchange_buffer(now.read_parity, p.nb, n, p.W, i), -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    } else if (STEP && !INV_COUNT && now.merge) {
         // which buffers take part: Eq. 4 over the whole state, every buffer on its own (Eq. 6)
         mail = u.mail[i];
         if (tid == 0) {
@@ -789,8 +983,12 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
         delta_mask = sh.delta;
     }
     if (blk == 0 && tid == 0) {
-        if (MODE != 0) st_next->sw = sw;
-        st_after->vabs = st_after->n2 = 0;               // (nobody looks at it in this launch)
+        if constexpr (KEPT) {
+            if (MODE != 0) sh.size[now.slot_next].sw = sw;
+        } else {
+            if (MODE != 0) st_next->sw = sw;
+            st_after->vabs = st_after->n2 = 0;           // (nobody looks at it in this launch)
+        }
     }
     auto peer_of = [&](int n) -> int {                   // recipient of copy n of this worker's message, -1: lost on the way
         if (p.drop_thr && message_dropped(p.seed, now.round, i, p.drop_thr, n)) return -1;
@@ -807,7 +1005,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
     const int rows = MODE == 1 ? u.kpad : k;             // padding rows are written once
     for (int c = blk * ngrp + grp; c < rows; c += u.blocks * ngrp) {
         const bool real = MODE != 1 || c < k;
-        const int cn = STEP ? split_count(u, p.W, k, i, c) : 0;
+        const int cn = STEP ? (KEPT ? kept_cnt[c] : split_count(u, p.W, k, i, c)) : 0;
         int rowmask = delta_mask;
         float inv = inv_all;
         if (ROWWISE) {
@@ -853,7 +1051,12 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
                 split_row8(mid, u.m, j0, d);
                 if (STEP) {
                     float sm[8];
-                    split_sums8(sm, u, p.W, k, i, c, j0, d);
+                    if constexpr (KEPT) {
+                        split_kept_sums8(sm, a, smem, c, cn, j0, d);
+                        split_kept_clear8(a, smem, c, j0, d);
+                    } else {
+                        split_sums8(sm, u, p.W, k, i, c, j0, d);
+                    }
                     if (INV_COUNT) {
 #pragma unroll
                         for (int e = 0; e < 8; ++e)
@@ -865,7 +1068,17 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
                         for (int n = 0; n < p.nb; ++n)
                             if (rowmask >> n & 1) {
                                 float ev[8];
-                                split_row8(ev, p.slot + exchange_buffer(now.read_parity, p.nb, n, p.W, i) * kd + (size_t)c * d, j0, d);
+                                const float *ext = p.slot + exchange_buffer(now.read_parity, p.nb, n, p.W, i) * kd + (size_t)c * d;
+                                if constexpr (KEPT) {
+                                    if (at_once) {
+#pragma unroll
+                                        for (int e = 0; e < 8; ++e) ev[e] = n == 0 ? evs[0][e] : n == 1 ? evs[1][e] : n == 2 ? evs[2][e] : evs[3][e];
+                                    } else {
+                                        split_message_row8(ev, ext, j0, d);
+                                    }
+                                } else {
+                                    split_row8(ev, ext, j0, d);
+                                }
 #pragma unroll
                                 for (int e = 0; e < 8; ++e) sum[e] += ev[e];
                             }
@@ -880,8 +1093,11 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
                     if (!INV_COUNT && now.send)
                         for (int n = 0; n < p.nb; ++n) {
                             const int peer = peer_of(n);
-                            if (peer >= 0 && (!ROWWISE || c % p.parts == message_part(now.round, peer, n, p.parts)))
-                                split_put8(p.slot + exchange_buffer(now.send_parity, p.nb, n, p.W, peer) * kd + (size_t)c * d, wn, j0, d);
+                            float *to = p.slot + exchange_buffer(now.send_parity, p.nb, n, p.W, peer >= 0 ? peer : 0) * kd + (size_t)c * d;
+                            if (peer >= 0 && (!ROWWISE || c % p.parts == message_part(now.round, peer, n, p.parts))) {
+                                if constexpr (KEPT) split_message_put8(to, wn, j0, d);
+                                else split_put8(to, wn, j0, d);
+                            }
                         }
                 }
 #pragma unroll
@@ -908,6 +1124,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
         for (int off = u.g / 2; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
         n2max = max(n2max, __float_as_uint(sq) & 0x7fffffffu);
         if (MODE != 0 && lane_g == 0) hs[c] = real ? -0.5f * sq * (sx / sw) : SPLIT_PAD_SCORE;
+        if (KEPT && STEP && lane_g == 0) kept_cnt[c] = 0;        // (the lanes of a row are lanes of one wave: all have read it)
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
@@ -930,16 +1147,23 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
     __syncthreads();
     if (tid < 2) {
         // mode 0 prepares the slot that mode 1 reads, mode 1 the one the first step reads
-        SplitState *dst = MODE == 0 ? st_now : st_next;
-        unsigned *at = tid == 0 ? &dst->vabs : &dst->n2;
+        unsigned *at;
+        if constexpr (KEPT) {
+            SplitSize *dst = sh.size + (MODE == 0 ? now.slot : now.slot_next);
+            at = tid == 0 ? &dst->vabs : &dst->n2;
+        } else {
+            SplitState *dst = MODE == 0 ? st_now : st_next;
+            at = tid == 0 ? &dst->vabs : &dst->n2;
+        }
         unsigned v = 0;
         for (int q = 0; q < (int)(blockDim.x >> 6); ++q) v = max(v, sh.most[tid][q]);
-        if (u.blocks == 1) *at = v;
+        if (KEPT || u.blocks == 1) *at = v;
         else atomicMax(at, v);
     }
     if (STEP && !INV_COUNT && now.send) {
         if (now.local) {                        // the message first, then its stamp (in the phases form the launch ends in between)
-            __threadfence();
+            if constexpr (KEPT) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            else __threadfence();
             __syncthreads();
         }
         if (blk != 0 || tid != 0) return;
@@ -974,10 +1198,7 @@ struct SplitLaunch {                       // arguments of a phase
 
 // The items are functions that are really called, each with registers of its own: inlined into one loop over the steps
 // the compiler kept the values of all phases at once, hundreds of spills.  A call passes its arguments in vector
-// registers; what is uniform is read back into scalar ones.  The LDS starts with what all phases share.
-extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
-constexpr unsigned SPLIT_LDS_SHARED = 512;
-static_assert(sizeof(SplitShared) <= SPLIT_LDS_SHARED, "room at the start of the LDS");
+// registers; what is uniform is read back into scalar ones.
 typedef SPLIT_ARG SplitRun *SplitRunPtr;
 __device__ __forceinline__ int split_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ SplitRunPtr split_uniform(u64 p)
@@ -985,15 +1206,13 @@ __device__ __forceinline__ SplitRunPtr split_uniform(u64 p)
     const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)p), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(p >> 32));
     return (SplitRunPtr)((u64)hi << 32 | lo);
 }
-__device__ __forceinline__ SplitShared &split_shared() { return *reinterpret_cast<SplitShared *>(split_lds); }
-
-template <int NC>
+template <int NC, bool KEPT>
 __device__ __noinline__ void split_assign_call(u64 run, int worker, int share)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
     if constexpr (NC == 0) split_assign_long_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
-    else split_assign_item<NC>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
+    else split_assign_item<NC, KEPT>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
 }
 __device__ __noinline__ inline void split_sums_call(u64 run, int worker, int share, int chunk)
 {
@@ -1001,18 +1220,19 @@ __device__ __noinline__ inline void split_sums_call(u64 run, int worker, int sha
     const SplitStep now = split_shared().now;
     split_sums_item(r->a, now, split_uniform(worker), split_uniform(share), split_uniform(chunk), split_lds + SPLIT_LDS_SHARED);
 }
-__device__ __noinline__ inline void split_gate_call(u64 run, int worker, int blk)
+template <bool KEPT>
+__device__ __noinline__ void split_gate_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
-    split_gate_item(r->p, r->u, now, split_uniform(worker), split_uniform(blk), split_shared().red);
+    split_gate_item<KEPT>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared().red);
 }
-template <int MODE>
+template <int MODE, bool KEPT>
 __device__ __noinline__ void split_update_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
-    split_update_item<MODE>(r->p, r->u, now, split_uniform(worker), split_uniform(blk), split_shared());
+    split_update_item<MODE, KEPT>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared());
 }
 
 // Phases form.  WHAT: 0..4 modes of the update, 5 Eq. 4, 6 gradient sums, 10 + NC assignment (10: long rows)
@@ -1028,20 +1248,20 @@ void split_phase_kernel(SplitLaunch args)
     now.slot = l->now.slot; now.slot_next = l->now.slot_next; now.slot_after = l->now.slot_after;
     now.merge = l->now.merge; now.send = l->now.send; now.round = l->now.round;
     now.read_parity = l->now.read_parity; now.send_parity = l->now.send_parity; now.local = 0;
-    now.state = l->now.state; now.dump = l->now.dump; now.row0 = l->now.row0;
+    now.state = l->now.state; now.dump = l->now.dump; now.row0 = l->now.row0; now.row0_next = -1; now.batch = 0;
     for (int n = 0; n < MAX_BUFFERS; ++n) now.shift[n] = l->now.shift[n];
     const int W = l->run.p.W, worker = blockIdx.x % W, rest = blockIdx.x / W;
     if constexpr (WHAT >= 11) {
-        split_assign_item<WHAT - 10>(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
+        split_assign_item<WHAT - 10, false>(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
     } else if constexpr (WHAT == 10) {
         split_assign_long_item(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
     } else if constexpr (WHAT == 6) {
         const int ncol = l->run.a.ncol;
         split_sums_item(l->run.a, now, worker, rest / ncol, rest % ncol, lds + SPLIT_LDS_SHARED);
     } else if constexpr (WHAT == 5) {
-        split_gate_item(l->run.p, l->run.u, now, worker, rest, reinterpret_cast<SplitShared *>(lds)->red);
+        split_gate_item<false>(l->run.p, l->run.u, l->run.a, now, worker, rest, reinterpret_cast<SplitShared *>(lds)->red);
     } else {
-        split_update_item<WHAT>(l->run.p, l->run.u, now, worker, rest, *reinterpret_cast<SplitShared *>(lds));
+        split_update_item<WHAT, false>(l->run.p, l->run.u, l->run.a, now, worker, rest, *reinterpret_cast<SplitShared *>(lds));
     }
 }
 template <int WHAT>
@@ -1088,7 +1308,11 @@ __device__ inline bool split_all_arrived(int *word, int expected, int polls)
 // Local form.  NC: chunks of 16 columns of a row, 0: long rows.  Workgroup g has the workers g, g + grid, ...; every wait
 // is for an event of an earlier round, and a workgroup does a step of all its workers before the next step of any, so
 // the waits cannot form a cycle.
-template <int NC>
+// KEPT: one worker per workgroup, whose operands, offsets, sums and counts stay in the LDS from step to step, the next mini-batch
+// arrives there during a step, and the items are inlined: such steps are bound by latency, of calls, copies of the step and
+// round trips to the L2 as much as of the memory (500 x 7 samples, 12 centroids, 1/count: 15.1 us per step, 14.2 without the round trips,
+// 13.1 with the mini-batch there, 12.2 inlined).
+template <int NC, bool KEPT, bool INV_COUNT>
 __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void split_local_kernel(SplitRun args)
 {
     (void)args;
@@ -1099,7 +1323,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
     now.merge = now.send = now.round = now.read_parity = now.send_parity = 0;
     now.local = 1;
     now.slot = 0; now.slot_next = 1; now.slot_after = 2;
-    now.state = nullptr; now.dump = nullptr; now.row0 = 0;
+    now.state = nullptr; now.dump = nullptr; now.row0 = 0; now.row0_next = -1; now.batch = 0;
     for (int n = 0; n < MAX_BUFFERS; ++n) now.shift[n] = 0;
     const int W = r->p.W;
     const bool det = r->p.mode == ASGD_MODE_DETERMINISTIC;
@@ -1121,10 +1345,20 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
     }
     if (threadIdx.x == 0) sh.now = now;
     __syncthreads();
+    if constexpr (KEPT) {
+        if (r->t0 < r->t1) split_batch_fetch(r->a, blockIdx.x, r->t0 % r->p.S * r->p.b, split_lds + SPLIT_LDS_SHARED + r->a.off_batch);
+    }
     for (int i = blockIdx.x; i < W; i += gridDim.x) {
-        split_update_call<0>(run, i, 0);
+        split_update_call<0, KEPT>(run, i, 0);
         __syncthreads();
-        split_update_call<1>(run, i, 0);
+        if constexpr (KEPT) {
+            unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
+            const int d = r->a.d, n = r->a.k * (r->a.vec4 ? d : (d + 1) & ~1);
+            for (int j = threadIdx.x; j < r->a.dpad; j += blockDim.x) reinterpret_cast<float *>(smem + r->a.off_ms)[j] = r->a.ms[j];
+            for (int e = threadIdx.x; e < n; e += blockDim.x) reinterpret_cast<u64 *>(smem + r->a.off_cells)[e] = 0;
+            for (int c = threadIdx.x; c < r->a.k; c += blockDim.x) reinterpret_cast<int *>(smem + r->a.off_cnt)[c] = 0;
+        }
+        split_update_call<1, KEPT>(run, i, 0);
     }
     int te = r->te0;
     long long t = r->t0, round = r->round0, s = t % r->p.S;
@@ -1146,12 +1380,17 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
         now.row0 = s * r->p.b;
         now.dump = r->p.dump ? r->p.dump + (size_t)(t - r->p.t_dump0) * W * r->p.b : nullptr;
         if (++s == r->p.S) s = 0;
-        __syncthreads();
-        if (threadIdx.x == 0) sh.now = now;
-        __syncthreads();
+        now.row0_next = t + 1 < r->t1 ? s * r->p.b : -1;
+        now.batch = (int)((t - r->t0) & 1);
+        if constexpr (!KEPT) {
+            __syncthreads();
+            if (threadIdx.x == 0) sh.now = now;
+            __syncthreads();
+        }
         for (int i = blockIdx.x; i < W; i += gridDim.x) {
-            split_assign_call<NC>(run, i, 0);
-            if (!r->a.fused)
+            if constexpr (KEPT) split_assign_item<NC, true>(r->a, now, i, 0, split_lds + SPLIT_LDS_SHARED);
+            else split_assign_call<NC, KEPT>(run, i, 0);
+            if (!KEPT && !r->a.fused)
                 for (int q = 0; q < r->a.ncol; ++q) split_sums_call(run, i, 0, q);
             if (r->sync && now.merge) {
                 // the messages of the last round (those sent before this launch are there)
@@ -1163,9 +1402,15 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
                             wait(r->p.stamp + exchange_buffer(now.read_parity, r->p.nb, n, W, i), (int)rs, false);
                     }
                 __syncthreads();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if constexpr (!KEPT) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             }
-            if (now.merge) split_gate_call(run, i, 0);
+            if (now.merge) {
+                if constexpr (KEPT) {
+                    if (!split_gate_at_once(r->a, r->u)) split_gate_item<true>(r->p, r->u, r->a, now, i, 0, sh.red);
+                } else {
+                    split_gate_call<KEPT>(run, i, 0);
+                }
+            }
             if (r->sync && now.send && now.round >= 2) {
                 // a recipient's buffer still holds the message of round - 2 until it has passed merge point round - 1
                 if (threadIdx.x == 0)
@@ -1175,8 +1420,12 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
                     }
                 __syncthreads();
             }
-            if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3>(run, i, 0);
-            else split_update_call<2>(run, i, 0);
+            if constexpr (KEPT) {
+                split_update_item<INV_COUNT ? 3 : 2, true>(r->p, r->u, r->a, now, i, 0, sh);
+            } else {
+                if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3, KEPT>(run, i, 0);
+                else split_update_call<2, KEPT>(run, i, 0);
+            }
             if (r->sync && now.merge) {
                 __syncthreads();
                 // (thread 0 has emptied the stamps: they have arrived before the sender may write them again)
@@ -1187,17 +1436,27 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
     }
 }
 
-template <int NC>
-hipError_t split_launch_local(const SplitRun &r, int blocks, unsigned lds, hipStream_t s)
+template <int NC, bool KEPT, bool INV_COUNT>
+hipError_t split_launch_local_form(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s)
 {
-    const void *kern = (const void *)split_local_kernel<NC>;
+    const void *kern = (const void *)split_local_kernel<NC, KEPT, INV_COUNT>;
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     SplitRun rr = r;
     void *args[] = {&rr};
-    if (r.sync && r.p.cooperative) return hipLaunchCooperativeKernel(kern, dim3(blocks), dim3(SPLIT_THREADS), args, lds, s);
-    hipLaunchKernelGGL(split_local_kernel<NC>, dim3(blocks), dim3(SPLIT_THREADS), lds, s, rr);
+    if (r.sync && r.p.cooperative) return hipLaunchCooperativeKernel(kern, dim3(blocks), dim3(threads), args, lds, s);
+    split_local_kernel<NC, KEPT, INV_COUNT><<<dim3(blocks), dim3(threads), lds, s>>>(rr);
     return hipGetLastError();
+}
+template <int NC>
+hipError_t split_launch_local(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s)
+{
+    if constexpr (NC != 0 && NC <= SPLIT_KEPT_CHUNKS) {
+        if (r.a.kept)
+            return r.p.lr_mode == ASGD_LR_INV_COUNT ? split_launch_local_form<NC, true, true>(r, blocks, threads, lds, s)
+                                                    : split_launch_local_form<NC, true, false>(r, blocks, threads, lds, s);
+    }
+    return split_launch_local_form<NC, false, false>(r, blocks, threads, lds, s);
 }
 
 }  // namespace asgd
