@@ -39,7 +39,8 @@ struct asgd_ctx {
     long long seen = 0;            // streaming kernel: it has looked at the mini-batches [0, seen) (flag_host[3]: and met an element
                                    // beyond the limits it forms of xsample)
     bool xabsmax_valid = false;    // xabsmax and flag_host[1], [2] are those of the loaded samples
-    float *xsample = nullptr;      // streaming kernel only: column maxima over a part of the samples, and scratch
+    float *xsample = nullptr;      // streaming kernel only: column maxima over a part of the samples, and scratch (behind qpart)
+    bool xsample_clear = false;    // its counter of workgroups is zero
     float *xnorm2max = nullptr;    // matrix-core kernel only, allocated on first use
     size_t slot_bytes = 0;         // size of the exchange buffers (both parities, all workers)
     int *shift_tab = nullptr;      // schedule table of the small-state kernel, grown on demand
@@ -100,7 +101,7 @@ size_t kd_of(const asgd_ctx *c) { return (size_t)c->k * c->d; }
 void free_all(asgd_ctx *c)
 {
     void *ptrs[] = {c->w, c->slot, c->acc, c->xabsmax, c->mean, c->stamp, c->consumed, c->cnt, c->assign_tmp,
-                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->split_data, c->load_scratch, c->xsample};
+                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->split_data, c->load_scratch};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (c->flag_host) (void)hipHostFree(c->flag_host);
@@ -358,6 +359,7 @@ int asgd_create(asgd_ctx **out, int k, int d, int W, int b, float lr)
         c->slot_bytes_one = exchange_buffers_total(1, W) * (plain > own ? plain : own);
         c->slot_bytes = c->slot_bytes_one;
     }
+    const bool small = small_kernel_supports(k, d, b);
     struct { void **p; size_t bytes; } allocs[] = {
         {(void **)&c->w, Wz * kd * sizeof(float)},
         {(void **)&c->slot, c->slot_bytes},
@@ -370,18 +372,14 @@ int asgd_create(asgd_ctx **out, int k, int d, int W, int b, float lr)
         {(void **)&c->assign_tmp, Wz * (size_t)b * sizeof(int)},
         {(void **)&c->ncum, Wz * k * sizeof(long long)},
         {(void **)&c->counters, Wz * CNT_STRIDE * sizeof(long long)},
-        {(void **)&c->qpart, (size_t)quant_partials_count() * sizeof(double)},
+        {(void **)&c->qpart, (size_t)quant_partials_count() * sizeof(double) + (small ? sample_scratch_bytes(d) : 0)},
         {(void **)&c->qout, sizeof(double)},
     };
     for (auto &a : allocs) {
         e = hipMalloc(a.p, a.bytes);
         if (e != hipSuccess) { fail(e); break; }
     }
-    if (rc == ASGD_OK && small_kernel_supports(k, d, b)) {
-        e = hipMalloc((void **)&c->xsample, sample_scratch_bytes(d));
-        if (e == hipSuccess) e = hipMemset(c->xsample, 0, sample_scratch_bytes(d));
-        if (e != hipSuccess) fail(e);
-    }
+    if (rc == ASGD_OK && small) c->xsample = reinterpret_cast<float *>(c->qpart + quant_partials_count());
     if (rc == ASGD_OK && (e = hipHostMalloc((void **)&c->flag_host, 4 * sizeof(int), hipHostMallocDefault)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev0)) != hipSuccess) fail(e);
     if (rc == ASGD_OK && (e = hipEventCreate(&c->ev1)) != hipSuccess) fail(e);
@@ -520,6 +518,10 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     if (small_kernel_supports(ctx->k, ctx->d, ctx->b)) {             // (the other kernels look at the stamps first)
         l.slot = reinterpret_cast<unsigned *>(ctx->slot);
         l.slot_words = ctx->slot_bytes / sizeof(unsigned);
+    }
+    if (ctx->xsample && !ctx->xsample_clear) {
+        HIP_TRY(ctx, hipMemsetAsync(ctx->xsample, 0, sample_scratch_bytes(ctx->d), ctx->stream));
+        ctx->xsample_clear = true;
     }
     HIP_TRY(ctx, launch_load(l, ctx->xsample, ctx->stream));
     ctx->fill_kernel = 0;
