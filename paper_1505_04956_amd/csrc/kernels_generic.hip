@@ -62,7 +62,7 @@ __device__ __forceinline__ double gen_wave_sum(double v)
 // the counters, and, for the streaming kernel, column maxima over a part of the samples.
 constexpr int LOAD_BLOCKS = 1024;
 // Maxima over a part: pieces of 16 sweeps of a workgroup, a thread always in one column (d <= 16).  All of them up to
-// 4096 pieces (64 MB), then evenly spread ones, 1 in 128 at the least; whoever uses the maxima looks out for elements
+// 8191 pieces (128 MB), then 4096 and more evenly spread ones, 1 in 128 at the least; whoever uses the maxima looks out for elements
 // beyond them.  (All samples of N = 1e8, d = 10: 675 us, as long as an epoch over them.)
 __host__ __device__ inline long long sample_pieces(long long total, int d)
 {
