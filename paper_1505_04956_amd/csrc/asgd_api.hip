@@ -6,6 +6,7 @@
 #include <vector>
 
 #include "asgd_internal.h"
+#include "launch_cuts.h"
 
 using namespace asgd;
 
@@ -79,9 +80,6 @@ struct asgd_ctx {
 };
 
 namespace {
-
-// rounds one launch with in-kernel waits covers at most (a longer call becomes several such launches)
-constexpr long long ONE_LAUNCH_MAX_ROUNDS = 1024;
 
 // device memory the step kernels with fp16-split operands may take besides the context's own (a state's operands are
 // padded to 64 rows and 16 columns, which for a great many tiny states is a multiple of their size)
@@ -784,12 +782,9 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     // device), or a launch never crosses a multiple of E, so that the message was written by an
     // earlier launch on the same stream.
     const bool rounds = (ctx->mode == ASGD_MODE_DETERMINISTIC && ctx->E > 0 && ctx->W > 1);
-    // The streaming kernel looks out for elements beyond its limits in the first epoch after loading (6 % of the time of an epoch;
-    // looking at all samples while loading took as long as an epoch).  A call that begins with that epoch and goes on for more
-    // than sixteen is cut after it.
     auto first_epoch_end = [&](long long from) -> long long {        // step at which a launch from `from` on is cut, or t_end
-        if (kernel != ASGD_KERNEL_SMALL || p.within_limits || from > ctx->seen || from >= ctx->S || t_end - from <= 16 * ctx->S) return t_end;
-        return rounds ? (ctx->S + ctx->E - 1) / ctx->E * ctx->E : ctx->S;
+        if (kernel != ASGD_KERNEL_SMALL || p.within_limits || from > ctx->seen || from >= ctx->S) return t_end;
+        return first_epoch_cut(t_end, ctx->S, rounds ? ctx->E : 0);
     };
     auto looked_at = [&](long long from, long long to) -> int {       // steps [from, to) have been launched
         if (kernel != ASGD_KERNEL_SMALL || from > ctx->seen) return ASGD_OK;
@@ -815,13 +810,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         // (a one-launch run leaves exactly these values behind: no need to write them again for the run that follows it)
         if (ctx->passed_t != ctx->t)
             HIP_TRY(ctx, hipMemsetD32Async((hipDeviceptr_t)ctx->consumed, passed, (size_t)ctx->W, ctx->stream));
-        // A launch covers at most ONE_LAUNCH_MAX_ROUNDS rounds and ends on a round boundary: the waits of a workgroup
-        // draw on one budget of polls per launch, which the short waits of a healthy run must not use up however long
-        // the call is.
         while (t_done < t_end) {
-            long long tb = (t_done / ctx->E + ONE_LAUNCH_MAX_ROUNDS) * (long long)ctx->E;
-            const long long cut = first_epoch_end(t_done);
-            if (tb > cut) tb = cut;
+            const long long cut = first_epoch_end(t_done), tb = one_launch_end(t_done, t_end, cut, ctx->E);
             int one = 0;
             hipError_t e = ctx->refuse_one_launch == 1 ? hipErrorCooperativeLaunchTooLarge
                            : split_local ? launch_split_steps(p, t_done, tb, ctx->split_data, ctx->split_scratch, ctx->stream, &one)

@@ -92,3 +92,26 @@ def test_later_epochs_give_the_same_bits(B, samples, W, b, beyond):
     many.run_steps(18 * S + 3)
     assert np.array_equal(one.get_state(), many.get_state())
     assert many.stats().launches <= 2 + (18 * S + 3) // 2 // 1024
+
+
+# a call of more than sixteen epochs that is shorter than a round: it ends with its own last step, not with the round
+@pytest.mark.parametrize("E", [49, 100, 2000])
+def test_a_call_ends_before_its_round(B, samples, E):
+    import torch
+    W, b, steps, guard = 4, 283_333, 51, 4096             # three steps an epoch
+    whole, cut = (load(B, samples, W=W, b=b, E=E) for _ in range(2))
+    assert whole.S == 3
+    size = steps * W * b
+    dumps = [torch.full((size + guard,), -7, dtype=torch.int32, device="cuda:0") for _ in range(2)]
+    B.asgd_set_assign_dump(whole.h, dumps[0].data_ptr(), size)
+    whole.run_steps(steps)
+    done = 0
+    for n in (1, 2, 30, 18):
+        B.asgd_set_assign_dump(cut.h, dumps[1].data_ptr() + 4 * done * W * b, n * W * b)
+        cut.run_steps(n)
+        done += n
+    assert done == steps and whole.stats().steps == steps and whole.stats().samples == steps * W * b
+    assert np.array_equal(whole.get_state(), cut.get_state())
+    assert np.array_equal(whole.worker_counters(), cut.worker_counters())
+    assert whole.worker_counters()[:, 0].tolist() == [steps // E] * W
+    assert torch.equal(dumps[0], dumps[1]) and bool((dumps[0][size:] == -7).all()) and bool((dumps[0][:size] >= 0).all())
