@@ -6,6 +6,7 @@
 // pass in which every centroid row is owned by exactly one wavefront, so that all sums are
 // formed in a fixed order and a run is reproducible bit for bit.
 #include "asgd_internal.h"
+#include "sample_index.h"
 
 namespace asgd {
 
@@ -61,32 +62,18 @@ __device__ __forceinline__ double gen_wave_sum(double v)
 // starts from the first k rows of its own shard), the exchange buffers emptied (all bits set; slot_words 0: left alone),
 // the counters, and, for the streaming kernel, column maxima over a part of the samples.
 constexpr int LOAD_BLOCKS = 1024;
-// Maxima over a part: pieces of 16 sweeps of a workgroup, a thread always in one column (d <= 16).  All of them up to
-// 8191 pieces (128 MB), then 4096 and more evenly spread ones, 1 in 128 at the least; whoever uses the maxima looks out for elements
-// beyond them.  (All samples of N = 1e8, d = 10: 675 us, as long as an epoch over them.)
-__host__ __device__ inline long long sample_pieces(long long total, int d)
-{
-    const long long piece = 16LL * (256 - 256 % d);
-    return (total + piece - 1) / piece;
-}
-__host__ __device__ inline long long sample_every(long long pieces)
-{
-    const long long n = pieces / 4096;
-    return n < 1 ? 1 : n > 128 ? 128 : n;
-}
 __device__ void sample_columns(const LoadParams &l, float *red)
 {
-    const int d = l.d, T = 256 - 256 % d, t = threadIdx.x;
-    const long long total = l.H * l.W * d, piece = 16LL * T, pieces = sample_pieces(total, d), every = sample_every(pieces);
+    const int d = l.d, T = sample_threads(d), t = threadIdx.x;
+    const long long total = l.H * l.W * d, pieces = sample_pieces(total, d), every = sample_every(pieces);
     float m = 0.0f;
     if (t < T)
         for (long long q = (long long)blockIdx.x * every; q < pieces; q += (long long)LOAD_BLOCKS * every) {
-            const long long e = q * piece + t;
-            float v[16];
+            float v[SAMPLE_SWEEPS];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) v[u] = l.x[e + u * T < total ? e + u * T : t];
+            for (int u = 0; u < SAMPLE_SWEEPS; ++u) v[u] = l.x[sample_element(q, u, t, total, d)];
 #pragma unroll
-            for (int u = 0; u < 16; ++u) m = fmaxf(m, fabsf(v[u]));
+            for (int u = 0; u < SAMPLE_SWEEPS; ++u) m = fmaxf(m, fabsf(v[u]));
         }
     red[t] = t < T ? m : 0.0f;
     __syncthreads();
@@ -134,7 +121,7 @@ __global__ __launch_bounds__(256) void load_kernel(LoadParams l)
     if (threadIdx.x == 0) last = __hip_atomic_fetch_add(l.arrived, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == LOAD_BLOCKS - 1;
     __syncthreads();
     if (!last) return;
-    const int T = 256 - 256 % l.d, t = threadIdx.x;
+    const int T = sample_threads(l.d), t = threadIdx.x;
     float m = 0.0f;
     if (t < T)
         for (int q0 = t; q0 < LOAD_BLOCKS * l.d; q0 += 16 * T) {

@@ -115,3 +115,24 @@ def test_a_call_ends_before_its_round(B, samples, E):
     assert np.array_equal(whole.worker_counters(), cut.worker_counters())
     assert whole.worker_counters()[:, 0].tolist() == [steps // E] * W
     assert torch.equal(dumps[0], dumps[1]) and bool((dumps[0][size:] == -7).all()) and bool((dumps[0][:size] >= 0).all())
+
+
+# fewer samples than a workgroup looks at in one sweep, with other values behind them: those are not looked at.  (Silent mode: states
+# that are the first samples themselves have a zero gradient in the first steps, both sides of Eq. 4 are the same then.)
+@pytest.mark.parametrize("behind", [1e30, np.inf, 3e4])
+@pytest.mark.parametrize("k,d,W,H,b", [(10, 10, 1, 10, 10), (10, 10, 2, 12, 5), (4, 4, 4, 4, 3), (4, 4, 1, 40, 7), (8, 8, 3, 9, 4), (8, 16, 1, 15, 6),
+                                       (16, 8, 1, 16, 16), (16, 12, 1, 20, 9)])
+def test_values_behind_small_data(B, oracle, k, d, W, H, b, behind):
+    import torch
+    rng = np.random.default_rng(k * d + H)
+    X = rng.uniform(0.0, 10.0, (W * H, d)).astype(np.float32)
+    more = torch.full((W * H + 64, d), behind, dtype=torch.float32, device="cuda:0")
+    more[:W * H] = torch.from_numpy(X).to("cuda:0")
+    g = B.ASGD(k, d, W, b, 0.05, kernel=2)
+    g.load_shards(more[:W * H])
+    o = oracle.OracleASGD(X, k=k, W=W, b=b, lr=0.05, E=0, seed=1)
+    g.run_steps(7)
+    o.run_steps(7)
+    # 1e-6: sums of b < 2^5 terms that are good to 2^-22 of a column's largest element
+    err = rel_fro(g.get_state().astype(np.float64), np.asarray(o.w)).max()
+    assert err <= 1e-6
