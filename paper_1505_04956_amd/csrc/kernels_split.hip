@@ -38,8 +38,6 @@ hipError_t launch_split_assign_8(const SplitLaunch &l, int blocks, int threads, 
 namespace {
 
 constexpr int SPLIT_SAMPLE_ROWS = 1024;     // rows looked at for the middle of the data
-constexpr unsigned SPLIT_LDS = 150 * 1024;
-constexpr int SPLIT_CUS = 256;
 
 // ---- once per set of samples: middle of the data, scale of the samples, scales of the fixed-point sums ----
 // m_j: mean of up to SPLIT_SAMPLE_ROWS rows spread over the data (any value is a valid reference; one near the middle
@@ -103,121 +101,6 @@ bool split_kernel_supports(int k, int d, int b) { return k >= 2 && k <= 7680 && 
 
 namespace {
 
-struct SplitPlan {
-    int nch, dpad, nblk, kpad, npair;
-    size_t frag_bytes;
-    bool longrow, fused, resident, kept;
-    int waves, shares, share_len, grid;
-    unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes, lds;
-    int dc, ncol, sum_shares, sum_len;      // sums in a launch of their own: columns per workgroup, shares
-    unsigned lds_sums;
-    int g, upd_blocks;             // update: lanes per row, workgroups per worker
-};
-
-int padded_row(int d) { return d > 128 ? (d + 127) / 128 * 128 : (d + 15) / 16 * 16; }
-unsigned round16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
-
-SplitPlan make_plan(const StepParams &p, bool local)
-{
-    SplitPlan q;
-    memset(&q, 0, sizeof(q));
-    q.longrow = p.d > 128;
-    q.dpad = padded_row(p.d);
-    q.nch = q.dpad / 16;
-    q.nblk = (p.k + 31) / 32;
-    q.npair = (q.nblk + 1) / 2;
-    q.kpad = q.npair * 64;
-    q.frag_bytes = (size_t)q.npair * q.nch * 4 * SPLIT_PIECE;
-    const size_t cells = (size_t)p.k * ((p.d + 1) & ~1) * sizeof(u64) + (size_t)p.k * sizeof(int);
-    const size_t fixed = (size_t)q.kpad * 4 + (size_t)q.dpad * 4 + 8 * 64 * 4 + 64;
-    const size_t stage2 = q.longrow ? 0 : (size_t)2 * q.nch * 4 * SPLIT_PIECE;
-    if (q.longrow) {
-        q.resident = q.fused = false;
-    } else if (q.frag_bytes + cells + fixed <= SPLIT_LDS) {
-        q.resident = q.fused = true;
-    } else if (stage2 + cells + fixed <= SPLIT_LDS) {
-        q.resident = false;
-        q.fused = true;
-    } else {
-        q.fused = false;
-        q.resident = q.frag_bytes + fixed <= SPLIT_LDS;
-    }
-    unsigned o = round16(q.resident ? q.frag_bytes : stage2);
-    q.off_cells = o;
-    if (q.fused) o += round16((size_t)p.k * ((p.d + 1) & ~1) * sizeof(u64));
-    q.off_cnt = o;
-    if (q.fused) o += round16((size_t)p.k * sizeof(int));
-    q.off_hs = o;  o += round16((size_t)q.kpad * 4);
-    q.off_ms = o;  o += round16((size_t)q.dpad * 4);
-    q.off_args = o; o += 8 * 64 * 4 * (q.longrow ? 5 : 1);
-    // (two mini-batches of a kept worker: the next one arrives while the current one is worked on)
-    q.batch_bytes = (unsigned)(((size_t)(p.b < 16384 ? p.b : 16384) * p.d * 4 + 1023) / 1024 * 1024);
-    q.kept = local && q.fused && q.resident && q.nch <= SPLIT_KEPT_CHUNKS && p.W <= SPLIT_CUS && p.b <= 16384 && (size_t)o + 2 * (size_t)q.batch_bytes + SPLIT_LDS_SHARED <= 160 * 1024;
-    o = (o + 1023) / 1024 * 1024;
-    q.off_batch = o;
-    if (q.kept) o += 2 * q.batch_bytes;
-    q.lds = o;
-    // Phases: waves of a workgroup and shares of a mini-batch - enough workgroups for the compute units first, then as many
-    // waves per workgroup as share the staged operands, and as many workgroups as are resident at once (three waves per
-    // SIMD up to 32 columns, two above).
-    const int groups = (p.b + 63) / 64;
-    q.waves = 8;
-    q.shares = 1;
-    if (q.longrow) {
-        // (the waves of a workgroup share the row pairs of its groups of samples, see split_assign_long_item)
-        int rsplit = 1;
-        while (2 * rsplit <= q.npair && 2 * rsplit <= 8) rsplit *= 2;
-        const int max_shares = (groups + 8 / rsplit - 1) / (8 / rsplit);
-        if (!local) q.shares = (2 * SPLIT_CUS + p.W - 1) / p.W;
-        if (q.shares > max_shares) q.shares = max_shares;
-        if (q.shares > 64) q.shares = 64;
-    } else if (!local) {
-        int nw = q.lds <= 50 * 1024 ? 4 : 8;
-        // (with one workgroup per compute unit a second round must not begin)
-        const int fill = q.lds > 78 * 1024 ? SPLIT_CUS * 3 / 8 : SPLIT_CUS;
-        while (nw > 1 && (long long)p.W * ((groups + nw - 1) / nw) < fill) nw /= 2;
-        q.waves = nw;
-        const int max_shares = (groups + nw - 1) / nw;
-        const int want = SPLIT_CUS * (q.nch <= 2 && q.lds <= 50 * 1024 ? 12 : 8) / nw;
-        q.shares = (want + p.W - 1) / p.W;
-        if (q.shares > max_shares) q.shares = max_shares;
-        if (q.shares > 64) q.shares = 64;
-    }
-    q.share_len = (groups + q.shares - 1) / q.shares * 64;
-    q.shares = (p.b + q.share_len - 1) / q.share_len;
-    if (!q.fused) {
-        auto bytes = [&](int dc) { return (size_t)p.k * ((dc + 1) * 8 + 4); };
-        int dc = 64;
-        while (dc > 8 && bytes(dc) > 72 * 1024) dc /= 2;
-        if (dc < 16 && bytes(16) <= SPLIT_LDS) dc = 16;         // (rows in pieces of 64 bytes, even with one workgroup per compute unit)
-        while (dc > 1 && bytes(dc) > SPLIT_LDS) dc /= 2;
-        q.dc = dc;
-        q.ncol = (p.d + dc - 1) / dc;
-        q.lds_sums = round16(bytes(dc));
-        // (every share writes and the update reads the sums of a whole state: no more than fill the device)
-        int ss = local ? 1 : 2 * SPLIT_CUS / (p.W * q.ncol);
-        if (ss > groups / 8) ss = groups / 8;
-        if (ss < 1) ss = 1;
-        q.sum_len = (groups + ss - 1) / ss * 64;
-        q.sum_shares = (p.b + q.sum_len - 1) / q.sum_len;
-    } else {
-        q.sum_shares = q.shares;
-        q.sum_len = q.share_len;
-    }
-    int g = 1;
-    while (g < q.dpad / 8 && g < 64) g *= 2;
-    q.g = g;
-    // workgroups of the update per worker (256 threads): enough for four on every compute unit, as long as each has rows to do
-    q.upd_blocks = local ? 1 : (4 * SPLIT_CUS + p.W - 1) / p.W;
-    const int row_groups = (p.k + 256 / g - 1) / (256 / g);
-    if (q.upd_blocks > row_groups) q.upd_blocks = row_groups;
-    q.grid = p.W < SPLIT_CUS ? p.W : SPLIT_CUS;
-    if (local && !q.fused && q.lds < q.lds_sums) q.lds = q.lds_sums;
-    q.lds_sums += SPLIT_LDS_SHARED;
-    q.lds += SPLIT_LDS_SHARED;
-    return q;
-}
-
 // What depends on the samples only, computed once after they are loaded.
 struct Data { size_t m, ms, xmeta, colscale, bytes; };
 Data data_layout(int d)
@@ -226,7 +109,7 @@ Data data_layout(int d)
     size_t o = 0;
     auto take = [&](size_t bytes) { const size_t at = o; o += (bytes + 255) / 256 * 256; return at; };
     s.m = take((size_t)d * 4);
-    s.ms = take((size_t)padded_row(d) * 4);
+    s.ms = take((size_t)split_padded_row(d) * 4);
     s.xmeta = take(16);
     s.colscale = take((size_t)d * 16);
     s.bytes = o;
@@ -261,7 +144,7 @@ Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
 // (Where they do not fill the device, phases cut their mini-batches: k = 12, d = 7, b = 2000, W = 32 24.9, 29.6.)
 static bool split_kept(const StepParams &p)
 {
-    return p.parts == 1 && !p.phases_only && 4LL * p.W >= 3LL * SPLIT_CUS && make_plan(p, true).kept;
+    return p.parts == 1 && !p.phases_only && 4LL * p.W >= 3LL * SPLIT_CUS && split_plan(p.k, p.d, p.b, p.W, true).kept;
 }
 
 // Local form: kept workers, or workers that fill the device, one workgroup of eight waves each
@@ -280,7 +163,7 @@ bool split_local_form(const StepParams &p)
     return split_kept(p) || (4LL * p.W >= 3LL * rounds * SPLIT_CUS && (rounds == 1 || p.one_launch) && (!exchange || p.E >= 4));
 }
 
-size_t split_scratch_bytes(const StepParams &p) { return scratch_layout(p, make_plan(p, split_local_form(p))).bytes; }
+size_t split_scratch_bytes(const StepParams &p) { return scratch_layout(p, split_plan(p.k, p.d, p.b, p.W, split_local_form(p))).bytes; }
 
 size_t split_data_bytes(int d) { return data_layout(d).bytes; }
 
@@ -289,7 +172,7 @@ hipError_t launch_split_data(const StepParams &p, void *data, hipStream_t s)
     const Data l = data_layout(p.d);
     unsigned char *base = static_cast<unsigned char *>(data);
     hipLaunchKernelGGL(split_middle_kernel, dim3((p.d + 63) / 64), dim3(1024), 0, s, p.x, p.H * p.W, p.d, (float *)(base + l.m));
-    hipLaunchKernelGGL(split_scales_kernel, dim3(1), dim3(256), 0, s, p.xabsmax, (float *)(base + l.m), p.d, padded_row(p.d), p.b,
+    hipLaunchKernelGGL(split_scales_kernel, dim3(1), dim3(256), 0, s, p.xabsmax, (float *)(base + l.m), p.d, split_padded_row(p.d), p.b,
                        (float *)(base + l.ms), (float *)(base + l.xmeta), (double *)(base + l.colscale));
     return hipGetLastError();
 }
@@ -297,7 +180,7 @@ hipError_t launch_split_data(const StepParams &p, void *data, hipStream_t s)
 hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, const void *data, void *scratch, hipStream_t s, int *launches)
 {
     const bool local = split_local_form(p);
-    const SplitPlan q = make_plan(p, local);
+    const SplitPlan q = split_plan(p.k, p.d, p.b, p.W, local);
     const Scratch l = scratch_layout(p, q);
     unsigned char *base = static_cast<unsigned char *>(scratch);
     SplitArgs a;
@@ -424,8 +307,8 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
     const size_t all = (size_t)npair * chunks * 4 * SPLIT_PIECE, two = (size_t)2 * chunks * 4 * SPLIT_PIECE;
     a.resident = d <= 128 && all + (size_t)(a.kpad + a.dpad) * 4 <= SPLIT_LDS;
     unsigned o = (unsigned)(a.resident ? all : two);
-    a.off_hs = o; o += round16((size_t)a.kpad * 4);
-    a.off_m = o;  o += round16((size_t)a.dpad * 4);
+    a.off_hs = o; o += split_round16((size_t)a.kpad * 4);
+    a.off_m = o;  o += split_round16((size_t)a.dpad * 4);
     switch (d > 128 ? 0 : chunks) {
         case 0: return launch_split_quant_0(a, nblocks, o, s);
         case 1: return launch_split_quant_1(a, nblocks, o, s);

@@ -21,6 +21,7 @@
 #include <type_traits>
 
 #include "asgd_internal.h"
+#include "split_plan.h"
 
 namespace asgd {
 
@@ -31,7 +32,6 @@ typedef float sfloatx16 __attribute__((ext_vector_type(16)));
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));      // rows of any length: 4-byte aligned
 typedef unsigned long long u64;
 
-constexpr int SPLIT_PIECE = 1024;                 // bytes of 32 rows x 16 columns of one part
 constexpr float SPLIT_PAD_SCORE = -1.0e30f;       // offset of the padding rows: never the nearest
 constexpr float SPLIT_ULP_PER_MFMA = 6.0f;
 

@@ -1,0 +1,130 @@
+// Step kernels with fp16-split operands: what lies where in the LDS of a workgroup, how a mini-batch is cut into shares, and when a
+// worker is kept in the LDS from step to step.  The launcher and a host-only check (tests/host/check_split_plan.cpp) use it.  Plain
+// C++, no HIP types.
+#pragma once
+
+#include <stddef.h>
+
+namespace asgd {
+
+constexpr int SPLIT_PIECE = 1024;                 // bytes of 32 rows x 16 columns of one part
+constexpr unsigned SPLIT_LDS_SHARED = 512;        // what all phases share, before everything else
+constexpr unsigned SPLIT_LDS_ALL = 160 * 1024;    // LDS of a compute unit
+constexpr unsigned SPLIT_LDS = 150 * 1024;        // what operands and cells may take of it
+constexpr int SPLIT_CUS = 256;
+constexpr int SPLIT_KEPT_CHUNKS = 4;              // longest rows of a kept worker: beyond, its kernel needs more registers than there are
+
+struct SplitPlan {
+    int nch, dpad, nblk, kpad, npair;
+    size_t frag_bytes;
+    bool longrow, fused, resident, kept;
+    int waves, shares, share_len, grid;
+    unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes, lds;
+    int dc, ncol, sum_shares, sum_len;      // sums in a launch of their own: columns per workgroup, shares
+    unsigned lds_sums;
+    int g, upd_blocks;             // update: lanes per row, workgroups per worker
+};
+
+inline int split_padded_row(int d) { return d > 128 ? (d + 127) / 128 * 128 : (d + 15) / 16 * 16; }
+inline unsigned split_round16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
+
+inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
+{
+    SplitPlan q = {};
+    q.longrow = d > 128;
+    q.dpad = split_padded_row(d);
+    q.nch = q.dpad / 16;
+    q.nblk = (k + 31) / 32;
+    q.npair = (q.nblk + 1) / 2;
+    q.kpad = q.npair * 64;
+    q.frag_bytes = (size_t)q.npair * q.nch * 4 * SPLIT_PIECE;
+    const size_t cells = (size_t)k * ((d + 1) & ~1) * 8 + (size_t)k * 4;
+    const size_t fixed = (size_t)q.kpad * 4 + (size_t)q.dpad * 4 + 8 * 64 * 4 + 64;
+    const size_t stage2 = q.longrow ? 0 : (size_t)2 * q.nch * 4 * SPLIT_PIECE;
+    if (q.longrow) {
+        q.resident = q.fused = false;
+    } else if (q.frag_bytes + cells + fixed <= SPLIT_LDS) {
+        q.resident = q.fused = true;
+    } else if (stage2 + cells + fixed <= SPLIT_LDS) {
+        q.resident = false;
+        q.fused = true;
+    } else {
+        q.fused = false;
+        q.resident = q.frag_bytes + fixed <= SPLIT_LDS;
+    }
+    unsigned o = split_round16(q.resident ? q.frag_bytes : stage2);
+    q.off_cells = o;
+    if (q.fused) o += split_round16((size_t)k * ((d + 1) & ~1) * 8);
+    q.off_cnt = o;
+    if (q.fused) o += split_round16((size_t)k * 4);
+    q.off_hs = o;  o += split_round16((size_t)q.kpad * 4);
+    q.off_ms = o;  o += split_round16((size_t)q.dpad * 4);
+    q.off_args = o; o += 8 * 64 * 4 * (q.longrow ? 5 : 1);
+    // (two mini-batches of a kept worker: the next one arrives while the current one is worked on; a fetch writes whole KBs)
+    q.batch_bytes = (unsigned)(((size_t)(b < 16384 ? b : 16384) * d * 4 + 1023) / 1024 * 1024);
+    q.kept = local && q.fused && q.resident && q.nch <= SPLIT_KEPT_CHUNKS && W <= SPLIT_CUS && b <= 16384 && (size_t)o + 2 * (size_t)q.batch_bytes + SPLIT_LDS_SHARED <= SPLIT_LDS_ALL;
+    q.off_batch = o;
+    if (q.kept) o += 2 * q.batch_bytes;
+    q.lds = o;
+    // Phases: waves of a workgroup and shares of a mini-batch - enough workgroups for the compute units first, then as many
+    // waves per workgroup as share the staged operands, and as many workgroups as are resident at once (three waves per
+    // SIMD up to 32 columns, two above).
+    const int groups = (b + 63) / 64;
+    q.waves = 8;
+    q.shares = 1;
+    if (q.longrow) {
+        // (the waves of a workgroup share the row pairs of its groups of samples, see split_assign_long_item)
+        int rsplit = 1;
+        while (2 * rsplit <= q.npair && 2 * rsplit <= 8) rsplit *= 2;
+        const int max_shares = (groups + 8 / rsplit - 1) / (8 / rsplit);
+        if (!local) q.shares = (2 * SPLIT_CUS + W - 1) / W;
+        if (q.shares > max_shares) q.shares = max_shares;
+        if (q.shares > 64) q.shares = 64;
+    } else if (!local) {
+        int nw = q.lds <= 50 * 1024 ? 4 : 8;
+        // (with one workgroup per compute unit a second round must not begin)
+        const int fill = q.lds > 78 * 1024 ? SPLIT_CUS * 3 / 8 : SPLIT_CUS;
+        while (nw > 1 && (long long)W * ((groups + nw - 1) / nw) < fill) nw /= 2;
+        q.waves = nw;
+        const int max_shares = (groups + nw - 1) / nw;
+        const int want = SPLIT_CUS * (q.nch <= 2 && q.lds <= 50 * 1024 ? 12 : 8) / nw;
+        q.shares = (want + W - 1) / W;
+        if (q.shares > max_shares) q.shares = max_shares;
+        if (q.shares > 64) q.shares = 64;
+    }
+    q.share_len = (groups + q.shares - 1) / q.shares * 64;
+    q.shares = (b + q.share_len - 1) / q.share_len;
+    if (!q.fused) {
+        auto bytes = [&](int dc) { return (size_t)k * ((dc + 1) * 8 + 4); };
+        int dc = 64;
+        while (dc > 8 && bytes(dc) > 72 * 1024) dc /= 2;
+        if (dc < 16 && bytes(16) <= SPLIT_LDS) dc = 16;         // (rows in pieces of 64 bytes, even with one workgroup per compute unit)
+        while (dc > 1 && bytes(dc) > SPLIT_LDS) dc /= 2;
+        q.dc = dc;
+        q.ncol = (d + dc - 1) / dc;
+        q.lds_sums = split_round16(bytes(dc));
+        // (every share writes and the update reads the sums of a whole state: no more than fill the device)
+        int ss = local ? 1 : 2 * SPLIT_CUS / (W * q.ncol);
+        if (ss > groups / 8) ss = groups / 8;
+        if (ss < 1) ss = 1;
+        q.sum_len = (groups + ss - 1) / ss * 64;
+        q.sum_shares = (b + q.sum_len - 1) / q.sum_len;
+    } else {
+        q.sum_shares = q.shares;
+        q.sum_len = q.share_len;
+    }
+    int g = 1;
+    while (g < q.dpad / 8 && g < 64) g *= 2;
+    q.g = g;
+    // workgroups of the update per worker (256 threads): enough for four on every compute unit, as long as each has rows to do
+    q.upd_blocks = local ? 1 : (4 * SPLIT_CUS + W - 1) / W;
+    const int row_groups = (k + 256 / g - 1) / (256 / g);
+    if (q.upd_blocks > row_groups) q.upd_blocks = row_groups;
+    q.grid = W < SPLIT_CUS ? W : SPLIT_CUS;
+    if (local && !q.fused && q.lds < q.lds_sums) q.lds = q.lds_sums;
+    q.lds_sums += SPLIT_LDS_SHARED;
+    q.lds += SPLIT_LDS_SHARED;
+    return q;
+}
+
+}  // namespace asgd

@@ -17,7 +17,6 @@ namespace asgd {
 // chunks of 16; [row pair][chunk][block of the pair][hi, lo] pieces of 1 KB, piece = 64 lanes x 8 fp16, lane l holding row
 // l % 32, columns 8 * (l / 32) .. + 7 of the chunk.
 constexpr int SPLIT_THREADS = 512;
-constexpr int SPLIT_KEPT_CHUNKS = 4;              // longest rows of a kept worker: beyond, its kernel needs more registers than there are
 
 struct SplitState {                // one per worker and step modulo 3
     float sw;                      // scale of the operands
@@ -73,7 +72,6 @@ struct SplitShared {                       // start of the LDS: the step, and sp
 
 // The LDS starts with what all phases share.
 extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
-constexpr unsigned SPLIT_LDS_SHARED = 512;
 static_assert(sizeof(SplitShared) <= SPLIT_LDS_SHARED, "room at the start of the LDS");
 __device__ __forceinline__ SplitShared &split_shared() { return *reinterpret_cast<SplitShared *>(split_lds); }
 

@@ -1,0 +1,37 @@
+// Host-only check of the LDS layout of the step kernels with fp16-split operands (csrc/split_plan.h): whatever the state and the
+// mini-batch, a workgroup's LDS fits a compute unit, the regions do not overlap, and the two mini-batches of a kept worker have room
+// for what their fetch writes.
+#include <cstdio>
+#include <cstdlib>
+
+#include "split_plan.h"
+
+using namespace asgd;
+
+#define REQUIRE(c) do { if (!(c)) { printf("FAIL %s: k %d d %d b %d W %d local %d\n", #c, k, d, b, W, local); return 1; } } while (0)
+
+int main(int argc, char **argv)
+{
+    const int d = argc > 1 ? atoi(argv[1]) : 7, W = argc > 2 ? atoi(argv[2]) : 192;
+    long long plans = 0, kept = 0, full = 0;
+    for (int k = 2; k <= 7680; k += k < 1200 ? 1 : 61)
+        for (int b = 1; b <= 20000; b += b < 3000 ? 3 : 59)
+            for (int local = 0; local < 2; ++local) {
+                const SplitPlan q = split_plan(k, d, b, W, local != 0);
+                REQUIRE(q.lds <= SPLIT_LDS_ALL && q.lds_sums <= SPLIT_LDS_ALL);
+                REQUIRE(q.off_cells % 16 == 0 && q.off_cnt % 16 == 0 && q.off_hs % 16 == 0 && q.off_ms % 16 == 0 && q.off_args % 16 == 0 && q.off_batch % 16 == 0);
+                REQUIRE(q.off_cells >= (q.resident ? q.frag_bytes : 0) && q.off_hs >= q.off_cnt + (q.fused ? 4u * k : 0));
+                REQUIRE(!q.fused || q.off_cnt >= q.off_cells + 8u * k * ((d + 1) / 2 * 2));
+                REQUIRE(q.off_ms >= q.off_hs + 4u * q.kpad && q.off_args >= q.off_ms + 4u * q.dpad);
+                if (q.kept) {
+                    REQUIRE(local && q.fused && q.resident && q.shares == 1 && q.waves == 8);
+                    REQUIRE(q.off_batch >= q.off_args + 8 * 64 * 4 && q.off_batch + 2 * q.batch_bytes + SPLIT_LDS_SHARED <= q.lds);
+                    REQUIRE(q.batch_bytes % 1024 == 0 && q.batch_bytes >= 4u * b * d);       // sweeps of 1 KB (16 bytes a lane) or 256 bytes
+                    ++kept;
+                    full += q.lds > SPLIT_LDS_ALL - 1024;
+                }
+                ++plans;
+            }
+    printf("ok %lld plans, %lld kept, %lld of them within 1 KB of the limit\n", plans, kept, full);
+    return 0;
+}

@@ -16,6 +16,8 @@ SPLIT = 2
     (2, 1, 192, 1, 1, 1, 0), (3, 2, 193, 63, 2, 2, 0), (12, 7, 256, 130, 0, 1, 1), (31, 7, 192, 64, 1, 1, 0), (32, 8, 200, 65, 1, 3, 0),
     (33, 9, 192, 513, 3, 1, 0), (64, 32, 256, 129, 1, 2, 0), (65, 16, 192, 200, 0, 1, 1), (40, 31, 192, 96, 2, 1, 0), (100, 60, 192, 70, 1, 2, 0),
     (20, 64, 192, 80, 5, 1, 0), (513, 8, 192, 520, 2, 1, 0), (500, 5, 192, 500, 1, 1, 0), (12, 7, 192, 1025, 4, 1, 0),
+    # two mini-batches end within 1 KB of the LDS of a compute unit
+    (12, 7, 192, 2743, 1, 1, 0), (128, 7, 200, 2560, 2, 1, 0), (128, 12, 192, 1430, 0, 1, 1), (37, 15, 192, 1246, 1, 2, 0),
 ])
 def test_kept_workers(B, oracle, k, d, W, b, E, buffers, mean):
     X = make_data(W * max(3 * b + 2, k) + 1, d, k, seed=300 + d)
