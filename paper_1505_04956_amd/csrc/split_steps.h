@@ -748,12 +748,14 @@ __device__ __forceinline__ void split_kept_clear8(SPLIT_ARG SplitArgs &a, unsign
 // Messages between workgroups of one launch: written and read past the caches that are not shared, element by element, so that
 // neither side needs a fence (which writes back or invalidates a whole L2: k = 64, d = 32, b = 500, a message every step, 105 us
 // per step with fences).
-// (sixteen bytes with the scope bit of an agent-scope access; a load waits in the same block)
+// (sixteen bytes with the scope bit of an agent-scope access; a load waits in the same block.  A store of more than eight bytes
+// reads its data late: two wait states before anything may write these registers, which the compiler, who does not look into the
+// block, would not leave.)
 __device__ __forceinline__ void split_message_put16(float *row, const float (&v)[8])
 {
     typedef float f4 __attribute__((ext_vector_type(4)));
     const f4 a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\tglobal_store_dwordx4 %0, %2, off offset:16 sc1" ::"v"(row), "v"(a), "v"(b) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\tglobal_store_dwordx4 %0, %2, off offset:16 sc1\n\ts_nop 1" ::"v"(row), "v"(a), "v"(b) : "memory");
 }
 __device__ __forceinline__ void split_message_row16(float (&v)[8], const float *row)
 {
