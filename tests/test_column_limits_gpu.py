@@ -136,3 +136,18 @@ def test_values_behind_small_data(B, oracle, k, d, W, H, b, behind):
     # 1e-6: sums of b < 2^5 terms that are good to 2^-22 of a column's largest element
     err = rel_fro(g.get_state().astype(np.float64), np.asarray(o.w)).max()
     assert err <= 1e-6
+
+
+# ten equal centroids: every sample is a tie and decided exactly, once, also where a step is formed a second time
+@pytest.mark.parametrize("W,b", [(4, 1000), (4, 300), (300, 500), (1100, 700)])
+def test_a_dropped_attempt_does_not_count_its_exact_decisions(B, samples, W, b):
+    X = samples.copy()
+    H = N // W
+    for i in range(0, W, 3):
+        rows = np.arange(i * H, i * H + b)
+        rows = rows[(rows // PIECE) % 2 == 1]
+        X[rows[:2], 3] = np.float32(5000.0)
+    g = load(B, X, W=W, b=b)
+    g.set_state(-1, np.full((K, D), 5.0, dtype=np.float32))
+    g.run_steps(1)
+    assert g.stats().exact_rechecks == W * b
