@@ -486,10 +486,11 @@ struct SmallKeeper {
         //   h_k (D squares and adds, one product) . (D+1) u max|h| each, two of them in h_k - h_0
         //   the subtraction and the +1 ............ 2 u (Hd + 1)
         //   index in the low 4 mantissa bits ...... 32 u (A + Hd + 1)
-        // Two values that differ by more than twice the sum (times 1.5 to spare) are ordered correctly.
+        // Two values that differ by more than twice the sum are ordered correctly.  To spare: times 1.5, of the part with A
+        // times 1.275 (max|x_j| is the largest element that is let through, up to a quarter above the largest one there is).
         const float Abound = wave_max_nonneg(dabs) * sum_xmax;
         return 3.0f * 5.9604645e-8f *
-               ((float)(D + 33) * Abound + (float)(D + 34) * (hdmax + 1.0f) + (float)(2 * D + 2) * hmax);
+               (0.85f * (float)(D + 33) * Abound + (float)(D + 34) * (hdmax + 1.0f) + (float)(2 * D + 2) * hmax);
     }
 
     // The state again, from the copy that publish() wrote: four registers that are not held across the streaming part.
