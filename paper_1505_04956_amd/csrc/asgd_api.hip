@@ -681,7 +681,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     if (kernel == ASGD_KERNEL_SMALL) {
         p.xabsmax = ctx->xsample;
         p.beyond_flag = ctx->flag_host + 3;
-        p.within_limits = sample_is_all(ctx->H * ctx->W, ctx->d) || (ctx->seen >= ctx->S && ctx->flag_host[3] == 0);
+        p.within_limits = sample_is_all(ctx->H * ctx->W, ctx->d) ? 2 : ctx->seen >= ctx->S && ctx->flag_host[3] == 0;
     }
     const long long t_end = ctx->t + steps;
     if (kernel == ASGD_KERNEL_SMALL && ctx->mode == ASGD_MODE_DETERMINISTIC && ctx->E > 0 && ctx->W > 1 && steps > 0) {

@@ -28,7 +28,7 @@ struct StepParams {
     int *assign_tmp;       // W x b assignment scratch
     int32_t *dump;         // optional assignment dump (step-major), or nullptr
     const float *xabsmax;  // d per-dimension max |x| over the loaded samples (small-state kernel: over a part of them)
-    int within_limits;     // small-state kernel: it is known that no element is beyond the limits that go with xabsmax
+    int within_limits;     // small-state kernel: it is known that no element is beyond the limits that go with xabsmax (1), or beyond xabsmax itself (2)
     int *beyond_flag;      // pinned host memory, set to 1 by the small-state kernel when it meets one
     int *error_flag;       // pinned host memory, set to 1 by a kernel whose bounded wait expired
     const int *shift_tab;  // deterministic schedule: cyclic shift of round r at [r - shift_r0] (small-state kernel)

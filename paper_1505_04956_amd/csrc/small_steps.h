@@ -918,7 +918,7 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
         phase_fence();
         if constexpr (!CHECK) inverse = inverse_scales[wave][kp.tq];
     };
-    set_scales(p.xabsmax, false);
+    set_scales(p.xabsmax, !CHECK && p.within_limits == 2);
     const unsigned wave_cells = (unsigned)(size_t)(lds_u32_ptr)&acc[wave][0][0];
     const unsigned lane_cell = wave_cells + (unsigned)(lane % RL) * 4u;
     unsigned scratch_cell = lane_cell + (unsigned)K * CENT_BYTES;
