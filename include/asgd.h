@@ -217,7 +217,7 @@ int asgd_set_exchange(asgd_ctx *ctx, const float *values_host, const int32_t *ro
  * calls (deterministic mode: bit for bit), the time does: with the streaming kernel, and
  * with the others where the workers fill the device and exchange every fourth step or less
  * often (or at any step, where a worker's state and two mini-batches fit a compute unit), a call of two communication rounds or more is ONE kernel launch for every 1024 rounds
- * it covers (the streaming kernel: a call of more than sixteen epochs that begins with the first after loading, one more),
+ * it covers (the streaming kernel: a call of more than two epochs that begins with the first after loading or after asgd_set_step(), one more),
  * and the start and the tail of a launch are then paid once per launch, not once per epoch (asgd_stats.launches); else a round, or every phase of a step, is a launch over all
  * workers.
  */

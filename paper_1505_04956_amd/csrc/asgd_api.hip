@@ -37,8 +37,11 @@ struct asgd_ctx {
     long long t = 0;
 
     float *w = nullptr, *slot = nullptr, *acc = nullptr, *xabsmax = nullptr, *mean = nullptr;
-    long long seen = 0;            // streaming kernel: it has looked at the mini-batches [0, seen) (flag_host[3]: and met an element
-                                   // beyond the limits it forms of xsample)
+    SeenSteps seen;                // streaming kernel: mini-batches it has looked at (flag_host[3]: and met an element beyond the
+                                   // limits it forms of xsample)
+    int *marks = nullptr;          // ... and, once it has looked at all, which ones hold such an element, allocated on first use
+    size_t marks_bytes = 0;
+    int marks_state = 0;           // 0: not made for the loaded samples, 1: made, -1: cannot be
     bool xabsmax_valid = false;    // xabsmax and flag_host[1], [2] are those of the loaded samples
     float *xsample = nullptr;      // streaming kernel only: column maxima over a part of the samples, and scratch (behind qpart)
     bool xsample_clear = false;    // its counter of workgroups is zero
@@ -99,7 +102,7 @@ size_t kd_of(const asgd_ctx *c) { return (size_t)c->k * c->d; }
 void free_all(asgd_ctx *c)
 {
     void *ptrs[] = {c->w, c->slot, c->acc, c->xabsmax, c->mean, c->stamp, c->consumed, c->cnt, c->assign_tmp,
-                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->split_data, c->load_scratch};
+                    c->ncum, c->counters, c->qpart, c->qout, c->xnorm2max, c->shift_tab, c->split_scratch, c->split_data, c->load_scratch, c->marks};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
     if (c->flag_host) (void)hipHostFree(c->flag_host);
@@ -280,6 +283,41 @@ int take_absmax(asgd_ctx *c)
     HIP_TRY(c, launch_absmax(c->x, c->H * c->W, c->d, c->xabsmax, c->flag_host + 1, c->flag_host + 2, c->load_scratch, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     c->xabsmax_valid = true;
+    return ASGD_OK;
+}
+
+// Whether a run of the streaming kernel need not compare its terms with the limits (within_limits): all samples were looked at while
+// loading; or in an epoch since, and no element was beyond them, or those mini-batches are marked (p->marks).  The stream is idle.
+// (Where the list is full, or mini-batches are so short that the table would take a sixteenth of the samples' room, later
+// epochs compare like the first.)
+int take_limits(asgd_ctx *c, const SeenSteps &seen, StepParams *p)
+{
+    p->within_limits = 0;
+    p->marks = nullptr;
+    if (sample_is_all(c->H * c->W, c->d)) p->within_limits = 2;
+    else if (seen.all(c->S)) {
+        if (c->flag_host[3] != 0 && c->marks_state == 0) {
+            int n = 0;
+            const size_t bytes = (size_t)c->W * c->S * sizeof(int);
+            HIP_TRY(c, hipMemcpy(&n, p->found, sizeof(int), hipMemcpyDeviceToHost));
+            c->marks_state = -1;
+            if (n <= FOUND_MAX && (double)c->b * c->d >= 16.0) {
+                if (bytes > c->marks_bytes) {
+                    if (c->marks) (void)hipFree(c->marks);
+                    c->marks = nullptr;
+                    c->marks_bytes = 0;
+                    if (hipMalloc((void **)&c->marks, bytes) == hipSuccess) c->marks_bytes = bytes;
+                    else (void)hipGetLastError();
+                }
+                if (c->marks) {
+                    HIP_TRY(c, launch_marks(p->found, c->d, c->S, c->W, c->marks, c->stream));
+                    c->marks_state = 1;
+                }
+            }
+        }
+        p->within_limits = c->flag_host[3] == 0 || c->marks_state == 1;
+        if (c->flag_host[3] != 0 && p->within_limits) p->marks = c->marks;
+    }
     return ASGD_OK;
 }
 
@@ -506,7 +544,8 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     ctx->xnorm2max_valid = false;
     ctx->split_data_valid = false;
     ctx->xabsmax_valid = false;
-    ctx->seen = 0;
+    ctx->seen = SeenSteps();
+    ctx->marks_state = 0;
     ctx->flag_host[3] = 0;
     LoadParams l;
     memset(&l, 0, sizeof(l));
@@ -518,7 +557,7 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
         l.slot_words = ctx->slot_bytes / sizeof(unsigned);
     }
     if (ctx->xsample && !ctx->xsample_clear) {
-        HIP_TRY(ctx, hipMemsetAsync(ctx->xsample, 0, sample_scratch_bytes(ctx->d), ctx->stream));
+        HIP_TRY(ctx, hipMemsetAsync(ctx->xsample, 0, (size_t)(ctx->d + 1) * sizeof(float), ctx->stream));
         ctx->xsample_clear = true;
     }
     HIP_TRY(ctx, launch_load(l, ctx->xsample, ctx->stream));
@@ -678,10 +717,15 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         if (rc != ASGD_OK) return rc;
     }
     StepParams p = make_params(ctx);
+    SeenSteps seen = ctx->seen;
     if (kernel == ASGD_KERNEL_SMALL) {
         p.xabsmax = ctx->xsample;
         p.beyond_flag = ctx->flag_host + 3;
-        p.within_limits = sample_is_all(ctx->H * ctx->W, ctx->d) ? 2 : ctx->seen >= ctx->S && ctx->flag_host[3] == 0;
+        p.found = sample_found(ctx->xsample, ctx->d);
+        if (steps > 0) seen.begin(ctx->t);
+        p.note_until = seen.from + ctx->S;
+        const int rc = take_limits(ctx, seen, &p);
+        if (rc != ASGD_OK) return rc;
     }
     const long long t_end = ctx->t + steps;
     if (kernel == ASGD_KERNEL_SMALL && ctx->mode == ASGD_MODE_DETERMINISTIC && ctx->E > 0 && ctx->W > 1 && steps > 0) {
@@ -783,16 +827,16 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     // earlier launch on the same stream.
     const bool rounds = (ctx->mode == ASGD_MODE_DETERMINISTIC && ctx->E > 0 && ctx->W > 1);
     auto first_epoch_end = [&](long long from) -> long long {        // step at which a launch from `from` on is cut, or t_end
-        if (kernel != ASGD_KERNEL_SMALL || p.within_limits || from > ctx->seen || from >= ctx->S) return t_end;
-        return first_epoch_cut(t_end, ctx->S, rounds ? ctx->E : 0);
+        if (kernel != ASGD_KERNEL_SMALL || p.within_limits) return t_end;
+        const long long cut = first_epoch_cut(t_end, seen.from, ctx->S, rounds ? ctx->E : 0, (double)ctx->W * ctx->b * ctx->d);
+        return cut > from ? cut : t_end;
     };
-    auto looked_at = [&](long long from, long long to) -> int {       // steps [from, to) have been launched
-        if (kernel != ASGD_KERNEL_SMALL || from > ctx->seen) return ASGD_OK;
-        if (to < t_end) {
-            HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-            p.within_limits = p.within_limits || (to >= ctx->S && ctx->flag_host[3] == 0);
-        }
-        return ASGD_OK;
+    auto ran_to = [&](long long t, bool cut) -> int {                 // a launch up to step t has been enqueued
+        if (kernel != ASGD_KERNEL_SMALL) return ASGD_OK;
+        seen.ran(t);
+        if (!cut) return ASGD_OK;
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        return take_limits(ctx, seen, &p);
     };
     int launches = 0;
     *ctx->flag_host = 0;         // (no kernel of this context is in flight: every run ends with a wait for the stream)
@@ -827,10 +871,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             }
             if (e == hipSuccess) {
                 ++launches;
-                if (tb == cut && cut < t_end) {
-                    const int rc = looked_at(t_done, tb);
-                    if (rc != ASGD_OK) return rc;
-                }
+                const int rc = ran_to(tb, tb == cut && cut < t_end);
+                if (rc != ASGD_OK) return rc;
                 t_done = tb;
                 ctx->passed_t = tb;
                 if (split_local && *ctx->flag_host) break;       // an expired wait: nothing more may run on these states
@@ -869,10 +911,8 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
                            : launch_generic_steps(p, ta, tb, ctx->stream);
         HIP_TRY(ctx, e);
         ++launches;
-        if (!rounds && tb < t_end) {
-            const int rc = looked_at(ta, tb);
-            if (rc != ASGD_OK) return rc;
-        }
+        const int rc = ran_to(tb, !rounds && tb < t_end);
+        if (rc != ASGD_OK) return rc;
         ta = tb;
         ctx->passed_t = -1;
     }
@@ -892,7 +932,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         ctx->desynced = true;
         return ASGD_ESYNC;
     }
-    if (kernel == ASGD_KERNEL_SMALL && ctx->t <= ctx->seen && t_end > ctx->seen) ctx->seen = t_end;
+    ctx->seen = seen;
     ctx->t = t_end;
     return ASGD_OK;
 }

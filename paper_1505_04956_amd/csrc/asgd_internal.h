@@ -30,6 +30,9 @@ struct StepParams {
     const float *xabsmax;  // d per-dimension max |x| over the loaded samples (small-state kernel: over a part of them)
     int within_limits;     // small-state kernel: it is known that no element is beyond the limits that go with xabsmax (1), or beyond xabsmax itself (2)
     int *beyond_flag;      // pinned host memory, set to 1 by the small-state kernel when it meets one
+    int *found;            // ... and where, for steps before note_until: a count, then FOUND_MAX entries of worker, mini-batch, d column maxima
+    long long note_until;
+    const int *marks;      // within_limits: W x S entries of `found` (from 1 on) of the mini-batches that have one, else 0; may be null
     int *error_flag;       // pinned host memory, set to 1 by a kernel whose bounded wait expired
     const int *shift_tab;  // deterministic schedule: cyclic shift of round r at [r - shift_r0] (small-state kernel)
     long long shift_r0;
@@ -63,11 +66,16 @@ struct LoadParams {
     long long H;
     int k, d, W;
     float *sample, *sample_part;      // (set by launch_load)
-    int *arrived;
+    int *arrived, *found;
 };
+constexpr int FOUND_MAX = 4096;       // (some 60 per column where one in 128 elements is looked at and the tails are heavy)
+__host__ __device__ inline size_t found_entry(int d, int n) { return 1 + (size_t)n * (2 + d); }      // word of entry n
 // What asgd_load_shards() begins with.  sample_scratch (may be null; d <= 16): sample_scratch_bytes() of device memory, zero before the
 // first use; its first d floats become maxima of |x_j| over a part of the samples.
 size_t sample_scratch_bytes(int d);
+int *sample_found(void *sample_scratch, int d);  // StepParams::found
+// marks: W * S words of device memory.  Enqueued only; the list holds no more than FOUND_MAX entries.
+hipError_t launch_marks(const int *found, int d, long long S, int W, int *marks, hipStream_t s);
 bool sample_is_all(long long rows, int d);       // whether that part is all of them
 hipError_t launch_load(LoadParams l, void *sample_scratch, hipStream_t s);
 // nonfinite, wide: pinned host memory, set to 1 if an element is infinite or not a number; if the typical element of a column

@@ -113,6 +113,7 @@ __global__ __launch_bounds__(256) void load_kernel(LoadParams l)
     for (size_t e = g; e < (size_t)l.W * l.k; e += n) l.ncum[e] = 0;
     for (size_t e = g; e < (size_t)l.W * CNT_STRIDE; e += n) l.counters[e] = 0;
     if (!l.sample_part) return;
+    if (g == 0) *l.found = 0;
     sample_columns(l, red);
     // The last workgroup to get here forms the maxima of all.  (The parts are written past the caches and have arrived before
     // the workgroup counts itself: no fence, which would write back a cache full of states.)
@@ -139,6 +140,20 @@ __global__ __launch_bounds__(256) void load_kernel(LoadParams l)
         l.sample[t] = m;
     }
     if (t == 0) *l.arrived = 0;          // (for the next load)
+}
+
+__global__ __launch_bounds__(256) void clear_marks_kernel(int *marks, size_t n)
+{
+    for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < n; e += (size_t)gridDim.x * 256) marks[e] = 0;
+}
+// (the same mini-batch may be listed more than once, with the same maxima)
+__global__ __launch_bounds__(256) void set_marks_kernel(const int *found, int d, long long S, int W, int *marks)
+{
+    const int n = min(found[0], FOUND_MAX);
+    for (int q = threadIdx.x; q < n; q += 256) {
+        const int *e = found + found_entry(d, q);
+        if (e[0] >= 0 && e[0] < W && e[1] >= 0 && e[1] < S) marks[(size_t)e[0] * S + e[1]] = q + 1;
+    }
 }
 
 // partial[block][j] = max |x[row][j]| over the elements this block visits.  The flat array is walked with a stride that is
@@ -577,7 +592,9 @@ __global__ void mean_state_kernel(const float *w, int W, int kd, float *out)
 
 // ------------------------------------------------------------------------------------------
 bool sample_is_all(long long rows, int d) { return sample_every(sample_pieces(rows * d, d)) == 1; }
-size_t sample_scratch_bytes(int d) { return ((size_t)(LOAD_BLOCKS + 1) * d + 1) * sizeof(float); }
+// d maxima, a counter, d maxima per workgroup, the list of what goes past the limits
+size_t sample_scratch_bytes(int d) { return ((size_t)(LOAD_BLOCKS + 1) * d + 1 + found_entry(d, FOUND_MAX)) * sizeof(float); }
+int *sample_found(void *sample_scratch, int d) { return static_cast<int *>(sample_scratch) + (size_t)(LOAD_BLOCKS + 1) * d + 1; }
 
 hipError_t launch_load(LoadParams l, void *sample_scratch, hipStream_t s)
 {
@@ -586,6 +603,7 @@ hipError_t launch_load(LoadParams l, void *sample_scratch, hipStream_t s)
         l.sample = static_cast<float *>(sample_scratch);
         l.arrived = reinterpret_cast<int *>(l.sample + l.d);
         l.sample_part = l.sample + l.d + 1;
+        l.found = sample_found(sample_scratch, l.d);
     }
     hipLaunchKernelGGL(load_kernel, dim3(LOAD_BLOCKS), dim3(256), 0, s, l);
     return hipGetLastError();
@@ -687,6 +705,14 @@ hipError_t launch_schedule_table(uint64_t seed, long long r0, int n, int W, int 
 hipError_t launch_broadcast_state(const float *src, int W, int kd, float *w, hipStream_t s)
 {
     hipLaunchKernelGGL(broadcast_state_kernel, dim3((kd + 255) / 256, W < 1024 ? W : 1024), dim3(256), 0, s, src, W, kd, w);
+    return hipGetLastError();
+}
+
+hipError_t launch_marks(const int *found, int d, long long S, int W, int *marks, hipStream_t s)
+{
+    const size_t n = (size_t)W * S, blocks = (n + 255) / 256;
+    hipLaunchKernelGGL(clear_marks_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, s, marks, n);
+    hipLaunchKernelGGL(set_marks_kernel, dim3(1), dim3(256), 0, s, found, d, S, W, marks);
     return hipGetLastError();
 }
 

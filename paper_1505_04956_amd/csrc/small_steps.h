@@ -816,14 +816,17 @@ constexpr int small_waves_per_simd()
     return (K - 1) * SmallGeo<K, D>::RW + PF * D + 96 <= 256 ? RS : 1;
 }
 
-template <int K, int D, int PF, int NW, int RS, int NB, bool PARTS, bool AHEAD, bool CHECK>
+// LOOK: what is done about elements beyond the limits that go with p.xabsmax (see below)
+enum { LOOK_AT_NONE = 0, LOOK_AT_TERMS = 1, LOOK_AT_MARKS = 2 };
+template <int K, int D, int PF, int NW, int RS, int NB, bool PARTS, bool AHEAD, int LOOK>
 __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(small_waves_per_simd<K, D, PF, RS>(), small_waves_per_simd<K, D, PF, RS>())))
 void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
 {
     using G = SmallGeo<K, D>;
     constexpr int NQ = G::NQ, RW = G::RW, NT = G::NT, NPART = G::NPART;
-    constexpr bool LEAN = CHECK && (K - 1) * RW + PF * D + 96 > 230;
+    constexpr bool CHECK = LOOK == LOOK_AT_TERMS;
+    constexpr bool LEAN = LOOK != LOOK_AT_NONE && (K - 1) * RW + PF * D + 96 > 230;
     // copies of an accumulator cell per wave: one per lane, or sixteen (lanes r, r + 16, r + 32, r + 48 share one; 32 where
     // the once-per-step sums need that many to give every lane of a task four)
     constexpr int RL = RS == 1 ? 64 : (16 >= 4 * NPART ? 16 : 32);
@@ -871,10 +874,10 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
     kp.init(p, lane);
     // the budget of polls grows with the rounds the launch covers: a healthy run of the streaming workload spends up
     // to ~30 polls per round on the workgroup that waits most
-    // (CHECK: and every step of a neighbour may be formed twice, each sample of the second attempt be decided in fp64)
+    // (And where there are elements beyond the limits every step of a neighbour may be formed twice, each sample of the second attempt be decided in fp64, those of a marked step too)
     if (p.wait_polls <= 0 && p.E > 0) {
         long long more = (long long)WAIT_PER_ROUND * ((t1 - t0) / p.E + 1);
-        if constexpr (CHECK) more += (long long)WAIT_PER_GROUP * (ngw + 1) * (t1 - t0) * ((W + (int)gridDim.x - 1) / (int)gridDim.x);
+        if constexpr (LOOK != LOOK_AT_NONE) more += (long long)WAIT_PER_GROUP * (ngw + 1) * (t1 - t0) * ((W + (int)gridDim.x - 1) / (int)gridDim.x);
         kp.budget += (int)min(more, (long long)WAIT_BUDGET_MAX - WAIT_BUDGET);
     }
     for (int q = lane; q < ((K + 1) * CE + 4) * RL; q += 64) (&acc[wave][0][0])[q] = 0u;
@@ -884,8 +887,10 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
     // (the count needs none), and the LDS byte address of this lane's copy of element 0 of centroid 0.
     // p.xabsmax are maxima over a part of the samples only (launch_load), so every term is compared with the
     // limit of fx_term_limit(); the sums of a step whose mini-batch holds an element beyond it are dropped and the step is
-    // formed again with the maxima of that mini-batch (`column_maxima`).  CHECK = false: it is known that no element is beyond
-    // its limit (fx_term_limit() of the same maxima: the terms and with them the results are the same), nothing is compared.
+    // formed again with the maxima of that mini-batch (`column_maxima`).  Where it is known that no element is beyond
+    // its limit nothing is compared (LOOK_AT_NONE; fx_term_limit() of the same maxima: the terms and with them the results are the
+    // same), nor where it is known which mini-batches hold one: they are marked (LOOK_AT_MARKS), with the maxima that were found in
+    // them.  (A look at the mark in every kernel cost one that has none 2.5 %: W = 4, b = 500.)
     constexpr unsigned ELEM_BYTES = RL * 4u, CENT_BYTES = (unsigned)CE * ELEM_BYTES;
     // A term is the bit pattern of fma(x, scale, magic).  With scales of one and more (ordinary data) the terms are formed
     // among the denormal numbers, where the bit pattern counts on linearly from zero: magic = limit * 2^-149, what
@@ -919,6 +924,7 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
         if constexpr (!CHECK) inverse = inverse_scales[wave][kp.tq];
     };
     set_scales(p.xabsmax, !CHECK && p.within_limits == 2);
+    int scales_of = 0;                              // the mark of the mini-batch that the scales go with
     const unsigned wave_cells = (unsigned)(size_t)(lds_u32_ptr)&acc[wave][0][0];
     const unsigned lane_cell = wave_cells + (unsigned)(lane % RL) * 4u;
     unsigned scratch_cell = lane_cell + (unsigned)K * CENT_BYTES;
@@ -993,6 +999,13 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
 
             bool again = false;         // this step is formed a second time, with the maxima of its own mini-batch
             for (int ls = 0; ls < wk.seg;) {
+                if constexpr (LOOK == LOOK_AT_MARKS) {
+                    const int mark = uniform_load(p.marks + ((size_t)i * (unsigned)wk.S + (unsigned)s_epoch));
+                    if (mark != scales_of) {
+                        set_scales(mark ? reinterpret_cast<const float *>(p.found + found_entry(D, mark - 1) + 2) : p.xabsmax, mark != 0);
+                        scales_of = mark;
+                    }
+                }
                 // ---- wave-uniform copies of the state: every lane gets w_k - w_0 and (h_k - h_0) + 1 ----
                 const float thr = kp.publish(wst[wave], wdt[wave]);
                 phase_fence();      // the copies are per wave: the lanes of this wave only have to see each other's writes
@@ -1164,6 +1177,13 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
                     if (lane == 0) __hip_atomic_store(p.beyond_flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                     // `before` holds the totals with this attempt's terms in them: they are out of the next difference
                     column_maxima(xb);
+                    if (wave == 0 && t0 + (wk.done + ls) < p.note_until) {
+                        int n = 0;
+                        if (lane == 0) n = atomicAdd(p.found, 1);
+                        n = __builtin_amdgcn_readfirstlane(n);
+                        int *entry = p.found + found_entry(D, n);
+                        if (n >= 0 && n < FOUND_MAX && lane < D + 2) entry[lane] = lane == 0 ? i : lane == 1 ? s_epoch : (int)cmax[lane - 2];
+                    }
                     set_scales(reinterpret_cast<const float *>(cmax), true);
                     again = true;
                     rechecks = rechecks_before[wave][here];
@@ -1256,23 +1276,23 @@ hipError_t launch_kernel(int threads, const StepParams &p, long long t0, long lo
 // Like waves.  Several buffers: the message pairs of all buffers sit in registers during a step, so the ring depth is
 // at most 4, and 2 for four buffers; the caller limits it.  Several buffers and partial messages are only built for
 // the shapes with shared rows.
-template <int K, int D, int PF, int NW, int RS, bool CHECK>
+template <int K, int D, int PF, int NW, int RS, int LOOK>
 hipError_t launch_variant_of(const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
 {
     // (two groups per wave: 256 < b <= 512)
     if constexpr (PF == 2 && NW == 4) {
         if (p.nb == 1 && p.parts == 1 && (p.b + 63) / 64 <= 2 * NW)
-            return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, true, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+            return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, true, LOOK>>(64 * NW, p, t0, t1, s, persistent);
     }
     if (p.nb == 1 && p.parts == 1)
-        return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+        return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
     if constexpr (PF <= 4 && RS == 2 && NW <= 2) {
-        if (p.nb == 1) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 2) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 2, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 3) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 3, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 1) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 2) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 2, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 3) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 3, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
     }
     if constexpr (PF == 2 && RS == 2 && NW <= 2) {
-        if (p.nb == 4) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 4, true, false, CHECK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 4) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 4, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
     }
     return hipErrorInvalidValue;
 }
@@ -1280,8 +1300,9 @@ hipError_t launch_variant_of(const StepParams &p, long long t0, long long t1, hi
 template <int K, int D, int PF, int NW, int RS>
 hipError_t launch_variant(const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
 {
-    return p.within_limits ? launch_variant_of<K, D, PF, NW, RS, false>(p, t0, t1, s, persistent)
-                           : launch_variant_of<K, D, PF, NW, RS, true>(p, t0, t1, s, persistent);
+    if (!p.within_limits) return launch_variant_of<K, D, PF, NW, RS, LOOK_AT_TERMS>(p, t0, t1, s, persistent);
+    return p.marks ? launch_variant_of<K, D, PF, NW, RS, LOOK_AT_MARKS>(p, t0, t1, s, persistent)
+                   : launch_variant_of<K, D, PF, NW, RS, LOOK_AT_NONE>(p, t0, t1, s, persistent);
 }
 
 // ring depth the registers of a shape leave room for: the wave-uniform copy of w_k - w_0 takes (K - 1) * RW registers,

@@ -16,10 +16,10 @@ int main()
         for (long long E : {0LL, 1LL, 2LL, 8LL, 100LL, 2000LL, 1000000LL, 2000000000LL})
             for (long long steps : {1LL, S, 15 * S, 16 * S, 16 * S + 1, 17 * S, 17 * S + 3, 40 * S + 1, 16 * S + E, 17 * S + E + 2})
                 for (long long t : {0LL, 1LL, S - 1, E, 5 * S}) {
-                    const long long t_end = t + steps, cut = first_epoch_cut(t_end, S, E);
+                    const long long t_end = t + steps, cut = first_epoch_cut(t_end, t, S, E, 1e7);
                     REQUIRE(cut <= t_end);
-                    REQUIRE(cut == t_end || (cut >= S && cut < t_end && (E == 0 || cut % E == 0)));
-                    REQUIRE(t > 0 || E > S || steps <= 16 * S + E || cut < t_end);
+                    REQUIRE(cut == t_end || (cut >= t + S && cut < t_end && (E == 0 || cut % E == 0)));
+                    REQUIRE(steps <= 2 * S + E || steps <= S + E + 54 || cut < t_end);
                     cuts += cut < t_end;
                     ++calls;
                     if (E == 0) continue;
@@ -34,8 +34,27 @@ int main()
                     REQUIRE(launches <= 2 + steps / E / ONE_LAUNCH_MAX_ROUNDS + 1);
                 }
     // the cut would lie behind the end of the call
-    if (first_epoch_cut(1649, 97, 2000) != 1649 || one_launch_end(0, 1649, first_epoch_cut(1649, 97, 2000), 2000) != 1649) return 1;
-    if (first_epoch_cut(51, 3, 100) != 51 || first_epoch_cut(20 * 97, 97, 8) != 104 || first_epoch_cut(20 * 97, 97, 0) != 97) return 1;
+    const double all = 1.024e7;                            // 1024 workers, 1000 samples of ten columns: 97 steps are 4 GB
+    if (first_epoch_cut(1649, 0, 97, 2000, all) != 1649 || one_launch_end(0, 1649, first_epoch_cut(1649, 0, 97, 2000, all), 2000) != 1649) return 1;
+    if (first_epoch_cut(51, 0, 3, 100, all) != 51 || first_epoch_cut(3 * 97, 0, 97, 8, all) != 104 || first_epoch_cut(3 * 97, 0, 97, 0, all) != 97) return 1;
+    if (first_epoch_cut(2 * 97, 0, 97, 0, all) != 2 * 97 || first_epoch_cut(16 * 3, 0, 3, 0, all) != 16 * 3 || first_epoch_cut(20 * 3, 0, 3, 0, all) != 3) return 1;
+    // runs in pieces, a step back, a jump: only an unbroken stretch of S steps is all mini-batches
+    SeenSteps seen;
+    for (long long t : {0LL, 40LL, 80LL}) {
+        if (seen.all(97)) return 1;
+        seen.begin(t);
+        seen.ran(t + 40);
+    }
+    if (!seen.all(97)) return 1;
+    seen.begin(60);
+    seen.ran(70);
+    if (!seen.all(97) || seen.to != 120) return 1;
+    seen.begin(1000);
+    seen.ran(1050);
+    if (seen.all(97)) return 1;
+    seen.begin(1050);
+    seen.ran(1097);
+    if (!seen.all(97)) return 1;
     printf("ok %lld calls, %lld cut\n", calls, cuts);
     return 0;
 }

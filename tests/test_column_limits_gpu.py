@@ -75,7 +75,7 @@ def test_elements_beyond_the_limits(B, oracle, samples, W, b, factor):
         assert np.all(np.linalg.norm((wg - wo)[:, :, j], axis=1) <= TOL * den + 1e-30), j
 
 
-# a second epoch, and all but the first of a call of more than sixteen, are not compared with the limits any more
+# a second epoch, and all but the first of a call with more than an epoch and 2^29 elements after it, are not compared with the limits any more
 @pytest.mark.parametrize("W,b,beyond", [(4, 4000, False), (300, 3000, False), (1100, 700, False), (300, 3000, True)])
 def test_later_epochs_give_the_same_bits(B, samples, W, b, beyond):
     X = samples
@@ -94,7 +94,7 @@ def test_later_epochs_give_the_same_bits(B, samples, W, b, beyond):
     assert many.stats().launches <= 2 + (18 * S + 3) // 2 // 1024
 
 
-# a call of more than sixteen epochs that is shorter than a round: it ends with its own last step, not with the round
+# a call long enough to be cut after its first epoch, but shorter than a round: it ends with its own last step, not with the round
 @pytest.mark.parametrize("E", [49, 100, 2000])
 def test_a_call_ends_before_its_round(B, samples, E):
     import torch
@@ -151,3 +151,44 @@ def test_a_dropped_attempt_does_not_count_its_exact_decisions(B, samples, W, b):
     g.set_state(-1, np.full((K, D), 5.0, dtype=np.float32))
     g.run_steps(1)
     assert g.stats().exact_rechecks == W * b
+
+
+# once all mini-batches were looked at, those that hold an element beyond the limits are marked and later epochs compare nothing: the
+# same bits as a call that compares all along.  few: some elements (an infinity among them); many: more than the list has room for
+@pytest.mark.parametrize("W,b,E,many", [(4, 4000, 2, False), (56, 300, 3, False), (300, 3000, 2, False), (1100, 700, 0, False), (300, 100, 8, True)])
+def test_marked_mini_batches_give_the_same_bits(B, samples, W, b, E, many):
+    X = samples.copy()
+    H = N // W
+    S = H // b
+    rng = np.random.default_rng(W)
+    rows = np.arange(N // (2 * PIECE)) * 2 * PIECE + PIECE + 200 if many else unseen_rows(rng, 60, W * H)
+    X[rows, rng.integers(0, 8, len(rows))] *= np.float32(50.0)
+    if not many:
+        X[rows[0], 2] = np.inf
+    epochs = 5
+    one, many_calls, odd = (load(B, X, W=W, b=b, E=E) for _ in range(3))
+    one.run_epochs(epochs)
+    for _ in range(epochs):
+        many_calls.run_epochs(1)
+    done = 0
+    for n in (1, S - 1, 2, S, S + S // 2):
+        odd.run_steps(n)
+        done += n
+    odd.run_steps(epochs * S - done)
+    assert np.array_equal(one.get_state(), many_calls.get_state(), equal_nan=True)
+    assert np.array_equal(one.get_state(), odd.get_state(), equal_nan=True)
+    assert np.array_equal(one.worker_counters(), odd.worker_counters())
+    # samples that a comparison sent to the exact decision twice are counted once, marked ones too
+    if many:
+        assert one.stats().exact_rechecks == many_calls.stats().exact_rechecks
+    # a run that is taken up in the middle of the second epoch in another context: it looks at a whole epoch first
+    first, second = (load(B, X, W=W, b=b, E=E) for _ in range(2))
+    t = S + S // 2
+    first.run_steps(t)
+    second.set_state(-2, first.get_state())
+    second.set_step(t)
+    if E:
+        second.set_exchange(*first.get_exchange())
+    for n in (1, S, S - 1, epochs * S - t - 2 * S):
+        second.run_steps(n)
+    assert np.array_equal(one.get_state(), second.get_state(), equal_nan=True)
