@@ -275,10 +275,16 @@ int import_exchange(asgd_ctx *c, int kernel, const float *values, const int32_t 
 // Per-dimension max |x| over the rows the workers own (inputs of the rounding-error bounds that decide when an assignment is
 // recomputed exactly, and of the scales of fixed-point sums), and whether they are finite and of ordinary size.
 // Synchronises the stream.
-int take_absmax(asgd_ctx *c)
+int take_absmax_scratch(asgd_ctx *c)
 {
     const size_t bytes = absmax_scratch_bytes(c->d);
     if (bytes && !c->load_scratch) HIP_TRY(c, hipMalloc(&c->load_scratch, bytes));
+    return ASGD_OK;
+}
+int take_absmax(asgd_ctx *c)
+{
+    const int rc = take_absmax_scratch(c);
+    if (rc != ASGD_OK) return rc;
     c->flag_host[1] = c->flag_host[2] = 0;
     HIP_TRY(c, launch_absmax(c->x, c->H * c->W, c->d, c->xabsmax, c->flag_host + 1, c->flag_host + 2, c->load_scratch, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
@@ -534,6 +540,13 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     const long long H = N / ctx->W;
     if (H < ctx->k || H < ctx->b) return ASGD_EINVAL;
     HIP_TRY(ctx, hipSetDevice(ctx->device));
+    // The streaming kernel makes do with maxima over a part of the samples; those over all of them are formed by the first run
+    // of another kernel.
+    const bool whole = !(ctx->xsample && ctx->lr_mode == ASGD_LR_CONST && (ctx->kernel_opt == ASGD_KERNEL_AUTO || ctx->kernel_opt == ASGD_KERNEL_SMALL));
+    if (whole) {                          // (no memory: the context keeps the samples it has)
+        const int rc = take_absmax_scratch(ctx);
+        if (rc != ASGD_OK) return rc;
+    }
     ctx->x = x_dev; ctx->N = N; ctx->H = H; ctx->S = H / ctx->b;
     ctx->stream = (hipStream_t)hip_stream;
     ctx->t = 0;
@@ -562,9 +575,7 @@ int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_str
     }
     HIP_TRY(ctx, launch_load(l, ctx->xsample, ctx->stream));
     ctx->fill_kernel = 0;
-    // The streaming kernel makes do with maxima over a part of the samples; those over all of them are formed by the first run
-    // of another kernel.
-    if (!(ctx->xsample && ctx->lr_mode == ASGD_LR_CONST && (ctx->kernel_opt == ASGD_KERNEL_AUTO || ctx->kernel_opt == ASGD_KERNEL_SMALL))) {
+    if (whole) {
         const int rc = take_absmax(ctx);
         if (rc != ASGD_OK) return rc;
     }
@@ -682,6 +693,12 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
     if (kernel == ASGD_KERNEL_SMALL && !small_ok) return ASGD_EINVAL;
     if (kernel == ASGD_KERNEL_MFMA && !mfma_ok) return ASGD_EINVAL;
 
+    // (before the exchange buffers are touched: it may find no memory, and the messages are still there for another attempt)
+    if (kernel != ASGD_KERNEL_SMALL && !ctx->xabsmax_valid && steps > 0) {
+        const int rc = take_absmax(ctx);
+        if (rc != ASGD_OK) return rc;
+    }
+
     // The kernels keep a message in flight in different formats.  Messages handed over by asgd_set_exchange(), and
     // those a run of another kernel left behind, are written into the buffers in the format of this run's kernel.
     const bool switched = ctx->last_kernel != 0 && kernel != ctx->last_kernel && ctx->E > 0 && ctx->W > 1 && ctx->t > 0;
@@ -712,10 +729,6 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         if (rc != ASGD_OK) return rc;
     }
 
-    if (kernel != ASGD_KERNEL_SMALL && !ctx->xabsmax_valid && steps > 0) {
-        const int rc = take_absmax(ctx);
-        if (rc != ASGD_OK) return rc;
-    }
     StepParams p = make_params(ctx);
     SeenSteps seen = ctx->seen;
     if (kernel == ASGD_KERNEL_SMALL) {
