@@ -735,7 +735,7 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
         p.xabsmax = ctx->xsample;
         p.beyond_flag = ctx->flag_host + 3;
         p.found = sample_found(ctx->xsample, ctx->d);
-        if (steps > 0) seen.begin(ctx->t);
+        if (steps > 0) seen.begin(ctx->t, ctx->S);
         p.note_until = seen.from + ctx->S;
         const int rc = take_limits(ctx, seen, &p);
         if (rc != ASGD_OK) return rc;

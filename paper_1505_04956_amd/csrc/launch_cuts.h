@@ -13,9 +13,9 @@ constexpr long long ONE_LAUNCH_MAX_ROUNDS = 1024;
 struct SeenSteps {
     long long from = 0, to = 0;
     bool all(long long S) const { return to - from >= S; }
-    void begin(long long t)                       // a run goes on at step t
+    void begin(long long t, long long S)          // a run goes on at step t
     {
-        if (t < from || t > to) from = to = t;
+        if (!all(S) && (t < from || t > to)) from = to = t;
     }
     void ran(long long t)                         // ... and has got to step t
     {

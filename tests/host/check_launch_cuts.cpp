@@ -40,20 +40,19 @@ int main()
     if (first_epoch_cut(2 * 97, 0, 97, 0, all) != 2 * 97 || first_epoch_cut(16 * 3, 0, 3, 0, all) != 16 * 3 || first_epoch_cut(20 * 3, 0, 3, 0, all) != 3) return 1;
     // runs in pieces, a step back, a jump: only an unbroken stretch of S steps is all mini-batches
     SeenSteps seen;
-    for (long long t : {0LL, 40LL, 80LL}) {
-        if (seen.all(97)) return 1;
-        seen.begin(t);
+    for (long long t : {0LL, 40LL, 10LL}) {
+        seen.begin(t, 97);
         seen.ran(t + 40);
+        if (seen.all(97)) return 1;
     }
-    if (!seen.all(97)) return 1;
-    seen.begin(60);
-    seen.ran(70);
-    if (!seen.all(97) || seen.to != 120) return 1;
-    seen.begin(1000);
+    seen.begin(1000, 97);
     seen.ran(1050);
-    if (seen.all(97)) return 1;
-    seen.begin(1050);
+    if (seen.all(97) || seen.from != 1000) return 1;
+    seen.begin(1050, 97);
     seen.ran(1097);
+    if (!seen.all(97)) return 1;
+    seen.begin(5, 97);
+    seen.ran(6);
     if (!seen.all(97)) return 1;
     printf("ok %lld calls, %lld cut\n", calls, cuts);
     return 0;
