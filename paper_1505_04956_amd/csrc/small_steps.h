@@ -840,6 +840,8 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
     static_assert(RS == 1 || RS == 2, "one copy of the cells per lane, or shared copies");
     static_assert(PF >= 2, "the ring needs the previous group's buffer");
     static_assert(RL % NPART == 0 && RPP % 4 == 0, "state too large for this kernel");
+    static_assert(!CHECK || D % 2 == 0, "terms are compared in pairs");
+    static_assert(!CHECK || D % 4 != 3, "the last element of a centroid's last task is padding, which the flag of a step travels in");
 
     // acc[wave][c * CE + j][r]: copy r (lanes r, r + RL, ...) of the fixed-point sum of element j of the samples of
     // centroid c, j = D: their count; centroid K is scratch for masked lanes; four elements of slack behind it for the
