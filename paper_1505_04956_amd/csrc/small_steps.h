@@ -1231,9 +1231,12 @@ void small_steps_kernel(StepParams p, long long t0, long long t1, int sync)
 }
 
 // resident workgroups of a kernel on the current device (queried once per device and kernel: the kernel is a template
-// argument, all of them have the same type)
+// argument, all of them have the same type).  WAVES: per SIMD, what the kernel was compiled for.  The hardware never holds more
+// (the compiler asks for registers that see to it), but the runtime counts the registers that are used: k = 16, d = 8 uses
+// 252 and asks for 257, and of 1100 workgroups that were to wait for each other 1024 had a place.
 typedef void (*SmallKernel)(StepParams, long long, long long, int);
-template <SmallKernel KERN>
+constexpr int SIMDS = 4;                // of a compute unit
+template <SmallKernel KERN, int WAVES>
 hipError_t resident_capacity(int threads, long long *out)
 {
     static long long cached_capacity[64] = {0};
@@ -1246,14 +1249,15 @@ hipError_t resident_capacity(int threads, long long *out)
         e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, KERN, threads, 0);
         if (e != hipSuccess) return e;
-        capacity = (long long)per_cu * cus;
+        const int most = SIMDS * WAVES * 64 / threads;
+        capacity = (long long)(per_cu < most ? per_cu : most) * cus;
         if (dev >= 0 && dev < 64) cached_capacity[dev] = capacity;
     }
     *out = capacity;
     return hipSuccess;
 }
 
-template <SmallKernel KERN>
+template <SmallKernel KERN, int WAVES>
 hipError_t launch_kernel(int threads, const StepParams &p, long long t0, long long t1, hipStream_t s, bool persistent)
 {
     if (!persistent) {
@@ -1262,7 +1266,7 @@ hipError_t launch_kernel(int threads, const StepParams &p, long long t0, long lo
     }
     // one launch for the whole run: every workgroup must be resident at the same time
     long long capacity = 0;
-    hipError_t e = resident_capacity<KERN>(threads, &capacity);
+    hipError_t e = resident_capacity<KERN, WAVES>(threads, &capacity);
     if (e != hipSuccess) return e;
     if (capacity < 1) return hipErrorCooperativeLaunchTooLarge;
     const int grid = (int)(p.W < capacity ? p.W : capacity);
@@ -1284,17 +1288,17 @@ hipError_t launch_variant_of(const StepParams &p, long long t0, long long t1, hi
     // (two groups per wave: 256 < b <= 512)
     if constexpr (PF == 2 && NW == 4) {
         if (p.nb == 1 && p.parts == 1 && (p.b + 63) / 64 <= 2 * NW)
-            return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, true, LOOK>>(64 * NW, p, t0, t1, s, persistent);
+            return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, true, LOOK>, small_waves_per_simd<K, D, PF, RS>()>(64 * NW, p, t0, t1, s, persistent);
     }
     if (p.nb == 1 && p.parts == 1)
-        return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
+        return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, false, false, LOOK>, small_waves_per_simd<K, D, PF, RS>()>(64 * NW, p, t0, t1, s, persistent);
     if constexpr (PF <= 4 && RS == 2 && NW <= 2) {
-        if (p.nb == 1) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 2) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 2, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
-        if (p.nb == 3) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 3, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 1) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 1, true, false, LOOK>, small_waves_per_simd<K, D, PF, RS>()>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 2) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 2, true, false, LOOK>, small_waves_per_simd<K, D, PF, RS>()>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 3) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 3, true, false, LOOK>, small_waves_per_simd<K, D, PF, RS>()>(64 * NW, p, t0, t1, s, persistent);
     }
     if constexpr (PF == 2 && RS == 2 && NW <= 2) {
-        if (p.nb == 4) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 4, true, false, LOOK>>(64 * NW, p, t0, t1, s, persistent);
+        if (p.nb == 4) return launch_kernel<small_steps_kernel<K, D, PF, NW, RS, 4, true, false, LOOK>, small_waves_per_simd<K, D, PF, RS>()>(64 * NW, p, t0, t1, s, persistent);
     }
     return hipErrorInvalidValue;
 }
