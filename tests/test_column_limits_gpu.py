@@ -192,3 +192,36 @@ def test_marked_mini_batches_give_the_same_bits(B, samples, W, b, E, many):
     for n in (1, S, S - 1, epochs * S - t - 2 * S):
         second.run_steps(n)
     assert np.array_equal(one.get_state(), second.get_state(), equal_nan=True)
+
+
+# the other states with a streaming kernel: one, two and four waves per worker, with elements beyond the limits and an epoch after
+# they have been marked
+@pytest.mark.parametrize("W,b", [(20, 300), (300, 500), (1100, 300)])
+@pytest.mark.parametrize("k,d", [(4, 4), (8, 8), (8, 16), (16, 8), (16, 12)])
+def test_other_states(B, oracle, k, d, W, b):
+    piece = 16 * (256 - 256 % d)
+    n = 8600 * piece // d                          # 8600 pieces: one in two is looked at
+    rng = np.random.default_rng(k + d + W)
+    centres = rng.uniform(0.0, 10.0, (k, d))
+    X = (centres[rng.integers(0, k, n)] + rng.standard_normal((n, d))).astype(np.float32)
+    H, steps = n // W, 9
+    for i in range(0, W, max(1, W // 20)):
+        rows = rng.integers(i * H, i * H + steps * b, 200)
+        rows = rows[rows * d // piece % 2 == 1][:4]
+        X[rows, rng.integers(0, d, len(rows))] *= np.float32(40.0)
+    import torch
+    x = torch.from_numpy(X).to("cuda:0")
+    one, two = (B.ASGD(k, d, W, b, 0.05, E=3, kernel=2) for _ in range(2))
+    o = oracle.OracleASGD(X, k=k, W=W, b=b, lr=0.05, E=3, seed=1)
+    for g in (one, two):
+        g.load_shards(x)
+    one.run_steps(steps)
+    o.run_steps(steps)
+    assert rel_fro(one.get_state().astype(np.float64), np.asarray(o.w)).max() <= TOL
+    check_counters(one.worker_counters(), o.counters, o.parzen_near)
+    S = H // b
+    one.run_steps(S + 2 * steps)                   # compared: steps < S were looked at when this call begins
+    two.run_steps(S)
+    two.run_steps(3 * steps)                       # marked
+    assert np.array_equal(one.get_state(), two.get_state())
+    assert np.array_equal(one.worker_counters(), two.worker_counters())
