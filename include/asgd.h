@@ -143,7 +143,8 @@ typedef struct asgd_stats {
  * Requires k, d, W, b >= 1 and lr > 0 (Alg. 5 "Require"; W = 1 is allowed and equals
  * Alg. 4).  Allocates W*k*d floats of state and the exchange buffers on the current
  * device.  More is allocated by the first call that needs it and kept until asgd_destroy():
- * 8 KB per column at the first asgd_load_shards() (d <= 8192; where the streaming kernel runs: at the first run of another), and the operands and sums of the
+ * 8 KB per column at the first asgd_load_shards() (d <= 8192; where the streaming kernel runs: at the first run of another; that
+ * kernel takes 4 bytes per worker and mini-batch once it has met large elements, see asgd_load_shards()), and the operands and sums of the
  * kernels with fp16-split operands at a run, several times W*k*d floats and 32 GiB at most
  * (a kernel that needs none takes over where there is no room).  *out is set only on success and must be released with asgd_destroy().
  */
@@ -165,7 +166,7 @@ int asgd_set_option(asgd_ctx *ctx, int key, double value);
  * Effects: every worker's state is set to the first k rows of its own shard, exchange
  * buffers, counters and the step counter are cleared.  Synchronises the stream.
  * Column maxima are formed over all rows, where the streaming kernel runs over a part of them: it looks out for larger elements
- * in the first epoch.
+ * in the first epoch, forms the steps that hold one a second time, and knows them from then on.
  */
 int asgd_load_shards(asgd_ctx *ctx, const float *x_dev, int64_t N, void *hip_stream);
 

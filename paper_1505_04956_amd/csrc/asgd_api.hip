@@ -333,7 +333,8 @@ int take_limits(asgd_ctx *c, const SeenSteps &seen, StepParams *p)
 //   mini-batches of 512 and more: W = 4, k = 12, d = 8: b = 512 20, 17; b = 2000 50, 26; W = 32, k = 64, d = 32, b = 512: 24, 23;
 //     k = d = 100: W = 4 72, 45; W = 256 84, 79 (150 samples: W = 32, k = 64, d = 32: 14, 21).  A call of one step: 0.94 to 1.7
 //     times as fast.  Not where the workers fill the device and exchange (one launch with waits on either side) and steps are
-//     short (W = 256, b = 512, k = 64, d = 32: 34, 37; k = 12, d = 8: 27.6, 28);
+//     short (W = 256, b = 512: k = 64, d = 32: 34, 37; k = 12, d = 8: 27.6, 28, both with workers that are not kept; the split
+//     kernels keep them now and are the faster ones here, E = 8 29.2, 20.8 and 25.4, 12.2, but the line has not been moved);
 //   k > 256, any mini-batch: a state that does not fit the LDS as fp32 is streamed (k = 1000, d = 64, b = 16, W = 4: 125, 56); one
 //     that does: k = 300, d = 16, b = 64: W = 4 29, 27; W = 200 39, 34; k = 500, d = 24: W = 200 52, 51, but W = 4 42, 48;
 //   exchange at every step, 100 workers and more: always (fp32 waits for messages every step: W = 150, k = 12, d = 8, b = 100: 33,

@@ -68,7 +68,7 @@ struct LoadParams {
     float *sample, *sample_part;      // (set by launch_load)
     int *arrived, *found;
 };
-constexpr int FOUND_MAX = 4096;       // (some 60 per column where one in 128 elements is looked at and the tails are heavy)
+constexpr int FOUND_MAX = 4096;       // (one in n elements looked at, n <= 128: some n per column at most, if the tails are heavy)
 __host__ __device__ inline size_t found_entry(int d, int n) { return 1 + (size_t)n * (2 + d); }      // word of entry n
 // What asgd_load_shards() begins with.  sample_scratch (may be null; d <= 16): sample_scratch_bytes() of device memory, zero before the
 // first use; its first d floats become maxima of |x_j| over a part of the samples.

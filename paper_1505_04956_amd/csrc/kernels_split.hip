@@ -137,7 +137,7 @@ Scratch scratch_layout(const StepParams &p, const SplitPlan &q)
 
 }  // namespace
 
-// Kept workers: what a step needs besides messages is in the LDS when it begins, so it takes 11 to 25 us and never a launch, also
+// Kept workers: what a step needs besides messages is in the LDS when it begins, and it never needs a launch, also
 // with a message every step.  Microseconds per step of long calls, W = 256 (phases where E < 4, else the local form that is not kept; kept): k = 12,
 // d = 7: b = 100, E = 0 15.0, 11.2; b = 500, E = 0 17.5, 13.5; E = 2 26.5, 18.4; b = 2000, E = 4 52.9, 30.7; k = 64, d = 32, b = 500, E = 1 33.4, 24.6;
 // k = 100, d = 60, b = 120, E = 1 45.9, 37.5; k = 500, d = 8, b = 256, E = 1 47.5, 37.0; k = 400, d = 10, b = 1000, E = 2 59.6, 47.5.
