@@ -885,11 +885,12 @@ int asgd_run_steps(asgd_ctx *ctx, int64_t steps)
             }
             if (e == hipSuccess) {
                 ++launches;
-                const int rc = ran_to(tb, tb == cut && cut < t_end);
+                const bool waited = tb == cut && cut < t_end;
+                const int rc = ran_to(tb, waited);
                 if (rc != ASGD_OK) return rc;
                 t_done = tb;
                 ctx->passed_t = tb;
-                if (split_local && *ctx->flag_host) break;       // an expired wait: nothing more may run on these states
+                if ((split_local || waited) && *ctx->flag_host) break;       // an expired wait: nothing more may run on these states
             } else if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
                 (void)hipGetLastError();     // the rest (or all of it): one launch per round
                 break;

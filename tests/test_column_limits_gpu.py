@@ -225,3 +225,14 @@ def test_other_states(B, oracle, k, d, W, b):
     two.run_steps(3 * steps)                       # marked
     assert np.array_equal(one.get_state(), two.get_state())
     assert np.array_equal(one.worker_counters(), two.worker_counters())
+
+
+# a wait that expires before the cut (a sender that sends nothing, a tiny budget of polls): the rest of the call is not run
+def test_an_expired_wait_ends_a_call_that_is_cut(B, samples):
+    W, b = 300, 500
+    g = load(B, samples, W=W, b=b, E=2, drop_rate=1.0)
+    g.set_option(B.OPT_DROP_UNANNOUNCED, 1)
+    g.set_option(B.OPT_WAIT_POLLS, 50)
+    with pytest.raises(B.AsgdError) as e:
+        g.run_epochs(40)                           # more than 2^29 elements after the first epoch
+    assert e.value.code == B.ESYNC and g.stats().steps == 0 and g.stats().launches == 1
