@@ -63,6 +63,9 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
     // (two mini-batches of a kept worker: the next one arrives while the current one is worked on; a fetch writes whole KBs)
     q.batch_bytes = (unsigned)(((size_t)(b < 16384 ? b : 16384) * d * 4 + 1023) / 1024 * 1024);
     q.kept = local && q.fused && q.resident && q.nch <= SPLIT_KEPT_CHUNKS && W <= SPLIT_CUS && b <= 16384 && (size_t)o + 2 * (size_t)q.batch_bytes + SPLIT_LDS_SHARED <= SPLIT_LDS_ALL;
+    // (at whole KBs where there is room: k = 64, d = 32, W = 256, b = 500, E = 1, 31 steps 1303 -> 1300 us)
+    const unsigned whole = (o + 1023) / 1024 * 1024;
+    if (q.kept && (size_t)whole + 2 * (size_t)q.batch_bytes + SPLIT_LDS_SHARED <= SPLIT_LDS_ALL) o = whole;
     q.off_batch = o;
     if (q.kept) o += 2 * q.batch_bytes;
     q.lds = o;
