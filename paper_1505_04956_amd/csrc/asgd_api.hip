@@ -415,7 +415,7 @@ int asgd_create(asgd_ctx **out, int k, int d, int W, int b, float lr)
         {(void **)&c->assign_tmp, Wz * (size_t)b * sizeof(int)},
         {(void **)&c->ncum, Wz * k * sizeof(long long)},
         {(void **)&c->counters, Wz * CNT_STRIDE * sizeof(long long)},
-        {(void **)&c->qpart, (size_t)quant_partials_count() * sizeof(double) + (small ? sample_scratch_bytes(d) : 0)},
+        {(void **)&c->qpart, (size_t)quant_partials_count() * sizeof(double) + (small ? sample_scratch_bytes(d) : quant_operand_bytes(k, d))},
         {(void **)&c->qout, sizeof(double)},
     };
     for (auto &a : allocs) {

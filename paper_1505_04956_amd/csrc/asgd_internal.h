@@ -118,14 +118,15 @@ hipError_t launch_mfma_steps(const StepParams &p, long long t0, long long t1, co
 hipError_t launch_schedule_table(uint64_t seed, long long r0, int n, int W, int *shift_tab, hipStream_t s);
 hipError_t launch_broadcast_state(const float *src, int W, int kd, float *w, hipStream_t s);     // the same state to all workers
 hipError_t launch_mean_state(const float *w, int W, int kd, float *out, hipStream_t s);
-// Eq. 8 over rows [0, N): partials is scratch of quant_partials_count() doubles.
+// Eq. 8 over rows [0, N): partials is scratch of quant_partials_count() doubles with quant_operand_bytes() bytes after them.
 int quant_partials_count();
+size_t quant_operand_bytes(int k, int d);        // operands of a state that is split once per call (0: none kept)
 // specialisations of Eq. 8 (each fills `nblocks` <= quant_partials_count() partial sums; the generic launcher
 // below picks one and adds the partials in a fixed order)
 hipError_t launch_quant_error_small(const float *x, long long N, int d, int k, const float *w, double *partials, int nblocks,
                                     hipStream_t s);   // shapes of small_kernel_supports()
 bool split_quant_supports(int k, int d);
-hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, const float *w, double *partials, int nblocks,
+hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, const float *w, double *partials, void *operands, int *nblocks,
                                     bool nan_is_inf, hipStream_t s);
 bool mfma_quant_error_supports(int k, int d, const void *x);
 hipError_t launch_quant_error_mfma(const float *x, long long N, int d, int k, const float *w, double *partials,

@@ -655,13 +655,17 @@ int quant_partials_count() { return QE_BLOCKS; }
 // rows of d < 8 (20e6 samples: k = 20, d = 5: 1640, 1410; k = 40, d = 3: 1620, 1270; k = 100, d = 3: 1970, 3130; k = 4, d = 9:
 // 1030, 876; k = 12, d = 9: 1100, 2350; k = 2, d = 16: 1140, 1360).  Its workgroups split the state first, 20 us with the
 // launch, which few samples of small rows do not repay (1000 samples: k = 20, d = 9: 20, 29; k = 100, d = 9: 26, 82).
-// Against the fp32 matrix kernel it needs more than 128 centroids (k = d = 100: the same; k = 64, d = 32, 2e6 samples: 168,
-// 110), and samples enough for that start (k = 256, d = 16: 7e4 samples 29, 35; 2e6 216, 315; k = 300, d = 128: 2e4 70, 65, 7e4
-// 89, 112; k = 1024, d = 128: 7e4 200, 309).
+// Against the fp32 matrix kernel it needs work enough for its second launch, sooner with many centroids (k = 64, d = 64: 1.4e5 samples 30, 27, 3e5
+// 41, 39; k = 64, d = 32: 3e5 33, 25, 4e6 182, 235; k = 32, d = 128: 7e4 36, 33, 1.4e5 44, 45; k = d = 100: 3e4 25, 26, 1.4e5 43, 53; k = 300, d = 128: 2e4
+// 32, 63).  More than 128 centroids and 65536 samples: always, also where that was no faster, because the other kernel's scores are
+// relative to the origin and useless for data far from it.
 static bool quant_error_split_pays(const float *x, long long N, int d, int k)
 {
     if (!split_quant_supports(k, d)) return false;
-    if (mfma_quant_error_supports(k, d, x)) return k > 128 && N > 65536;
+    if (mfma_quant_error_supports(k, d, x)) {
+        const double work = (double)N * k * d;
+        return work > 1.2e9 || (k >= 96 && work > 3.0e8) || (k > 128 && N > 65536);
+    }
     return (d >= 16 || k * d > (d >= 8 ? 48 : 160)) && (N > 100000 || k * d > 150);
 }
 
@@ -674,8 +678,7 @@ hipError_t launch_quant_error(const float *x, long long N, int d, int k, const f
     if (small_kernel_supports(k, d, 1)) {
         e = launch_quant_error_small(x, N, d, k, w, partials, nparts, s);           // streaming shape: HBM bound
     } else if (quant_error_split_pays(x, N, d, k)) {
-        nparts = 256;                                                           // one workgroup per compute unit
-        e = launch_quant_error_split(x, N, d, k, w, partials, nparts, !mfma_quant_error_supports(k, d, x), s);
+        e = launch_quant_error_split(x, N, d, k, w, partials, partials + QE_BLOCKS, &nparts, !mfma_quant_error_supports(k, d, x), s);
     } else if (mfma_quant_error_supports(k, d, x)) {
         nparts = 256;                                                           // one workgroup per CU
         e = launch_quant_error_mfma(x, N, d, k, w, partials, nparts, s);       // contraction shape: matrix cores

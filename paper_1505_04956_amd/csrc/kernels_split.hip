@@ -1,20 +1,21 @@
 // Step kernel for any row length, host side: preparation of a call, sizes of the work items, launch.
 #include <string.h>
 
-#include "split_quant.h"
+#include "split_quant_screen.h"
 #include "split_steps.h"
 
 namespace asgd {
 
 hipError_t launch_split_quant_0(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_quant_1(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_2(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_3(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_4(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_5(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_6(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_7(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_8(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_1(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_2(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_3(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_4(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_5(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_6(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_7(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_screen_quant_8(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_local_0(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_assign_0(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s);
 hipError_t launch_split_local_1(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s);
@@ -294,32 +295,209 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, c
 // ---- Eq. 8 ----
 bool split_quant_supports(int k, int d) { return k >= 2 && k <= 8192 && d <= 8192; }
 
-hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, const float *w, double *partials, int nblocks,
+// One workgroup per pair of row blocks.  As the start of split_quant_kernel: m from nine rows, the scale of the state from the middle
+// of their sizes, h_c = -|v_c|^2/2 in scaled units, rows 2^10 times as large left out.
+__global__ __launch_bounds__(SPLITQ_THREADS) void splitq_operands_kernel(ScreenQuant a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ float most_of[16], red[4][8];
+    float *m = reinterpret_cast<float *>(smem);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const int k = a.q.k, d = a.q.d, dpad = a.q.dpad, nch = dpad / 16;
+    const float *w = a.q.w;
+    for (int j = tid; j < dpad; j += SPLITQ_THREADS) {
+        const float mid = splitq_middle_of(w, k, d, j);
+        m[j] = mid;
+        if (blockIdx.x == 0) a.m[j] = mid;
+    }
+    __syncthreads();
+    // largest |v_cj| of the nine rows, and of SCREENQ_ROWS samples (those that are finite)
+    auto widest = [&](const float *row) {
+        unsigned vb = 0;
+        for (int slot = lane; slot < dpad; slot += 64)
+            if (split_slot_used(slot, d)) vb = max(vb, __float_as_uint(row[split_column(slot, d)] - m[slot]) & 0x7fffffffu);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) vb = max(vb, (unsigned)__shfl_xor((int)vb, off, 64));
+        return __uint_as_float(min(vb, 0x7f800000u));
+    };
+    for (int r = wave; r < 9; r += 8) {
+        const float most = widest(w + (size_t)(r * k / 9) * d);
+        if (lane == 0) most_of[r] = most;
+    }
+    float far = 0.0f;
+#pragma unroll
+    for (int r = 0; r < SCREENQ_ROWS / 8; ++r) {
+        const float most = widest(a.q.x + (size_t)((8 * r + wave) * a.q.N / SCREENQ_ROWS) * d);
+        if (most < INFINITY) far = fmaxf(far, most);
+    }
+    if (lane == 0) red[0][wave] = far;
+    __syncthreads();
+    float nine[9];
+#pragma unroll
+    for (int r = 0; r < 9; ++r) nine[r] = most_of[r];
+    float typical = splitq_middle(nine);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) far = fmaxf(far, red[0][r]);
+    __syncthreads();
+    if (!(typical > 0.0f && typical < INFINITY)) {
+        // (at m itself: the largest of all the rows)
+        float most = 0.0f;
+        for (int c = wave; c < k; c += 8) {
+            const float v = widest(w + (size_t)c * d);
+            if (v < INFINITY) most = fmaxf(most, v);
+        }
+        if (lane == 0) red[0][wave] = most;
+        __syncthreads();
+        typical = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) typical = fmaxf(typical, red[0][r]);
+        __syncthreads();
+    }
+    const int sw_exp = splitq_exponent(typical, SPLITQ_TYPICAL);
+    const float sw = ldexpf(1.0f, sw_exp);
+    if (blockIdx.x == 0 && tid == 0) {
+        const int e = splitq_exponent(far, SCREENQ_SAMPLE), r = far > 0.0f ? min(e - sw_exp, SPLITQ_RATIO_MAX) : 0;
+        ScreenqHead h;
+        h.sw = sw; h.sw_exp = sw_exp;
+        h.ratio = ldexpf(1.0f, max(r, SPLITQ_RATIO_MIN));
+        h.direct = r < SPLITQ_RATIO_MIN || r + sw_exp < -126 || r + sw_exp > 126 ? 1.0f : 0.0f;
+        *reinterpret_cast<ScreenqHead *>(a.head) = h;
+    }
+    int g = 1;
+    while (g < dpad / 8) g *= 2;                              // (dpad <= 128: sixteen lanes at most)
+    float vmin = INFINITY, vmax = 0.0f, vfar = INFINITY, rest = 0.0f;
+    const int lane_g = tid & (g - 1), slot = 8 * lane_g;
+    for (int c0 = tid / g; c0 < 64; c0 += SPLITQ_THREADS / g) {
+        const int c = blockIdx.x * 64 + c0;
+        float v[8], sq = 0.0f, r2 = 0.0f;
+        unsigned vb = 0;
+        half8 hi, lo;
+        if (slot < dpad) splitq_row(v, w, m, c, k, slot, d);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const float y = slot < dpad ? v[e] * sw : 0.0f;
+            sq = fmaf(y, y, sq);
+            vb = max(vb, slot < dpad ? __float_as_uint(v[e]) & 0x7fffffffu : 0u);
+            hi[e] = (_Float16)y;
+            const float left = y - (float)hi[e];
+            lo[e] = (_Float16)left;
+            r2 = fmaf(left, left, r2);
+        }
+        for (int off = g / 2; off > 0; off >>= 1) {
+            sq += __shfl_xor(sq, off, 64);
+            r2 += __shfl_xor(r2, off, 64);
+            vb = max(vb, (unsigned)__shfl_xor((int)vb, off, 64));
+        }
+        const float most = __uint_as_float(min(vb, 0x7f800000u));
+        const bool scored = c < k && most * sw < (float)(1 << SPLITQ_LIMIT);
+        if (!scored) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) hi[e] = lo[e] = (_Float16)0.0f;
+        }
+        if (slot < dpad) {
+            const size_t at = ((((size_t)blockIdx.x * nch + (slot >> 4)) * 2 + (c0 >> 5)) * 64 + (c0 & 31) + 32 * ((slot >> 3) & 1)) * 16;
+            *reinterpret_cast<half8 *>(a.hi + at) = hi;
+            *reinterpret_cast<half8 *>(a.lo + at) = lo;
+        }
+        if (lane_g == 0) a.hs[c] = scored ? -0.5f * sq : SPLIT_PAD_SCORE;
+        if (scored) {
+            vmin = fminf(vmin, sq);
+            vmax = fmaxf(vmax, sq);
+            rest = fmaxf(rest, r2);
+        } else if (c < k && most < INFINITY) {
+            vfar = fminf(vfar, sq < 1.0e37f ? sq : 1.0e37f);
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        vmin = fminf(vmin, __shfl_xor(vmin, off, 64));
+        vmax = fmaxf(vmax, __shfl_xor(vmax, off, 64));
+        vfar = fminf(vfar, __shfl_xor(vfar, off, 64));
+        rest = fmaxf(rest, __shfl_xor(rest, off, 64));
+    }
+    if (lane == 0) { red[0][wave] = vmin; red[1][wave] = vmax; red[2][wave] = vfar; red[3][wave] = rest; }
+    __syncthreads();
+    if (tid < 4) {
+        float v = red[tid][0];
+        for (int r = 1; r < 8; ++r) v = (tid & 1) ? fmaxf(v, red[tid][r]) : fminf(v, red[tid][r]);
+        a.sizes[4 * blockIdx.x + tid] = v;
+    }
+}
+
+// Screening for rows of 8 to 128 columns, whatever k is; microseconds with three products for all samples, and screened: 4e6 samples, k = 12, d = 9: 164,
+// 100; k = 37, d = 75: 529, 333; k = 1000, d = 9: 917, 515; k = 1000, d = 32: 1040, 546; k = 100, d = 20: 303, 181; 2e6 samples, k = 512, d = 128:
+// 1227, 478; 20000 samples, k = 512, d = 125: 105, 38.  Also where prototypes lie close together and many samples stay undecided (k = 1000, d = 9,
+// sigma 0.3: 886, 439).  Shorter rows are loaded one by one, longer ones do not fit the registers.
+static bool quant_screens(int k, int d) { return split_quant_supports(k, d) && d >= 8 && d <= 128; }
+struct QuantOperands { size_t head, m, sizes, hs, hi, lo, bytes; };
+static QuantOperands quant_operands(int k, int d)
+{
+    const size_t npair = (size_t)(k + 63) / 64, dpad = split_padded_row(d);
+    QuantOperands l;
+    size_t o = 0;
+    auto take = [&](size_t bytes) { const size_t at = o; o += (bytes + 255) / 256 * 256; return at; };
+    l.head = take(sizeof(ScreenqHead));
+    l.m = take(dpad * 4);
+    l.sizes = take(npair * 16);
+    l.hs = take(npair * 64 * 4);
+    l.hi = take(npair * 64 * dpad * 2);
+    l.lo = take(npair * 64 * dpad * 2);
+    l.bytes = o;
+    return l;
+}
+size_t quant_operand_bytes(int k, int d) { return quant_screens(k, d) ? quant_operands(k, d).bytes : 0; }
+
+hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, const float *w, double *partials, void *operands, int *nblocks_out,
                                     bool nan_is_inf, hipStream_t s)
 {
     SplitQuant a;
     a.x = x; a.w = w; a.N = N; a.partials = partials; a.k = k; a.d = d;
-    a.dpad = d > 128 ? (d + 127) / 128 * 128 : (d + 15) / 16 * 16;
+    a.dpad = split_padded_row(d);
     a.nblk = (k + 31) / 32;
-    const int npair = (a.nblk + 1) / 2, chunks = d > 128 ? 8 : a.dpad / 16;
+    const int npair = (a.nblk + 1) / 2, chunks = d > 128 ? 8 : a.dpad / 16, nblocks = SPLIT_CUS;
+    *nblocks_out = nblocks;                       // one workgroup per compute unit
     a.kpad = npair * 64;
     a.nan_is_inf = nan_is_inf;
+    if (quant_screens(k, d)) {
+        ScreenQuant c;
+        c.q = a;
+        const QuantOperands l = quant_operands(k, d);
+        unsigned char *base = static_cast<unsigned char *>(operands);
+        c.head = (float *)(base + l.head); c.m = (float *)(base + l.m); c.sizes = (float *)(base + l.sizes); c.hs = (float *)(base + l.hs);
+        c.hi = base + l.hi; c.lo = base + l.lo;
+        hipLaunchKernelGGL(splitq_operands_kernel, dim3(npair), dim3(SPLITQ_THREADS), a.dpad * 4, s, c);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        unsigned o = split_round16((size_t)a.kpad * 4);
+        c.off_ms = o; o += split_round16((size_t)a.dpad * 4);
+        c.off_list = o; o += SCREENQ_WAVES * SCREENQ_LIST * 4;
+        c.off_stage = o = (o + 1023) / 1024 * 1024;
+        const unsigned pair = chunks * 2 * SPLIT_PIECE;
+        // The samples stay in the registers for their distances, with fewer tiles per wave, or come a second time: the first as long as the matrix
+        // work is small next to the memory (microseconds kept and not, 2e6 samples; d = 128: k = 16 253, 320, 128 260, 309, 192 389, 374, 512 539, 478; d = 80:
+        // k = 256 251, 269, 1024 491, 484; d = 64: k = 512 283, 276; up to 32 columns the tiles stay four: k = 1000, d = 20 534, 545).
+        c.keep = k <= (chunks <= 2 ? 8192 : chunks <= 6 ? 384 : 160);
+        c.pairs_per_stage = (int)((SPLIT_LDS_ALL / 2 - 256 - o) / (2 * pair));      // (at least one: 32 KB of offsets and 32 KB of operands at most)
+        if (c.pairs_per_stage > npair) c.pairs_per_stage = npair;
+        o += 2 * c.pairs_per_stage * pair;
+        *nblocks_out = 2 * SPLIT_CUS;
+        switch (chunks) {
+            case 1: return launch_screen_quant_1(c, 2 * SPLIT_CUS, o, s);
+            case 2: return launch_screen_quant_2(c, 2 * SPLIT_CUS, o, s);
+            case 3: return launch_screen_quant_3(c, 2 * SPLIT_CUS, o, s);
+            case 4: return launch_screen_quant_4(c, 2 * SPLIT_CUS, o, s);
+            case 5: return launch_screen_quant_5(c, 2 * SPLIT_CUS, o, s);
+            case 6: return launch_screen_quant_6(c, 2 * SPLIT_CUS, o, s);
+            case 7: return launch_screen_quant_7(c, 2 * SPLIT_CUS, o, s);
+            default: return launch_screen_quant_8(c, 2 * SPLIT_CUS, o, s);
+        }
+    }
     const size_t all = (size_t)npair * chunks * 4 * SPLIT_PIECE, two = (size_t)2 * chunks * 4 * SPLIT_PIECE;
     a.resident = d <= 128 && all + (size_t)(a.kpad + a.dpad) * 4 <= SPLIT_LDS;
     unsigned o = (unsigned)(a.resident ? all : two);
     a.off_hs = o; o += split_round16((size_t)a.kpad * 4);
     a.off_m = o;  o += split_round16((size_t)a.dpad * 4);
-    switch (d > 128 ? 0 : chunks) {
-        case 0: return launch_split_quant_0(a, nblocks, o, s);
-        case 1: return launch_split_quant_1(a, nblocks, o, s);
-        case 2: return launch_split_quant_2(a, nblocks, o, s);
-        case 3: return launch_split_quant_3(a, nblocks, o, s);
-        case 4: return launch_split_quant_4(a, nblocks, o, s);
-        case 5: return launch_split_quant_5(a, nblocks, o, s);
-        case 6: return launch_split_quant_6(a, nblocks, o, s);
-        case 7: return launch_split_quant_7(a, nblocks, o, s);
-        default: return launch_split_quant_8(a, nblocks, o, s);
-    }
+    return d > 128 ? launch_split_quant_0(a, nblocks, o, s) : launch_split_quant_1(a, nblocks, o, s);
 }
 
 }  // namespace asgd

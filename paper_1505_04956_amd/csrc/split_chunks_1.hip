@@ -1,5 +1,5 @@
 // Step and Eq. 8 kernels for rows of 1 to 16 columns.
-#include "split_quant.h"
+#include "split_quant_screen.h"
 #include "split_steps.h"
 
 namespace asgd {
@@ -15,6 +15,10 @@ hipError_t launch_split_assign_1(const SplitLaunch &l, int blocks, int threads, 
 hipError_t launch_split_quant_1(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s)
 {
     return split_launch_quant<1>(a, blocks, lds, s);
+}
+hipError_t launch_screen_quant_1(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s)
+{
+    return a.keep ? launch_screen_quant<1, true>(a, blocks, lds, s) : launch_screen_quant<1, false>(a, blocks, lds, s);
 }
 
 }  // namespace asgd

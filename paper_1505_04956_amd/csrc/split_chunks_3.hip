@@ -1,5 +1,5 @@
 // Step and Eq. 8 kernels for rows of 33 to 48 columns.
-#include "split_quant.h"
+#include "split_quant_screen.h"
 #include "split_steps.h"
 
 namespace asgd {
@@ -12,9 +12,9 @@ hipError_t launch_split_assign_3(const SplitLaunch &l, int blocks, int threads, 
 {
     return split_launch_phase<13>(l, blocks, threads, lds, s);
 }
-hipError_t launch_split_quant_3(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s)
+hipError_t launch_screen_quant_3(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s)
 {
-    return split_launch_quant<3>(a, blocks, lds, s);
+    return a.keep ? launch_screen_quant<3, true>(a, blocks, lds, s) : launch_screen_quant<3, false>(a, blocks, lds, s);
 }
 
 }  // namespace asgd

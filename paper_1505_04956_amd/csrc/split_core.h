@@ -357,6 +357,30 @@ __device__ __forceinline__ void split_convert(const float (&v)[8], float s, cons
     }
 }
 
+// 1 KB pieces [0, n) from global memory to LDS, the waves of the workgroup in turn; no registers pass the data
+__device__ __forceinline__ void split_stage(const unsigned char *src, unsigned char *dst, int n)
+{
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
+    for (int q = wave; q < n; q += nw)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (size_t)q * SPLIT_PIECE + lane * 16),
+                                         (__attribute__((address_space(3))) void *)(dst + q * SPLIT_PIECE), 16, 0, 0);
+}
+__device__ __forceinline__ void split_stage_wait()
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
+
+__device__ __forceinline__ void split_init_acc(sfloatx16 &acc, const float *hs, int block, int half)
+{
+    const float4 *hp = reinterpret_cast<const float4 *>(hs + block * 32 + 4 * half);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float4 h = hp[2 * q];
+        acc[4 * q + 0] = h.x; acc[4 * q + 1] = h.y; acc[4 * q + 2] = h.z; acc[4 * q + 3] = h.w;
+    }
+}
+
 }  // namespace
 
 }  // namespace asgd

@@ -1,4 +1,5 @@
-// Eq. 8 on the fp16 matrix instructions, any row length.  Scores with fp16-split operands (split_core.h) only screen: the
+// Eq. 8 on the fp16 matrix instructions, rows of less than 8 and of more than 128 columns (the others: split_quant_screen.h, which shares
+// the decisions and what follows about odd rows).  Scores with fp16-split operands (split_core.h) only screen: the
 // error of a score is bounded, and a sample whose runner-up lies within the bound is decided by distances in direct form -
 // two candidates by theirs, more by those to all the centroids.  So every sample adds the smallest of its direct fp32
 // distances, whatever the scores are worth, and the sum over the samples is fp64.
@@ -66,6 +67,20 @@ __device__ __forceinline__ float splitq_middle(const float (&v)[9])
 {
     return __builtin_amdgcn_fmed3f(__builtin_amdgcn_fmed3f(v[0], v[1], v[2]), __builtin_amdgcn_fmed3f(v[3], v[4], v[5]),
                                    __builtin_amdgcn_fmed3f(v[6], v[7], v[8]));
+}
+
+// of nine rows spread over the state, the column of slot j
+__device__ __forceinline__ float splitq_middle_of(const float *w, int k, int d, int j)
+{
+    if (!split_slot_used(j, d)) return 0.0f;
+    const float *col = w + split_column(j, d);
+    float v[9];
+#pragma unroll
+    for (int q = 0; q < 9; ++q) v[q] = col[(size_t)(q * k / 9) * d];
+#pragma unroll
+    for (int q = 0; q < 9; ++q)
+        if (!(fabsf(v[q]) < INFINITY)) v[q] = 0.0f;
+    return splitq_middle(v);
 }
 
 // exponent of the power of two that takes `most` to [2^(to - 1), 2^to) (some exponent when it is zero or not finite)
@@ -203,11 +218,13 @@ __device__ __forceinline__ u64 splitq_uniform(u64 v)
 // registers; what is uniform is read back into scalar ones.
 typedef const __attribute__((address_space(4))) SplitQuant *SplitQuantPtr;
 struct SplitqSize { float vmin, vmax, vfar; };       // of the scored rows, scaled; smallest |v_c| of those that are not scored
-template <bool TAIL>
+// LISTED: gw is the lane's own sample, below zero if it has none.
+template <bool TAIL, bool LISTED>
 __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any, SplitTop t, float n2, float ratio, bool direct, SplitqSize size)
 {
     const SplitQuantPtr a = (SplitQuantPtr)splitq_uniform(args);
-    const long long gw = (long long)splitq_uniform((u64)gw_any), N = a->N;
+    const long long gw = LISTED ? gw_any : (long long)splitq_uniform((u64)gw_any), N = a->N;
+    auto sample = [&](int at) -> long long { return LISTED ? (long long)__shfl((long long)gw, at, 64) : (gw + at < N ? gw + at : -1); };
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31, k = a->k, d = a->d;
     const float *x = a->x, *w = a->w;
     const int arg = min(max(t.i1, 0), k - 1), second = min(max(t.i2, 0), k - 1);
@@ -216,7 +233,7 @@ __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any,
         const float yn = sqrtf(n2) * 1.0001f, yr = yn / ratio;              // |y|, and in the units of the state
         const float v = fminf(size.vmax, 4.0f * yr + 2.0f * size.vmin);
         const float thr = split_c1(a->dpad) * (yn * v + 0.5f * v * v * ratio) + split_c2(a->dpad) * (yn + v);
-        const bool valid = gw + lane < N;
+        const bool valid = LISTED ? gw >= 0 : gw + lane < N;
         // no scored row, scores out of their range (or not a number), a row that was not scored may be nearest
         const bool all = direct || !(yn < 1.0e18f) || !(size.vmin < INFINITY) ||
                          (size.vfar < INFINITY && !(2.02f * yr + size.vmin < size.vfar));
@@ -226,11 +243,11 @@ __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any,
     const unsigned long long pairs = __ballot(close2 && !close3), many = __ballot(close3);
     float scanned = INFINITY;
     if (many) {
-        const float *xl = x + (size_t)(gw + lane < N ? gw + lane : N - 1) * d;
+        const float *xl = x + (size_t)(LISTED ? max(gw, 0LL) : gw + lane < N ? gw + lane : N - 1) * d;
         if (__popcll(many) <= 8) {
             for (unsigned long long left = many; left; left &= left - 1) {
                 const int L = __builtin_ctzll(left);           // (a valid sample)
-                const float best = splitq_scan_wave(x + (size_t)(gw + L) * d, w, k, d, lane);
+                const float best = splitq_scan_wave(x + (size_t)sample(L) * d, w, k, d, lane);
                 if (lane == L) scanned = best;
             }
         } else if (close3) {
@@ -245,8 +262,8 @@ __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any,
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int at = 32 * q + l32;
-        const long long n = gw + at;
-        const float *row = x + (size_t)(n < N ? n : N - 1) * d;
+        const long long n = sample(at);
+        const float *row = x + (size_t)(n < 0 ? N - 1 : n) * d;
         float d2 = splitq_distance<TAIL>(row, w + (size_t)__shfl(arg, at, 64) * d, d, half);
         d2 += __shfl_xor(d2, 32, 64);
         if (pairs) {
@@ -257,7 +274,7 @@ __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any,
         }
         const float s2 = __shfl(scanned, at, 64);
         if (many >> at & 1) d2 = s2;
-        if (half == 0 && n < N) sum += 0.5 * (double)d2;
+        if (half == 0 && n >= 0) sum += 0.5 * (double)d2;
     }
     return sum;
 }
@@ -265,7 +282,7 @@ __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any,
 template <bool TAIL>
 __device__ __noinline__ double splitq_finish(u64 args, long long gw, SplitTop t, float n2, float ratio, bool direct, SplitqSize size)
 {
-    return splitq_finish_here<TAIL>(args, gw, t, n2, ratio, direct, size);
+    return splitq_finish_here<TAIL, false>(args, gw, t, n2, ratio, direct, size);
 }
 
 template <int NC>
@@ -284,20 +301,7 @@ __global__ __launch_bounds__(SPLITQ_THREADS) __attribute__((amdgpu_waves_per_eu(
         return;
     }
     // m by slot: middle of nine rows spread over the state (any value would do; one near the data keeps the operands small)
-    for (int j = tid; j < a.dpad; j += SPLITQ_THREADS) {
-        float mid = 0.0f;
-        if (split_slot_used(j, d)) {
-            const float *col = a.w + split_column(j, d);
-            float v[9];
-#pragma unroll
-            for (int q = 0; q < 9; ++q) v[q] = col[(size_t)(q * k / 9) * d];
-#pragma unroll
-            for (int q = 0; q < 9; ++q)
-                if (!(fabsf(v[q]) < INFINITY)) v[q] = 0.0f;
-            mid = splitq_middle(v);
-        }
-        m[j] = mid;
-    }
+    for (int j = tid; j < a.dpad; j += SPLITQ_THREADS) m[j] = splitq_middle_of(a.w, k, d, j);
     __syncthreads();
     // Two passes over the state, g lanes per row.  First the largest |v_cj| of every row (infinite if one is not finite), from
     // which the scale follows; then h_c = -|v_c|^2/2 in scaled units and the smallest and largest |v_c|.
@@ -608,7 +612,7 @@ __global__ __launch_bounds__(SPLITQ_THREADS) __attribute__((amdgpu_waves_per_eu(
         SplitTop t;
         split_combine(top, t, half);
         swap2(n2[0], n2[1]);
-        if constexpr (NC == 0) sum += splitq_finish_here<false>((u64)args, gw, t, n2[0] + n2[1], half ? ratio[1] : ratio[0], half ? direct[1] : direct[0], size);
+        if constexpr (NC == 0) sum += splitq_finish_here<false, false>((u64)args, gw, t, n2[0] + n2[1], half ? ratio[1] : ratio[0], half ? direct[1] : direct[0], size);
         else sum += splitq_finish<NC % 4 != 0>((u64)args, gw, t, n2[0] + n2[1], half ? ratio[1] : ratio[0], half ? direct[1] : direct[0], size);
     }
     sum = split_wave_sum(sum);

@@ -194,20 +194,6 @@ __device__ inline void split_flush(SPLIT_ARG SplitArgs &a, int worker, int share
     for (int c = threadIdx.x; c < a.k; c += blockDim.x) oc[c] = cnt[c];
 }
 
-// 1 KB pieces [0, n) from global memory to LDS, the waves of the workgroup in turn; no registers pass the data
-__device__ __forceinline__ void split_stage(const unsigned char *src, unsigned char *dst, int n)
-{
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nw = blockDim.x >> 6;
-    for (int q = wave; q < n; q += nw)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (size_t)q * SPLIT_PIECE + lane * 16),
-                                         (__attribute__((address_space(3))) void *)(dst + q * SPLIT_PIECE), 16, 0, 0);
-}
-__device__ __forceinline__ void split_stage_wait()
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-}
-
 // A mini-batch of a kept worker on its way to the LDS.
 __device__ __forceinline__ void split_batch_fetch(SPLIT_ARG SplitArgs &a, int worker, long long row0, unsigned char *dst)
 {
@@ -221,16 +207,6 @@ __device__ __forceinline__ void split_batch_fetch(SPLIT_ARG SplitArgs &a, int wo
         for (int q = wave; q * 64 < total; q += nw)
             __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + min(q * 64 + lane, total - 1)),
                                              (__attribute__((address_space(3))) void *)(dst + q * 256), 4, 0, 0);
-    }
-}
-
-__device__ __forceinline__ void split_init_acc(sfloatx16 &acc, const float *hs, int block, int half)
-{
-    const float4 *hp = reinterpret_cast<const float4 *>(hs + block * 32 + 4 * half);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const float4 h = hp[2 * q];
-        acc[4 * q + 0] = h.x; acc[4 * q + 1] = h.y; acc[4 * q + 2] = h.z; acc[4 * q + 3] = h.w;
     }
 }
 
