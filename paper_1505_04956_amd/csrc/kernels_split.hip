@@ -201,6 +201,7 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, c
     a.vec4 = p.d % 4 == 0 && ((uintptr_t)p.x & 15u) == 0;
     a.kept = q.kept; a.off_batch = q.off_batch; a.batch_bytes = q.batch_bytes;
     a.off_cells = q.off_cells; a.off_cnt = q.off_cnt; a.off_hs = q.off_hs; a.off_ms = q.off_ms; a.off_args = q.off_args;
+    a.stage_pairs = q.stage_pairs; a.stages = q.stages; a.off_list = q.off_list;
     SplitUpdate u;
     u.frag = base + l.frag; u.hs = (float *)(base + l.hs);
     u.state = (SplitState *)(base + l.state); u.gate = (SplitGate *)(base + l.gate); u.mail = (SplitMail *)(base + l.mail);

@@ -187,31 +187,107 @@ __device__ inline int split_scan_own(const float *xl, const float *w, int k, int
     return arg;
 }
 
-// The exact-arithmetic nearest centroid of the fp32 state for the samples of a wave: lane l owns the sample in row l of
-// `xg` (valid or not), `t` its best scores.  Closer than thr: decided in fp64, two candidates by the sign of
+// Nearest of the rows [c_lo, c_hi) in fp64 to ONE sample, by a wave: sixteen lanes per centroid, four columns each, so that sixteen centroids are in
+// flight (a lane per centroid was a chain of d loads and took 0.2 ms for one sample, k = 256, d = 384).
+__device__ __forceinline__ void split_scan_wave(const float *xl, const float *w, int c_lo, int c_hi, int d, double &best, int &barg)
+{
+    const int lane = split_lane(), l16 = lane & 15, quarter = lane >> 4;
+    best = INFINITY;
+    barg = 0;
+    for (int c0 = c_lo; c0 < c_hi; c0 += 16) {
+        double sd[4] = {0.0, 0.0, 0.0, 0.0};
+        const float *wr[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) wr[q] = w + (size_t)min(c0 + 4 * q + quarter, c_hi - 1) * d;
+        for (int j = 4 * l16; j < d; j += 64) {
+            float xv[4], wv[4][4];
+            if (j + 4 <= d) {
+                const float4u x4 = *reinterpret_cast<const float4u *>(xl + j);
+                float4u w4[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w4[q] = *reinterpret_cast<const float4u *>(wr[q] + j);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    xv[e] = x4[e];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) wv[q][e] = w4[q][e];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const bool in = j + e < d;
+                    xv[e] = in ? xl[j + e] : 0.0f;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) wv[q][e] = in ? wr[q][j + e] : 0.0f;
+                }
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double diff = (double)xv[e] - (double)wv[q][e];
+                    sd[q] += diff * diff;
+                }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) sd[q] += __shfl_xor(sd[q], off, 64);
+            const int cq = c0 + 4 * q + quarter;
+            if (cq < c_hi && sd[q] < best) { best = sd[q]; barg = cq; }
+        }
+    }
+#pragma unroll
+    for (int off = 32; off > 8; off >>= 1) {
+        const double ob = __shfl_xor(best, off, 64);
+        const int oa = __shfl_xor(barg, off, 64);
+        if (ob < best || (ob == best && oa < barg)) { best = ob; barg = oa; }
+    }
+}
+
+// The exact-arithmetic nearest centroid of the fp32 state for the samples of a wave: a lane owns the sample in row `own` of
+// `xb` (valid or not, that of lane 0 always), `t` its best scores.  Closer than thr: decided in fp64, two candidates by the sign of
 // sum_j (w_aj - w_bj)(w_aj + w_bj - 2 x_j), more by all k distances in direct form; the lowest index wins exact ties.
 // thr may be infinite (then everything is decided in fp64); scores may be NaN.
-__device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool valid, const float *xg, const float *w, int k, int d,
-                                   int &rechecks)
+// DEFER: where all k distances are asked for, the sample's row goes to the workgroup's list `hard` as long as there is room, and the
+// result is -1 (split_scan_hard()).
+template <bool DEFER>
+__device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool valid, const float *xb, int own, const float *w, int k,
+                                            int d, int &rechecks, int *hard = nullptr, int *hard_count = nullptr)
 {
     const int lane = split_lane();
     int arg = min(max(t.i1, 0), k - 1);
     const int second = min(max(t.i2, 0), k - 1);
     const bool close2 = valid && !(t.v1 - t.v2 > thr);
-    const bool close3 = close2 && (!(t.v1 - t.v3 > thr) || __float_as_int(t.v1) == __float_as_int(t.v2) || second == arg);
+    bool close3 = close2 && (!(t.v1 - t.v3 > thr) || __float_as_int(t.v1) == __float_as_int(t.v2) || second == arg);
     rechecks += close2 ? 1 : 0;
     unsigned long long pm = __ballot(close2 && !close3);
+    if constexpr (DEFER) {
+        const unsigned long long all = __ballot(close3);
+        if (all) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(hard_count, __popcll(all));
+            const int at = __builtin_amdgcn_readfirstlane(base) + __popcll(all & ((1ULL << lane) - 1));
+            if (close3 && at < SPLIT_HARD) {
+                hard[at] = own;
+                arg = -1;
+                close3 = false;
+            }
+        }
+    }
     while (pm) {
-        int L[4], ca[4], cb[4];
+        int L[4], ca[4], cb[4], at[4];
         double dd[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             L[q] = -1; ca[q] = 0; cb[q] = 0; dd[q] = 0.0;
+            at[q] = __builtin_amdgcn_readfirstlane(own);
             if (pm) {
                 L[q] = __builtin_ctzll(pm);
                 pm &= pm - 1;
                 ca[q] = __builtin_amdgcn_readlane(arg, L[q]);
                 cb[q] = __builtin_amdgcn_readlane(second, L[q]);
+                at[q] = __builtin_amdgcn_readlane(own, L[q]);
             }
         }
         for (int j0 = 0; j0 < d; j0 += 128) {
@@ -223,7 +299,7 @@ __device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool v
                 for (int q = 0; q < 4; ++q) {
                     wa[h][q] = w[(size_t)ca[q] * d + jc];
                     wb[h][q] = w[(size_t)cb[q] * d + jc];
-                    xx[h][q] = xg[(size_t)(L[q] < 0 ? 0 : L[q]) * d + jc];                  // row 0 is always a valid one
+                    xx[h][q] = xb[(size_t)at[q] * d + jc];
                 }
             }
 #pragma unroll
@@ -243,69 +319,19 @@ __device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool v
     }
     unsigned long long fm = __ballot(close3);
     if (__popcll(fm) <= 8) {
-        // few: one sample at a time; sixteen lanes per centroid, four columns each, so that sixteen centroids are in
-        // flight (a lane per centroid was a chain of d loads and took 0.2 ms for one sample, k = 256, d = 384)
-        const int l16 = lane & 15, quarter = lane >> 4;
+        // few: one sample at a time
         while (fm) {
             const int L = __builtin_ctzll(fm);
             fm &= fm - 1;
-            const float *xl = xg + (size_t)L * d;
-            double best = INFINITY;
-            int barg = 0;
-            for (int c0 = 0; c0 < k; c0 += 16) {
-                double sd[4] = {0.0, 0.0, 0.0, 0.0};
-                const float *wr[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) wr[q] = w + (size_t)min(c0 + 4 * q + quarter, k - 1) * d;
-                for (int j = 4 * l16; j < d; j += 64) {
-                    float xv[4], wv[4][4];
-                    if (j + 4 <= d) {
-                        const float4u x4 = *reinterpret_cast<const float4u *>(xl + j);
-                        float4u w4[4];
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) w4[q] = *reinterpret_cast<const float4u *>(wr[q] + j);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            xv[e] = x4[e];
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) wv[q][e] = w4[q][e];
-                        }
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const bool in = j + e < d;
-                            xv[e] = in ? xl[j + e] : 0.0f;
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) wv[q][e] = in ? wr[q][j + e] : 0.0f;
-                        }
-                    }
-#pragma unroll
-                    for (int q = 0; q < 4; ++q)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const double diff = (double)xv[e] - (double)wv[q][e];
-                            sd[q] += diff * diff;
-                        }
-                }
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-#pragma unroll
-                    for (int off = 8; off > 0; off >>= 1) sd[q] += __shfl_xor(sd[q], off, 64);
-                    const int cq = c0 + 4 * q + quarter;
-                    if (cq < k && sd[q] < best) { best = sd[q]; barg = cq; }
-                }
-            }
-#pragma unroll
-            for (int off = 32; off > 8; off >>= 1) {
-                const double ob = __shfl_xor(best, off, 64);
-                const int oa = __shfl_xor(barg, off, 64);
-                if (ob < best || (ob == best && oa < barg)) { best = ob; barg = oa; }
-            }
+            const float *xl = xb + (size_t)__builtin_amdgcn_readlane(own, L) * d;
+            double best;
+            int barg;
+            split_scan_wave(xl, w, 0, k, d, best, barg);
             // (no distance below infinity: centroid 0, like a scan that starts there)
             if (lane == L) arg = best < INFINITY ? barg : 0;
         }
     } else if (close3) {
-        arg = split_scan_own(xg + (size_t)lane * d, w, k, d);
+        arg = split_scan_own(xb + (size_t)own * d, w, k, d);
     }
     return arg;
 }
@@ -379,6 +405,13 @@ __device__ __forceinline__ void split_init_acc(sfloatx16 &acc, const float *hs, 
         const float4 h = hp[2 * q];
         acc[4 * q + 0] = h.x; acc[4 * q + 1] = h.y; acc[4 * q + 2] = h.z; acc[4 * q + 3] = h.w;
     }
+}
+
+// (a call passes its arguments in vector registers; what is uniform is read back into scalar ones)
+__device__ __forceinline__ u64 split_uniform64(u64 v)
+{
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
+    return (u64)hi << 32 | lo;
 }
 
 }  // namespace

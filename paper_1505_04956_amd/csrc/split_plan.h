@@ -12,12 +12,18 @@ constexpr unsigned SPLIT_LDS_SHARED = 512;        // what all phases share, befo
 constexpr unsigned SPLIT_LDS_ALL = 160 * 1024;    // LDS of a compute unit
 constexpr unsigned SPLIT_LDS = 150 * 1024;        // what operands and cells may take of it
 constexpr int SPLIT_CUS = 256;
+constexpr int SPLIT_HARD = 32;                    // samples that may wait for a scan of all the rows by a whole workgroup
+constexpr int SPLIT_LISTED = 128;                 // of them at a time
+constexpr int SPLIT_LIST = 2048;                  // undecided samples of a screened mini-batch that are noted before they are scored again
 constexpr int SPLIT_KEPT_CHUNKS = 4;              // longest rows of a kept worker: beyond, its kernel needs more registers than there are
 
 struct SplitPlan {
     int nch, dpad, nblk, kpad, npair;
     size_t frag_bytes;
     bool longrow, fused, resident, kept;
+    bool screen;                   // samples are screened (split_screen.h)
+    int stage_pairs, stages;       // row pairs of a stage of high parts; stages of the state (one: it stays)
+    unsigned off_list;
     int waves, shares, share_len, grid;
     unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes, lds;
     int dc, ncol, sum_shares, sum_len;      // sums in a launch of their own: columns per workgroup, shares
@@ -52,7 +58,22 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
         q.fused = false;
         q.resident = q.frag_bytes + fixed <= SPLIT_LDS;
     }
+    // Screening (split_screen.h) saves two of three products and pays one pass over the state, and barriers, for the few samples it leaves open: where
+    // the state has to be streamed in any case and a step is one workgroup's.  Microseconds of a step, all three products and
+    // screened: k = 1024, d = 128: b = 100 323, 348, 500 383, 373, 2000 705, 543, 4096 1130, 780; k = 512, d = 128: b = 1000 293, 288, 4096 685, 544; k = 1024, d = 64: b = 1500
+    // 318, 254.  (Not where the state stays in the LDS: k = 200, d = 100, b = 2000 119, 142; not in phases, whose launches are
+    // as long as the slowest of the workgroups with something left open: k = 300, d = 128, W = 8, b = 500 36, 57.)
+    q.screen = local && !q.longrow && !q.fused && !q.resident && q.nch >= 2 && b >= 384;
     unsigned o = split_round16(q.resident ? q.frag_bytes : stage2);
+    if (q.screen) {
+        const size_t pair = (size_t)q.nch * 2 * SPLIT_PIECE, others = fixed + SPLIT_LIST * 4, listed = (size_t)SPLIT_LISTED / 32 * (q.nch > 3 ? q.nch : 3) * 2 * SPLIT_PIECE;      // (operands, then the best scores of eight waves)
+        q.resident = false;
+        q.stage_pairs = q.npair;
+        if (q.npair * pair + others > SPLIT_LDS) q.stage_pairs = (int)((SPLIT_LDS - others) / (2 * pair));
+        q.stages = (q.npair + q.stage_pairs - 1) / q.stage_pairs;
+        o = (unsigned)((q.stages > 1 ? 2 : 1) * q.stage_pairs * pair);
+        if (o < listed) o = (unsigned)listed;
+    }
     q.off_cells = o;
     if (q.fused) o += split_round16((size_t)k * ((d + 1) & ~1) * 8);
     q.off_cnt = o;
@@ -60,6 +81,7 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
     q.off_hs = o;  o += split_round16((size_t)q.kpad * 4);
     q.off_ms = o;  o += split_round16((size_t)q.dpad * 4);
     q.off_args = o; o += 8 * 64 * 4 * (q.longrow ? 5 : 1);
+    q.off_list = o; o += q.screen ? SPLIT_LIST * 4 : 0;
     // (two mini-batches of a kept worker: the next one arrives while the current one is worked on; a fetch writes whole KBs)
     q.batch_bytes = (unsigned)(((size_t)(b < 16384 ? b : 16384) * d * 4 + 1023) / 1024 * 1024);
     q.kept = local && q.fused && q.resident && q.nch <= SPLIT_KEPT_CHUNKS && W <= SPLIT_CUS && b <= 16384 && (size_t)o + 2 * (size_t)q.batch_bytes + SPLIT_LDS_SHARED <= SPLIT_LDS_ALL;

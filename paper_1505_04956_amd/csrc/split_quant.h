@@ -205,12 +205,6 @@ __device__ inline float splitq_scan_wave(const float *xl, const float *w, int k,
     return fminf(best, __shfl_xor(best, 32, 64));
 }
 
-__device__ __forceinline__ u64 splitq_uniform(u64 v)
-{
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)v), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(v >> 32));
-    return (u64)hi << 32 | lo;
-}
-
 // What the samples of a wave add to Eq. 8 once their scores are known (lane l: sample gw + l).  For rows whose operands stay in
 // registers this is a function that is really called, with registers of its own: inlined, what it needs was kept across the
 // loop over the samples (k = 1024, d = 128, 5e6 samples: 6.1 ms, called 4.9); for long rows the registers saved around the
@@ -222,8 +216,8 @@ struct SplitqSize { float vmin, vmax, vfar; };       // of the scored rows, scal
 template <bool TAIL, bool LISTED>
 __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any, SplitTop t, float n2, float ratio, bool direct, SplitqSize size)
 {
-    const SplitQuantPtr a = (SplitQuantPtr)splitq_uniform(args);
-    const long long gw = LISTED ? gw_any : (long long)splitq_uniform((u64)gw_any), N = a->N;
+    const SplitQuantPtr a = (SplitQuantPtr)split_uniform64(args);
+    const long long gw = LISTED ? gw_any : (long long)split_uniform64((u64)gw_any), N = a->N;
     auto sample = [&](int at) -> long long { return LISTED ? (long long)__shfl((long long)gw, at, 64) : (gw + at < N ? gw + at : -1); };
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31, k = a->k, d = a->d;
     const float *x = a->x, *w = a->w;

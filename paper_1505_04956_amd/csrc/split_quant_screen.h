@@ -55,7 +55,7 @@ template <int NC>
 __device__ __noinline__ double screenq_listed(u64 args, long long own, SplitqSize size, int sw_exp_any)
 {
     typedef const __attribute__((address_space(4))) ScreenQuant *Ptr;
-    const Ptr a = (Ptr)splitq_uniform(args);
+    const Ptr a = (Ptr)split_uniform64(args);
     const int sw_exp = __builtin_amdgcn_readfirstlane(sw_exp_any);
     const int lane = split_lane(), half = lane >> 5, l32 = lane & 31, d = a->q.d, nblk = a->q.nblk;
     const float *m = a->m;

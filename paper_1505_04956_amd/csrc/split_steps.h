@@ -9,7 +9,7 @@
 // write-back and invalidation of the L2 by every workgroup; 35 us per step where phases take 22.)
 #pragma once
 
-#include "split_core.h"
+#include "split_screen.h"
 
 namespace asgd {
 
@@ -21,7 +21,8 @@ constexpr int SPLIT_THREADS = 512;
 struct SplitState {                // one per worker and step modulo 3
     float sw;                      // scale of the operands
     unsigned vabs, n2;             // bit patterns of the largest |v_cj| and of the largest |sw v_c|^2; above those of all numbers if not finite
-    unsigned pad[29];              // a cache line each: atomics on one line wait for each other, and that took 15 us
+    unsigned rest;                 // of the largest |sw v_c - its high parts|^2
+    unsigned pad[28];              // a cache line each: atomics on one line wait for each other, and that took 15 us
 };
 
 struct SplitSize { float sw; unsigned vabs, n2; };
@@ -58,15 +59,19 @@ struct SplitArgs {
     int shares, share_len;           // share_len: samples of a share, a multiple of 64
     int sum_shares, sum_len, dc, ncol;       // sums in a phase of their own: shares, columns per item, groups of columns
     int resident, fused, vec4;
+    int stage_pairs, stages;         // screened samples
     int kept;                        // local form, one worker per workgroup: its operands, sums and counts stay in the LDS, and two mini-batches take turns there
-    unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes;
+    unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes, off_list;
 };
 
 struct SplitShared {                       // start of the LDS: the step, and space of the gate and update phases
     SplitStep now;
     double red[8];
     int delta;
-    unsigned most[2][8];
+    unsigned most[3][8];
+    int listed;                            // undecided samples in the list
+    int hard;                              // samples that wait for a scan of all the rows, SPLIT_HARD of them at most in `hard_rows`
+    int hard_rows[SPLIT_HARD];
     SplitSize size[3];                     // SplitState of a kept worker
 };
 
@@ -210,6 +215,23 @@ __device__ __forceinline__ void split_batch_fetch(SPLIT_ARG SplitArgs &a, int wo
     }
 }
 
+// Twice the error of a score of a sample with norm `yn`, infinite where everything is decided in fp64: a state that is not finite, has
+// outgrown the scale of its fp16 operands or has shrunk so far below it that its squares lose their last places, scores
+// that come near the offset of the padding rows.  rl: norm of the sample's low parts, where high parts alone were multiplied.
+template <bool SCREEN>
+__device__ __forceinline__ float split_threshold(SPLIT_ARG SplitArgs &a, const SplitSize &st, float rest, float yn, float rl)
+{
+    const float sw = st.sw, n2max = __uint_as_float(st.n2), vmax = sqrtf(n2max) * 1.0001f, ratio = a.xmeta[0] / sw;
+    const float offset = 0.5f * vmax * vmax * ratio;
+    float thr;
+    if (SCREEN) thr = screen_bound(yn, rl, vmax, sqrtf(rest) * 1.0001f, offset, a.dpad);
+    else thr = split_c1(a.dpad) * (yn * vmax + offset) + split_c2(a.dpad) * (yn + vmax);
+    if (st.n2 >= 0x7f800000u || st.vabs >= 0x7f800000u || !(__uint_as_float(st.vabs) * sw < 32768.0f) || !(n2max > 1.0e-27f) ||
+        !(yn * vmax + offset < -0.1f * SPLIT_PAD_SCORE))
+        thr = INFINITY;
+    return thr;
+}
+
 // What a wave does once the best scores of its 64 samples are known (lane l: sample l), the same in both assignment items.
 template <bool KEPT>
 __device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const SplitStep &now, const SplitTop &t, float n2, int worker, int g,
@@ -220,17 +242,10 @@ __device__ __forceinline__ void split_finish_group(SPLIT_ARG SplitArgs &a, const
     SplitSize st;
     if constexpr (KEPT) st = split_shared().size[now.slot];
     else st = SplitSize{now.state[worker].sw, now.state[worker].vabs, now.state[worker].n2};
-    const float sw = st.sw, n2max = __uint_as_float(st.n2), vmax = sqrtf(n2max) * 1.0001f, ratio = a.xmeta[0] / sw;
-    const float offset = 0.5f * vmax * vmax * ratio;
-    float thr = split_c1(a.dpad) * (yn * vmax + offset) + split_c2(a.dpad) * (yn + vmax);
-    // Everything in fp64: a state that is not finite, has outgrown the scale of its fp16 operands or has shrunk so far below it
-    // that its squares lose their last places, scores that come near the offset of the padding rows.
-    if (st.n2 >= 0x7f800000u || st.vabs >= 0x7f800000u || !(__uint_as_float(st.vabs) * sw < 32768.0f) || !(n2max > 1.0e-27f) ||
-        !(yn * vmax + offset < -0.1f * SPLIT_PAD_SCORE))
-        thr = INFINITY;
+    const float thr = split_threshold<false>(a, st, 0.0f, yn, 0.0f);
     const float *xg = xb + (size_t)g * a.d;
     const bool valid = g + lane < n_hi;
-    const int arg = split_settle(t, thr, valid, xg, a.w + (size_t)worker * a.k * a.d, a.k, a.d, rechecks);
+    const int arg = split_settle<false>(t, thr, valid, xg, lane, a.w + (size_t)worker * a.k * a.d, a.k, a.d, rechecks);
     if (valid) {
         if (a.idx) a.idx[(size_t)worker * a.b + g + lane] = arg;
         if (now.dump) now.dump[(size_t)worker * a.b + g + lane] = arg;
@@ -400,6 +415,312 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
     if (!KEPT && a.fused) {
         __syncthreads();
         split_flush(a, worker, share, cells, cnt);
+    }
+}
+
+// The samples in the workgroup's list of hard ones, by all its waves: a wave takes a part of the rows.  (One wave for all of them: 45 us
+// for one sample of k = 1024, d = 128, which the others waited for.)  `results`: SPLIT_HARD x waves x 16 bytes of LDS; the
+// caller's barriers are before and after.
+struct SplitHard { double best; int arg, pad; };
+__device__ inline void split_scan_hard(SPLIT_ARG SplitArgs &a, const float *xb, const float *w, int *idx, int32_t *dump, SplitHard *results)
+{
+    const int lane = split_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), nw = blockDim.x >> 6;
+    const int count = min(__builtin_amdgcn_readfirstlane(split_shared().hard), SPLIT_HARD);
+    const int part = ((a.k + nw - 1) / nw + 15) & ~15, c_lo = min(wave * part, a.k), c_hi = min(c_lo + part, a.k);
+    for (int q = 0; q < count; ++q) {
+        double best = INFINITY;
+        int arg = 0;
+        if (c_lo < c_hi) split_scan_wave(xb + (size_t)split_shared().hard_rows[q] * a.d, w, c_lo, c_hi, a.d, best, arg);
+        if (lane == 0) results[q * nw + wave] = SplitHard{best, arg, 0};
+    }
+    __syncthreads();
+    if ((int)threadIdx.x < count) {
+        const int row = split_shared().hard_rows[threadIdx.x];
+        double best = INFINITY;
+        int arg = 0;                          // (no distance below infinity: centroid 0, like a scan that starts there)
+        for (int v = 0; v < nw; ++v) {
+            const SplitHard r = results[threadIdx.x * nw + v];
+            if (r.best < best) { best = r.best; arg = r.arg; }
+        }
+        idx[row] = arg;
+        if (dump) dump[row] = arg;
+    }
+    if (threadIdx.x == 0) split_shared().hard = 0;
+}
+
+// ---- screened assignment: rows of 17 to 128 columns, a state that is streamed, sums in a pass of their own ----
+// High parts alone, up to four tiles of 32 samples per wave, the state's high parts through LDS stages; samples that are not decided by that go
+// to a list and are scored with all three products.  The decisions are those of the other items.
+// k = 1024, d = 128, b = 4096, W = 256, microseconds per step: 1130 with three products for all, 780 now: loading and converting the samples and
+// the stages 230, matrix instructions and insertions 130, the 3 % that are listed 95, sums 175, update 125.
+
+// The listed samples: 128 at a time, their operands in the LDS (where the stages were), every wave its own blocks of the state's rows with both
+// parts straight from the L2, a block ahead.
+template <int NC>
+__device__ __noinline__ void split_listed(u64 args_any, u64 state_any, long long row0_any, u64 dump_any, int worker_any, int share_any)
+{
+    SPLIT_ARG SplitArgs &a = *(SPLIT_ARG SplitArgs *)split_uniform64(args_any);
+    const SplitState *state = (const SplitState *)split_uniform64(state_any);
+    const long long row0 = (long long)split_uniform64((u64)row0_any);
+    int32_t *dump = (int32_t *)split_uniform64(dump_any);
+    const int worker = __builtin_amdgcn_readfirstlane(worker_any), n_lo = __builtin_amdgcn_readfirstlane(share_any) * a.share_len;
+    unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
+    const int lane = split_lane(), half = lane >> 5, l32 = lane & 31, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nw = blockDim.x >> 6, d = a.d, nblk = a.nblk;
+    constexpr int HC = (NC + 1) / 2, TILES = SPLIT_LISTED / 32;
+    const float *hs = reinterpret_cast<const float *>(smem + a.off_hs), *ms = reinterpret_cast<const float *>(smem + a.off_ms);
+    float *norms = reinterpret_cast<float *>(smem + a.off_args);          // [tile][half of the chunks][64]
+    float *tops = reinterpret_cast<float *>(smem);                        // [wave][pair of tiles][5][64], once the operands are used
+    half8 *operands = reinterpret_cast<half8 *>(smem);                    // [tile][chunk][hi, lo] pieces
+    const int *list = reinterpret_cast<const int *>(smem + a.off_list);
+    const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)row0 + n_lo) * d;
+    const float sx = a.xmeta[0];
+    const SplitSize st = {state[worker].sw, state[worker].vabs, state[worker].n2};
+    const int listed = __builtin_amdgcn_readfirstlane(split_shared().listed);
+    int rechecks = 0;
+    for (int p0 = 0; p0 < listed; p0 += SPLIT_LISTED) {
+        const int here = min(SPLIT_LISTED, listed - p0);
+        for (int un = wave; un < 2 * TILES; un += nw) {
+            const int tile = un >> 1, hh = un & 1;
+            const float *row = xb + (size_t)list[p0 + min(32 * tile + l32, here - 1)] * d;
+            float v[HC][8], n2 = 0.0f;
+#pragma unroll
+            for (int q = 0; q < HC; ++q) {
+                const int slot = (hh * HC + q) * 16 + 8 * half;
+                split_load8<false>(v[q], row, min(slot, d - 8), d);
+            }
+#pragma unroll
+            for (int q = 0; q < HC; ++q) {
+                const int ch = hh * HC + q;
+                if (ch >= NC) continue;
+                half8 hi, lo;
+                split_convert<true>(v[q], sx, ms, ch * 16 + 8 * half, d, hi, lo, n2);
+                half8 *to = operands + (tile * NC + ch) * 128 + lane;
+                to[0] = hi;
+                to[64] = lo;
+            }
+            norms[un * 64 + lane] = n2;
+        }
+        SplitTop top[TILES];
+        const float big = split_opaque_infinity();
+#pragma unroll
+        for (int m = 0; m < TILES; ++m) {
+            top[m].v1 = top[m].v2 = top[m].v3 = -INFINITY;
+            top[m].i1 = top[m].i2 = 0;
+        }
+        half8 A[2][2 * NC];
+        auto fetch = [&](half8 (&to)[2 * NC], int blk) {
+            const half8 *src = reinterpret_cast<const half8 *>(frag + ((size_t)(blk >> 1) * NC * 4 + (blk & 1) * 2) * SPLIT_PIECE) + lane;
+#pragma unroll
+            for (int ch = 0; ch < NC; ++ch) { to[2 * ch] = src[ch * 256]; to[2 * ch + 1] = src[ch * 256 + 64]; }
+        };
+        auto multiply = [&](const half8 (&from)[2 * NC], int blk) {
+#pragma unroll
+            for (int m = 0; m < TILES; ++m) {
+                if (32 * m >= here) break;
+                const half8 *B = reinterpret_cast<const half8 *>(smem) + m * NC * 128 + lane;
+                sfloatx16 acc;
+                split_init_acc(acc, hs, blk, half);
+#pragma unroll
+                for (int ch = 0; ch < NC; ++ch) {
+                    const half8 bh = B[ch * 128], bl = B[ch * 128 + 64];
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(from[2 * ch], bl, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(from[2 * ch + 1], bh, acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(from[2 * ch], bh, acc, 0, 0, 0);
+                    if (ch % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+                split_insert(top[m], acc, blk, big);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (wave < nblk) fetch(A[0], wave);
+        __syncthreads();                          // (the operands are there)
+        for (int blk = wave; blk < nblk; blk += 2 * nw) {
+            if (blk + nw < nblk) fetch(A[1], blk + nw);
+            multiply(A[0], blk);
+            if (blk + nw < nblk) {
+                if (blk + 2 * nw < nblk) fetch(A[0], blk + 2 * nw);
+                multiply(A[1], blk + nw);
+            }
+        }
+        __syncthreads();                          // (and used)
+#pragma unroll
+        for (int p = 0; p < TILES / 2; ++p) {
+            SplitTop t, pair[2] = {top[2 * p], top[2 * p + 1]};
+            split_combine(pair, t, half);
+            float *mine = tops + (wave * (TILES / 2) + p) * 5 * 64 + lane;
+            mine[0] = t.v1; mine[64] = t.v2; mine[128] = t.v3;
+            mine[192] = __int_as_float(t.i1); mine[256] = __int_as_float(t.i2);
+        }
+        __syncthreads();
+        // every wave settles its share of the samples
+        const int each = SPLIT_LISTED / nw;
+        for (int s0 = 0; s0 < each; s0 += 64) {
+            const int s = min(wave * each + s0 + lane, SPLIT_LISTED - 1);
+            const bool valid = s0 + lane < each && wave * each + s0 + lane < here;
+            SplitTop t = {-INFINITY, -INFINITY, -INFINITY, 0, 0};
+            for (int q = 0; q < nw; ++q) {
+                const float *o = tops + (q * (TILES / 2) + (s >> 6)) * 5 * 64 + (s & 63);
+                split_merge(t, o[0], __float_as_int(o[192]));
+                split_merge(t, o[64], __float_as_int(o[256]));
+                t.v3 = fmaxf(t.v3, o[128]);
+            }
+            const float *nr = norms + (s >> 5) * 128 + (s & 31);
+            const float thr = split_threshold<false>(a, st, 0.0f, sqrtf((nr[0] + nr[32]) + (nr[64] + nr[96])) * 1.0001f, 0.0f);
+            const int own = list[p0 + min(s, here - 1)];
+            const int arg = split_settle<true>(t, thr, valid, xb, own, a.w + (size_t)worker * a.k * d, a.k, d, rechecks, split_shared().hard_rows,
+                                               &split_shared().hard);
+            if (valid && arg >= 0) {
+                a.idx[(size_t)worker * a.b + n_lo + own] = arg;
+                if (dump) dump[(size_t)worker * a.b + n_lo + own] = arg;
+            }
+        }
+        __syncthreads();                          // (tops are used, the list of hard ones is complete)
+        if (split_shared().hard > 0)
+            split_scan_hard(a, xb, a.w + (size_t)worker * a.k * d, a.idx + (size_t)worker * a.b + n_lo, dump ? dump + (size_t)worker * a.b + n_lo : nullptr,
+                            reinterpret_cast<SplitHard *>(smem));
+        __syncthreads();                          // (operands and norms are written again)
+    }
+    split_count_rechecks(a, worker, rechecks);
+    if (threadIdx.x == 0) split_shared().listed = 0;
+    __syncthreads();
+}
+
+template <int NC>
+__device__ void split_screen_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
+{
+    const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len), n = n_hi - n_lo;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int nw = blockDim.x >> 6, npair = (a.nblk + 1) / 2, nstage = a.stages;
+    float *hs = reinterpret_cast<float *>(smem + a.off_hs), *ms = reinterpret_cast<float *>(smem + a.off_ms);
+    int *list = reinterpret_cast<int *>(smem + a.off_list);
+    const unsigned stage_bytes = (unsigned)a.stage_pairs * NC * 2 * SPLIT_PIECE;
+    const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0 + n_lo) * a.d;
+    const float sx = a.xmeta[0];
+    // the high parts of a stage: every other piece
+    auto stage_fetch = [&](int st, int buf) {
+        const unsigned char *src = frag + (size_t)st * 2 * stage_bytes + lane * 16;
+        unsigned char *dst = smem + buf * stage_bytes;
+        const int pieces = min(a.stage_pairs, npair - st * a.stage_pairs) * NC * 2;
+        for (int q = wave; q < pieces; q += nw)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + (size_t)q * 2 * SPLIT_PIECE),
+                                             (__attribute__((address_space(3))) void *)(dst + q * SPLIT_PIECE), 16, 0, 0);
+    };
+    __syncthreads();                            // (the item before this one is done with the LDS)
+    stage_fetch(0, 0);
+    for (int c = tid; c < a.kpad; c += blockDim.x) hs[c] = a.hs[(size_t)worker * a.kpad + c];
+    for (int j = tid; j < a.dpad; j += blockDim.x) ms[j] = a.ms[j];
+    if (tid == 0) split_shared().listed = split_shared().hard = 0;
+    __syncthreads();
+
+    int turn = 0;
+    bool staged = false;
+    // one sweep over this wave's 32 * T samples from g on (of the share)
+    auto sweep = [&](auto tiles, int g, bool last) {
+        constexpr int T = decltype(tiles)::value, HC = (NC + 1) / 2;
+        half8 b[T][NC];
+        float n2[T], r2[T];
+        ScreenTop top[T];
+        {
+            float v[3][HC][8];
+            // half tiles, two on their way while one is converted
+            auto load = [&](float (&to)[HC][8], int u) {
+                const float *row = xb + (unsigned)(min(g + 32 * (u >> 1) + l32, n - 1) * a.d);
+#pragma unroll
+                for (int q = 0; q < HC; ++q) {
+                    const int ch = (u & 1) * HC + q;
+                    if (ch < NC) split_load8<false>(to[q], row, ch + 1 < NC ? ch * 16 + 8 * half : min(ch * 16 + 8 * half, a.d - 8), a.d);
+                }
+            };
+            load(v[0], 0);
+            load(v[1], 1);
+#pragma unroll
+            for (int u = 0; u < 2 * T; ++u) {
+                const int t = u >> 1;
+                if (u + 2 < 2 * T) load(v[(u + 2) % 3], u + 2);
+                if ((u & 1) == 0) n2[t] = r2[t] = 0.0f;
+                const int hf = split_lane() >> 5;             // (ms is read again for every tile, not kept in 64 registers)
+#pragma unroll
+                for (int q = 0; q < HC; ++q) {
+                    const int ch = (u & 1) * HC + q;
+                    if (ch + 1 < NC) screen_convert<false>(v[u % 3][q], sx, ms, ch * 16 + 8 * hf, a.d, b[t][ch], n2[t], r2[t]);
+                    else if (ch + 1 == NC) screen_convert<true>(v[u % 3][q], sx, ms, ch * 16 + 8 * hf, a.d, b[t][ch], n2[t], r2[t]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                asm volatile("" : "+v"(n2[t]), "+v"(r2[t]));
+                if (u & 1) {
+                    top[t].v1 = top[t].v2 = -INFINITY;
+                    top[t].i1 = 0;
+                }
+            }
+        }
+        for (int st = 0; st < nstage; ++st) {
+            if (nstage > 1 || !staged) split_stage_wait();    // this stage is there, and nobody reads the other one any more
+            staged = true;
+            if (nstage > 1 && !(last && st + 1 == nstage)) stage_fetch(st + 1 < nstage ? st + 1 : 0, (turn + 1) & 1);
+            const unsigned char *from = smem + (turn & 1) * stage_bytes;
+            turn += nstage > 1;
+            const int blk0 = st * a.stage_pairs * 2, blks = g < n ? min(a.stage_pairs * 2, a.nblk - blk0) : 0;
+            for (int q = 0; q < blks; ++q) {
+                const half8 *A = reinterpret_cast<const half8 *>(from + ((q >> 1) * NC * 2 + (q & 1)) * SPLIT_PIECE) + lane;
+                sfloatx16 h, acc[T];
+                split_init_acc(h, hs, blk0 + q, half);
+                half8 ah = A[0];
+#pragma unroll
+                for (int ch = 0; ch < NC; ++ch) {
+                    half8 nh = ah;
+                    if (ch + 1 < NC) nh = A[(ch + 1) * 128];
+#pragma unroll
+                    for (int t = 0; t < T; ++t) acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ah, b[t][ch], ch == 0 ? h : acc[t], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    ah = nh;
+                }
+#pragma unroll
+                for (int t = 0; t < T; ++t) screen_insert(top[t], acc[t], blk0 + q);
+            }
+        }
+        if (g < n) {
+            const SplitSize st = {now.state[worker].sw, now.state[worker].vabs, now.state[worker].n2};
+            const float rest = __uint_as_float(now.state[worker].rest);
+#pragma unroll
+            for (int p = 0; p < T / 2; ++p) {
+                ScreenTop t;
+                screen_combine(top[2 * p], top[2 * p + 1], t, half);
+                swap2(n2[2 * p], n2[2 * p + 1]);
+                swap2(r2[2 * p], r2[2 * p + 1]);
+                const float thr = split_threshold<true>(a, st, rest, sqrtf(n2[2 * p] + n2[2 * p + 1]) * 1.0001f, sqrtf(r2[2 * p] + r2[2 * p + 1]) * 1.0001f);
+                const int at = g + 64 * p + lane;
+                const bool valid = at < n, open = valid && !(t.v1 - t.v2 > thr);
+                const unsigned long long o = __ballot(open);
+                int base = 0;
+                if (o != 0 && lane == 0) base = atomicAdd(&split_shared().listed, __popcll(o));
+                base = __builtin_amdgcn_readfirstlane(base);
+                if (open) list[base + __popcll(o & ((1ULL << lane) - 1))] = at;
+                if (valid && !open) {
+                    const int arg = min(max(t.i1, 0), a.k - 1);
+                    a.idx[(size_t)worker * a.b + n_lo + at] = arg;
+                    if (now.dump) now.dump[(size_t)worker * a.b + n_lo + at] = arg;
+                }
+            }
+        }
+    };
+    for (int g0 = 0; g0 < n;) {
+        const bool four = n - g0 > nw * 64;
+        const int next = g0 + nw * (four ? 128 : 64);
+        if (four) sweep(std::integral_constant<int, 4>{}, g0 + wave * 128, next >= n);
+        else sweep(std::integral_constant<int, 2>{}, g0 + wave * 64, next >= n);
+        g0 = next;
+        __syncthreads();
+        const int listed = split_shared().listed;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // (the stage that is on its way: the listed samples take its place)
+        __syncthreads();                          // (everybody has read the number before anybody adds to it)
+        if (listed > 0 && (g0 >= n || listed > SPLIT_LIST - nw * 128)) {
+            split_listed<NC>((u64)&a, (u64)now.state, now.row0, (u64)now.dump, worker, share);
+            if (g0 < n) stage_fetch(0, turn & 1);
+            staged = false;
+        }
     }
 }
 
@@ -842,8 +1163,9 @@ __device__ __forceinline__ bool split_gate_at_once(SPLIT_ARG SplitArgs &a, SPLIT
 
 // MODE 0: size of the states; 1: their operands; 2: a step; 3: a step with the 1/count step size (no exchange there);
 // 4: a step with partial messages.
+// REST: also the norms of what the rows' high parts leave over, for screened samples.
 // (A template: a phase this short is mostly the fetch of its own code.)
-template <int MODE, bool KEPT>
+template <int MODE, bool KEPT, bool REST>
 __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, SPLIT_ARG SplitArgs &a, const SplitStep &now, int i, int blk,
                                          SplitShared &sh)
 {
@@ -963,7 +1285,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
             if (MODE != 0) sh.size[now.slot_next].sw = sw;
         } else {
             if (MODE != 0) st_next->sw = sw;
-            st_after->vabs = st_after->n2 = 0;           // (nobody looks at it in this launch)
+            st_after->vabs = st_after->n2 = st_after->rest = 0;           // (nobody looks at it in this launch)
         }
     }
     auto peer_of = [&](int n) -> int {                   // recipient of copy n of this worker's message, -1: lost on the way
@@ -975,7 +1297,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
 
     // ---- Eq. 6 (one buffer: Eq. 7), Alg. 5, update and send; operands of the new state ----
     const int units = u.dpad / 8, nch = u.dpad / 16;
-    unsigned vabs = 0, n2max = 0;
+    unsigned vabs = 0, n2max = 0, restmax = 0;
     const float inv_all = 1.0f / (float)(__builtin_popcount(delta_mask) + 1);
     int nz = 0, accd = 0, near_row = 0;
     const int rows = MODE == 1 ? u.kpad : k;             // padding rows are written once
@@ -1014,7 +1336,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
             seen = p.ncum[(size_t)i * k + c] + cn;
             if (lane_g == 0) p.ncum[(size_t)i * k + c] = seen;
         }
-        float sq = 0.0f;
+        float sq = 0.0f, rest = 0.0f;
         for (int un = lane_g; un < units; un += u.g) {
             const int j0 = un * 8;
             const int lo_e = j0 + 8 <= d ? 0 : (d >= 8 ? 8 - (d - j0) : 0), hi_e = d >= 8 || j0 + 8 <= d ? 8 : d - j0;   // slots in use
@@ -1089,7 +1411,9 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     hi[e] = (_Float16)v[e];
-                    lo[e] = (_Float16)(v[e] - (float)hi[e]);
+                    const float left = v[e] - (float)hi[e];
+                    lo[e] = (_Float16)left;
+                    if (REST) rest = fmaf(left, left, rest);
                 }
                 half8 *dst = reinterpret_cast<half8 *>(frag + ((((size_t)(c >> 6) * nch + (j0 >> 4)) * 2 + ((c >> 5) & 1)) * 2) * SPLIT_PIECE) +
                              (c & 31) + 32 * ((j0 >> 3) & 1);
@@ -1097,8 +1421,12 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
                 dst[64] = lo;
             }
         }
-        for (int off = u.g / 2; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+        for (int off = u.g / 2; off > 0; off >>= 1) {
+            sq += __shfl_xor(sq, off, 64);
+            if (REST && MODE != 0) rest += __shfl_xor(rest, off, 64);
+        }
         n2max = max(n2max, __float_as_uint(sq) & 0x7fffffffu);
+        if (REST && MODE != 0) restmax = max(restmax, __float_as_uint(rest) & 0x7fffffffu);
         if (MODE != 0 && lane_g == 0) hs[c] = real ? -0.5f * sq * (sx / sw) : SPLIT_PAD_SCORE;
         if (KEPT && STEP && lane_g == 0) kept_cnt[c] = 0;        // (the lanes of a row are lanes of one wave: all have read it)
     }
@@ -1106,11 +1434,13 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
     for (int off = 32; off > 0; off >>= 1) {
         vabs = max(vabs, (unsigned)__shfl_xor((int)vabs, off, 64));
         n2max = max(n2max, (unsigned)__shfl_xor((int)n2max, off, 64));
+        if (REST && MODE != 0) restmax = max(restmax, (unsigned)__shfl_xor((int)restmax, off, 64));
         if (ROWWISE) { nz |= __shfl_xor(nz, off, 64); accd |= __shfl_xor(accd, off, 64); near_row |= __shfl_xor(near_row, off, 64); }
     }
     if ((tid & 63) == 0) {
         sh.most[0][tid >> 6] = vabs;
         sh.most[1][tid >> 6] = n2max;
+        if (REST) sh.most[2][tid >> 6] = restmax;
         if (ROWWISE && mail.has) {
             // buffers with a non-empty row, with an accepted row, a near-tie: whoever sets a flag first counts it
             const int flags = nz << 8 | accd << 16 | near_row << 24, fresh = flags & ~atomicOr(&u.mail[i].has, flags);
@@ -1121,7 +1451,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
         }
     }
     __syncthreads();
-    if (tid < 2) {
+    if (tid < (REST && MODE != 0 ? 3 : 2)) {
         // mode 0 prepares the slot that mode 1 reads, mode 1 the one the first step reads
         unsigned *at;
         if constexpr (KEPT) {
@@ -1129,7 +1459,7 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
             at = tid == 0 ? &dst->vabs : &dst->n2;
         } else {
             SplitState *dst = MODE == 0 ? st_now : st_next;
-            at = tid == 0 ? &dst->vabs : &dst->n2;
+            at = tid == 0 ? &dst->vabs : tid == 1 ? &dst->n2 : &dst->rest;
         }
         unsigned v = 0;
         for (int q = 0; q < (int)(blockDim.x >> 6); ++q) v = max(v, sh.most[tid][q]);
@@ -1177,11 +1507,7 @@ struct SplitLaunch {                       // arguments of a phase
 // registers; what is uniform is read back into scalar ones.
 typedef SPLIT_ARG SplitRun *SplitRunPtr;
 __device__ __forceinline__ int split_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ SplitRunPtr split_uniform(u64 p)
-{
-    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)p), hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(p >> 32));
-    return (SplitRunPtr)((u64)hi << 32 | lo);
-}
+__device__ __forceinline__ SplitRunPtr split_uniform(u64 p) { return (SplitRunPtr)split_uniform64(p); }
 template <int NC, bool KEPT>
 __device__ __noinline__ void split_assign_call(u64 run, int worker, int share)
 {
@@ -1189,6 +1515,13 @@ __device__ __noinline__ void split_assign_call(u64 run, int worker, int share)
     const SplitStep now = split_shared().now;
     if constexpr (NC == 0) split_assign_long_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
     else split_assign_item<NC, KEPT>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
+}
+template <int NC>
+__device__ __noinline__ void split_screen_call(u64 run, int worker, int share)
+{
+    SplitRunPtr r = split_uniform(run);
+    const SplitStep now = split_shared().now;
+    split_screen_item<NC>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
 }
 __device__ __noinline__ inline void split_sums_call(u64 run, int worker, int share, int chunk)
 {
@@ -1203,12 +1536,12 @@ __device__ __noinline__ void split_gate_call(u64 run, int worker, int blk)
     const SplitStep now = split_shared().now;
     split_gate_item<KEPT>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared().red);
 }
-template <int MODE, bool KEPT>
+template <int MODE, bool KEPT, bool REST>
 __device__ __noinline__ void split_update_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
-    split_update_item<MODE, KEPT>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared());
+    split_update_item<MODE, KEPT, REST>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared());
 }
 
 // Phases form.  WHAT: 0..4 modes of the update, 5 Eq. 4, 6 gradient sums, 10 + NC assignment (10: long rows)
@@ -1237,7 +1570,7 @@ void split_phase_kernel(SplitLaunch args)
     } else if constexpr (WHAT == 5) {
         split_gate_item<false>(l->run.p, l->run.u, l->run.a, now, worker, rest, reinterpret_cast<SplitShared *>(lds)->red);
     } else {
-        split_update_item<WHAT, false>(l->run.p, l->run.u, l->run.a, now, worker, rest, *reinterpret_cast<SplitShared *>(lds));
+        split_update_item<WHAT, false, false>(l->run.p, l->run.u, l->run.a, now, worker, rest, *reinterpret_cast<SplitShared *>(lds));
     }
 }
 template <int WHAT>
@@ -1325,7 +1658,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
         if (r->t0 < r->t1) split_batch_fetch(r->a, blockIdx.x, r->t0 % r->p.S * r->p.b, split_lds + SPLIT_LDS_SHARED + r->a.off_batch);
     }
     for (int i = blockIdx.x; i < W; i += gridDim.x) {
-        split_update_call<0, KEPT>(run, i, 0);
+        split_update_call<0, KEPT, false>(run, i, 0);
         __syncthreads();
         if constexpr (KEPT) {
             unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
@@ -1334,7 +1667,8 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             for (int e = threadIdx.x; e < n; e += blockDim.x) reinterpret_cast<u64 *>(smem + r->a.off_cells)[e] = 0;
             for (int c = threadIdx.x; c < r->a.k; c += blockDim.x) reinterpret_cast<int *>(smem + r->a.off_cnt)[c] = 0;
         }
-        split_update_call<1, KEPT>(run, i, 0);
+        if (NC >= 2 && !KEPT && r->a.stages) split_update_call<1, KEPT, NC >= 2 && !KEPT>(run, i, 0);
+        else split_update_call<1, KEPT, false>(run, i, 0);
     }
     int te = r->te0;
     long long t = r->t0, round = r->round0, s = t % r->p.S;
@@ -1364,8 +1698,13 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             __syncthreads();
         }
         for (int i = blockIdx.x; i < W; i += gridDim.x) {
-            if constexpr (KEPT) split_assign_item<NC, true>(r->a, now, i, 0, split_lds + SPLIT_LDS_SHARED);
-            else split_assign_call<NC, KEPT>(run, i, 0);
+            if constexpr (KEPT) {
+                split_assign_item<NC, true>(r->a, now, i, 0, split_lds + SPLIT_LDS_SHARED);
+            } else if (NC >= 2 && r->a.stages) {
+                if constexpr (NC >= 2) split_screen_call<NC>(run, i, 0);
+            } else {
+                split_assign_call<NC, KEPT>(run, i, 0);
+            }
             if (!KEPT && !r->a.fused)
                 for (int q = 0; q < r->a.ncol; ++q) split_sums_call(run, i, 0, q);
             if (r->sync && now.merge) {
@@ -1397,10 +1736,14 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
                 __syncthreads();
             }
             if constexpr (KEPT) {
-                split_update_item<INV_COUNT ? 3 : 2, true>(r->p, r->u, r->a, now, i, 0, sh);
+                split_update_item<INV_COUNT ? 3 : 2, true, false>(r->p, r->u, r->a, now, i, 0, sh);
             } else {
-                if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3, KEPT>(run, i, 0);
-                else split_update_call<2, KEPT>(run, i, 0);
+                auto update = [&](auto rest) {
+                    if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3, KEPT, decltype(rest)::value>(run, i, 0);
+                    else split_update_call<2, KEPT, decltype(rest)::value>(run, i, 0);
+                };
+                if (NC >= 2 && r->a.stages) update(std::integral_constant<bool, (NC >= 2)>{});
+                else update(std::false_type{});
             }
             if (r->sync && now.merge) {
                 __syncthreads();

@@ -30,6 +30,13 @@ int main(int argc, char **argv)
                     ++kept;
                     full += q.lds > SPLIT_LDS_ALL - 1024;
                 }
+                if (q.screen) {
+                    const unsigned pair = q.nch * 2 * SPLIT_PIECE, operands = SPLIT_LISTED / 32 * pair, best = 8 * SPLIT_LISTED / 64 * 5 * 64 * 4;
+                    REQUIRE(q.stage_pairs >= 1 && q.stages * q.stage_pairs >= q.npair && (q.stages - 1) * q.stage_pairs < q.npair);
+                    REQUIRE(q.off_cells >= (q.stages > 1 ? 2 : 1) * q.stage_pairs * pair && q.off_cells >= operands && q.off_cells >= best && q.off_cells >= SPLIT_HARD * 8 * 16);
+                    REQUIRE(q.off_list >= q.off_args + 2 * SPLIT_LISTED / 32 * 64 * 4 && q.off_list + 4 * SPLIT_LIST + SPLIT_LDS_SHARED <= q.lds);
+                    REQUIRE(SPLIT_LIST >= 2 * 8 * 128);            // a sweep of eight waves adds at most as many as there is room
+                }
                 ++plans;
             }
     printf("ok %lld plans, %lld kept, %lld of them within 1 KB of the limit\n", plans, kept, full);
