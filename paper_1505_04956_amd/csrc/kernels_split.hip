@@ -197,7 +197,7 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, c
     a.counters = p.counters;
     a.H = p.H;
     a.k = p.k; a.d = p.d; a.b = p.b; a.W = p.W; a.kpad = q.kpad; a.nblk = q.nblk; a.dpad = q.dpad;
-    a.shares = q.shares; a.share_len = q.share_len; a.sum_shares = q.sum_shares; a.sum_len = q.sum_len; a.dc = q.dc; a.ncol = q.ncol; a.resident = q.resident; a.fused = q.fused;
+    a.shares = q.shares; a.share_len = q.share_len; a.sum_shares = q.sum_shares; a.sum_len = q.sum_len; a.dc = q.dc; a.ncol = q.ncol; a.resident = q.resident; a.fused = q.fused; a.wide = q.wide;
     a.vec4 = p.d % 4 == 0 && ((uintptr_t)p.x & 15u) == 0;
     a.kept = q.kept; a.off_batch = q.off_batch; a.batch_bytes = q.batch_bytes;
     a.off_cells = q.off_cells; a.off_cnt = q.off_cnt; a.off_hs = q.off_hs; a.off_ms = q.off_ms; a.off_args = q.off_args;

@@ -10,7 +10,7 @@ hipError_t launch_split_local_0(const SplitRun &r, int blocks, int threads, unsi
 }
 hipError_t launch_split_assign_0(const SplitLaunch &l, int blocks, int threads, unsigned lds, hipStream_t s)
 {
-    return split_launch_phase<10>(l, blocks, threads, lds, s);
+    return l.run.a.wide ? split_launch_phase<9>(l, blocks, threads, lds, s) : split_launch_phase<10>(l, blocks, threads, lds, s);
 }
 hipError_t launch_split_quant_0(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s)
 {

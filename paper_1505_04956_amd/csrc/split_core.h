@@ -250,7 +250,7 @@ __device__ __forceinline__ void split_scan_wave(const float *xl, const float *w,
 // sum_j (w_aj - w_bj)(w_aj + w_bj - 2 x_j), more by all k distances in direct form; the lowest index wins exact ties.
 // thr may be infinite (then everything is decided in fp64); scores may be NaN.
 // DEFER: where all k distances are asked for, the sample's row goes to the workgroup's list `hard` as long as there is room, and the
-// result is -1 (split_scan_hard()).
+// result is -1 (split_scan_hard()); without it `own` is the lane.
 template <bool DEFER>
 __device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool valid, const float *xb, int own, const float *w, int k,
                                             int d, int &rechecks, int *hard = nullptr, int *hard_count = nullptr)
@@ -281,13 +281,13 @@ __device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool v
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             L[q] = -1; ca[q] = 0; cb[q] = 0; dd[q] = 0.0;
-            at[q] = __builtin_amdgcn_readfirstlane(own);
+            at[q] = DEFER ? __builtin_amdgcn_readfirstlane(own) : 0;
             if (pm) {
                 L[q] = __builtin_ctzll(pm);
                 pm &= pm - 1;
                 ca[q] = __builtin_amdgcn_readlane(arg, L[q]);
                 cb[q] = __builtin_amdgcn_readlane(second, L[q]);
-                at[q] = __builtin_amdgcn_readlane(own, L[q]);
+                at[q] = DEFER ? __builtin_amdgcn_readlane(own, L[q]) : L[q];
             }
         }
         for (int j0 = 0; j0 < d; j0 += 128) {
@@ -323,7 +323,7 @@ __device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool v
         while (fm) {
             const int L = __builtin_ctzll(fm);
             fm &= fm - 1;
-            const float *xl = xb + (size_t)__builtin_amdgcn_readlane(own, L) * d;
+            const float *xl = xb + (size_t)(DEFER ? __builtin_amdgcn_readlane(own, L) : L) * d;
             double best;
             int barg;
             split_scan_wave(xl, w, 0, k, d, best, barg);
@@ -331,7 +331,7 @@ __device__ __forceinline__ int split_settle(const SplitTop &t, float thr, bool v
             if (lane == L) arg = best < INFINITY ? barg : 0;
         }
     } else if (close3) {
-        arg = split_scan_own(xb + (size_t)own * d, w, k, d);
+        arg = split_scan_own(xb + (size_t)(DEFER ? own : lane) * d, w, k, d);
     }
     return arg;
 }

@@ -21,6 +21,7 @@ struct SplitPlan {
     int nch, dpad, nblk, kpad, npair;
     size_t frag_bytes;
     bool longrow, fused, resident, kept;
+    bool wide;                     // rows of more than 128 columns, the operands of 64 samples fit the LDS
     bool screen;                   // samples are screened (split_screen.h)
     int stage_pairs, stages;       // row pairs of a stage of high parts; stages of the state (one: it stays)
     unsigned off_list;
@@ -47,6 +48,13 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
     const size_t cells = (size_t)k * ((d + 1) & ~1) * 8 + (size_t)k * 4;
     const size_t fixed = (size_t)q.kpad * 4 + (size_t)q.dpad * 4 + 8 * 64 * 4 + 64;
     const size_t stage2 = q.longrow ? 0 : (size_t)2 * q.nch * 4 * SPLIT_PIECE;
+    const size_t group = (size_t)64 * q.dpad * 4, wide_others = (size_t)q.kpad * 4 + (size_t)q.dpad * 4 + 8 * 64 * 4 * 7 + 64;
+    // One workgroup per compute unit, 64 samples at a time, its waves share the state's blocks of 32 rows: with few blocks only as long as there are few
+    // groups of 64 for a workgroup, because elsewhere every wave has one of its own.  Microseconds per step before and with it: k = 256, d = 384,
+    // b = 512: W = 64 171, 110, W = 256 497, 374; k = 300, d = 500, b = 1000, W = 16 196, 78; k = 160, d = 200, b = 4000, W = 256 1394, 1067; k = 128 974,
+    // 949; d = 150: k = 100, b = 2000, W = 256 523, 515; k = 20, b = 1000, W = 64 (four groups) 73, 71, b = 2000 90, 118; k = 50, b = 2000, W = 256 368, 473.
+    const int groups = (b + 63) / 64, one_round = W < SPLIT_CUS && !local ? SPLIT_CUS / W : 1;
+    q.wide = q.longrow && group + wide_others <= SPLIT_LDS && (q.nblk >= 4 || (groups + one_round - 1) / one_round <= 4);
     if (q.longrow) {
         q.resident = q.fused = false;
     } else if (q.frag_bytes + cells + fixed <= SPLIT_LDS) {
@@ -74,13 +82,14 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
         o = (unsigned)((q.stages > 1 ? 2 : 1) * q.stage_pairs * pair);
         if (o < listed) o = (unsigned)listed;
     }
+    if (q.wide) o = (unsigned)group;
     q.off_cells = o;
     if (q.fused) o += split_round16((size_t)k * ((d + 1) & ~1) * 8);
     q.off_cnt = o;
     if (q.fused) o += split_round16((size_t)k * 4);
     q.off_hs = o;  o += split_round16((size_t)q.kpad * 4);
     q.off_ms = o;  o += split_round16((size_t)q.dpad * 4);
-    q.off_args = o; o += 8 * 64 * 4 * (q.longrow ? 5 : 1);
+    q.off_args = o; o += 8 * 64 * 4 * (q.wide ? 7 : q.longrow ? 5 : 1);
     q.off_list = o; o += q.screen ? SPLIT_LIST * 4 : 0;
     // (two mini-batches of a kept worker: the next one arrives while the current one is worked on; a fetch writes whole KBs)
     q.batch_bytes = (unsigned)(((size_t)(b < 16384 ? b : 16384) * d * 4 + 1023) / 1024 * 1024);
@@ -94,15 +103,15 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
     // Phases: waves of a workgroup and shares of a mini-batch - enough workgroups for the compute units first, then as many
     // waves per workgroup as share the staged operands, and as many workgroups as are resident at once (three waves per
     // SIMD up to 32 columns, two above).
-    const int groups = (b + 63) / 64;
     q.waves = 8;
     q.shares = 1;
     if (q.longrow) {
-        // (the waves of a workgroup share the row pairs of its groups of samples, see split_assign_long_item)
-        int rsplit = 1;
+        // (the waves of a workgroup share the rows of its groups of samples, see split_assign_wide_item and split_assign_long_item)
+        int rsplit = q.wide ? 8 : 1;
         while (2 * rsplit <= q.npair && 2 * rsplit <= 8) rsplit *= 2;
         const int max_shares = (groups + 8 / rsplit - 1) / (8 / rsplit);
-        if (!local) q.shares = (2 * SPLIT_CUS + W - 1) / W;
+        // (with one workgroup per compute unit a second round must not begin)
+        if (!local) q.shares = q.wide ? one_round : (2 * SPLIT_CUS + W - 1) / W;
         if (q.shares > max_shares) q.shares = max_shares;
         if (q.shares > 64) q.shares = 64;
     } else if (!local) {

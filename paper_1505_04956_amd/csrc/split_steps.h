@@ -58,7 +58,7 @@ struct SplitArgs {
     int k, d, b, W, kpad, nblk, dpad;
     int shares, share_len;           // share_len: samples of a share, a multiple of 64
     int sum_shares, sum_len, dc, ncol;       // sums in a phase of their own: shares, columns per item, groups of columns
-    int resident, fused, vec4;
+    int resident, fused, vec4, wide;
     int stage_pairs, stages;         // screened samples
     int kept;                        // local form, one worker per workgroup: its operands, sums and counts stay in the LDS, and two mini-batches take turns there
     unsigned off_cells, off_cnt, off_hs, off_ms, off_args, off_batch, batch_bytes, off_list;
@@ -850,6 +850,164 @@ __device__ inline void split_assign_long_item(SPLIT_ARG SplitArgs &a, const Spli
     split_count_rechecks(a, worker, rechecks);
 }
 
+// Rows whose operands fit the LDS for 64 samples (up to some 500 columns): they are split once, by all the waves, and every wave multiplies them
+// with its own blocks of the state's rows, whose operands come straight from the L2, two chunks ahead.  No barrier inside.  The next 64
+// samples are on their way meanwhile.
+// (k = 256, d = 384, b = 512, W = 64: 110 us per launch where every wave split its samples for itself and one wave decided for 64; 45 now.)
+__device__ inline void split_assign_wide_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
+{
+    const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len);
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int nw = blockDim.x >> 6, nch = a.dpad / 16, d = a.d;
+    float *hs = reinterpret_cast<float *>(smem + a.off_hs), *ms = reinterpret_cast<float *>(smem + a.off_ms);
+    float *tops = reinterpret_cast<float *>(smem + a.off_args), *norms = tops + 8 * 5 * 64;          // [wave][5][64], [wave][tile][64]
+    half8 *operands = reinterpret_cast<half8 *>(smem);                    // [tile][chunk][hi, lo] pieces
+    const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0) * d;
+    const float sx = a.xmeta[0];
+    __syncthreads();
+    for (int c = tid; c < a.kpad; c += blockDim.x) hs[c] = a.hs[(size_t)worker * a.kpad + c];
+    for (int j = tid; j < a.dpad; j += blockDim.x) ms[j] = a.ms[j];
+    if (tid == 0) split_shared().hard = 0;
+    // the columns of a wave's chunks wave, wave + nw, .. of 32 samples of each tile, up to LOADS chunks ahead in registers
+    constexpr int LOADS = 4;
+    float v[LOADS][2][8];
+    auto load = [&](int g, int q, float (&to)[2][8]) {
+        const int ch = wave + q * nw;
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const int n = g + 32 * m + l32;
+            split_load8<false>(to[m], xb + (size_t)(n < n_hi ? n : n_lo) * d, min(min(ch, nch - 1) * 16 + 8 * half, d - 8), d);
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < LOADS; ++q) load(n_lo, q, v[q]);
+    __syncthreads();
+
+    int rechecks = 0;
+    for (int g = n_lo; g < n_hi; g += 64) {
+        float n2[2] = {0.0f, 0.0f};
+        auto put = [&](int q, const float (&from)[2][8]) {
+            const int ch = wave + q * nw;
+            if (ch >= nch) return;
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                half8 hi, lo;
+                split_convert<true>(from[m], sx, ms, ch * 16 + 8 * half, d, hi, lo, n2[m]);
+                half8 *to = operands + (m * nch + ch) * 128 + lane;
+                to[0] = hi;
+                to[64] = lo;
+            }
+        };
+#pragma unroll
+        for (int q = 0; q < LOADS; ++q) put(q, v[q]);
+        for (int q = LOADS; wave + q * nw < nch; ++q) {
+            float w8[2][8];
+            load(g, q, w8);
+            put(q, w8);
+        }
+        norms[(wave * 2 + 0) * 64 + lane] = n2[0];
+        norms[(wave * 2 + 1) * 64 + lane] = n2[1];
+        __syncthreads();                          // (the operands are there)
+        if (g + 64 < n_hi) {
+#pragma unroll
+            for (int q = 0; q < LOADS; ++q) load(g + 64, q, v[q]);
+        }
+        SplitTop top[2];
+        const float big = split_opaque_infinity();
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            top[m].v1 = top[m].v2 = top[m].v3 = -INFINITY;
+            top[m].i1 = top[m].i2 = 0;
+        }
+        for (int blk = wave; blk < a.nblk; blk += nw) {
+            const half8 *A = reinterpret_cast<const half8 *>(frag + ((size_t)(blk >> 1) * nch * 4 + (blk & 1) * 2) * SPLIT_PIECE) + lane;
+            const half8 *B = operands + lane;
+            sfloatx16 acc[2];
+            split_init_acc(acc[0], hs, blk, half);
+            acc[1] = acc[0];
+            half8 a0[2][2], a1[2][2];             // two chunks per set: high and low parts
+            auto fetch = [&](half8 (&av)[2][2], int ch) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const int c = min(ch + u, nch - 1);
+                    av[u][0] = A[c * 256];
+                    av[u][1] = A[c * 256 + 64];
+                }
+            };
+            auto multiply = [&](const half8 (&av)[2][2], int ch) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                    for (int m = 0; m < 2; ++m) {
+                        const half8 bh = B[(m * nch + ch + u) * 128], bl = B[(m * nch + ch + u) * 128 + 64];
+                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[u][0], bl, acc[m], 0, 0, 0);
+                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[u][1], bh, acc[m], 0, 0, 0);
+                        acc[m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[u][0], bh, acc[m], 0, 0, 0);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            half8 a2[2][2], a3[2][2];
+            fetch(a0, 0);
+            fetch(a1, 2);
+            fetch(a2, 4);
+            for (int ch = 0; ch < nch; ch += 8) {          // (nch is a multiple of eight)
+                fetch(a3, ch + 6);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a0, ch);
+                fetch(a0, ch + 8);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a1, ch + 2);
+                fetch(a1, ch + 10);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a2, ch + 4);
+                fetch(a2, ch + 12);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a3, ch + 6);
+            }
+            split_insert(top[0], acc[0], blk, big);
+            split_insert(top[1], acc[1], blk, big);
+        }
+        SplitTop t;
+        split_combine(top, t, half);
+        float *mine = tops + wave * 5 * 64 + lane;
+        mine[0] = t.v1; mine[64] = t.v2; mine[128] = t.v3;
+        mine[192] = __int_as_float(t.i1); mine[256] = __int_as_float(t.i2);
+        __syncthreads();
+        // every wave settles its share of the samples
+        {
+            const int each = 64 / nw, s = min(wave * each + lane, 63), n = min(g + s, n_hi - 1);
+            const bool valid = lane < each && g + s < n_hi;
+            float n2s = 0.0f;
+            t = SplitTop{-INFINITY, -INFINITY, -INFINITY, 0, 0};
+            for (int q = 0; q < nw; ++q) {
+                const float *o = tops + q * 5 * 64 + s;
+                split_merge(t, o[0], __float_as_int(o[192]));
+                split_merge(t, o[64], __float_as_int(o[256]));
+                t.v3 = fmaxf(t.v3, o[128]);
+                const float *nr = norms + (q * 2 + (s >> 5)) * 64 + (s & 31);
+                n2s += nr[0] + nr[32];
+            }
+            const SplitSize st = {now.state[worker].sw, now.state[worker].vabs, now.state[worker].n2};
+            const float thr = split_threshold<false>(a, st, 0.0f, sqrtf(n2s) * 1.0001f, 0.0f);
+            const int arg = split_settle<true>(t, thr, valid, xb, n, a.w + (size_t)worker * a.k * d, a.k, d, rechecks, split_shared().hard_rows,
+                                               &split_shared().hard);
+            if (valid && arg >= 0) {
+                a.idx[(size_t)worker * a.b + n] = arg;
+                if (now.dump) now.dump[(size_t)worker * a.b + n] = arg;
+            }
+        }
+        __syncthreads();                          // (tops are used, the list of hard ones is complete)
+        if (split_shared().hard > 0) {
+            split_scan_hard(a, xb, a.w + (size_t)worker * a.k * d, a.idx + (size_t)worker * a.b, now.dump ? now.dump + (size_t)worker * a.b : nullptr,
+                            reinterpret_cast<SplitHard *>(tops));
+            __syncthreads();
+        }
+    }
+    split_count_rechecks(a, worker, rechecks);
+}
+
 // ---- gradient sums of a (worker, share, group of dc columns) where the cells of a whole state do not fit LDS ----
 // 64-bit fixed-point cells as in the fused form, a centroid's row padded by one so that rows start in different banks.
 // Aligned rows: four columns per lane, four rows per lane in flight (one column per lane took 356 us for 256 workers of
@@ -1516,6 +1674,12 @@ __device__ __noinline__ void split_assign_call(u64 run, int worker, int share)
     if constexpr (NC == 0) split_assign_long_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
     else split_assign_item<NC, KEPT>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
 }
+__device__ __noinline__ inline void split_wide_call(u64 run, int worker, int share)
+{
+    SplitRunPtr r = split_uniform(run);
+    const SplitStep now = split_shared().now;
+    split_assign_wide_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
+}
 template <int NC>
 __device__ __noinline__ void split_screen_call(u64 run, int worker, int share)
 {
@@ -1544,9 +1708,9 @@ __device__ __noinline__ void split_update_call(u64 run, int worker, int blk)
     split_update_item<MODE, KEPT, REST>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared());
 }
 
-// Phases form.  WHAT: 0..4 modes of the update, 5 Eq. 4, 6 gradient sums, 10 + NC assignment (10: long rows)
+// Phases form.  WHAT: 0..4 modes of the update, 5 Eq. 4, 6 gradient sums, 9 assignment of long rows whose operands fit the LDS, 10 + NC assignment (10: longer rows)
 template <int WHAT>
-__global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(WHAT >= 13 || WHAT == 10 ? 2 : 3)))
+__global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(WHAT >= 13 || WHAT == 9 || WHAT == 10 ? 2 : 3)))
 void split_phase_kernel(SplitLaunch args)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
@@ -1564,6 +1728,8 @@ void split_phase_kernel(SplitLaunch args)
         split_assign_item<WHAT - 10, false>(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
     } else if constexpr (WHAT == 10) {
         split_assign_long_item(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
+    } else if constexpr (WHAT == 9) {
+        split_assign_wide_item(l->run.a, now, worker, rest, lds + SPLIT_LDS_SHARED);
     } else if constexpr (WHAT == 6) {
         const int ncol = l->run.a.ncol;
         split_sums_item(l->run.a, now, worker, rest / ncol, rest % ncol, lds + SPLIT_LDS_SHARED);
@@ -1621,7 +1787,8 @@ __device__ inline bool split_all_arrived(int *word, int expected, int polls)
 // arrives there during a step, and the items are inlined: such steps are bound by latency, of calls, copies of the step and
 // round trips to the L2 as much as of the memory (500 x 7 samples, 12 centroids, 1/count: 15.1 us per step, 14.2 without the round trips,
 // 13.1 with the mini-batch there, 12.2 inlined).
-template <int NC, bool KEPT, bool INV_COUNT>
+// OTHER: the other assignment of its row length, wide for NC = 0, screened else.
+template <int NC, bool KEPT, bool INV_COUNT, bool OTHER>
 __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2, 2))) void split_local_kernel(SplitRun args)
 {
     (void)args;
@@ -1667,8 +1834,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             for (int e = threadIdx.x; e < n; e += blockDim.x) reinterpret_cast<u64 *>(smem + r->a.off_cells)[e] = 0;
             for (int c = threadIdx.x; c < r->a.k; c += blockDim.x) reinterpret_cast<int *>(smem + r->a.off_cnt)[c] = 0;
         }
-        if (NC >= 2 && !KEPT && r->a.stages) split_update_call<1, KEPT, NC >= 2 && !KEPT>(run, i, 0);
-        else split_update_call<1, KEPT, false>(run, i, 0);
+        split_update_call<1, KEPT, OTHER && NC != 0>(run, i, 0);
     }
     int te = r->te0;
     long long t = r->t0, round = r->round0, s = t % r->p.S;
@@ -1700,8 +1866,10 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
         for (int i = blockIdx.x; i < W; i += gridDim.x) {
             if constexpr (KEPT) {
                 split_assign_item<NC, true>(r->a, now, i, 0, split_lds + SPLIT_LDS_SHARED);
-            } else if (NC >= 2 && r->a.stages) {
-                if constexpr (NC >= 2) split_screen_call<NC>(run, i, 0);
+            } else if constexpr (OTHER && NC == 0) {
+                split_wide_call(run, i, 0);
+            } else if constexpr (OTHER) {
+                split_screen_call<NC>(run, i, 0);
             } else {
                 split_assign_call<NC, KEPT>(run, i, 0);
             }
@@ -1738,12 +1906,8 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             if constexpr (KEPT) {
                 split_update_item<INV_COUNT ? 3 : 2, true, false>(r->p, r->u, r->a, now, i, 0, sh);
             } else {
-                auto update = [&](auto rest) {
-                    if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3, KEPT, decltype(rest)::value>(run, i, 0);
-                    else split_update_call<2, KEPT, decltype(rest)::value>(run, i, 0);
-                };
-                if (NC >= 2 && r->a.stages) update(std::integral_constant<bool, (NC >= 2)>{});
-                else update(std::false_type{});
+                if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3, KEPT, OTHER && NC != 0>(run, i, 0);
+                else split_update_call<2, KEPT, OTHER && NC != 0>(run, i, 0);
             }
             if (r->sync && now.merge) {
                 __syncthreads();
@@ -1755,16 +1919,16 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
     }
 }
 
-template <int NC, bool KEPT, bool INV_COUNT>
+template <int NC, bool KEPT, bool INV_COUNT, bool OTHER>
 hipError_t split_launch_local_form(const SplitRun &r, int blocks, int threads, unsigned lds, hipStream_t s)
 {
-    const void *kern = (const void *)split_local_kernel<NC, KEPT, INV_COUNT>;
+    const void *kern = (const void *)split_local_kernel<NC, KEPT, INV_COUNT, OTHER>;
     hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     SplitRun rr = r;
     void *args[] = {&rr};
     if (r.sync && r.p.cooperative) return hipLaunchCooperativeKernel(kern, dim3(blocks), dim3(threads), args, lds, s);
-    split_local_kernel<NC, KEPT, INV_COUNT><<<dim3(blocks), dim3(threads), lds, s>>>(rr);
+    split_local_kernel<NC, KEPT, INV_COUNT, OTHER><<<dim3(blocks), dim3(threads), lds, s>>>(rr);
     return hipGetLastError();
 }
 template <int NC>
@@ -1772,10 +1936,13 @@ hipError_t split_launch_local(const SplitRun &r, int blocks, int threads, unsign
 {
     if constexpr (NC != 0 && NC <= SPLIT_KEPT_CHUNKS) {
         if (r.a.kept)
-            return r.p.lr_mode == ASGD_LR_INV_COUNT ? split_launch_local_form<NC, true, true>(r, blocks, threads, lds, s)
-                                                    : split_launch_local_form<NC, true, false>(r, blocks, threads, lds, s);
+            return r.p.lr_mode == ASGD_LR_INV_COUNT ? split_launch_local_form<NC, true, true, false>(r, blocks, threads, lds, s)
+                                                    : split_launch_local_form<NC, true, false, false>(r, blocks, threads, lds, s);
     }
-    return split_launch_local_form<NC, false, false>(r, blocks, threads, lds, s);
+    if constexpr (NC != 1) {
+        if (NC == 0 ? r.a.wide : r.a.stages) return split_launch_local_form<NC, false, false, true>(r, blocks, threads, lds, s);
+    }
+    return split_launch_local_form<NC, false, false, false>(r, blocks, threads, lds, s);
 }
 
 }  // namespace asgd

@@ -37,6 +37,10 @@ int main(int argc, char **argv)
                     REQUIRE(q.off_list >= q.off_args + 2 * SPLIT_LISTED / 32 * 64 * 4 && q.off_list + 4 * SPLIT_LIST + SPLIT_LDS_SHARED <= q.lds);
                     REQUIRE(SPLIT_LIST >= 2 * 8 * 128);            // a sweep of eight waves adds at most as many as there is room
                 }
+                if (q.wide) {
+                    REQUIRE(q.longrow && q.waves == 8 && q.off_cells >= 64u * 4 * q.dpad && q.off_args + 8 * 64 * 4 * 7 + SPLIT_LDS_SHARED <= q.lds);
+                    REQUIRE(SPLIT_HARD * 8 * 16 <= 8 * 64 * 4 * 5 && (local || W > SPLIT_CUS || W * q.shares <= SPLIT_CUS));
+                }
                 ++plans;
             }
     printf("ok %lld plans, %lld kept, %lld of them within 1 KB of the limit\n", plans, kept, full);

@@ -30,3 +30,22 @@ def test_many_undecided_samples(B, oracle, k, d, b):
     X[::3] = X[0]                            # one row a third of the data: dozens of equal prototypes, wherever workers start
     w0 = X[rng.integers(0, 64, k)]
     run_both(B, oracle, X, k, W, b, 0.05, 0, 1, kernel=B.KERNEL_GENERIC, check_qe=False, w0=w0)
+
+
+# ---- long rows whose operands fit the LDS ----
+# one block of 32 rows to more than the waves can take at once, row lengths around the chunks that a wave keeps ahead, groups of 64 samples with ragged ends
+@pytest.mark.parametrize("k,d,W,b,E,form", [(2, 129, 4, 64, 0, "SPLIT_PHASES"), (33, 200, 3, 65, 2, "SPLIT_PHASES"), (300, 385, 8, 200, 1, "SPLIT_PHASES"), (70, 500, 5, 130, 4, "SPLIT_PHASES"),
+                                            (260, 256, 192, 130, 4, "SPLIT_LAUNCH"), (100, 150, 200, 257, 0, "SPLIT_LAUNCH"), (600, 300, 6, 70, 2, "SPLIT_PHASES")])
+def test_long_rows(B, oracle, k, d, W, b, E, form):
+    H = max(2 * b + 11, k)
+    g, _ = run_both(B, oracle, make_data(W * H, d, k, seed=k + d), k, W, b, 0.05, E, max(2, E + 2), kernel=B.KERNEL_GENERIC, check_qe=False)
+    assert g.last_run_form() == getattr(B, "FORM_" + form)
+
+
+@pytest.mark.parametrize("k,d,W,b", [(150, 200, 4, 300), (150, 200, 192, 300), (40, 300, 6, 150)])
+def test_many_equal_rows(B, oracle, k, d, W, b):
+    # dozens of prototypes are the same: more samples than the list for the whole workgroup takes have to be tried against all of them
+    X = make_data(W * max(b + 5, k), d, 8, seed=d)
+    X[::2] = X[0]
+    w0 = X[np.random.default_rng(k).integers(0, 16, k)]
+    run_both(B, oracle, X, k, W, b, 0.05, 0, 1, kernel=B.KERNEL_GENERIC, check_qe=False, w0=w0)
