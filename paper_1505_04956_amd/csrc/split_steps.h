@@ -412,7 +412,8 @@ __device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
         }
     }
     split_count_rechecks(a, worker, rechecks);
-    if (!KEPT && a.fused) {
+    // (one launch: Eq. 4 and the update of this worker come next and take the sums from the cells)
+    if (!KEPT && a.fused && !now.local) {
         __syncthreads();
         split_flush(a, worker, share, cells, cnt);
     }
@@ -1268,7 +1269,8 @@ __device__ __forceinline__ void split_gate8(const float (&wv)[8], const float (&
 }
 
 // Eq. 4 at a merge point: which buffers hold a message, and (whole states) the sums over a workgroup's rows, in fp64.
-template <bool KEPT>
+// CELLS: the sums are in the LDS still, where the assignment left them.
+template <bool KEPT, bool CELLS>
 __device__ inline void split_gate_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, SPLIT_ARG SplitArgs &a, const SplitStep &now, int i, int blk, double *red)
 {
     unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
@@ -1294,17 +1296,14 @@ __device__ inline void split_gate_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitU
         if (mail.has >> n & 1) {
             const float *ext = p.slot + exchange_buffer(now.read_parity, p.nb, n, p.W, i) * kd;
             for (int c = blk * ngrp + grp; c < k; c += u.blocks * ngrp) {
-                const int cn = KEPT ? reinterpret_cast<const int *>(smem + a.off_cnt)[c] : split_count(u, p.W, k, i, c);
+                const int cn = CELLS ? reinterpret_cast<const int *>(smem + a.off_cnt)[c] : split_count(u, p.W, k, i, c);
                 for (int j0 = lane_g * 8; j0 < d; j0 += u.g * 8) {
                     float wv[8], sm[8], ev[8];
                     split_row8(wv, w + (size_t)c * d, j0, d);
-                    if constexpr (KEPT) {
-                        split_message_row8(ev, ext + (size_t)c * d, j0, d);
-                        split_kept_sums8(sm, a, smem, c, cn, j0, d);
-                    } else {
-                        split_row8(ev, ext + (size_t)c * d, j0, d);
-                        split_sums8(sm, u, p.W, k, i, c, j0, d);
-                    }
+                    if constexpr (KEPT) split_message_row8(ev, ext + (size_t)c * d, j0, d);
+                    else split_row8(ev, ext + (size_t)c * d, j0, d);
+                    if constexpr (CELLS) split_kept_sums8(sm, a, smem, c, cn, j0, d);
+                    else split_sums8(sm, u, p.W, k, i, c, j0, d);
                     split_gate8(wv, sm, ev, cn, j0, p, lhs, rhs, nrm);
                 }
             }
@@ -1323,7 +1322,7 @@ __device__ __forceinline__ bool split_gate_at_once(SPLIT_ARG SplitArgs &a, SPLIT
 // 4: a step with partial messages.
 // REST: also the norms of what the rows' high parts leave over, for screened samples.
 // (A template: a phase this short is mostly the fetch of its own code.)
-template <int MODE, bool KEPT, bool REST>
+template <int MODE, bool KEPT, bool REST, bool CELLS>
 __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG SplitUpdate &u, SPLIT_ARG SplitArgs &a, const SplitStep &now, int i, int blk,
                                          SplitShared &sh)
 {
@@ -1459,9 +1458,28 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
     const float inv_all = 1.0f / (float)(__builtin_popcount(delta_mask) + 1);
     int nz = 0, accd = 0, near_row = 0;
     const int rows = MODE == 1 ? u.kpad : k;             // padding rows are written once
+    // A unit per lane and row (up to 512 columns): what does not depend on the row is fetched once, a state row while the one before it is worked
+    // on; row after row was a chain of latencies.
+    const bool one = !KEPT && units <= u.g;
+    const int c_step = u.blocks * ngrp, j_one = lane_g * 8;
+    float mid_one[8], w_next[8];
+    int at_one[CELLS ? 8 : 1];
+    double inv_one[CELLS ? 8 : 1];
+    if (one && j_one < d) {
+        split_row8(mid_one, u.m, j_one, d);
+        split_row8(w_next, w + (size_t)min(blk * ngrp + grp, k - 1) * d, j_one, d);
+        if constexpr (CELLS) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int j = min(split_column(j_one + e, d), d - 1);
+                at_one[e] = split_cell(a, j);
+                inv_one[e] = a.colscale[d + j];
+            }
+        }
+    }
     for (int c = blk * ngrp + grp; c < rows; c += u.blocks * ngrp) {
         const bool real = MODE != 1 || c < k;
-        const int cn = STEP ? (KEPT ? kept_cnt[c] : split_count(u, p.W, k, i, c)) : 0;
+        const int cn = STEP ? (CELLS ? kept_cnt[c] : split_count(u, p.W, k, i, c)) : 0;
         int rowmask = delta_mask;
         float inv = inv_all;
         if (ROWWISE) {
@@ -1503,13 +1521,25 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
             for (int e = 0; e < 8; ++e) v[e] = 0.0f;
             if (real && j0 < d) {
                 float wn[8], mid[8];
-                split_row8(wn, w + (size_t)c * d, j0, d);
-                split_row8(mid, u.m, j0, d);
+                if (one) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) { wn[e] = w_next[e]; mid[e] = mid_one[e]; }
+                    split_row8(w_next, w + (size_t)min(c + c_step, k - 1) * d, j0, d);      // (another row: the stores below do not touch it)
+                } else {
+                    split_row8(wn, w + (size_t)c * d, j0, d);
+                    split_row8(mid, u.m, j0, d);
+                }
                 if (STEP) {
                     float sm[8];
-                    if constexpr (KEPT) {
-                        split_kept_sums8(sm, a, smem, c, cn, j0, d);
-                        split_kept_clear8(a, smem, c, j0, d);
+                    if constexpr (CELLS) {
+                        if (one) {
+                            const u64 *cells = reinterpret_cast<const u64 *>(smem + a.off_cells) + c * split_cell_stride(a);
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) sm[e] = split_sum(cells[at_one[e]], cn, inv_one[e]);
+                        } else {
+                            split_kept_sums8(sm, a, smem, c, cn, j0, d);
+                        }
+                        if constexpr (KEPT) split_kept_clear8(a, smem, c, j0, d);
                     } else {
                         split_sums8(sm, u, p.W, k, i, c, j0, d);
                     }
@@ -1693,19 +1723,19 @@ __device__ __noinline__ inline void split_sums_call(u64 run, int worker, int sha
     const SplitStep now = split_shared().now;
     split_sums_item(r->a, now, split_uniform(worker), split_uniform(share), split_uniform(chunk), split_lds + SPLIT_LDS_SHARED);
 }
-template <bool KEPT>
+template <bool KEPT, bool CELLS>
 __device__ __noinline__ void split_gate_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
-    split_gate_item<KEPT>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared().red);
+    split_gate_item<KEPT, CELLS>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared().red);
 }
-template <int MODE, bool KEPT, bool REST>
+template <int MODE, bool KEPT, bool REST, bool CELLS>
 __device__ __noinline__ void split_update_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
-    split_update_item<MODE, KEPT, REST>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared());
+    split_update_item<MODE, KEPT, REST, CELLS>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared());
 }
 
 // Phases form.  WHAT: 0..4 modes of the update, 5 Eq. 4, 6 gradient sums, 9 assignment of long rows whose operands fit the LDS, 10 + NC assignment (10: longer rows)
@@ -1734,9 +1764,9 @@ void split_phase_kernel(SplitLaunch args)
         const int ncol = l->run.a.ncol;
         split_sums_item(l->run.a, now, worker, rest / ncol, rest % ncol, lds + SPLIT_LDS_SHARED);
     } else if constexpr (WHAT == 5) {
-        split_gate_item<false>(l->run.p, l->run.u, l->run.a, now, worker, rest, reinterpret_cast<SplitShared *>(lds)->red);
+        split_gate_item<false, false>(l->run.p, l->run.u, l->run.a, now, worker, rest, reinterpret_cast<SplitShared *>(lds)->red);
     } else {
-        split_update_item<WHAT, false, false>(l->run.p, l->run.u, l->run.a, now, worker, rest, *reinterpret_cast<SplitShared *>(lds));
+        split_update_item<WHAT, false, false, false>(l->run.p, l->run.u, l->run.a, now, worker, rest, *reinterpret_cast<SplitShared *>(lds));
     }
 }
 template <int WHAT>
@@ -1803,6 +1833,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
     for (int n = 0; n < MAX_BUFFERS; ++n) now.shift[n] = 0;
     const int W = r->p.W;
     const bool det = r->p.mode == ASGD_MODE_DETERMINISTIC;
+    constexpr bool CELLS = NC != 0 && !OTHER;           // sums may be formed along with the assignment
     // (the test hook is a budget for all the waits of the launch)
     int budget = r->p.wait_polls > 0 ? r->p.wait_polls : r->wait_polls;
     auto wait = [&](const int *flag, int want, bool at_least) {            // (thread 0)
@@ -1825,7 +1856,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
         if (r->t0 < r->t1) split_batch_fetch(r->a, blockIdx.x, r->t0 % r->p.S * r->p.b, split_lds + SPLIT_LDS_SHARED + r->a.off_batch);
     }
     for (int i = blockIdx.x; i < W; i += gridDim.x) {
-        split_update_call<0, KEPT, false>(run, i, 0);
+        split_update_call<0, KEPT, false, false>(run, i, 0);
         __syncthreads();
         if constexpr (KEPT) {
             unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
@@ -1834,7 +1865,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             for (int e = threadIdx.x; e < n; e += blockDim.x) reinterpret_cast<u64 *>(smem + r->a.off_cells)[e] = 0;
             for (int c = threadIdx.x; c < r->a.k; c += blockDim.x) reinterpret_cast<int *>(smem + r->a.off_cnt)[c] = 0;
         }
-        split_update_call<1, KEPT, OTHER && NC != 0>(run, i, 0);
+        split_update_call<1, KEPT, OTHER && NC != 0, false>(run, i, 0);
     }
     int te = r->te0;
     long long t = r->t0, round = r->round0, s = t % r->p.S;
@@ -1889,9 +1920,10 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             }
             if (now.merge) {
                 if constexpr (KEPT) {
-                    if (!split_gate_at_once(r->a, r->u)) split_gate_item<true>(r->p, r->u, r->a, now, i, 0, sh.red);
+                    if (!split_gate_at_once(r->a, r->u)) split_gate_item<true, true>(r->p, r->u, r->a, now, i, 0, sh.red);
                 } else {
-                    split_gate_call<KEPT>(run, i, 0);
+                    if (CELLS && r->a.fused) split_gate_call<KEPT, CELLS>(run, i, 0);
+                    else split_gate_call<KEPT, false>(run, i, 0);
                 }
             }
             if (r->sync && now.send && now.round >= 2) {
@@ -1904,10 +1936,14 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
                 __syncthreads();
             }
             if constexpr (KEPT) {
-                split_update_item<INV_COUNT ? 3 : 2, true, false>(r->p, r->u, r->a, now, i, 0, sh);
+                split_update_item<INV_COUNT ? 3 : 2, true, false, true>(r->p, r->u, r->a, now, i, 0, sh);
             } else {
-                if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3, KEPT, OTHER && NC != 0>(run, i, 0);
-                else split_update_call<2, KEPT, OTHER && NC != 0>(run, i, 0);
+                auto update = [&](auto cells) {
+                    if (r->p.lr_mode == ASGD_LR_INV_COUNT) split_update_call<3, KEPT, OTHER && NC != 0, decltype(cells)::value>(run, i, 0);
+                    else split_update_call<2, KEPT, OTHER && NC != 0, decltype(cells)::value>(run, i, 0);
+                };
+                if (CELLS && r->a.fused) update(std::integral_constant<bool, CELLS>{});
+                else update(std::false_type{});
             }
             if (r->sync && now.merge) {
                 __syncthreads();
