@@ -458,7 +458,7 @@ __device__ inline void split_scan_hard(SPLIT_ARG SplitArgs &a, const float *xb, 
 // The listed samples: 128 at a time, their operands in the LDS (where the stages were), every wave its own blocks of the state's rows with both
 // parts straight from the L2, a block ahead.
 template <int NC>
-__device__ __noinline__ void split_listed(u64 args_any, u64 state_any, long long row0_any, u64 dump_any, int worker_any, int share_any)
+__device__ __forceinline__ void split_listed(u64 args_any, u64 state_any, long long row0_any, u64 dump_any, int worker_any, int share_any)
 {
     SPLIT_ARG SplitArgs &a = *(SPLIT_ARG SplitArgs *)split_uniform64(args_any);
     const SplitState *state = (const SplitState *)split_uniform64(state_any);
@@ -1690,32 +1690,18 @@ struct SplitLaunch {                       // arguments of a phase
     SplitStep now;
 };
 
-// The items are functions that are really called, each with registers of its own: inlined into one loop over the steps
-// the compiler kept the values of all phases at once, hundreds of spills.  A call passes its arguments in vector
-// registers; what is uniform is read back into scalar ones.
+// The items are inlined into the loop over the steps, each with its own copy of the step's values.  (Called, a function saves the half of the
+// registers that it uses and a caller may have use for: for an assignment 200 KB of a compute unit per call, out to memory and back.  k = d = 100,
+// W = 512: 9300 us a run with all of them called, 8720 with the assignment inlined, 8610 with Eq. 4 and the update.)  Those that
+// are called pass their arguments in vector registers; what is uniform is read back into scalar ones.
 typedef SPLIT_ARG SplitRun *SplitRunPtr;
 __device__ __forceinline__ int split_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 __device__ __forceinline__ SplitRunPtr split_uniform(u64 p) { return (SplitRunPtr)split_uniform64(p); }
-template <int NC, bool KEPT>
-__device__ __noinline__ void split_assign_call(u64 run, int worker, int share)
+__device__ __noinline__ inline void split_long_call(u64 run, int worker, int share)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
-    if constexpr (NC == 0) split_assign_long_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
-    else split_assign_item<NC, KEPT>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
-}
-__device__ __noinline__ inline void split_wide_call(u64 run, int worker, int share)
-{
-    SplitRunPtr r = split_uniform(run);
-    const SplitStep now = split_shared().now;
-    split_assign_wide_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
-}
-template <int NC>
-__device__ __noinline__ void split_screen_call(u64 run, int worker, int share)
-{
-    SplitRunPtr r = split_uniform(run);
-    const SplitStep now = split_shared().now;
-    split_screen_item<NC>(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
+    split_assign_long_item(r->a, now, split_uniform(worker), split_uniform(share), split_lds + SPLIT_LDS_SHARED);
 }
 __device__ __noinline__ inline void split_sums_call(u64 run, int worker, int share, int chunk)
 {
@@ -1724,14 +1710,14 @@ __device__ __noinline__ inline void split_sums_call(u64 run, int worker, int sha
     split_sums_item(r->a, now, split_uniform(worker), split_uniform(share), split_uniform(chunk), split_lds + SPLIT_LDS_SHARED);
 }
 template <bool KEPT, bool CELLS>
-__device__ __noinline__ void split_gate_call(u64 run, int worker, int blk)
+__device__ __forceinline__ void split_gate_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
     split_gate_item<KEPT, CELLS>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared().red);
 }
 template <int MODE, bool KEPT, bool REST, bool CELLS>
-__device__ __noinline__ void split_update_call(u64 run, int worker, int blk)
+__device__ __forceinline__ void split_update_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
@@ -1897,12 +1883,13 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
         for (int i = blockIdx.x; i < W; i += gridDim.x) {
             if constexpr (KEPT) {
                 split_assign_item<NC, true>(r->a, now, i, 0, split_lds + SPLIT_LDS_SHARED);
-            } else if constexpr (OTHER && NC == 0) {
-                split_wide_call(run, i, 0);
-            } else if constexpr (OTHER) {
-                split_screen_call<NC>(run, i, 0);
+            } else if constexpr (NC == 0 && !OTHER) {
+                split_long_call(run, i, 0);
             } else {
-                split_assign_call<NC, KEPT>(run, i, 0);
+                const SplitStep then = sh.now;
+                if constexpr (NC == 0) split_assign_wide_item(r->a, then, i, 0, split_lds + SPLIT_LDS_SHARED);
+                else if constexpr (OTHER) split_screen_item<NC>(r->a, then, i, 0, split_lds + SPLIT_LDS_SHARED);
+                else split_assign_item<NC, false>(r->a, then, i, 0, split_lds + SPLIT_LDS_SHARED);
             }
             if (!KEPT && !r->a.fused)
                 for (int q = 0; q < r->a.ncol; ++q) split_sums_call(run, i, 0, q);
