@@ -1458,9 +1458,9 @@ __device__ inline void split_update_item(SPLIT_ARG StepParams &p, SPLIT_ARG Spli
     const float inv_all = 1.0f / (float)(__builtin_popcount(delta_mask) + 1);
     int nz = 0, accd = 0, near_row = 0;
     const int rows = MODE == 1 ? u.kpad : k;             // padding rows are written once
-    // A unit per lane and row (up to 512 columns): what does not depend on the row is fetched once, a state row while the one before it is worked
+    // One launch, a unit per lane and row: what does not depend on the row is fetched once, a state row while the one before it is worked
     // on; row after row was a chain of latencies.
-    const bool one = !KEPT && units <= u.g;
+    const bool one = !KEPT && (CELLS || REST) && units <= u.g;
     const int c_step = u.blocks * ngrp, j_one = lane_g * 8;
     float mid_one[8], w_next[8];
     int at_one[CELLS ? 8 : 1];
