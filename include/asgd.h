@@ -141,8 +141,8 @@ typedef struct asgd_stats {
  * Create a context for the problem of Sec. 5.1 (k prototypes for points in R^d) run by
  * Alg. 5 with W workers ("nodes"), mini-batch size b and step size eps = lr.
  * Requires k, d, W, b >= 1 and lr > 0 (Alg. 5 "Require"; W = 1 is allowed and equals
- * Alg. 4).  Allocates W*k*d floats of state and the exchange buffers on the current
- * device.  More is allocated by the first call that needs it and kept until asgd_destroy():
+ * Alg. 4).  Allocates W*k*d floats of state, the exchange buffers and the operands of one state (Eq. 8; 4 bytes per
+ * padded element, rows of 8 to 128 columns) on the current device.  More is allocated by the first call that needs it and kept until asgd_destroy():
  * 8 KB per column at the first asgd_load_shards() (d <= 8192; where the streaming kernel runs: at the first run of another; that
  * kernel takes 4 bytes per worker and mini-batch once it has met large elements, see asgd_load_shards()), and the operands and sums of the
  * kernels with fp16-split operands at a run, several times W*k*d floats and 32 GiB at most

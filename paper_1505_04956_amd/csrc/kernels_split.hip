@@ -306,37 +306,60 @@ __global__ __launch_bounds__(SPLITQ_THREADS) void splitq_operands_kernel(ScreenQ
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int k = a.q.k, d = a.q.d, dpad = a.q.dpad, nch = dpad / 16;
     const float *w = a.q.w;
+    // this workgroup's rows, sixteen lanes per row at most, so twice 32 of them at most
+    int g = 1;
+    while (g < dpad / 8) g *= 2;
+    const int lane_g = tid & (g - 1), slot = 8 * lane_g;
+    float raw[2][8];
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int c = min((int)blockIdx.x * 64 + tid / g + q * (SPLITQ_THREADS / g), k - 1);
+        split_load8<true>(raw[q], w + (size_t)c * d, slot < d ? slot : 0, d);
+    }
     for (int j = tid; j < dpad; j += SPLITQ_THREADS) {
         const float mid = splitq_middle_of(w, k, d, j);
         m[j] = mid;
         if (blockIdx.x == 0) a.m[j] = mid;
     }
     __syncthreads();
-    // largest |v_cj| of the nine rows, and of SCREENQ_ROWS samples (those that are finite)
-    auto widest = [&](const float *row) {
-        unsigned vb = 0;
-        for (int slot = lane; slot < dpad; slot += 64)
-            if (split_slot_used(slot, d)) vb = max(vb, __float_as_uint(row[split_column(slot, d)] - m[slot]) & 0x7fffffffu);
+    auto size_of = [&](float v, int slot) { return __float_as_uint(v - m[slot]) & 0x7fffffffu; };
+    auto largest = [&](unsigned v) {
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) vb = max(vb, (unsigned)__shfl_xor((int)vb, off, 64));
-        return __uint_as_float(min(vb, 0x7f800000u));
+        for (int off = 32; off > 0; off >>= 1) v = max(v, (unsigned)__shfl_xor((int)v, off, 64));
+        return __uint_as_float(min(v, 0x7f800000u));
     };
-    for (int r = wave; r < 9; r += 8) {
-        const float most = widest(w + (size_t)(r * k / 9) * d);
-        if (lane == 0) most_of[r] = most;
-    }
-    float far = 0.0f;
+    // largest |v_cj| of the nine rows, and the largest finite one of SCREENQ_ROWS samples; all loads of a wave in flight (one row after the
+    // other: 8 us of 17)
+    constexpr int ROWS = SCREENQ_ROWS / 8;
+    float nine[9], typical, far = 0.0f;
+    {
+        unsigned own = 0, last = 0;
+        for (int slot = lane; slot < dpad; slot += 64) {
+            if (!split_slot_used(slot, d)) continue;
+            const int j = split_column(slot, d);
+            float xv[ROWS];
+            const float wv = w[(size_t)(wave * k / 9) * d + j], w8 = w[(size_t)(8 * k / 9) * d + j];
 #pragma unroll
-    for (int r = 0; r < SCREENQ_ROWS / 8; ++r) {
-        const float most = widest(a.q.x + (size_t)((8 * r + wave) * a.q.N / SCREENQ_ROWS) * d);
-        if (most < INFINITY) far = fmaxf(far, most);
+            for (int r = 0; r < ROWS; ++r) xv[r] = a.q.x[(size_t)((8 * r + wave) * a.q.N / SCREENQ_ROWS) * d + j];
+            own = max(own, size_of(wv, slot));
+            last = max(last, size_of(w8, slot));
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                const float v = __uint_as_float(size_of(xv[r], slot));
+                if (v < INFINITY) far = fmaxf(far, v);
+            }
+        }
+        const float own_most = largest(own), last_most = largest(last), far_most = largest(__float_as_uint(far));
+        if (lane == 0) {
+            most_of[wave] = own_most;
+            if (wave == 0) most_of[8] = last_most;
+            red[0][wave] = far_most;
+        }
     }
-    if (lane == 0) red[0][wave] = far;
     __syncthreads();
-    float nine[9];
 #pragma unroll
     for (int r = 0; r < 9; ++r) nine[r] = most_of[r];
-    float typical = splitq_middle(nine);
+    typical = splitq_middle(nine);
 #pragma unroll
     for (int r = 0; r < 8; ++r) far = fmaxf(far, red[0][r]);
     __syncthreads();
@@ -344,7 +367,10 @@ __global__ __launch_bounds__(SPLITQ_THREADS) void splitq_operands_kernel(ScreenQ
         // (at m itself: the largest of all the rows)
         float most = 0.0f;
         for (int c = wave; c < k; c += 8) {
-            const float v = widest(w + (size_t)c * d);
+            unsigned row = 0;
+            for (int slot = lane; slot < dpad; slot += 64)
+                if (split_slot_used(slot, d)) row = max(row, size_of(w[(size_t)c * d + split_column(slot, d)], slot));
+            const float v = largest(row);
             if (v < INFINITY) most = fmaxf(most, v);
         }
         if (lane == 0) red[0][wave] = most;
@@ -364,16 +390,16 @@ __global__ __launch_bounds__(SPLITQ_THREADS) void splitq_operands_kernel(ScreenQ
         h.direct = r < SPLITQ_RATIO_MIN || r + sw_exp < -126 || r + sw_exp > 126 ? 1.0f : 0.0f;
         *reinterpret_cast<ScreenqHead *>(a.head) = h;
     }
-    int g = 1;
-    while (g < dpad / 8) g *= 2;                              // (dpad <= 128: sixteen lanes at most)
     float vmin = INFINITY, vmax = 0.0f, vfar = INFINITY, rest = 0.0f;
-    const int lane_g = tid & (g - 1), slot = 8 * lane_g;
-    for (int c0 = tid / g; c0 < 64; c0 += SPLITQ_THREADS / g) {
-        const int c = blockIdx.x * 64 + c0;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        const int c0 = tid / g + q * (SPLITQ_THREADS / g), c = blockIdx.x * 64 + c0;
+        if (c0 >= 64) continue;                               // (the same for all lanes of a row)
         float v[8], sq = 0.0f, r2 = 0.0f;
         unsigned vb = 0;
         half8 hi, lo;
-        if (slot < dpad) splitq_row(v, w, m, c, k, slot, d);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = c < k && slot < d && split_slot_used(slot + e, d) ? raw[q][e] - m[slot + e] : 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const float y = slot < dpad ? v[e] * sw : 0.0f;
@@ -425,7 +451,7 @@ __global__ __launch_bounds__(SPLITQ_THREADS) void splitq_operands_kernel(ScreenQ
     }
 }
 
-// Screening for rows of 8 to 128 columns, whatever k is; microseconds with three products for all samples, and screened: 4e6 samples, k = 12, d = 9: 164,
+// Screening for rows of 8 to 128 columns, whatever k is (the operands of a state, that is; see also launch_quant_error_split); microseconds with three products for all samples, and screened: 4e6 samples, k = 12, d = 9: 164,
 // 100; k = 37, d = 75: 529, 333; k = 1000, d = 9: 917, 515; k = 1000, d = 32: 1040, 546; k = 100, d = 20: 303, 181; 2e6 samples, k = 512, d = 128:
 // 1227, 478; 20000 samples, k = 512, d = 125: 105, 38.  Also where prototypes lie close together and many samples stay undecided (k = 1000, d = 9,
 // sigma 0.3: 886, 439).  Shorter rows are loaded one by one, longer ones do not fit the registers.
@@ -459,7 +485,8 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
     *nblocks_out = nblocks;                       // one workgroup per compute unit
     a.kpad = npair * 64;
     a.nan_is_inf = nan_is_inf;
-    if (quant_screens(k, d)) {
+    // (short rows, few samples: the launch for the state does not pay, k = 20, d = 9, 3000 samples 17.6 us without it, 20.0 with it, k = 40, d = 13, 1500 the same)
+    if (quant_screens(k, d) && !(d <= 16 && N <= 8192)) {
         ScreenQuant c;
         c.q = a;
         const QuantOperands l = quant_operands(k, d);

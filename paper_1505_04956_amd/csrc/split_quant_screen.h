@@ -7,7 +7,7 @@
 // registers each, so that a state operand read from the LDS is used as often.  k = 1024, d = 128, 5e6 samples: 4.8 ms with three
 // products and the state split by every workgroup for every 512 samples, 1.6 now, of which the matrix instructions and insertions take
 // 0.85, loading and converting the samples 0.6 (4.3 TB/s) and the distances 0.4; waves that start apart, priorities and a
-// deeper queue of stages changed nothing.  k = 37, d = 75, 4e6 samples: 507 us, 305 now (3.9 TB/s).
+// deeper queue of stages changed nothing.  k = 37, d = 75, 4e6 samples: 507 us, 283 now (4.2 TB/s).
 //
 // The samples share one power-of-two scale, from 64 of them, which leaves room for elements a hundred times as large as those;
 // larger ones go to the list, where every sample has its own.  So the offsets of the rows are the same for all samples and are
