@@ -8,6 +8,7 @@ namespace asgd {
 
 hipError_t launch_split_quant_0(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_quant_1(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
+hipError_t launch_split_quant_2(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_screen_quant_1(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_screen_quant_2(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_screen_quant_3(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
@@ -485,8 +486,10 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
     *nblocks_out = nblocks;                       // one workgroup per compute unit
     a.kpad = npair * 64;
     a.nan_is_inf = nan_is_inf;
-    // (short rows, few samples: the launch for the state does not pay, k = 20, d = 9, 3000 samples 17.6 us without it, 20.0 with it, k = 40, d = 13, 1500 the same)
-    if (quant_screens(k, d) && !(d <= 16 && N <= 8192)) {
+    // (Short rows, few samples: the launch for the state and a wave's pass over its few undecided samples do not pay.  Microseconds without and with
+    // them: k = 100, d = 14: 20000 samples 19.9, 22.1, 80000 20.8, 24.3, 160000 27.4, 26.9; k = 1000, d = 9: 80000 55.6, 60.5, 160000 83.2, 72.1; k = 31, d = 20: 100000
+    // 18.9, 23.4, 300000 31.4, 29.6.)
+    if (quant_screens(k, d) && !(d <= 32 && N <= 120000)) {
         ScreenQuant c;
         c.q = a;
         const QuantOperands l = quant_operands(k, d);
@@ -525,7 +528,7 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
     unsigned o = (unsigned)(a.resident ? all : two);
     a.off_hs = o; o += split_round16((size_t)a.kpad * 4);
     a.off_m = o;  o += split_round16((size_t)a.dpad * 4);
-    return d > 128 ? launch_split_quant_0(a, nblocks, o, s) : launch_split_quant_1(a, nblocks, o, s);
+    return d > 128 ? launch_split_quant_0(a, nblocks, o, s) : d > 16 ? launch_split_quant_2(a, nblocks, o, s) : launch_split_quant_1(a, nblocks, o, s);
 }
 
 }  // namespace asgd

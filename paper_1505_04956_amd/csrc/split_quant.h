@@ -1,4 +1,4 @@
-// Eq. 8 on the fp16 matrix instructions, rows of less than 8 and of more than 128 columns (the others: split_quant_screen.h, which shares
+// Eq. 8 on the fp16 matrix instructions, rows of less than 8 and of more than 128 columns, few samples of up to 32 (the others: split_quant_screen.h, which shares
 // the decisions and what follows about odd rows).  Scores with fp16-split operands (split_core.h) only screen: the
 // error of a score is bounded, and a sample whose runner-up lies within the bound is decided by distances in direct form -
 // two candidates by theirs, more by those to all the centroids.  So every sample adds the smallest of its direct fp32
