@@ -15,6 +15,7 @@ constexpr int SPLIT_CUS = 256;
 constexpr int SPLIT_HARD = 32;                    // samples that may wait for a scan of all the rows by a whole workgroup
 constexpr int SPLIT_LISTED = 128;                 // of them at a time
 constexpr int SPLIT_LIST = 2048;                  // undecided samples of a screened mini-batch that are noted before they are scored again
+constexpr int SPLIT_UNSCREENED = 15;              // items without screening after one that was given up
 constexpr int SPLIT_KEPT_CHUNKS = 4;              // longest rows of a kept worker: beyond, its kernel needs more registers than there are
 
 struct SplitPlan {
@@ -34,6 +35,14 @@ struct SplitPlan {
 
 inline int split_padded_row(int d) { return d > 128 ? (d + 127) / 128 * 128 : (d + 15) / 16 * 16; }
 inline unsigned split_round16(size_t v) { return (unsigned)((v + 15) / 16 * 16); }
+
+// Of `screened` samples of a workgroup `open` are undecided: is the rest better off without screening?  An undecided sample costs its screening, a
+// second read and conversion and all three products, with few other samples to share the state's operands.  Microseconds per step with three
+// products for all, with all of them screened, and given up (samples next to one of two equal rows, share): k = 1024, d = 128, b = 4096: 10 %
+// 13510, 11070, -, 20 % 20720, 20310, 20720, 30 % 21870, 28730, 21890, all 30150, 83880, 30130; k = 600, d = 60, b = 1500: 20 % 211, 210, -, 30 % 219, 230, 238, all 273,
+// 381, 294; k = 2000, d = 20, b = 800: 30 % 262, 229, -, 50 % 273, 267, 282, all 297, 350, 310.  One column a thousand times as wide as the others:
+// k = 1024, d = 64, b = 1500 6457, 18126, 6477.
+inline constexpr bool split_screen_gives_up(int open, int screened, int nch) { return (long long)open * (nch <= 3 ? 2 : nch == 4 ? 4 : 6) > screened; }
 
 inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
 {

@@ -72,6 +72,7 @@ struct SplitShared {                       // start of the LDS: the step, and sp
     int listed;                            // undecided samples in the list
     int hard;                              // samples that wait for a scan of all the rows, SPLIT_HARD of them at most in `hard_rows`
     int hard_rows[SPLIT_HARD];
+    int unscreened;                        // items that this workgroup does not screen
     SplitSize size[3];                     // SplitState of a kept worker
 };
 
@@ -276,10 +277,11 @@ __device__ __forceinline__ void split_count_rechecks(SPLIT_ARG SplitArgs &a, int
 // registers (NC * 16 registers); the state's operands come from LDS, resident when they fit, else one row pair at a time
 // through two stages.  fused: the gradient sums are formed right away from a second, coalesced read of the wave's
 // samples (in a cache still), in 64-bit fixed-point cells in LDS.
+// `first`: samples of the share that are decided already.
 template <int NC, bool KEPT>
-__device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
+__device__ void split_assign_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem, int first = 0)
 {
-    const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len);
+    const int n_lo = share * a.share_len + first, n_hi = min(a.b, share * a.share_len + a.share_len);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int nw = blockDim.x >> 6, npair = (a.nblk + 1) / 2;
     u64 *cells = reinterpret_cast<u64 *>(smem + a.off_cells);
@@ -451,7 +453,8 @@ __device__ inline void split_scan_hard(SPLIT_ARG SplitArgs &a, const float *xb, 
 
 // ---- screened assignment: rows of 17 to 128 columns, a state that is streamed, sums in a pass of their own ----
 // High parts alone, up to four tiles of 32 samples per wave, the state's high parts through LDS stages; samples that are not decided by that go
-// to a list and are scored with all three products.  The decisions are those of the other items.
+// to a list and are scored with all three products.  The decisions are those of the other items.  A workgroup that finds too many of its samples
+// open (split_screen_gives_up()) goes on with the item without screening, and begins the next SPLIT_UNSCREENED mini-batches with it.
 // k = 1024, d = 128, b = 4096, W = 256, microseconds per step: 1130 with three products for all, 780 now: loading and converting the samples and
 // the stages 230, matrix instructions and insertions 130, the 3 % that are listed 95, sums 175, update 125.
 
@@ -588,8 +591,9 @@ __device__ __forceinline__ void split_listed(u64 args_any, u64 state_any, long l
     __syncthreads();
 }
 
+// Returns the first sample of the share that is left to the item without screening, -1 if all are decided.
 template <int NC>
-__device__ void split_screen_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
+__device__ int split_screen_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
 {
     const int n_lo = share * a.share_len, n_hi = min(a.b, n_lo + a.share_len), n = n_hi - n_lo;
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
@@ -616,7 +620,7 @@ __device__ void split_screen_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
     if (tid == 0) split_shared().listed = split_shared().hard = 0;
     __syncthreads();
 
-    int turn = 0;
+    int turn = 0, done = 0;                     // done: samples before it are decided, none of them is in the list
     bool staged = false;
     // one sweep over this wave's 32 * T samples from g on (of the share)
     auto sweep = [&](auto tiles, int g, bool last) {
@@ -714,15 +718,18 @@ __device__ void split_screen_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, 
         else sweep(std::integral_constant<int, 2>{}, g0 + wave * 64, next >= n);
         g0 = next;
         __syncthreads();
-        const int listed = split_shared().listed;
+        const int listed = __builtin_amdgcn_readfirstlane(split_shared().listed);
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");          // (the stage that is on its way: the listed samples take its place)
         __syncthreads();                          // (everybody has read the number before anybody adds to it)
+        if (split_screen_gives_up(listed, min(g0, n) - done, NC)) return done;
         if (listed > 0 && (g0 >= n || listed > SPLIT_LIST - nw * 128)) {
             split_listed<NC>((u64)&a, (u64)now.state, now.row0, (u64)now.dump, worker, share);
             if (g0 < n) stage_fetch(0, turn & 1);
             staged = false;
+            done = g0;
         }
     }
+    return -1;
 }
 
 // ---- assignment for rows of more than 128 columns ----
@@ -1709,6 +1716,23 @@ __device__ __noinline__ inline void split_sums_call(u64 run, int worker, int sha
     const SplitStep now = split_shared().now;
     split_sums_item(r->a, now, split_uniform(worker), split_uniform(share), split_uniform(chunk), split_lds + SPLIT_LDS_SHARED);
 }
+// Screened, as long as that decides enough; the item without it is called, not inlined, because ordinary data never need it.
+template <int NC>
+__device__ __noinline__ void split_assign_call(u64 run, int worker, int first)
+{
+    SplitRunPtr r = split_uniform(run);
+    const SplitStep now = split_shared().now;
+    split_assign_item<NC, false>(r->a, now, split_uniform(worker), 0, split_lds + SPLIT_LDS_SHARED, split_uniform(first));
+}
+template <int NC>
+__device__ __forceinline__ void split_screen_call(u64 run, const SplitStep &now, int worker)
+{
+    SplitRunPtr r = split_uniform(run);
+    const int off = split_uniform(split_shared().unscreened), first = off > 0 ? 0 : split_screen_item<NC>(r->a, now, worker, 0, split_lds + SPLIT_LDS_SHARED);
+    __syncthreads();                            // (everybody has read it)
+    if (threadIdx.x == 0) split_shared().unscreened = off > 0 ? off - 1 : first >= 0 ? SPLIT_UNSCREENED : 0;
+    if (first >= 0) split_assign_call<NC>(run, worker, first);
+}
 template <bool KEPT, bool CELLS>
 __device__ __forceinline__ void split_gate_call(u64 run, int worker, int blk)
 {
@@ -1836,7 +1860,10 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
         __syncthreads();
         if (!sh.delta) return;
     }
-    if (threadIdx.x == 0) sh.now = now;
+    if (threadIdx.x == 0) {
+        sh.now = now;
+        sh.unscreened = 0;
+    }
     __syncthreads();
     if constexpr (KEPT) {
         if (r->t0 < r->t1) split_batch_fetch(r->a, blockIdx.x, r->t0 % r->p.S * r->p.b, split_lds + SPLIT_LDS_SHARED + r->a.off_batch);
@@ -1888,7 +1915,7 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
             } else {
                 const SplitStep then = sh.now;
                 if constexpr (NC == 0) split_assign_wide_item(r->a, then, i, 0, split_lds + SPLIT_LDS_SHARED);
-                else if constexpr (OTHER) split_screen_item<NC>(r->a, then, i, 0, split_lds + SPLIT_LDS_SHARED);
+                else if constexpr (OTHER) split_screen_call<NC>(run, then, i);
                 else split_assign_item<NC, false>(r->a, then, i, 0, split_lds + SPLIT_LDS_SHARED);
             }
             if (!KEPT && !r->a.fused)

@@ -36,6 +36,7 @@ int main(int argc, char **argv)
                     REQUIRE(q.off_cells >= (q.stages > 1 ? 2 : 1) * q.stage_pairs * pair && q.off_cells >= operands && q.off_cells >= best && q.off_cells >= SPLIT_HARD * 8 * 16);
                     REQUIRE(q.off_list >= q.off_args + 2 * SPLIT_LISTED / 32 * 64 * 4 && q.off_list + 4 * SPLIT_LIST + SPLIT_LDS_SHARED <= q.lds);
                     REQUIRE(SPLIT_LIST >= 2 * 8 * 128);            // a sweep of eight waves adds at most as many as there is room
+                    REQUIRE(q.off_cells >= 2u * q.nch * 4 * SPLIT_PIECE && !q.fused && !q.resident);            // the stages of the item without screening
                 }
                 if (q.wide) {
                     REQUIRE(q.longrow && q.waves == 8 && q.off_cells >= 64u * 4 * q.dpad && q.off_args + 8 * 64 * 4 * 7 + SPLIT_LDS_SHARED <= q.lds);

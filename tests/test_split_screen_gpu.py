@@ -49,3 +49,57 @@ def test_many_equal_rows(B, oracle, k, d, W, b):
     X[::2] = X[0]
     w0 = X[np.random.default_rng(k).integers(0, 16, k)]
     run_both(B, oracle, X, k, W, b, 0.05, 0, 1, kernel=B.KERNEL_GENERIC, check_qe=False, w0=w0)
+
+
+# ---- data of which screening leaves a part open ----
+def hard_data(k, d, b, share, seed, wide=0.0):
+    """Samples of W workers and a common state whose last two eighths are copies of the first one.  share(n): how many of the samples n of a mini-batch
+    lie next to one of the three copies.  wide: size of one column that says nothing about the others."""
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    q = k // 8
+    w = 10.0 * torch.rand((k, d), generator=gen, device="cuda:0")
+    w[k - q:] = w[:q]
+    w[k - 2 * q:k - q] = w[:q]
+    hard = torch.rand((W, b), generator=gen, device="cuda:0") < share(torch.arange(b, device="cuda:0"))
+    at = torch.where(hard, torch.randint(0, q, (W, b), generator=gen, device="cuda:0"), torch.randint(q, k - 2 * q, (W, b), generator=gen, device="cuda:0"))
+    x = w[at.reshape(-1)]
+    x += torch.randn((W * b, d), generator=gen, device="cuda:0")
+    if wide:
+        x[:, 0] = wide * torch.rand(W * b, generator=gen, device="cuda:0")
+        w[:, 0] = wide * torch.rand(k, generator=gen, device="cuda:0")
+    return x.contiguous(), w.cpu().numpy()
+
+
+def decisions(B, x, w, b, tune=0, steps=1):
+    g = B.ASGD(w.shape[0], w.shape[1], W, b, 0.05, E=0, kernel=B.KERNEL_GENERIC, tune=tune)
+    g.load_shards(x)
+    g.set_state(-1, w)
+    g.enable_assign_dump(steps)
+    g.run_steps(steps)
+    assert g.last_run_form() == (B.FORM_SPLIT_PHASES if tune else B.FORM_SPLIT_LAUNCH)
+    out = g.assign_dump(steps), g.get_state(), g.last_run_ms()
+    g.close()
+    return out
+
+
+# A state in one stage and in several; lists that are emptied in the middle of a mini-batch (1024 samples and more, with rows that have two
+# equals), and a workgroup that gives screening up later than at the first sweep: before its list was emptied once (samples 6000 on) and after (11000 on)
+@pytest.mark.parametrize("k,d", [(600, 60), (577, 101)])
+@pytest.mark.parametrize("b,from_on", [(11300, None), (7777, 6000), (12800, 11000)])
+def test_partly_undecided_samples(B, k, d, b, from_on):
+    import torch
+    at = b if from_on is None else from_on
+    x, w = hard_data(k, d, b, lambda n: torch.where(n >= at, 1.0, 0.10), seed=k + b)
+    idx, state, _ = decisions(B, x, w, b, steps=2)
+    want, state_want, _ = decisions(B, x, w, b, tune=4, steps=2)             # (phases do not screen)
+    assert np.array_equal(idx, want) and np.array_equal(state, state_want)
+
+
+@pytest.mark.parametrize("k,d,b", [(600, 60, 1500), (400, 128, 2000)])
+def test_undecided_samples_do_not_pay_for_screening(B, k, d, b):
+    # (screened nevertheless: three to four times what phases take)
+    x, w = hard_data(k, d, 4 * b, lambda n: 0.5 + 0.0 * n, seed=d, wide=1.0e4)
+    ms = [min(decisions(B, x, w, b, tune=tune, steps=4)[2] for _ in range(3)) for tune in (0, 4)]
+    assert ms[0] < 2.0 * ms[1], ms
