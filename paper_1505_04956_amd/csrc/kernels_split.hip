@@ -501,7 +501,7 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
         if (e != hipSuccess) return e;
         unsigned o = split_round16((size_t)a.kpad * 4);
         c.off_ms = o; o += split_round16((size_t)a.dpad * 4);
-        c.off_list = o; o += SCREENQ_WAVES * SCREENQ_LIST * 4;
+        c.off_list = o; o += SCREENQ_WAVES * (SCREENQ_LIST * 4 + SCREENQ_QUEUE);
         c.off_stage = o = (o + 1023) / 1024 * 1024;
         const unsigned pair = chunks * 2 * SPLIT_PIECE;
         // The samples stay in the registers for their distances, with fewer tiles per wave, or come a second time: the first as long as the matrix

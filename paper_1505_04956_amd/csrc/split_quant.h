@@ -205,78 +205,89 @@ __device__ inline float splitq_scan_wave(const float *xl, const float *w, int k,
     return fminf(best, __shfl_xor(best, 32, 64));
 }
 
-// What the samples of a wave add to Eq. 8 once their scores are known (lane l: sample gw + l).  For rows whose operands stay in
-// registers this is a function that is really called, with registers of its own: inlined, what it needs was kept across the
-// loop over the samples (k = 1024, d = 128, 5e6 samples: 6.1 ms, called 4.9); for long rows the registers saved around the
-// call were the dearer (k = 256, d = 384, 250000: called 0.98 ms, inlined 0.55).  A call passes its arguments in vector
-// registers; what is uniform is read back into scalar ones.
 typedef const __attribute__((address_space(4))) SplitQuant *SplitQuantPtr;
 struct SplitqSize { float vmin, vmax, vfar; };       // of the scored rows, scaled; smallest |v_c| of those that are not scored
-// LISTED: gw is the lane's own sample, below zero if it has none.
-template <bool TAIL, bool LISTED>
+
+// What the scores of a sample leave open: two candidates, or more.  Of those, the nearest row's score is `limit` or more (infinite where no score says
+// anything about it).
+struct SplitqOpen { bool two, more; float limit; };
+__device__ __forceinline__ SplitqOpen splitq_open(const SplitTop &t, int arg, int second, bool valid, float n2, float ratio, bool direct, const SplitqSize &size, int dpad)
+{
+    const float yn = sqrtf(n2) * 1.0001f, yr = yn / ratio;              // |y|, and in the units of the state
+    const float v = fminf(size.vmax, 4.0f * yr + 2.0f * size.vmin);
+    const float thr = split_c1(dpad) * (yn * v + 0.5f * v * v * ratio) + split_c2(dpad) * (yn + v);
+    // no scored row, scores out of their range (or not a number), a row that was not scored may be nearest
+    const bool all = direct || !(yn < 1.0e18f) || !(size.vmin < INFINITY) ||
+                     (size.vfar < INFINITY && !(2.02f * yr + size.vmin < size.vfar));
+    SplitqOpen o;
+    const bool close2 = valid && (all || !(t.v1 - t.v2 > thr));
+    o.more = close2 && (all || !(t.v1 - t.v3 > thr) || __float_as_int(t.v1) == __float_as_int(t.v2) || second == arg);
+    o.two = close2 && !o.more;
+    // (the bound holds the tags' part of a score; those of the score zero, where y and v are zero and it too, are below 2^-144)
+    o.limit = o.more && !all && fabsf(t.v1 - thr) < INFINITY ? t.v1 - thr - 1.0e-37f : INFINITY;
+    return o;
+}
+// Smallest direct distance to any of the rows for the samples of the lanes in `some` (n: the lane's sample, -1 without one).
+__device__ __forceinline__ float splitq_scan(SplitQuantPtr a, unsigned long long some, long long n, int lane)
+{
+    float scanned = INFINITY;
+    if (!some) return scanned;
+    const float *xl = a->x + (size_t)max(n, 0LL) * a->d;
+    if (__popcll(some) <= 8) {
+        for (unsigned long long left = some; left; left &= left - 1) {
+            const int L = __builtin_ctzll(left);           // (a valid sample)
+            const float best = splitq_scan_wave(a->x + (size_t)__shfl(n, L, 64) * a->d, a->w, a->k, a->d, lane);
+            if (lane == L) scanned = best;
+        }
+    } else if (some >> lane & 1) {
+        scanned = splitq_scan_own(xl, a->w, a->k, a->d);
+    }
+    if ((some >> lane & 1) && !(scanned < INFINITY) && !a->nan_is_inf) {
+        scanned = 0.0f;
+        for (int j = 0; j < a->d; ++j) scanned = fmaf(xl[j] - a->w[j], xl[j] - a->w[j], scanned);
+    }
+    return scanned;
+}
+
+// What the samples of a wave add to Eq. 8 once their scores are known (lane l: sample gw + l).  For rows whose operands stay in
+// registers this is a function that is really called, with registers of its own; for long rows the registers saved around the
+// call were the dearer (k = 256, d = 384, 250000: called 0.98 ms, inlined 0.55).  A call passes its arguments in vector
+// registers; what is uniform is read back into scalar ones.
+template <bool TAIL>
 __device__ __forceinline__ double splitq_finish_here(u64 args, long long gw_any, SplitTop t, float n2, float ratio, bool direct, SplitqSize size)
 {
     const SplitQuantPtr a = (SplitQuantPtr)split_uniform64(args);
-    const long long gw = LISTED ? gw_any : (long long)split_uniform64((u64)gw_any), N = a->N;
-    auto sample = [&](int at) -> long long { return LISTED ? (long long)__shfl((long long)gw, at, 64) : (gw + at < N ? gw + at : -1); };
+    const long long gw = (long long)split_uniform64((u64)gw_any), N = a->N;
     const int lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31, k = a->k, d = a->d;
     const float *x = a->x, *w = a->w;
     const int arg = min(max(t.i1, 0), k - 1), second = min(max(t.i2, 0), k - 1);
-    bool close2, close3;
-    {
-        const float yn = sqrtf(n2) * 1.0001f, yr = yn / ratio;              // |y|, and in the units of the state
-        const float v = fminf(size.vmax, 4.0f * yr + 2.0f * size.vmin);
-        const float thr = split_c1(a->dpad) * (yn * v + 0.5f * v * v * ratio) + split_c2(a->dpad) * (yn + v);
-        const bool valid = LISTED ? gw >= 0 : gw + lane < N;
-        // no scored row, scores out of their range (or not a number), a row that was not scored may be nearest
-        const bool all = direct || !(yn < 1.0e18f) || !(size.vmin < INFINITY) ||
-                         (size.vfar < INFINITY && !(2.02f * yr + size.vmin < size.vfar));
-        close2 = valid && (all || !(t.v1 - t.v2 > thr));
-        close3 = close2 && (all || !(t.v1 - t.v3 > thr) || __float_as_int(t.v1) == __float_as_int(t.v2) || second == arg);
-    }
-    const unsigned long long pairs = __ballot(close2 && !close3), many = __ballot(close3);
-    float scanned = INFINITY;
-    if (many) {
-        const float *xl = x + (size_t)(LISTED ? max(gw, 0LL) : gw + lane < N ? gw + lane : N - 1) * d;
-        if (__popcll(many) <= 8) {
-            for (unsigned long long left = many; left; left &= left - 1) {
-                const int L = __builtin_ctzll(left);           // (a valid sample)
-                const float best = splitq_scan_wave(x + (size_t)sample(L) * d, w, k, d, lane);
-                if (lane == L) scanned = best;
-            }
-        } else if (close3) {
-            scanned = splitq_scan_own(xl, w, k, d);
-        }
-        if (close3 && !(scanned < INFINITY) && !a->nan_is_inf) {
-            scanned = 0.0f;
-            for (int j = 0; j < d; ++j) scanned = fmaf(xl[j] - w[j], xl[j] - w[j], scanned);
-        }
-    }
+    const SplitqOpen open = splitq_open(t, arg, second, gw + lane < N, n2, ratio, direct, size, a->dpad);
+    const unsigned long long pairs = __ballot(open.two), many = __ballot(open.more);
+    const float scanned = splitq_scan(a, many, gw + lane < N ? gw + lane : -1, lane);
     double sum = 0.0;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         const int at = 32 * q + l32;
-        const long long n = sample(at);
-        const float *row = x + (size_t)(n < 0 ? N - 1 : n) * d;
+        const long long n = gw + at;
+        const float *row = x + (size_t)(n < N ? n : N - 1) * d;
         float d2 = splitq_distance<TAIL>(row, w + (size_t)__shfl(arg, at, 64) * d, d, half);
         d2 += __shfl_xor(d2, 32, 64);
         if (pairs) {
-            const int c2 = __shfl(close2 ? second : arg, at, 64);
+            const int c2 = __shfl(open.two ? second : arg, at, 64);
             float o2 = splitq_distance<TAIL>(row, w + (size_t)c2 * d, d, half);
             o2 += __shfl_xor(o2, 32, 64);
             d2 = o2 < d2 ? o2 : d2;
         }
         const float s2 = __shfl(scanned, at, 64);
         if (many >> at & 1) d2 = s2;
-        if (half == 0 && n >= 0) sum += 0.5 * (double)d2;
+        if (half == 0 && n < N) sum += 0.5 * (double)d2;
     }
     return sum;
 }
 
-template <bool TAIL>
-__device__ __noinline__ double splitq_finish(u64 args, long long gw, SplitTop t, float n2, float ratio, bool direct, SplitqSize size)
+__device__ __noinline__ inline double splitq_finish(u64 args, long long gw, SplitTop t, float n2, float ratio, bool direct, SplitqSize size)
 {
-    return splitq_finish_here<TAIL, false>(args, gw, t, n2, ratio, direct, size);
+    return splitq_finish_here<true>(args, gw, t, n2, ratio, direct, size);
 }
 
 template <int NC>
@@ -606,8 +617,8 @@ __global__ __launch_bounds__(SPLITQ_THREADS) __attribute__((amdgpu_waves_per_eu(
         SplitTop t;
         split_combine(top, t, half);
         swap2(n2[0], n2[1]);
-        if constexpr (NC == 0) sum += splitq_finish_here<false, false>((u64)args, gw, t, n2[0] + n2[1], half ? ratio[1] : ratio[0], half ? direct[1] : direct[0], size);
-        else sum += splitq_finish<NC % 4 != 0>((u64)args, gw, t, n2[0] + n2[1], half ? ratio[1] : ratio[0], half ? direct[1] : direct[0], size);
+        if constexpr (NC == 0) sum += splitq_finish_here<false>((u64)args, gw, t, n2[0] + n2[1], half ? ratio[1] : ratio[0], half ? direct[1] : direct[0], size);
+        else sum += splitq_finish((u64)args, gw, t, n2[0] + n2[1], half ? ratio[1] : ratio[0], half ? direct[1] : direct[0], size);
     }
     sum = split_wave_sum(sum);
     if (lane == 0) red[wave] = sum;

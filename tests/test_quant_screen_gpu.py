@@ -1,5 +1,5 @@
-"""Eq. 8 with screened samples: whole sweeps of the device, the half sweep after them and its ragged end, both ways to form the distances, and
-lists of undecided samples that overflow, against 64-bit distances."""
+"""Eq. 8 with screened samples: whole sweeps of the device, the half sweep after them and its ragged end, both ways to form the distances, lists of
+undecided samples that overflow, and screening that is given up, against 64-bit distances."""
 import numpy as np
 import pytest
 
@@ -15,6 +15,33 @@ def exact_error(x, w):
             d2 = torch.minimum(d2, ((x[lo:lo + 8192].double()[:, None] - w[None, c:c + 32]) ** 2).sum(-1).min(1).values)
         total += 0.5 * float(d2.sum())
     return total
+
+
+def quant_error(x, w):
+    import torch
+    from paper_1505_04956_amd import binding as B
+    out = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    B.asgd_quant_error_noalloc(x.data_ptr(), x.shape[0], w.shape[0], w.shape[1], w.data_ptr(), out.data_ptr(), torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    return float(out[0])
+
+
+def with_copies(k, d, N, share, seed):
+    """Even numbers from 0 to 14; the last quarter of the rows are copies of the first, and a share of the samples lies next to them, so that no score decides
+    them.  Two samples lie far beyond the common scale of the others.  Differences are even and below 6001, their squares multiples of four below 2^26, and so
+    are the sums of up to 128 of them: exact in fp32, whoever adds them."""
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(seed)
+    w = 2.0 * torch.randint(0, 8, (k, d), generator=gen, device="cuda:0").float()
+    q = max(1, k // 4)
+    w[k - q:] = w[:q]
+    near = torch.rand(N, generator=gen, device="cuda:0") < share
+    x = w[torch.where(near, torch.randint(0, q, (N,), generator=gen, device="cuda:0"), torch.randint(q, k - q, (N,), generator=gen, device="cuda:0"))]
+    x += 2.0 * (0.75 * torch.randn((N, d), generator=gen, device="cuda:0")).round()
+    x.clamp_(0.0, 14.0)
+    x[[N // 3, N - 1][:N], [0, d - 1][:N]] = 6000.0
+    return x.contiguous(), w
 
 
 # Samples of a sweep: 2048 waves of 128 (k = 600; k = 12, d = 9), 64 (k = 37) and 32 (k = 16, d = 121) samples
@@ -41,12 +68,53 @@ def test_sweeps_and_lists(k, d, N, ties):
     assert np.isfinite(exact)
 
 
+# Rows longer than 16 bytes of a lane by one to three, the fewest columns, several equals of a row: with more than two candidates the distances to those alone are formed
+@pytest.mark.parametrize("k,d,N", [(64, 8, 300000), (300, 11, 250000), (90, 29, 200000), (64, 64, 400000), (257, 70, 150000), (100, 112, 200000), (1024, 128, 150000)])
+@pytest.mark.parametrize("copies", [2, 8, 1000])
+def test_many_candidates(k, d, N, copies):
+    import torch
+    x, w = with_copies(k, d, N, 0.2, seed=k * d)
+    w = w[torch.arange(k, device="cuda:0") % max(2, k // copies)]
+    for rows in (w.contiguous(), w.flip(0).contiguous()):
+        assert quant_error(x, rows) == exact_error(x, rows)
+
+
+# Several candidates for most samples, because rows coincide or one column is a thousand times as wide as the others.  The limits are half of what such data cost while
+# every sample with more than two candidates was compared with all k rows (times that of ordinary data: 17, 25, 66, 33), and twice what they cost now.
+@pytest.mark.parametrize("k,d,N,kind,limit", [(100, 100, 1000000, "copies", 9.0), (300, 48, 1000000, "copies", 12.0), (1024, 128, 500000, "copies", 30.0), (1000, 32, 1000000, "wide", 16.0)])
+def test_time_of_undecided_samples(k, d, N, kind, limit):
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(k)
+    c = 10.0 * torch.rand((k, d), generator=gen, device="cuda:0")
+    x = c[torch.randint(0, k, (N,), generator=gen, device="cuda:0")]
+    x += torch.randn((N, d), generator=gen, device="cuda:0")
+
+    def time(x, w):
+        ms = []
+        for _ in range(6):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            quant_error(x, w)
+            end.record()
+            end.synchronize()
+            ms.append(start.elapsed_time(end))
+        return min(ms[1:])
+    w = c + torch.randn((k, d), generator=gen, device="cuda:0")
+    plain = time(x, w)
+    if kind == "copies":
+        w = w[torch.arange(k, device="cuda:0") % (k // 8)].contiguous()
+    else:
+        w[:, 0] *= 1000.0
+        x[:, 0] *= 1000.0
+    assert time(x, w) < limit * plain
+
+
 @pytest.mark.parametrize("k,d,N", [(37, 75, 300001), (1024, 128, 300001), (100, 100, 200001), (1000, 20, 300001), (12, 9, 300001), (500, 60, 200001)])
 def test_every_decision_on_a_grid(k, d, N):
     # Multiples of 1/8 below 2^5: differences, squares and sums of up to 128 of them are exact in fp32, so a single sample at another
     # prototype than its nearest would show.
     import torch
-    from paper_1505_04956_amd import binding as B
     gen = torch.Generator(device="cuda:0")
     gen.manual_seed(d)
     w = 10.0 * torch.rand((k, d), generator=gen, device="cuda:0")
@@ -54,7 +122,4 @@ def test_every_decision_on_a_grid(k, d, N):
     w += 0.7 * torch.randn((k, d), generator=gen, device="cuda:0")
     w[: k // 3] = w[k // 3: 2 * (k // 3)] + 0.3 * torch.randn((k // 3, d), generator=gen, device="cuda:0")       # pairs close together
     x, w = ((8.0 * v).round() / 8.0 for v in (x, w))
-    out = torch.zeros(1, dtype=torch.float64, device="cuda:0")
-    B.asgd_quant_error_noalloc(x.contiguous().data_ptr(), N, k, d, w.contiguous().data_ptr(), out.data_ptr(), torch.cuda.current_stream().cuda_stream)
-    torch.cuda.synchronize()
-    assert float(out[0]) == exact_error(x, w)
+    assert quant_error(x.contiguous(), w.contiguous()) == exact_error(x, w)
