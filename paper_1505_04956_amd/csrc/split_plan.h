@@ -44,6 +44,28 @@ inline unsigned split_round16(size_t v) { return (unsigned)((v + 15) / 16 * 16);
 // k = 1024, d = 64, b = 1500 6457, 18126, 6477.
 inline constexpr bool split_screen_gives_up(int open, int screened, int nch) { return (long long)open * (nch <= 3 ? 2 : nch == 4 ? 4 : 6) > screened; }
 
+// Rows of more than 128 columns, phases, one workgroup per compute unit: the cut of a mini-batch of `groups` groups of 64 samples that takes the fewest
+// groups one after the other, half a group counted for a workgroup's start.  `even`: in one round that fills the device,
+// or of two groups at most.
+// (256 / W shares, rounded down, one beyond 256 workers: microseconds per step with those and with these, k = 160, d = 200, b = 2000: W = 100 258, 239, 129
+// 432, 308, 190 482, 413, 257 838, 582, 380 939, 779, 600 1507, 1331; k = 256, d = 384, b = 512: W = 150 287, 271, 300 560, 497; the same cut at W = 64, 120, 256,
+// 512.)
+struct SplitCut { int shares; bool even; };
+inline SplitCut split_wide_cut(int W, int groups)
+{
+    SplitCut best = {1, true};
+    long long least = -1;
+    for (int s = 1; s <= groups && s <= 64; ++s) {
+        const int len = (groups + s - 1) / s, cut = (groups + len - 1) / len;
+        const long long rounds = ((long long)W * cut + SPLIT_CUS - 1) / SPLIT_CUS, cost = rounds * (2 * len + 1);
+        if (least >= 0 && cost >= least) continue;
+        least = cost;
+        best.shares = cut;
+        best.even = rounds == 1 && (len <= 2 || 4LL * W * cut >= 3 * SPLIT_CUS);
+    }
+    return best;
+}
+
 inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
 {
     SplitPlan q = {};
@@ -62,8 +84,12 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
     // groups of 64 for a workgroup, because elsewhere every wave has one of its own.  Microseconds per step before and with it: k = 256, d = 384,
     // b = 512: W = 64 171, 110, W = 256 497, 374; k = 300, d = 500, b = 1000, W = 16 196, 78; k = 160, d = 200, b = 4000, W = 256 1394, 1067; k = 128 974,
     // 949; d = 150: k = 100, b = 2000, W = 256 523, 515; k = 20, b = 1000, W = 64 (four groups) 73, 71, b = 2000 90, 118; k = 50, b = 2000, W = 256 368, 473.
+    // Four groups that do not fill the device, one or two blocks: k = 20, d = 150, b = 250, W = 150 50, 58, W = 300 98, 111; fewer groups: k = 20, d = 150, b = 130,
+    // W = 150 47, 46, W = 300 81, 76; b = 64, W = 600 106, 74; b = 500, W = 4 50, 32.
     const int groups = (b + 63) / 64, one_round = W < SPLIT_CUS && !local ? SPLIT_CUS / W : 1;
-    q.wide = q.longrow && group + wide_others <= SPLIT_LDS && (q.nblk >= 4 || (groups + one_round - 1) / one_round <= 4);
+    const SplitCut cut = q.longrow && !local ? split_wide_cut(W, groups) : SplitCut{1, true};
+    const bool wide_few = (groups + one_round - 1) / one_round <= 4 && (q.nblk == 3 || cut.even || groups <= 3);
+    q.wide = q.longrow && group + wide_others <= SPLIT_LDS && (q.nblk >= 4 || wide_few);
     if (q.longrow) {
         q.resident = q.fused = false;
     } else if (q.frag_bytes + cells + fixed <= SPLIT_LDS) {
@@ -119,8 +145,7 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
         int rsplit = q.wide ? 8 : 1;
         while (2 * rsplit <= q.npair && 2 * rsplit <= 8) rsplit *= 2;
         const int max_shares = (groups + 8 / rsplit - 1) / (8 / rsplit);
-        // (with one workgroup per compute unit a second round must not begin)
-        if (!local) q.shares = q.wide ? one_round : (2 * SPLIT_CUS + W - 1) / W;
+        if (!local) q.shares = q.wide ? cut.shares : (2 * SPLIT_CUS + W - 1) / W;
         if (q.shares > max_shares) q.shares = max_shares;
         if (q.shares > 64) q.shares = 64;
     } else if (!local) {

@@ -40,7 +40,13 @@ int main(int argc, char **argv)
                 }
                 if (q.wide) {
                     REQUIRE(q.longrow && q.waves == 8 && q.off_cells >= 64u * 4 * q.dpad && q.off_args + 8 * 64 * 4 * 7 + SPLIT_LDS_SHARED <= q.lds);
-                    REQUIRE(SPLIT_HARD * 8 * 16 <= 8 * 64 * 4 * 5 && (local || W > SPLIT_CUS || W * q.shares <= SPLIT_CUS));
+                    REQUIRE(SPLIT_HARD * 8 * 16 <= 8 * 64 * 4 * 5 && (!local || q.shares == 1));
+                    // no other cut leaves a compute unit fewer groups of 64 samples one after the other, starts counted as half a group
+                    auto cost = [&](long long shares, long long len) { return (W * shares + SPLIT_CUS - 1) / SPLIT_CUS * (2 * len + 1); };
+                    for (int len = 1; !local && k % 32 == 0 && len <= 64; ++len) {
+                        const int shares = ((b + 63) / 64 + len - 1) / len;
+                        REQUIRE(shares > 64 || cost(q.shares, q.share_len / 64) <= cost(shares, len));
+                    }
                 }
                 ++plans;
             }

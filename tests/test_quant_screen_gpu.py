@@ -46,9 +46,9 @@ def with_copies(k, d, N, share, seed):
 # Every instance, whole sweeps of the device, the half sweep after them and its ragged end; no row length is a multiple of four, which the fp32 matrix kernel would
 # take.  Samples of a sweep: 2048 waves of 128, 64 or 32 (up to 32 columns, or many rows; up to 96; more).  Share 0.3 fills the lists past 64 entries,
 # with a share of 1 screening is given up after the first sweep.
-@pytest.mark.parametrize("k,d,N", [(12, 9, 262144), (12, 9, 262144 + 131072 + 1), (600, 21, 262144 + 65), (37, 45, 2 * 131072 - 1), (500, 45, 262144 + 77),
-                                   (37, 61, 131072 + 4001), (400, 63, 2 * 262144 + 1), (37, 75, 131072 + 4001), (37, 75, 2 * 131072 - 1), (600, 77, 262144 + 131072 + 77),
-                                   (20, 90, 131072 + 1), (500, 90, 262144 + 130), (90, 101, 3 * 65536 + 31), (300, 101, 262144 + 1), (16, 121, 3 * 65536 + 31),
+@pytest.mark.parametrize("k,d,N", [(12, 9, 3 * 262144), (12, 9, 262144 + 131072 + 1), (600, 21, 262144 + 65), (37, 45, 2 * 131072 - 1), (500, 45, 262144 + 77),
+                                   (37, 61, 5 * 131072 + 4001), (400, 63, 2 * 262144 + 1), (37, 75, 131072 + 4001), (37, 75, 2 * 131072 - 1), (600, 77, 262144 + 131072 + 77),
+                                   (20, 90, 131072 + 1), (500, 90, 262144 + 130), (90, 101, 3 * 65536 + 31), (300, 101, 262144 + 1), (16, 121, 9 * 65536 + 31),
                                    (33, 127, 65537), (200, 125, 3 * 262144 - 1), (37, 33, 1), (5, 37, 64), (37, 75, 130), (8, 125, 2000)])
 @pytest.mark.parametrize("share", [0.0, 0.3, 1.0])
 def test_sweeps_and_lists(k, d, N, share):

@@ -24,3 +24,10 @@ def test_layout_fits_a_compute_unit(checker, d, W):
     assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout
     if d <= 64 and W == 192:
         assert int(out.stdout.split()[3]) > 1000
+
+
+# rows of more than 128 columns, workers that do and do not divide the compute units evenly: the cut of the mini-batches
+@pytest.mark.parametrize("W", [64, 100, 129, 150, 190, 257, 400, 600])
+def test_long_rows_fill_the_device(checker, W):
+    out = subprocess.run([checker, "384", str(W)], stdout=subprocess.PIPE, text=True)
+    assert out.returncode == 0 and out.stdout.startswith("ok "), out.stdout

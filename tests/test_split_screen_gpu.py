@@ -103,3 +103,10 @@ def test_undecided_samples_do_not_pay_for_screening(B, k, d, b):
     x, w = hard_data(k, d, 4 * b, lambda n: 0.5 + 0.0 * n, seed=d, wide=1.0e4)
     ms = [min(decisions(B, x, w, b, tune=tune, steps=4)[2] for _ in range(3)) for tune in (0, 4)]
     assert ms[0] < 2.0 * ms[1], ms
+
+
+# long rows where a mini-batch's shares do not divide the compute units: more than one round of workgroups, ragged last shares
+@pytest.mark.parametrize("k,d,W,b", [(130, 140, 150, 300), (40, 150, 300, 130), (100, 200, 129, 515), (20, 150, 150, 250)])
+def test_long_rows_in_rounds(B, oracle, k, d, W, b):
+    g, _ = run_both(B, oracle, make_data(W * (2 * b + 3), d, k, seed=W + b), k, W, b, 0.05, 2, 3, kernel=B.KERNEL_GENERIC, check_qe=False)
+    assert g.last_run_form() == B.FORM_SPLIT_PHASES
