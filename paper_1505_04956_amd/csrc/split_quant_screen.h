@@ -374,6 +374,9 @@ __global__ __launch_bounds__(SCREENQ_THREADS) __attribute__((amdgpu_waves_per_eu
     size.rows.vfar = sqrtf(size.rows.vfar) * 0.9999f;
     size.rest = sqrtf(size.rest) * 1.0001f;
 
+    // Norm of a sample, in scaled units, whose squared distance to the smallest row an fp32 number holds (others are infinite, which the list sees to)
+    const float yn_limit = fminf(SCREENQ_LIMIT, 1.8e19f * scale - size.rows.vmin * head.ratio);
+
     double sum = 0.0;
     int listed = 0, turn = 0, open_own = 0;
     bool staged = false;
@@ -468,7 +471,7 @@ __global__ __launch_bounds__(SCREENQ_THREADS) __attribute__((amdgpu_waves_per_eu
                 // (why rows of that size are enough: split_quant.h; one that is larger has a rest of 2^-11 of it at most)
                 const float vn = fminf(size.rows.vmax, 4.0f * yr + 2.0f * size.rows.vmin), vl = fminf(size.rest, 4.8877e-4f * vn + 1.0e-6f);
                 const float thr = screen_bound(yn, rl, vn, vl, 0.5f * vn * vn * head.ratio, a.q.dpad);
-                const bool all = head.direct != 0.0f || !(yn < SCREENQ_LIMIT) || !(size.rows.vmin < INFINITY) ||
+                const bool all = head.direct != 0.0f || !(yn < yn_limit) || !(size.rows.vmin < INFINITY) ||
                                  (size.rows.vfar < INFINITY && !(2.02f * yr + size.rows.vmin < size.rows.vfar));
                 const bool valid = gw + 64 * p + lane < N && (T > 1 || half == 0), open = valid && (all || !(t.v1 - t.v2 > thr));
                 const unsigned long long o = __ballot(open);

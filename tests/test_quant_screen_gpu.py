@@ -111,3 +111,21 @@ def test_every_decision_on_a_grid(k, d, N):
     w[: k // 3] = w[k // 3: 2 * (k // 3)] + 0.3 * torch.randn((k // 3, d), generator=gen, device="cuda:0")       # pairs close together
     x, w = ((8.0 * v).round() / 8.0 for v in (x, w))
     assert quant_error(x.contiguous(), w.contiguous()) == exact_error(x, w)
+
+
+# Differences of 1e19 have squares that fp32 numbers hold, of one sample alone the sum is larger than all of them: infinite, whoever adds it.  (Rows are 1e20 apart: every
+# sample would be decided by screening.)
+@pytest.mark.parametrize("k,d,N", [(12, 9, 130000), (37, 75, 3000), (100, 45, 3000), (600, 45, 3000), (200, 125, 9000)])
+def test_distances_beyond_fp32(k, d, N):
+    import torch
+    c = torch.arange(k, device="cuda:0")
+    w = torch.zeros((k, d), device="cuda:0")
+    w[c, c % d] = 1.0e20 * (1.0 + c // d)
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(k)
+    x = w[torch.randint(0, k, (N,), generator=gen, device="cuda:0")]
+    x[:, 0] += 1.0e19
+    exact = exact_error(x, w)
+    assert abs(quant_error(x, w) - exact) <= (d + 3) * 2.0 ** -24 * exact
+    x[N // 2, 1] += 1.8e19
+    assert quant_error(x, w) == float("inf")
