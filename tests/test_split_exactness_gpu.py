@@ -28,7 +28,9 @@ def check_quant_error(B, oracle, X, w):
     assert abs(q - o) <= (X.shape[1] + 3) * 2.0 ** -24 * o, (q, o, q / o - 1.0)
 
 
-SHAPES = [(37, 75, 1500), (256, 384, 700), (12, 9, 101000), (31, 9, 3000), (300, 129, 700), (600, 40, 120000), (600, 101, 900)]
+SHAPES = [(37, 75, 1500), (256, 384, 700), (12, 9, 101000), (31, 9, 3000), (300, 129, 700), (600, 40, 120000), (600, 101, 900),
+          # rows of up to 32 columns are screened beyond 120000 samples
+          (12, 9, 121000), (40, 17, 130000), (70, 27, 121001)]
 
 
 @pytest.mark.parametrize("k,d,N", SHAPES)
@@ -51,7 +53,8 @@ def test_quant_error_with_one_wide_column(B, oracle, k, d, N, levels):
     check_quant_error(B, oracle, X, w)
 
 
-@pytest.mark.parametrize("k,d,N", [(39, 13, 3000), (37, 75, 1500), (12, 9, 101000), (600, 40, 120000), (300, 129, 700)])
+@pytest.mark.parametrize("k,d,N", [(39, 13, 3000), (37, 75, 1500), (12, 9, 101000), (600, 40, 120000), (300, 129, 700), (12, 9, 121000), (39, 13, 130000),
+                                   (40, 31, 121001)])
 def test_quant_error_of_groups_far_apart(B, oracle, k, d, N):
     rng = np.random.default_rng(k + d)
     groups = rng.uniform(0.0, 1.0e4, (6, d))
