@@ -649,22 +649,25 @@ hipError_t launch_generic_steps(const StepParams &p, long long t0, long long t1,
 
 int quant_partials_count() { return QE_BLOCKS; }
 
-// fp16-split operands or not; in microseconds, the split kernel and the other one:
+// fp16-split operands or not.  Pairs of times are microseconds of the split kernel and of the one it is compared with.
 // Against a thread per sample: 0.5 to 0.7 ps per sample and k * d for rows shorter than a quarter of a cache line, 3 ps and
 // more for others, where the split kernel takes 50 to 58 ps per sample for up to 32 centroids and 16 columns, and 80 ps from the
 // rows of d < 8 (20e6 samples: k = 20, d = 5: 1640, 1410; k = 40, d = 3: 1620, 1270; k = 100, d = 3: 1970, 3130; k = 4, d = 9:
 // 1030, 876; k = 12, d = 9: 1100, 2350; k = 2, d = 16: 1140, 1360).  Its workgroups split the state first, 20 us with the
 // launch, which few samples of small rows do not repay (1000 samples: k = 20, d = 9: 20, 29; k = 100, d = 9: 26, 82).
-// Against the fp32 matrix kernel it needs work enough for its second launch, sooner with many centroids (k = 64, d = 64: 1.4e5 samples 30, 27, 3e5
-// 41, 39; k = 64, d = 32: 3e5 33, 25, 4e6 182, 235; k = 32, d = 128: 7e4 36, 33, 1.4e5 44, 45; k = d = 100: 3e4 25, 26, 1.4e5 43, 53; k = 300, d = 128: 2e4
-// 32, 63).  More than 128 centroids and 65536 samples: always, also where that was no faster, because the other kernel's scores are
-// relative to the origin and useless for data far from it.
+// Against the fp32 matrix kernel, whose time does not depend on the data: the screened kernel is faster on ordinary data from few samples on, sooner with
+// many centroids, and slower where screening leaves every sample open.  Fp32 matrix kernel; screened, ordinary data and one column a thousand times as
+// wide as the others: k = 64, d = 64: 1.5e5 samples 25; 25, 57, 6e5 68; 56, 128, 2e6 217; 139, -; k = 64, d = 32: 6e5 43; 42, 87, 2e6 114; 93, -; k = 64,
+// d = 128: 1.5e5 45; 40, 96, 6e5 132; 96, 232; k = 100, d = 32: 1.5e5 23; 25, 56, 6e5 60; 43, 110; k = 100, d = 64: 5e4 17; 18, -, 1.5e5 35; 26, 68; k = 100, d = 128: 5e4
+// 30; 25, -, 6e5 195; 103, 308; k = 300, d = 64: 1e4 35; 19, 49; k = 1000, d = 128: 1e4 171; 43, 225.  (Such a column costs the other kernel 1.6e-5 of the
+// result, whose scores are relative to the origin.)  So up to 128 centroids there has to be a quarter to gain.  More than 128 and 65536 samples: always, also where
+// that was no faster, because the other kernel's scores are useless for data far from the origin.
 static bool quant_error_split_pays(const float *x, long long N, int d, int k)
 {
     if (!split_quant_supports(k, d)) return false;
     if (mfma_quant_error_supports(k, d, x)) {
         const double work = (double)N * k * d;
-        return work > 1.2e9 || (k >= 96 && work > 3.0e8) || (k > 128 && N > 65536);
+        return work > (k < 96 ? 2.0e9 : k <= 128 ? 6.0e8 : 3.0e8) || (k > 128 && N > 65536);
     }
     return (d >= 16 || k * d > (d >= 8 ? 48 : 160)) && (N > 100000 || k * d > 150);
 }

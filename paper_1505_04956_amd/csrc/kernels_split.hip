@@ -8,7 +8,6 @@ namespace asgd {
 
 hipError_t launch_split_quant_0(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_split_quant_1(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
-hipError_t launch_split_quant_2(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_screen_quant_1(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_screen_quant_2(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
 hipError_t launch_screen_quant_3(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s);
@@ -486,10 +485,12 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
     *nblocks_out = nblocks;                       // one workgroup per compute unit
     a.kpad = npair * 64;
     a.nan_is_inf = nan_is_inf;
-    // (Short rows, few samples: the launch for the state and a wave's pass over its few undecided samples do not pay.  Microseconds without and with
-    // them: k = 100, d = 14: 20000 samples 19.9, 22.1, 80000 20.8, 24.3, 160000 27.4, 26.9; k = 1000, d = 9: 80000 55.6, 60.5, 160000 83.2, 72.1; k = 31, d = 20: 100000
-    // 18.9, 23.4, 300000 31.4, 29.6.)
-    if (quant_screens(k, d) && !(d <= 32 && N <= 120000)) {
+    // (Short rows, few rows and samples: the launch for the state and a wave's pass over its few undecided samples do not pay.  Microseconds without
+    // and with them: k = 100, d = 9: 20000 samples 19, 20, 120000 20, 22; k = 150 22, 23; k = 300 27, 26 and 28, 29; d = 16: k = 31, 120000 samples 17, 17;
+    // k = 1000, 60000 samples 54, 47.  Longer rows: k = 31, d = 20: 1000 samples 17, 14, 120000 18, 16; k = 300, d = 32: 60000 samples 31, 19.  Data with many
+    // undecided samples, one column a thousand times as wide as the others: k = 100, d = 9 61, 25; k = 4000, d = 32, 5000 samples 2720, 372, the fp32 matrix
+    // kernel 254.)
+    if (quant_screens(k, d) && !(d <= 16 && k < 300 && N <= 120000)) {
         ScreenQuant c;
         c.q = a;
         const QuantOperands l = quant_operands(k, d);
@@ -528,7 +529,7 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
     unsigned o = (unsigned)(a.resident ? all : two);
     a.off_hs = o; o += split_round16((size_t)a.kpad * 4);
     a.off_m = o;  o += split_round16((size_t)a.dpad * 4);
-    return d > 128 ? launch_split_quant_0(a, nblocks, o, s) : d > 16 ? launch_split_quant_2(a, nblocks, o, s) : launch_split_quant_1(a, nblocks, o, s);
+    return d > 128 ? launch_split_quant_0(a, nblocks, o, s) : launch_split_quant_1(a, nblocks, o, s);
 }
 
 }  // namespace asgd

@@ -12,10 +12,6 @@ hipError_t launch_split_assign_2(const SplitLaunch &l, int blocks, int threads, 
 {
     return split_launch_phase<12>(l, blocks, threads, lds, s);
 }
-hipError_t launch_split_quant_2(const SplitQuant &a, int blocks, unsigned lds, hipStream_t s)
-{
-    return split_launch_quant<2>(a, blocks, lds, s);
-}
 hipError_t launch_screen_quant_2(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s)
 {
     return a.keep ? launch_screen_quant<2, true>(a, blocks, lds, s) : launch_screen_quant<2, false>(a, blocks, lds, s);

@@ -1,5 +1,5 @@
-// Eq. 8 on the fp16 matrix instructions, rows of less than 8 and of more than 128 columns, few samples of up to 32 (the others: split_quant_screen.h, which shares
-// the decisions and what follows about odd rows).  Scores with fp16-split operands (split_core.h) only screen: the
+// Eq. 8 on the fp16 matrix instructions, rows of less than 8 and of more than 128 columns, few samples and centroids of up to 16 columns (the others:
+// split_quant_screen.h, which shares the decisions and what follows about odd rows).  Scores with fp16-split operands (split_core.h) only screen: the
 // error of a score is bounded, and a sample whose runner-up lies within the bound is decided by distances in direct form -
 // two candidates by theirs, more by those to all the centroids.  So every sample adds the smallest of its direct fp32
 // distances, whatever the scores are worth, and the sum over the samples is fp64.
@@ -250,7 +250,9 @@ __device__ __forceinline__ float splitq_scan(SplitQuantPtr a, unsigned long long
 }
 
 // What the samples of a wave add to Eq. 8 once their scores are known (lane l: sample gw + l).  For rows whose operands stay in
-// registers this is a function that is really called, with registers of its own; for long rows the registers saved around the
+// registers this is a function that is really called, with registers of its own: inlined it was 2 to 10 % faster where few samples are
+// undecided and up to twice as slow where many are (microseconds called and inlined, 2e6 samples: k = 100, d = 5 144, 133, k = 1000 526, 563, one
+// column a thousand times as wide as the others 2376, 3414; k = 300, d = 3, every row twice 355, 523).  For long rows the registers saved around the
 // call were the dearer (k = 256, d = 384, 250000: called 0.98 ms, inlined 0.55).  A call passes its arguments in vector
 // registers; what is uniform is read back into scalar ones.
 template <bool TAIL>

@@ -29,7 +29,7 @@ def check_quant_error(B, oracle, X, w):
 
 
 SHAPES = [(37, 75, 1500), (256, 384, 700), (12, 9, 101000), (31, 9, 3000), (300, 129, 700), (600, 40, 120000), (600, 101, 900),
-          # rows of up to 32 columns are screened beyond 120000 samples
+          # rows of up to 16 columns, less than 300 of them, are screened beyond 120000 samples
           (12, 9, 121000), (40, 17, 130000), (70, 27, 121001)]
 
 

@@ -6,7 +6,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-# (up to 32 columns samples are screened beyond 120000)
+# (up to 16 columns samples are screened beyond 120000)
 @pytest.mark.parametrize("d,N", [(d, 4001) for d in (17, 31, 33, 47, 49, 51, 63, 65, 75, 79, 81, 95, 97, 111, 113, 127)] + [(d, 121001) for d in (8, 9, 10, 11, 13, 15, 17, 18, 19, 22, 25, 31)])
 def test_quant_error_row_lengths(d, N):
     import torch
