@@ -197,7 +197,8 @@ hipError_t launch_split_steps(const StepParams &p, long long t0, long long t1, c
     a.counters = p.counters;
     a.H = p.H;
     a.k = p.k; a.d = p.d; a.b = p.b; a.W = p.W; a.kpad = q.kpad; a.nblk = q.nblk; a.dpad = q.dpad;
-    a.shares = q.shares; a.share_len = q.share_len; a.sum_shares = q.sum_shares; a.sum_len = q.sum_len; a.dc = q.dc; a.ncol = q.ncol; a.resident = q.resident; a.fused = q.fused; a.wide = q.wide;
+    a.shares = q.shares; a.share_len = q.share_len; a.sum_shares = q.sum_shares; a.sum_len = q.sum_len;
+    a.dc = q.dc; a.ncol = q.ncol; a.resident = q.resident; a.fused = q.fused; a.wide = q.wide;
     a.vec4 = p.d % 4 == 0 && ((uintptr_t)p.x & 15u) == 0;
     a.kept = q.kept; a.off_batch = q.off_batch; a.batch_bytes = q.batch_bytes;
     a.off_cells = q.off_cells; a.off_cnt = q.off_cnt; a.off_hs = q.off_hs; a.off_ms = q.off_ms; a.off_args = q.off_args;
@@ -451,10 +452,11 @@ __global__ __launch_bounds__(SPLITQ_THREADS) void splitq_operands_kernel(ScreenQ
     }
 }
 
-// Screening for rows of 8 to 128 columns, whatever k is (the operands of a state, that is; see also launch_quant_error_split); microseconds with three products for all samples, and screened: 4e6 samples, k = 12, d = 9: 164,
-// 100; k = 37, d = 75: 529, 333; k = 1000, d = 9: 917, 515; k = 1000, d = 32: 1040, 546; k = 100, d = 20: 303, 181; 2e6 samples, k = 512, d = 128:
-// 1227, 478; 20000 samples, k = 512, d = 125: 105, 38.  Also where prototypes lie close together and many samples stay undecided (k = 1000, d = 9,
-// sigma 0.3: 886, 439).  Shorter rows are loaded one by one, longer ones do not fit the registers.
+// Screening for rows of 8 to 128 columns, whatever k is (the operands of a state, that is; see also launch_quant_error_split); microseconds with
+// three products for all samples, and screened: 4e6 samples, k = 12, d = 9: 164, 100; k = 37, d = 75: 529, 333; k = 1000, d = 9: 917, 515; k =
+// 1000, d = 32: 1040, 546; k = 100, d = 20: 303, 181; 2e6 samples, k = 512, d = 128: 1227, 478; 20000 samples, k = 512, d = 125: 105, 38.  Also
+// where prototypes lie close together and many samples stay undecided (k = 1000, d = 9, sigma 0.3: 886, 439).  Shorter rows are loaded one by one,
+// longer ones do not fit the registers.
 static bool quant_screens(int k, int d) { return split_quant_supports(k, d) && d >= 8 && d <= 128; }
 struct QuantOperands { size_t head, m, sizes, hs, hi, lo, bytes; };
 static QuantOperands quant_operands(int k, int d)
@@ -508,7 +510,7 @@ hipError_t launch_quant_error_split(const float *x, long long N, int d, int k, c
         // The samples stay in the registers for their distances, with fewer tiles per wave, or come a second time: the first as long as the matrix
         // work is small next to the memory (microseconds kept and not, 2e6 samples; d = 128: k = 16 253, 320, 128 260, 309, 192 389, 374, 512 539, 478; d = 80:
         // k = 256 251, 269, 1024 491, 484; d = 64: k = 512 283, 276; up to 32 columns the tiles stay four: k = 1000, d = 20 534, 545).
-        c.keep = k <= (chunks <= 2 ? 8192 : chunks <= 6 ? 384 : 160);
+        c.keep = chunks <= 2 || k <= (chunks <= 6 ? 384 : 160);
         c.pairs_per_stage = (int)((SPLIT_LDS_ALL / 2 - 256 - o) / (2 * pair));      // (at least one: 32 KB of offsets and 32 KB of operands at most)
         if (c.pairs_per_stage > npair) c.pairs_per_stage = npair;
         o += 2 * c.pairs_per_stage * pair;

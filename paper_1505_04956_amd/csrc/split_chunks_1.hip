@@ -18,7 +18,7 @@ hipError_t launch_split_quant_1(const SplitQuant &a, int blocks, unsigned lds, h
 }
 hipError_t launch_screen_quant_1(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s)
 {
-    return a.keep ? launch_screen_quant<1, true>(a, blocks, lds, s) : launch_screen_quant<1, false>(a, blocks, lds, s);
+    return launch_screen_quant<1, true>(a, blocks, lds, s);          // (always kept)
 }
 
 }  // namespace asgd

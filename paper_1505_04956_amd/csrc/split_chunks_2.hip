@@ -14,7 +14,7 @@ hipError_t launch_split_assign_2(const SplitLaunch &l, int blocks, int threads, 
 }
 hipError_t launch_screen_quant_2(const ScreenQuant &a, int blocks, unsigned lds, hipStream_t s)
 {
-    return a.keep ? launch_screen_quant<2, true>(a, blocks, lds, s) : launch_screen_quant<2, false>(a, blocks, lds, s);
+    return launch_screen_quant<2, true>(a, blocks, lds, s);          // (always kept)
 }
 
 }  // namespace asgd

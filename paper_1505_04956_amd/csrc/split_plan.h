@@ -109,7 +109,8 @@ inline SplitPlan split_plan(int k, int d, int b, int W, bool local)
     q.screen = local && !q.longrow && !q.fused && !q.resident && q.nch >= 2 && b >= 384;
     unsigned o = split_round16(q.resident ? q.frag_bytes : stage2);
     if (q.screen) {
-        const size_t pair = (size_t)q.nch * 2 * SPLIT_PIECE, others = fixed + SPLIT_LIST * 4, listed = (size_t)SPLIT_LISTED / 32 * (q.nch > 3 ? q.nch : 3) * 2 * SPLIT_PIECE;      // (operands, then the best scores of eight waves)
+        const size_t pair = (size_t)q.nch * 2 * SPLIT_PIECE, others = fixed + SPLIT_LIST * 4;
+        const size_t listed = (size_t)SPLIT_LISTED / 32 * (q.nch > 3 ? q.nch : 3) * 2 * SPLIT_PIECE;      // (operands, then the best scores of eight waves)
         q.resident = false;
         q.stage_pairs = q.npair;
         if (q.npair * pair + others > SPLIT_LDS) q.stage_pairs = (int)((SPLIT_LDS - others) / (2 * pair));

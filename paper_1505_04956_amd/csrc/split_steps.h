@@ -461,14 +461,11 @@ __device__ inline void split_scan_hard(SPLIT_ARG SplitArgs &a, const float *xb, 
 // The listed samples: 128 at a time, their operands in the LDS (where the stages were), every wave its own blocks of the state's rows with both
 // parts straight from the L2, a block ahead.
 template <int NC>
-__device__ __forceinline__ void split_listed(u64 args_any, u64 state_any, long long row0_any, u64 dump_any, int worker_any, int share_any)
+__device__ __forceinline__ void split_listed(SPLIT_ARG SplitArgs &a, const SplitStep &now, int worker, int share, unsigned char *smem)
 {
-    SPLIT_ARG SplitArgs &a = *(SPLIT_ARG SplitArgs *)split_uniform64(args_any);
-    const SplitState *state = (const SplitState *)split_uniform64(state_any);
-    const long long row0 = (long long)split_uniform64((u64)row0_any);
-    int32_t *dump = (int32_t *)split_uniform64(dump_any);
-    const int worker = __builtin_amdgcn_readfirstlane(worker_any), n_lo = __builtin_amdgcn_readfirstlane(share_any) * a.share_len;
-    unsigned char *smem = split_lds + SPLIT_LDS_SHARED;
+    const SplitState *state = now.state;
+    int32_t *dump = now.dump;
+    const int n_lo = share * a.share_len;
     const int lane = split_lane(), half = lane >> 5, l32 = lane & 31, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nw = blockDim.x >> 6, d = a.d, nblk = a.nblk;
     constexpr int HC = (NC + 1) / 2, TILES = SPLIT_LISTED / 32;
@@ -478,7 +475,7 @@ __device__ __forceinline__ void split_listed(u64 args_any, u64 state_any, long l
     half8 *operands = reinterpret_cast<half8 *>(smem);                    // [tile][chunk][hi, lo] pieces
     const int *list = reinterpret_cast<const int *>(smem + a.off_list);
     const unsigned char *frag = a.frag + (size_t)worker * a.frag_bytes;
-    const float *xb = a.x + ((size_t)worker * a.H + (size_t)row0 + n_lo) * d;
+    const float *xb = a.x + ((size_t)worker * a.H + (size_t)now.row0 + n_lo) * d;
     const float sx = a.xmeta[0];
     const SplitSize st = {state[worker].sw, state[worker].vabs, state[worker].n2};
     const int listed = __builtin_amdgcn_readfirstlane(split_shared().listed);
@@ -723,7 +720,7 @@ __device__ int split_screen_item(SPLIT_ARG SplitArgs &a, const SplitStep &now, i
         __syncthreads();                          // (everybody has read the number before anybody adds to it)
         if (split_screen_gives_up(listed, min(g0, n) - done, NC)) return done;
         if (listed > 0 && (g0 >= n || listed > SPLIT_LIST - nw * 128)) {
-            split_listed<NC>((u64)&a, (u64)now.state, now.row0, (u64)now.dump, worker, share);
+            split_listed<NC>(a, now, worker, share, smem);
             if (g0 < n) stage_fetch(0, turn & 1);
             staged = false;
             done = g0;
@@ -1699,7 +1696,8 @@ struct SplitLaunch {                       // arguments of a phase
 
 // The items are inlined into the loop over the steps, each with its own copy of the step's values.  (Called, a function saves the half of the
 // registers that it uses and a caller may have use for: for an assignment 200 KB of a compute unit per call, out to memory and back.  k = d = 100,
-// W = 512: 9300 us a run with all of them called, 8720 with the assignment inlined, 8610 with Eq. 4 and the update.)  Those that
+// W = 512: 9300 us a run with all of them called, 8720 with the assignment inlined, 8610 with Eq. 4 and the update.)  The screened kernel of eight
+// chunks keeps 160 vector registers in scratch memory even so, that of five 61, most of them what split_listed() needs.  Items that
 // are called pass their arguments in vector registers; what is uniform is read back into scalar ones.
 typedef SPLIT_ARG SplitRun *SplitRunPtr;
 __device__ __forceinline__ int split_uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -1733,12 +1731,12 @@ __device__ __forceinline__ void split_screen_call(u64 run, const SplitStep &now,
     if (threadIdx.x == 0) split_shared().unscreened = off > 0 ? off - 1 : first >= 0 ? SPLIT_UNSCREENED : 0;
     if (first >= 0) split_assign_call<NC>(run, worker, first);
 }
-template <bool KEPT, bool CELLS>
+template <bool CELLS>
 __device__ __forceinline__ void split_gate_call(u64 run, int worker, int blk)
 {
     SplitRunPtr r = split_uniform(run);
     const SplitStep now = split_shared().now;
-    split_gate_item<KEPT, CELLS>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared().red);
+    split_gate_item<false, CELLS>(r->p, r->u, r->a, now, split_uniform(worker), split_uniform(blk), split_shared().red);
 }
 template <int MODE, bool KEPT, bool REST, bool CELLS>
 __device__ __forceinline__ void split_update_call(u64 run, int worker, int blk)
@@ -1936,8 +1934,8 @@ __global__ __launch_bounds__(SPLIT_THREADS) __attribute__((amdgpu_waves_per_eu(2
                 if constexpr (KEPT) {
                     if (!split_gate_at_once(r->a, r->u)) split_gate_item<true, true>(r->p, r->u, r->a, now, i, 0, sh.red);
                 } else {
-                    if (CELLS && r->a.fused) split_gate_call<KEPT, CELLS>(run, i, 0);
-                    else split_gate_call<KEPT, false>(run, i, 0);
+                    if (CELLS && r->a.fused) split_gate_call<CELLS>(run, i, 0);
+                    else split_gate_call<false>(run, i, 0);
                 }
             }
             if (r->sync && now.send && now.round >= 2) {
