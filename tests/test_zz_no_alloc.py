@@ -1,5 +1,5 @@
 """The entry point that allocates nothing (Eq. 8 with its scratch in a static device array) against asgd_quant_error(),
-through the C ABI: two calls in a row, the second with a smaller input, for the three Eq. 8 kernels."""
+through the C ABI: two calls in a row, the second with a smaller input, for every Eq. 8 kernel."""
 import numpy as np
 import pytest
 
@@ -17,6 +17,8 @@ def make_data(N, d, k, seed):
     (10, 10, 300_007, 4_001),       # streaming kernel
     (64, 32, 50_000, 777),          # matrix-core kernel
     (7, 5, 20_003, 64),             # generic kernel
+    (100, 3, 20_003, 777),          # fp16-split kernel
+    (37, 75, 20_003, 64),           # screened samples: the operands of the state are scratch too
 ])
 def test_no_alloc_entry_point_matches_quant_error(k, d, N1, N2):
     import torch
