@@ -1,5 +1,5 @@
 """Steps whose samples are screened with the high parts of their operands: a streamed state, sweeps of four and of two tiles, ragged ends, lists that
-overflow and samples with dozens of nearest rows, against the oracle."""
+are emptied, screening that is given up and samples with dozens of nearest rows, against the oracle or the kernels that do not screen."""
 import numpy as np
 import pytest
 
@@ -23,7 +23,7 @@ def test_screened_steps(B, oracle, k, d, b, E):
 
 @pytest.mark.parametrize("k,d,b", [(600, 60, 1500), (512, 100, 2100)])
 def test_many_undecided_samples(B, oracle, k, d, b):
-    # every prototype twice or more: no score decides anything, lists overflow (more than 1024 samples), ties go to the lowest index
+    # every prototype twice or more: no score decides anything, screening is given up after the first sweep, ties go to the lowest index
     H = max(b + 5, k)
     X = make_data(W * H, d, 8, seed=d)
     rng = np.random.default_rng(k)
