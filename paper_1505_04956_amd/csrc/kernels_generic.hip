@@ -659,9 +659,9 @@ int quant_partials_count() { return QE_BLOCKS; }
 // many centroids, and slower where screening leaves every sample open.  Fp32 matrix kernel; screened, ordinary data and one column a thousand times as
 // wide as the others: k = 64, d = 64: 1.5e5 samples 25; 25, 57, 6e5 68; 56, 128, 2e6 217; 139, -; k = 64, d = 32: 6e5 43; 42, 87, 2e6 114; 93, -; k = 64,
 // d = 128: 1.5e5 45; 40, 96, 6e5 132; 96, 232; k = 100, d = 32: 1.5e5 23; 25, 56, 6e5 60; 43, 110; k = 100, d = 64: 5e4 17; 18, -, 1.5e5 35; 26, 68; k = 100, d = 128: 5e4
-// 30; 25, -, 6e5 195; 103, 308; k = 300, d = 64: 1e4 35; 19, 49; k = 1000, d = 128: 1e4 171; 43, 225.  (Such a column costs the other kernel 1.6e-5 of the
-// result, whose scores are relative to the origin.)  So up to 128 centroids there has to be a quarter to gain.  More than 128 and 65536 samples: always, also where
-// that was no faster, because the other kernel's scores are useless for data far from the origin.
+// 30; 25, -, 6e5 195; 103, 308; k = 300, d = 64: 1e4 35; 19, 49; k = 1000, d = 128: 1e4 171; 43, 225.  So up to 128 centroids there has to be a quarter to
+// gain.  The fp32 matrix kernel decides by its scores, which such a column of 1e3 makes 1e-5 of the result wrong, one of 1e5 up to 5e-4; the others are exact: a
+// reason to draw the line early.
 static bool quant_error_split_pays(const float *x, long long N, int d, int k)
 {
     if (!split_quant_supports(k, d)) return false;

@@ -1359,12 +1359,16 @@ __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(2, 2))
 }
 
 // Eq. 8 for the contraction shapes: the same matrix-core scores as phase 1 of the step kernel, for ONE state and
-// all N samples.  The centroid with the largest score x.w_c - |w_c|^2/2 is the nearest one: only the running
+// all N samples, with the state relative to a point m near the data (the middle of nine samples, column by column): a score
+// x.(w_c - m) - (w_c - m).(w_c + m)/2 is off by some 1e-6 of |x||w_c - m|, with m = 0 it would say nothing about data far from the origin.  The centroid
+// with the largest score is the nearest one: only the running
 // maximum per sample is kept, with the place it came from in its low mantissa bits, and the distance to that
 // centroid is then formed directly as sum_j (x_j - w_cj)^2 (no cancellation).  A workgroup (8 waves) walks tiles of 256 samples with a fixed stride, every lane pair adds its samples
 // in fp64 in a fixed order, the partials are added in a fixed order: the result does not depend on scheduling.
 // RES: the whole padded state fits LDS and is staged once per launch (no barriers in the loop over the samples); then a
 // last half-block of at most eight centroids goes to 4x4 matrix tiles as in the step kernel.
+// (scores of large numbers may be far below zero)
+constexpr float QE_PAD_SCORE = -3.0e38f;
 template <int NCH, bool RES>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void quant_error_mfma_kernel(
     const float *__restrict__ x, long long N, int k, int d, const float *__restrict__ w, double *partials)
@@ -1378,23 +1382,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     const int kpad = (k + WB - 1) / WB * WB, nblocks = kpad / WB;
     float *Ws = reinterpret_cast<float *>(smem_raw);                      // (RES ? kpad : 2 x WB) x DP
     float *hs = Ws + (size_t)(RES ? kpad : 2 * WB) * DP;                  // kpad
+    float *ms = hs + kpad;                                                // DP8, zero beyond d
     constexpr bool TAILOK = RES && NCH <= 13;
     const int tail_groups = (TAILOK && (k & 31) >= 1 && (k & 31) <= 8 && ((k >> 5) & 1)) ? ((k & 31) + 3) / 4 : 0;
     const int tail_row0 = k & ~31;
-
-    for (int c0 = wave * RB; c0 < kpad; c0 += NWV * RB) {                 // h_c = -|w_c|^2 / 2
-#pragma unroll
-        for (int q = 0; q < RB; ++q) {
-            const int c = c0 + q;
-            float sq = 0.0f;
-            for (int j = lane; j < d; j += 64) {
-                const float v = w[(size_t)(c < k ? c : 0) * d + j];
-                sq = fmaf(v, v, sq);
-            }
-            sq = wave_sum_f(sq);
-            if (lane == 0) hs[c] = c < k ? -0.5f * sq : PAD_SCORE;
-        }
-    }
     const int col0 = (half && d >= 8) ? 4 : 0;
     const int collim = half ? (d >= 8 ? (d - 8) / 8 * 8 + 4 : 0) : (d - 4) / 8 * 8;
     auto fetch_block = [&](float4(&st)[NST], int cb) {
@@ -1404,30 +1395,57 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int r = (e < NVEC ? e : 0) / ROW4, c4 = (e < NVEC ? e : 0) - r * ROW4;
             const int c = cb * WB + r, col = 4 * c4;
             const bool ok = c < k && col < d;
-            float4 v = *reinterpret_cast<const float4 *>(w + (size_t)(ok ? c : 0) * d + (ok ? col : 0));
-            if (!ok) v = make_float4(0.f, 0.f, 0.f, 0.f);
-            st[q] = v;
+            st[q] = *reinterpret_cast<const float4 *>(w + (size_t)(ok ? c : 0) * d + (ok ? col : 0));
         }
     };
-    auto store_block = [&](const float4(&st)[NST], float *dst) {
+    auto store_block = [&](const float4(&st)[NST], float *dst, int cb) {
 #pragma unroll
         for (int q = 0; q < NST; ++q) {
             const int e = tid + q * MF_THREADS;
             if (e < NVEC) {
                 const int r = e / ROW4, c4 = e - r * ROW4;
-                *reinterpret_cast<float4 *>(&dst[r * DP + 4 * c4]) = st[q];
+                const float4 mv = *reinterpret_cast<const float4 *>(ms + 4 * c4);
+                float4 v = make_float4(st[q].x - mv.x, st[q].y - mv.y, st[q].z - mv.z, st[q].w - mv.w);
+                if (cb * WB + r >= k || 4 * c4 >= d) v = make_float4(0.f, 0.f, 0.f, 0.f);
+                *reinterpret_cast<float4 *>(&dst[r * DP + 4 * c4]) = v;
             }
         }
     };
 
-    if constexpr (RES) {
-        float4 st[NST];
-        for (int cb = 0; cb < nblocks; ++cb) {
-            fetch_block(st, cb);
-            store_block(st, Ws + (size_t)cb * WB * DP);
+    float4 st[NST];
+    fetch_block(st, 0);
+    for (int j = tid; j < DP8; j += MF_THREADS) {
+        float v[9];
+#pragma unroll
+        for (int q = 0; q < 9; ++q) {
+            v[q] = x[(size_t)(q * N / 9) * d + (j < d ? j : 0)];
+            if (!(fabsf(v[q]) < INFINITY)) v[q] = 0.0f;
         }
-        __syncthreads();                 // state rows and hs complete
+        auto mid = [&](int q) { return __builtin_amdgcn_fmed3f(v[q], v[q + 1], v[q + 2]); };
+        ms[j] = j < d ? __builtin_amdgcn_fmed3f(mid(0), mid(3), mid(6)) : 0.0f;
     }
+    __syncthreads();
+    if constexpr (RES) {
+        for (int cb = 0; cb < nblocks; ++cb) {
+            store_block(st, Ws + (size_t)cb * WB * DP, cb);
+            if (cb + 1 < nblocks) fetch_block(st, cb + 1);
+        }
+        __syncthreads();                 // state rows complete
+    }
+    for (int c0 = wave * RB; c0 < kpad; c0 += NWV * RB) {                 // h_c = -(w_c - m).(w_c + m) / 2
+#pragma unroll
+        for (int q = 0; q < RB; ++q) {
+            const int c = c0 + q;
+            float sq = 0.0f;
+            for (int j = lane; j < d; j += 64) {
+                const float m = ms[j], v = RES ? Ws[(size_t)c * DP + j] : w[(size_t)(c < k ? c : 0) * d + j] - m;
+                sq = fmaf(v, v + 2.0f * m, sq);
+            }
+            sq = wave_sum_f(sq);
+            if (lane == 0) hs[c] = c < k ? -0.5f * sq : QE_PAD_SCORE;
+        }
+    }
+    if constexpr (RES) __syncthreads();  // hs complete
     double sum = 0.0;
     for (long long tile0 = (long long)blockIdx.x * TM; tile0 < N; tile0 += (long long)gridDim.x * TM) {
         const long long n = tile0 + wave * 32 + l32;
@@ -1439,11 +1457,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
             const int col = ch * 8 + col0;
             xf[ch] = *reinterpret_cast<const float4 *>(row + (col < collim ? col : collim));
         }
-        float4 st[NST];
         if constexpr (!RES) {
             __syncthreads();             // nobody still reads the stage (and hs is complete)
             fetch_block(st, 0);
-            store_block(st, Ws);
+            store_block(st, Ws, 0);
         }
         float best = -INFINITY;         // largest score so far, the number of its accumulator register in its low 5 bits
         int bestcb = 0;                 // ... and the block it came from
@@ -1510,7 +1527,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                         acc1[r] = (__uint_as_float(sw[0]) + __uint_as_float(sw[1])) + hq[r];
                     }
 #pragma unroll
-                    for (int r = 4; r < 16; ++r) acc1[r] = PAD_SCORE;
+                    for (int r = 4; r < 16; ++r) acc1[r] = QE_PAD_SCORE;
                 }
             } else {
                 float4 a0 = *reinterpret_cast<const float4 *>(w0row);
@@ -1536,7 +1553,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
                     a0 = n0; a1 = n1;
                 }
             }
-            if (more) store_block(st, Ws + ((cb + 1) & 1) * WB * DP);
+            if (more) store_block(st, Ws + ((cb + 1) & 1) * WB * DP, cb + 1);
             float bm = -INFINITY;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
@@ -1588,14 +1605,14 @@ template <int NCH>
 hipError_t launch_qe_nch(const float *x, long long N, int d, int k, const float *w, double *partials, int nblocks, hipStream_t s)
 {
     const int kpad = (k + WB - 1) / WB * WB;
-    const size_t lds_res = ((size_t)kpad * (NCH * 8 + 4) + kpad) * sizeof(float);
-    if (lds_res <= MF_LDS_BUDGET) {
+    const size_t lds_res = ((size_t)kpad * (NCH * 8 + 4) + kpad + NCH * 8) * sizeof(float);
+    if (lds_res <= MF_LDS_BUDGET + NCH * 32) {           // (m comes on top, as below)
         hipError_t e = hipFuncSetAttribute((const void *)quant_error_mfma_kernel<NCH, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_res);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL((quant_error_mfma_kernel<NCH, true>), dim3(nblocks), dim3(512), lds_res, s, x, N, k, d, w, partials);
         return hipGetLastError();
     }
-    const size_t lds = ((size_t)2 * WB * (NCH * 8 + 4) + kpad) * sizeof(float);
+    const size_t lds = ((size_t)2 * WB * (NCH * 8 + 4) + kpad + NCH * 8) * sizeof(float);
     hipError_t e = hipFuncSetAttribute((const void *)quant_error_mfma_kernel<NCH, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((quant_error_mfma_kernel<NCH, false>), dim3(nblocks), dim3(512), lds, s, x, N, k, d, w, partials);

@@ -131,3 +131,22 @@ def test_distances_beyond_fp32(k, d, N):
     assert abs(quant_error(x, w) - exact) <= (d + 3) * 2.0 ** -24 * exact
     x[N // 2, 1] += 1.8e19
     assert quant_error(x, w) == float("inf")
+
+
+# Data far from the origin, in units of their spread: scores relative to the origin would say nothing.  The streaming and the fp32 matrix kernel (state resident, and
+# streamed) decide by scores, whose error (20 roundings of |x - m||w - m| and the tags) is a thousandth of such data's distances; the others are exact.
+@pytest.mark.parametrize("k,d,N,tol", [(10, 10, 30001, 1.0e-4), (4, 4, 5000, 1.0e-4), (8, 8, 3001, 1.0e-4), (8, 16, 3001, 1.0e-4), (16, 8, 3001, 1.0e-4), (16, 12, 3001, 1.0e-4),
+                                       (32, 16, 60000, 1.0e-4), (40, 20, 3786, 1.0e-4), (37, 100, 2001, 1.0e-4), (64, 32, 1, 1.0e-4), (65, 64, 40000, 1.0e-4), (100, 100, 160, 1.0e-4),
+                                       (128, 128, 5000, 1.0e-4), (243, 80, 33, 1.0e-4), (500, 128, 700, 1.0e-4), (8200, 16, 3000, 1.0e-4), (9000, 128, 300, 1.0e-4),
+                                       (7, 5, 3001, 0.0), (12, 9, 3001, 0.0), (100, 3, 3001, 0.0), (37, 75, 3001, 0.0), (1000, 48, 10000, 0.0), (50, 200, 3001, 0.0)])
+@pytest.mark.parametrize("mean", [300.0, 1.0e4])
+def test_data_far_from_the_origin(k, d, N, tol, mean):
+    import torch
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(k + d)
+    w = mean + 10.0 * torch.rand((k, d), generator=gen, device="cuda:0")
+    x = w[torch.randint(0, k, (N,), generator=gen, device="cuda:0")]
+    x += torch.randn((N, d), generator=gen, device="cuda:0")
+    w += torch.randn((k, d), generator=gen, device="cuda:0")
+    exact = exact_error(x, w)
+    assert abs(quant_error(x, w) - exact) <= max(tol, (d + 3) * 2.0 ** -24) * exact
